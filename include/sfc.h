@@ -271,8 +271,8 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
  *                + (b / dims[4])*strides[3] + (b % dims[4])*strides[4],
  * dims[0] = P, dims[1]*dims[2] >= A and dims[3]*dims[4] >= B (tiles, filters and
  * channels are padded up; entries beyond the true counts are padding).  Plain layouts
- * have dims[2] = dims[4] = 1; in requantized mode M is kept in blocks of 16 tiles x 4
- * filters (the 256 bytes one wave of the output transform reads per point).
+ * have dims[2] = dims[4] = 1; M is kept in blocks of 16 tiles x 4 filters (the 256 bytes
+ * one wave of the output transform reads per point).
  * V exists on SFC_PATH_STAGED and SFC_PATH_FUSED, M only on SFC_PATH_STAGED
  * (SFC_EUNSUPPORTED otherwise). */
 sfc_status sfc_tap_info(const sfc_plan_t* plan, const void* workspace_dev, int32_t which,

@@ -209,6 +209,7 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
     off = align_up(off + sfc::image_table_bytes(g), 256);
   if (d.mode == SFC_MODE_REQUANT_I8 && sfc::rows_table_offset(g) != ~0u)
     off = align_up(off + sfc::kRowsTabBytes, 256);
+  if (d.mode == SFC_MODE_EXACT) off = align_up(off + sfc::kRowsTabBytes, 256);  // every algorithm
   p->off_dq_single = off;
   p->off_U_single = off;
   p->quad_filters = 0;
@@ -376,10 +377,15 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   }
   if (plan->off_dq_single > plan->off_input_tab) {
     unsigned char* tab = reinterpret_cast<unsigned char*>(table(plan->off_input_tab));
-    if (g.alg == SFC_ALG_4X4_P46 || g.alg == SFC_ALG_4X4_P49) sfc::build_input_table(g.alg, inv_sx, tab);
-    if (sfc::image_input_supported(g))
-      sfc::build_image_input_table(g, inv_sx, tab + sfc::image_table_offset(g));
-    if (sfc::rows_table_offset(g) != ~0u) sfc::build_rows_table(g.alg, inv_sx, tab + sfc::rows_table_offset(g));
+    if (!requant) {
+      sfc::build_rows_table(g.alg, inv_sx, tab);
+    } else {
+      if (g.alg == SFC_ALG_4X4_P46 || g.alg == SFC_ALG_4X4_P49) sfc::build_input_table(g.alg, inv_sx, tab);
+      if (sfc::image_input_supported(g))
+        sfc::build_image_input_table(g, inv_sx, tab + sfc::image_table_offset(g));
+      if (sfc::rows_table_offset(g) != ~0u)
+        sfc::build_rows_table(g.alg, inv_sx, tab + sfc::rows_table_offset(g));
+    }
   }
   if (plan->dq_filters > 0) {
     const int pp = (g.P + 3) / 4 * 4;
@@ -404,6 +410,10 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the kernels of this plan's path that need more than the default 64 KB of dynamic LDS
   if (requant && sfc::prepare_kernels(plan->d.path, plan->d.out, g) != hipSuccess) return SFC_EHIP;
+  if (!requant) {
+    const hipError_t e = sfc::launch_input_exact(g, nullptr, nullptr, nullptr, nullptr, true);
+    if (e != hipSuccess && e != hipErrorNotSupported) return SFC_EHIP;
+  }
   if (hipMemcpyAsync(static_cast<char*>(filter_dev) + plan->off_dequant, plan->staging.data(),
                      table_bytes, hipMemcpyHostToDevice, s) != hipSuccess)
     return SFC_EHIP;
@@ -524,14 +534,9 @@ sfc_status sfc_tap_info(const sfc_plan_t* plan, const void* workspace_dev, int32
       *elem_bytes = plan->d.mode == SFC_MODE_REQUANT_I8 ? sfc::m_sum_bytes(g) : 4;
       dims[0] = g.P;
       strides[0] = (int64_t)g.Tp * g.Kp;
-      if (plan->d.mode == SFC_MODE_REQUANT_I8) {
-        // [P][tile block][filter quad][16 tiles][4 filters]
-        dims[1] = g.Tp / 16; dims[2] = 16; dims[3] = g.Kp / 4; dims[4] = 4;
-        strides[1] = (int64_t)g.Kp * 16; strides[2] = 4; strides[3] = 64; strides[4] = 1;
-      } else {
-        dims[1] = g.Tp; dims[2] = 1; dims[3] = g.Kp; dims[4] = 1;
-        strides[1] = g.Kp; strides[2] = 0; strides[3] = 1; strides[4] = 0;
-      }
+      // [P][tile block][filter quad][16 tiles][4 filters]
+      dims[1] = g.Tp / 16; dims[2] = 16; dims[3] = g.Kp / 4; dims[4] = 4;
+      strides[1] = (int64_t)g.Kp * 16; strides[2] = 4; strides[3] = 64; strides[4] = 1;
       return SFC_OK;
     default:
       return SFC_EINVAL;

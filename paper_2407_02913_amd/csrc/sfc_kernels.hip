@@ -1,13 +1,14 @@
 // HIP kernels of the staged path on gfx950 (wave64), every algorithm of sfc_points.hpp.
 //
 //   filter_transform_kernel   U = G f G^T               (once per layer)
-//   input_transform_kernel    V = B^T x B               (NCHW int8 -> [P][Tp][Cp])
-//   product_i16_kernel        M_p = V_p . U_p^T, exact mode (int16 operands, vector ALU)
-//   output_transform_kernel   y = A^T M A, corrections, NCHW store, exact mode
-// (the requantized-mode products and output transform are in sfc_gemm.hip)
+//   input_transform_kernel    V = B^T x B               (abs-max calibration; geometries the
+//                             matrix-core input kernels do not take)
+//   output_transform_kernel   y = A^T M A, corrections, NCHW store, exact mode, very large layers
+// (the requantized-mode products and output transform are in sfc_gemm.hip, exact mode in
+// sfc_exact.hip)
 //
 // Layouts (element strides): V[p][t][c] = (p*Tp + t)*Cp + c, U[p][k][c] =
-// (p*Kp + k)*Cp + c, M[p][t][k] = (p*Tp + t)*Kp + k.  Channels c >= Cin and
+// (p*Kp + k)*Cp + c, M in blocks of 16 tiles x 4 filters (sfc_gemm.hip).  Channels c >= Cin and
 // filters k >= Cout are zero in U, so padding never contributes to a sum.
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
@@ -263,34 +264,10 @@ __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v) {
   if (i < n) p[i] = v;
 }
 
-// exact mode: int16 operands, int32 sums on the vector ALU, 16x16 block per workgroup
-__global__ __launch_bounds__(256) void product_i16_kernel(const int16_t* __restrict__ V,
-                                                          const int16_t* __restrict__ U,
-                                                          int32_t* __restrict__ M, Geometry g) {
-  __shared__ int16_t sv[16][66];
-  __shared__ int16_t su[16][66];
-  const int kblocks = g.Kp >> 4;
-  const int kb = blockIdx.x % kblocks, tb = blockIdx.x / kblocks;
-  const int p = blockIdx.y;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  unsigned acc = 0;  // sums modulo 2^32: wrap-around is defined, exact while the true sum fits
-  for (int kc = 0; kc < g.Cp; kc += 64) {
-    for (int i = threadIdx.x; i < 16 * 64; i += 256) {
-      const int r = i >> 6, c = i & 63;
-      sv[r][c] = V[((size_t)p * g.Tp + tb * 16 + r) * g.Cp + kc + c];
-      su[r][c] = U[((size_t)p * g.Kp + kb * 16 + r) * g.Cp + kc + c];
-    }
-    __syncthreads();
-#pragma unroll 16
-    for (int c = 0; c < 64; ++c) acc += (unsigned)((int)sv[ty][c] * (int)su[tx][c]);
-    __syncthreads();
-  }
-  M[((size_t)p * g.Tp + tb * 16 + ty) * g.Kp + kb * 16 + tx] = (int32_t)acc;
-}
-
 // ---------------------------------------------------------------------------
-// output transform, exact mode: one thread per (tile, filter), lanes along filters;
-// the integer sums are divided by 36 (16 for SFC-4) exactly
+// output transform, exact mode, for M or y beyond the 32-bit offsets of output_exact_kernel:
+// one thread per (tile, filter), lanes along filters; the integer sums are divided by 36 (16
+// for SFC-4) exactly
 // ---------------------------------------------------------------------------
 template <int ALG, int OUT>
 __global__ __launch_bounds__(256) void output_transform_kernel(const int32_t* __restrict__ M,
@@ -301,7 +278,7 @@ __global__ __launch_bounds__(256) void output_transform_kernel(const int32_t* __
   const int t = blockIdx.x * (256 / kx) + (threadIdx.x / kx);
   if (k >= g.Cout || t >= g.T) return;
   const size_t pstride = (size_t)g.Tp * g.Kp;
-  const int32_t* m = M + (size_t)t * g.Kp + k;
+  const int32_t* m = M + ((size_t)(t >> 4) * (g.Kp >> 2) + (k >> 2)) * 64 + (t & 15) * 4 + (k & 3);
   const int tiles_per_image = g.th * g.tw;
   const int n = t / tiles_per_image;
   const int rem = t - n * tiles_per_image;
@@ -407,6 +384,8 @@ hipError_t launch_input_transform(int mode, const Geometry& g, const int8_t* x, 
     if (e != hipErrorNotSupported) return e;
     return launch_input_alg<1>(g, x, V, inv_sx, nullptr, s);
   }
+  const hipError_t e = launch_input_exact(g, x, V, input_tab, s);
+  if (e != hipErrorNotSupported) return e;
   return launch_input_alg<0>(g, x, V, inv_sx, nullptr, s);
 }
 
@@ -485,11 +464,7 @@ hipError_t launch_filter_transform(int mode, const Geometry& g, const int8_t* w,
 
 hipError_t launch_product(int mode, const Geometry& g, const void* V, const void* U, int32_t* M,
                           hipStream_t s) {
-  const int blocks = (g.Tp / 16) * (g.Kp / 16);
-  if (mode == 1) return launch_product_gemm_i8(g, V, U, M, s);
-  hipLaunchKernelGGL(product_i16_kernel, dim3(blocks, g.P), dim3(256), 0, s, (const int16_t*)V,
-                     (const int16_t*)U, M, g);
-  return hipGetLastError();
+  return mode == 1 ? launch_product_gemm_i8(g, V, U, M, s) : launch_product_exact(g, V, U, M, s);
 }
 
 template <int ALG>
@@ -497,6 +472,8 @@ static hipError_t launch_output_alg(int mode, int out, const Geometry& g, const 
                                     const FilterViews& f, float x_scale, float inv_y, void* y,
                                     hipStream_t s) {
   if (mode == 1) return launch_output_sums(out, g, M, f, x_scale, inv_y, y, s);
+  const hipError_t e = launch_output_exact(out == 1, g, M, f.wscale, x_scale, y, s);
+  if (e != hipErrorNotSupported) return e;
   int kx = 64;
   while (kx > g.Kp) kx >>= 1;  // Kp is a multiple of 16
   dim3 grid((g.T + (256 / kx) - 1) / (256 / kx), (g.Cout + kx - 1) / kx);

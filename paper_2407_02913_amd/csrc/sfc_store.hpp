@@ -21,12 +21,14 @@ __device__ __forceinline__ void write_tile_entry(int* tile_tab, int tl, bool liv
 // inverse along the horizontal axis, the wave's staging block [filter 0..3][tile
 // 0..15][o2] (64*M floats), then stores in which consecutive lanes hold consecutive
 // outputs of an image row (tiles of a strip are adjacent in y).
-// OUT: 0 float32, 2 int8 with ReLU (inv_y = 1 / output scale).  VEC2: M and W even,
+// OUT: 0 four-byte words, 2 int8 with ReLU (inv_y = 1 / output scale).  VEC2: M and W even,
 // pairs of outputs stay aligned.
-template <int ALG, int OUT, bool VEC2>
-__device__ __forceinline__ void store_pairs(
-    const float (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M], float* stage, const int* tile_tab,
-    int lane, int kq, float x_scale, float inv_y, __amdgpu_buffer_rsrc_t yres, int Cout, int H,
+// T, finish: type of the add network's values, and the function that makes an output of one
+// (returned as the bits of a float, whatever the four-byte word is).
+template <int ALG, int OUT, bool VEC2, typename T, typename Finish>
+__device__ __forceinline__ void store_pairs_as(
+    const T (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M], float* stage, const int* tile_tab,
+    int lane, int kq, Finish&& finish, float inv_y, __amdgpu_buffer_rsrc_t yres, int Cout, int H,
     int W) {
   constexpr int M = AlgTraits<ALG>::M;
   constexpr unsigned esz = OUT == 2 ? 1u : 4u;
@@ -57,15 +59,15 @@ __device__ __forceinline__ void store_pairs(
   float* wr = stage + ((lane >> 4) * 16 + (lane & 15)) * M;
 #pragma unroll
   for (int o1 = 0; o1 < M; ++o1) {
-    float out[M];
-    stream_row<ALG, float>(z, o1, out);
+    T out[M];
+    stream_row<ALG, T>(z, o1, out);
     if constexpr (M % 2 == 0) {
 #pragma unroll
       for (int o2 = 0; o2 < M; o2 += 2)
-        *(v2f*)(wr + o2) = v2f{out[o2] * x_scale, out[o2 + 1] * x_scale};
+        *(v2f*)(wr + o2) = v2f{finish(out[o2]), finish(out[o2 + 1])};
     } else {
 #pragma unroll
-      for (int o2 = 0; o2 < M; ++o2) wr[o2] = out[o2] * x_scale;
+      for (int o2 = 0; o2 < M; ++o2) wr[o2] = finish(out[o2]);
     }
     __builtin_amdgcn_wave_barrier();  // LDS accesses of one wave complete in order
     const unsigned yrow = esz * (unsigned)(o1 * W);
@@ -108,6 +110,15 @@ __device__ __forceinline__ void store_pairs(
     }
     __builtin_amdgcn_wave_barrier();
   }
+}
+
+template <int ALG, int OUT, bool VEC2>
+__device__ __forceinline__ void store_pairs(
+    const float (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M], float* stage, const int* tile_tab,
+    int lane, int kq, float x_scale, float inv_y, __amdgpu_buffer_rsrc_t yres, int Cout, int H,
+    int W) {
+  store_pairs_as<ALG, OUT, VEC2>(z, stage, tile_tab, lane, kq, [=](float v) { return v * x_scale; },
+                                 inv_y, yres, Cout, H, W);
 }
 
 // The same for feature maps that whole tiles cover exactly (H = M*th, W = M*tw) with th*tw

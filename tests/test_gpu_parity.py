@@ -64,6 +64,25 @@ def test_exact_mode_taps_and_sums_bit_exact(binding, shape, alg):
     assert rel_err(y, oracle.dequantize(acc_ref, xs, ws)) <= F32_TOL
 
 
+@pytest.mark.parametrize("alg", ["6x6_p88", "7x7_p144", "4x4_p46", "6x6_5x5_p184"])
+@pytest.mark.parametrize("shape", [
+    (5, 130, 70, 29, 31),  # three channel chunks, two filter blocks of 64, ragged tile blocks, odd W
+    (1, 64, 64, 48, 48),   # whole blocks of 64 filters and (4x4 and 6x6 tiles) of 64 tiles
+    (2, 145, 68, 6, 6),    # one or two tiles per image, a filter block with one quad
+])
+def test_exact_products_at_block_edges(binding, shape, alg):
+    """Operands at the ends of the int8 range (transform values of both signs with either sign
+    of their low byte), every sum bit-exact."""
+    x, w, xs, ws = uniform_case(shape, 150 + len(alg) + sum(shape), r=binding.KERNEL_SIZE[alg])
+    x[0], w[0] = -128, -128
+    print("case exact blocks", shape, alg, flush=True)
+    acc, taps = binding.conv2d(x, w, xs, ws, mode="exact", alg=alg, out="i32", return_taps=True)
+    acc_ref, taps_ref = oracle.conv_exact(x, w, alg, return_taps=True)
+    for name in ("V", "U", "M"):
+        assert np.array_equal(taps[name].astype(np.int64), taps_ref[name]), name
+    assert np.array_equal(acc.astype(np.int64), acc_ref)
+
+
 @pytest.mark.parametrize("alg", ALGS_STAGED)
 @pytest.mark.parametrize("shape", SMALL_SHAPES)
 def test_requant_mode_taps_bit_exact_and_output_close(binding, shape, alg):
