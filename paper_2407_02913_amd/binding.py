@@ -123,11 +123,21 @@ def _nbytes(t) -> int:
     return int(t.numel() * t.element_size())
 
 
-def _stream_ptr(stream):
-    import torch
+_torch = None  # torch, once a call has needed it
 
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+
+def _stream_ptr(stream):
+    """hipStream_t of `stream`, or of the current stream.  The raw handle is asked for: a
+    torch.cuda.Stream object takes 2.7 us to build, as long as the launch that follows, the
+    handle 0.1 us."""
+    global _torch
+    if stream is not None:
+        return stream.cuda_stream
+    if _torch is None:
+        import torch
+
+        _torch = torch
+    return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
 
 
 class Plan:
@@ -216,22 +226,26 @@ class Plan:
         self._keep = [filter_buf]
 
     def conv2d(self, x_dev, x_scale: float, y_dev, workspace, stream=None):
-        _check(load().sfc_conv2d_nchw(self._h, C.c_void_p(x_dev.data_ptr()), C.c_float(x_scale),
-                                      C.c_void_p(y_dev.data_ptr()), C.c_void_p(workspace.data_ptr()),
-                                      _nbytes(workspace), _stream_ptr(stream)),
-               "sfc_conv2d_nchw")
+        # (plain integers: ctypes converts them by the argument types load() declared)
+        status = (_lib or load()).sfc_conv2d_nchw(self._h, x_dev.data_ptr(), x_scale, y_dev.data_ptr(),
+                                                  workspace.data_ptr(), _nbytes(workspace),
+                                                  _stream_ptr(stream))
+        if status != SFC_OK:
+            raise SfcError(status, "sfc_conv2d_nchw")
 
     def conv2d_static(self, x_dev, x_scale: float, y_dev, stream=None):
         """sfc_conv2d_nchw with the library's built-in workspace (nothing is allocated)."""
-        _check(load().sfc_conv2d_nchw_static(self._h, C.c_void_p(x_dev.data_ptr()), C.c_float(x_scale),
-                                             C.c_void_p(y_dev.data_ptr()), _stream_ptr(stream)),
-               "sfc_conv2d_nchw_static")
+        status = (_lib or load()).sfc_conv2d_nchw_static(self._h, x_dev.data_ptr(), x_scale,
+                                                         y_dev.data_ptr(), _stream_ptr(stream))
+        if status != SFC_OK:
+            raise SfcError(status, "sfc_conv2d_nchw_static")
 
     def conv2d_stages(self, x_dev, x_scale: float, y_dev, workspace, mask: int, stream=None):
-        _check(load().sfc_conv2d_stages(self._h, C.c_void_p(x_dev.data_ptr()), C.c_float(x_scale),
-                                        C.c_void_p(y_dev.data_ptr()),
-                                        C.c_void_p(workspace.data_ptr()), _nbytes(workspace),
-                                        _stream_ptr(stream), int(mask)), "sfc_conv2d_stages")
+        status = (_lib or load()).sfc_conv2d_stages(self._h, x_dev.data_ptr(), x_scale, y_dev.data_ptr(),
+                                                    workspace.data_ptr(), _nbytes(workspace),
+                                                    _stream_ptr(stream), mask)
+        if status != SFC_OK:
+            raise SfcError(status, "sfc_conv2d_stages")
 
     def tap(self, which: str, workspace) -> np.ndarray:
         """Copy of V, U or M in canonical [P][tiles|Cout][Cin|Cout] order (synchronizes)."""
