@@ -33,6 +33,7 @@ struct sfc_plan_s {
   int dq_filters;    // filters in the [filter][processing position] dequantization table (0: none)
   bool quad16;       // filter operand in groups of 16 filters (sfc_quad16.hpp, sfc_splitk.hip)
   bool splitk;       // fused path: input channels split over the waves of a workgroup
+  bool small;        // single and fused paths: the kernels for small layers (sfc_small.hip)
   float inv_y;  // 1 / output scale (SFC_OUT_I8_RELU), 0: not set
 };
 
@@ -213,12 +214,17 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
   p->off_dq_single = off;
   p->off_U_single = off;
   p->quad_filters = 0;
-  p->splitk = d.path == SFC_PATH_FUSED && !sfc::quad16_supported(g) && sfc::splitk_supported(g);
-  p->quad16 = p->splitk || (d.path == SFC_PATH_FUSED && sfc::quad16_supported(g)) ||
+  p->small = d.path == SFC_PATH_SINGLE  ? sfc::single_small_supported(g)
+             : d.path == SFC_PATH_FUSED ? sfc::product_small_supported(g)
+                                        : false;
+  const bool fused_large = d.path == SFC_PATH_FUSED && !p->small;
+  p->splitk = fused_large && !sfc::quad16_supported(g) && sfc::splitk_supported(g);
+  p->quad16 = p->splitk || (fused_large && sfc::quad16_supported(g)) ||
               (d.path == SFC_PATH_SINGLE && (sfc::single16_supported(g) || sfc::single16k_supported(g)));
   if (d.path == SFC_PATH_SINGLE) p->quad_filters = p->quad16 ? g.Kp : (g.Cout + 63) / 64 * 64;
   if (d.path == SFC_PATH_FUSED)
-    p->quad_filters = p->splitk   ? sfc::splitk_filter_count(g)
+    p->quad_filters = p->small    ? sfc::product_small_filter_count(g)
+                      : p->splitk ? sfc::splitk_filter_count(g)
                       : p->quad16 ? sfc::quad16_filter_count(g)
                                   : sfc::quad_filter_count(g);
   // the staged output transform reads the same [filter][position] table as the fused kernels
@@ -445,7 +451,9 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
     const FilterViews f = views(plan, plan->filter_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    if (!plan->quad16)
+    if (plan->small)
+      e = sfc::launch_single_small(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
+    else if (!plan->quad16)
       e = sfc::launch_single_conv(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
     else if (plan->g.Cp <= 128)
       e = sfc::launch_single16(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
@@ -468,7 +476,8 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
   }
   if (fused) {
     if (tail &&
-        (plan->splitk   ? sfc::launch_splitk(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)
+        (plan->small    ? sfc::launch_product_small(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)
+         : plan->splitk ? sfc::launch_splitk(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)
          : plan->quad16 ? sfc::launch_quad16(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)
                         : sfc::launch_fused_quad(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)) !=
             hipSuccess)

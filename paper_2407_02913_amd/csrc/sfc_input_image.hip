@@ -179,14 +179,110 @@ __global__ __launch_bounds__(256, 2) void input_transform_image_kernel(
   }
 }
 
+// The same for layers of a few images, where the chain of one wave is the kernel's duration and a
+// wave alone on its SIMD issues an instruction every 8 clocks: a wave owns one tile and 16
+// channels (a quarter of the roundings), turns all its blocks round at once and stores 16 bytes
+// of V per position.
+template <int ALG, int KS>
+__global__ __launch_bounds__(256) void input_transform_image16_kernel(const int8_t* __restrict__ x,
+                                                                      int8_t* __restrict__ V,
+                                                                      const unsigned char* __restrict__ tab,
+                                                                      Geometry g) {
+  using Tr = AlgTraits<ALG>;
+  static_assert(Tr::R == 3, "3x3 filters");
+  constexpr int P = Tr::P, PP = Order<ALG>::PP, NPB = (PP + 15) / 16, NST = (16 * NPB + 63) / 64;
+  __shared__ __align__(16) unsigned char lds[4 * 256 * NPB];  // per wave [position][16 channels]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ranges = g.Cp >> 4;
+  const int unit = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + wave;
+  const int t = unit / ranges, c0 = (unit - t * ranges) * 16;
+  if (t >= g.T) return;  // (whole waves; the kernel has no workgroup barrier)
+  const int tpi = g.th * g.tw;
+  const int n = t / tpi, tile = t - n * tpi;
+  const float* inv_pos = (const float*)tab;
+  const int* point = (const int*)(tab + kImageTabPoint);
+  const unsigned char* ctab = tab + kImageTabCoeff + (unsigned)tile * (unsigned)(16 * NPB * 64 * KS);
+  const int base = ((const int*)(tab + kImageTabBase))[tile];
+  v4i coeff[NPB][KS];
+  float inv[NPB];
+#pragma unroll
+  for (int m = 0; m < NPB; ++m) {
+    const int pos = 16 * m + (lane & 15);
+    inv[m] = inv_pos[pos];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      coeff[m][s] = *(const v4i*)(ctab + pos * (64 * KS) + 64 * s + 16 * (lane >> 4));
+  }
+  int p[NST];
+#pragma unroll
+  for (int h = 0; h < NST; ++h) p[h] = 64 * h + lane < 16 * NPB ? point[64 * h + lane] : -1;
+  // operand A, as above; only the last channels of the tensor need the byte-wise tail
+  const int hw = g.H * g.W;
+  const unsigned xbytes = (unsigned)(g.N * g.Cin) * (unsigned)hw;
+  const __amdgpu_buffer_rsrc_t xres =
+      __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, (int)xbytes, kBufferFlags);
+  const int ch = c0 + (lane & 15);
+  const unsigned off = ch < g.Cin ? (unsigned)((n * g.Cin + ch) * hw + base + 16 * (lane >> 4)) : 0x80000000u;
+  const bool inside = (unsigned)((n * g.Cin + min(c0 + 15, g.Cin - 1)) * hw + base) + 64u * KS <= xbytes;
+  v4i a[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned o = off + 64u * s + 4u * i;
+      unsigned v = 0;
+      if (inside || o + 4u <= xbytes) {
+        v = __builtin_amdgcn_raw_buffer_load_b32(xres, o, 0, 0);
+      } else if (o < xbytes) {
+        for (unsigned bb = 0; o + bb < xbytes; ++bb)
+          v |= (unsigned)__builtin_amdgcn_raw_buffer_load_b8(xres, o + bb, 0, 0) << (8 * bb);
+      }
+      a[s][i] = (int)v;
+    }
+  unsigned char* blk = lds + wave * (256 * NPB);
+  constexpr float kMagic = 12582912.0f;
+  const float lo = kMagic - g.qmax, hi = kMagic + g.qmax;
+#pragma unroll
+  for (int m = 0; m < NPB; ++m) {
+    v4i d = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[0], coeff[m][0], v4i{0, 0, 0, 0}, 0, 0, 0);
+    if constexpr (KS == 2) d = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[1], coeff[m][1], d, 0, 0, 0);
+    unsigned b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float v = __fmaf_rn((float)d[i], inv[m], kMagic);
+      b[i] = __float_as_uint(__builtin_amdgcn_fmed3f(v, lo, hi));
+    }
+    const unsigned w = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) | __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
+    *(unsigned*)(blk + (16 * m + (lane & 15)) * 16 + 4 * (lane >> 4)) = w;
+  }
+  __builtin_amdgcn_wave_barrier();  // LDS accesses of one wave complete in order
+  const unsigned vplane = (unsigned)g.Tp * (unsigned)g.Cp;
+  const __amdgpu_buffer_rsrc_t vres =
+      __builtin_amdgcn_make_buffer_rsrc((void*)V, 0, (int)(vplane * (unsigned)P), kBufferFlags);
+#pragma unroll
+  for (int h = 0; h < NST; ++h) {
+    const v4i d = *(const v4i*)(blk + min(64 * h + lane, 16 * NPB - 1) * 16);
+    __builtin_amdgcn_raw_buffer_store_b128(d, vres, p[h] >= 0 ? (unsigned)p[h] * vplane + (unsigned)c0 : 0x80000000u,
+                                           (unsigned)t * (unsigned)g.Cp, 0);
+  }
+}
+
+// Layers of a few images: up to one wave of 64 channels per SIMD (256 channels on 14x14 maps, us of
+// the kernel at 2 / 8 / 16 images, 4.0 / 5.0 / 7.9 against 7.9 / 8.7 / 9.0 of the kernel that
+// stages whole images; 32 images 12.2 against 8.7; 512 channels on 7x7 maps 3.0 / 4.6 / 4.7 against
+// 4.4 / 4.5 / 4.8 of input_transform_image_kernel, 32 images level, 64 behind).
+static bool image_input_few(const Geometry& g) { return g.alg == 4 && (long long)g.T * (g.Cp / 64) <= 1024; }
+
 bool image_input_supported(const Geometry& g) {
   if (g.alg < 0 || g.alg > 5) return false;
   if (g.th * g.tw > kImageMaxTiles) return false;
   if (g.H * g.W > 64 && image_window(g) > 128) return false;
   // the SFC-4 forms on larger maps (16 tiles of a 14x14 image, each reading 128 bytes of every
   // plane) are faster through the kernel that stages whole images (256 channels on 14x14
-  // maps, batch 64: 9.1 against 14.2 us)
-  if (g.H * g.W > 64 && g.alg >= 4) return false;
+  // maps, batch 64: 9.1 against 14.2 us) once they fill the chip; a single image has four
+  // workgroups there
+  if (g.H * g.W > 64 && g.alg >= 4 && !image_input_few(g)) return false;
   const long long xb = (long long)g.N * g.Cin * g.H * g.W;
   const long long vb = (long long)g.P * g.Tp * g.Cp;
   return xb < (1ll << 31) && vb < (1ll << 31);
@@ -262,6 +358,17 @@ static hipError_t launch_image_alg(const Geometry& g, const int8_t* x, void* V,
                                    const unsigned char* tab, hipStream_t s) {
   // 64 channels per wave (128, with 128-byte pieces of V per store, measured no faster: 512
   // channels on 7x7 maps, 256 images, 7x7 tiles: 9.8 against 9.1 us)
+  if constexpr (ALG == 4) {
+    if (image_input_few(g)) {
+      const unsigned grid16 = (unsigned)(((long long)g.T * (g.Cp / 16) + 3) / 4);
+      auto launch16 = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid16), dim3(256), 0, s, x, (int8_t*)V, tab, g);
+        return hipGetLastError();
+      };
+      return image_steps(g) == 1 ? launch16(input_transform_image16_kernel<ALG, 1>)
+                                 : launch16(input_transform_image16_kernel<ALG, 2>);
+    }
+  }
   const int ranges = g.Cp / 64;
   const unsigned grid = (unsigned)(((long long)g.T * ranges + 3) / 4);
   auto launch = [&](auto kernel) {

@@ -122,6 +122,16 @@ hipError_t launch_single16(int out, const Geometry& g, const int8_t* x, const Fi
 bool single16k_supported(const Geometry& g);
 hipError_t launch_single16k(int out, const Geometry& g, const int8_t* x, const FilterViews& f,
                             float x_scale, float inv_y, void* y, hipStream_t s, bool prepare = false);
+// SFC-4 (46 points) on small layers (sfc_small.hip): the whole path up to 128 input channels, on
+// the operand and factors of launch_single16; products + output transform for 256 and 512
+// channels, on those of launch_fused_quad
+bool single_small_supported(const Geometry& g);
+hipError_t launch_single_small(int out, const Geometry& g, const int8_t* x, const FilterViews& f,
+                               float x_scale, float inv_y, void* y, hipStream_t s, bool prepare = false);
+bool product_small_supported(const Geometry& g);
+int product_small_filter_count(const Geometry& g);
+hipError_t launch_product_small(int out, const Geometry& g, const void* V, const FilterViews& f,
+                                float x_scale, float inv_y, void* y, hipStream_t s);
 // single-kernel path: whether it covers this geometry, the bytes of its filter operand,
 // the regrouping of the canonical U, the processing order (position -> canonical point)
 bool single_supported(const Geometry& g);

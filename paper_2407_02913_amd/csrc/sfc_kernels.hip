@@ -392,6 +392,7 @@ hipError_t launch_input_transform(int mode, const Geometry& g, const int8_t* x, 
 hipError_t prepare_kernels(int path, int out, const Geometry& g) {
   const FilterViews none{};
   if (path == 2) {
+    if (single_small_supported(g)) return launch_single_small(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
     if (single16_supported(g)) return launch_single16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
     if (single16k_supported(g)) return launch_single16k(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
     return launch_single_conv(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
@@ -399,6 +400,7 @@ hipError_t prepare_kernels(int path, int out, const Geometry& g) {
   // the generic input kernel (geometries the int8 one does not take) stays under 64 KB
   hipError_t e = launch_input_transform_i8(g, nullptr, nullptr, nullptr, nullptr, nullptr, true);
   if (e != hipSuccess && e != hipErrorNotSupported) return e;
+  if (path == 1 && product_small_supported(g)) return hipSuccess;  // static LDS only
   if (path == 1)
     return quad16_supported(g)   ? launch_quad16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true)
            : splitk_supported(g) ? launch_splitk(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true)

@@ -796,3 +796,34 @@ def test_single_kernel_path_with_many_channel_chunks(binding, shape, alg):
     with pytest.raises(binding.SfcError) as e:
         binding.Plan(1, shape[1], 16, 28, 28, alg=alg, path="single")
     assert e.value.code == 2
+
+
+SMALL_LAYER_SHAPES = [  # (path, shape): the kernels for small layers (sfc_small.hip, 46 points)
+    ("single", (1, 16, 16, 32, 32)),    # one group of 16 channels, one of 16 filters
+    ("single", (1, 17, 33, 56, 56)),    # channel and filter groups with one member; two filter groups per workgroup
+    ("single", (2, 128, 136, 11, 7)),   # two chunks, nine filter groups, odd W
+    ("single", (4, 65, 20, 14, 14)),    # second chunk with one channel, whole images
+    ("single", (3, 64, 64, 26, 30)),    # W even, ragged tiles
+    ("fused", (1, 256, 256, 14, 14)),   # four tiles per workgroup
+    ("fused", (1, 200, 6, 9, 5)),       # a chunk partly empty, a filter quad with two filters, odd W
+    ("fused", (3, 512, 100, 13, 12)),   # 36 tiles: a ragged last block, W a multiple of 4
+    ("fused", (8, 460, 64, 7, 7)),      # eight chunks, the last one partly empty
+]
+
+
+@pytest.mark.parametrize("path,shape", SMALL_LAYER_SHAPES)
+def test_kernels_for_small_layers(binding, path, shape):
+    alg = "4x4_p46"
+    x, w, xs, ws = uniform_case(shape, 1900 + sum(shape))
+    print("case small layer", path, shape, flush=True)
+    xc, _, _, _ = uniform_case(shape, 1950 + sum(shape))
+    sx = oracle.calibrate_act_scales(xc // 2, alg)
+    sw = oracle.calibrate_filter_scales(w, alg)
+    y_ref, taps_ref = oracle.conv_requant(x, w, sx, sw, xs, ws, alg, return_taps=True)
+    y, taps = binding.conv2d(x, w, xs, ws, mode="requant", alg=alg, path=path, sx=sx, sw=sw, return_taps=True)
+    for name in taps:
+        assert np.array_equal(taps[name].astype(np.int64), taps_ref[name]), name
+    assert rel_err(y, y_ref) <= F32_TOL
+    y_scale = float(np.float32(max(y_ref.max(), 1e-6) / 127.0 * 0.8))
+    y8 = binding.conv2d(x, w, xs, ws, mode="requant", alg=alg, path=path, out="i8", sx=sx, sw=sw, y_scale=y_scale)
+    assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
