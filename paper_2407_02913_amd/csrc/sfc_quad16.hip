@@ -4,19 +4,22 @@
 
 namespace sfc {
 
-// waves per workgroup = groups of 16 filters per workgroup
-constexpr int kQuad16Waves = 4;
+hipError_t launch_quad16_7tap(int out, const Geometry& g, const void* V, const FilterViews& f,
+                              float x_scale, float inv_y, void* y, hipStream_t s, bool prepare);
 
 bool quad16_supported(const Geometry& g) {
-  if (g.alg != 4 && g.alg != 5) return false;
+  if (g.alg != 4 && g.alg != 5 && g.alg != 8) return false;
   const int kc = g.Cp / 64;
   // Up to four channel chunks: with eight a wave's filter operand stream (8 KiB per point) is
   // not hidden behind its own arithmetic (sfc_splitk.hip and the one-pair-per-lane kernel take
   // those layers).
   if (kc != 1 && kc != 2 && kc != 4) return false;
   // A wave takes 256 (tile, filter) pairs: with fewer than one wave per SIMD of the chip the
-  // one-pair-per-lane kernel, whose waves take 64, fills it better.
-  if ((long long)(g.Tp / 16) * ((g.Cout + 15) / 16) < 1024) return false;
+  // one-pair-per-lane kernel, whose waves take 64, fills it better.  Not so with 184 points,
+  // where that kernel's fourfold matrix work and operand reads outweigh it at every size (7x7
+  // filters, layer: 16 channels on one 32x32 map 30.3 us against 26.3 here, 128 channels on one
+  // 28x28 map 35.2 against 32.1, 256 channels on 14x14 maps at batch 32 67.3 against 59.5).
+  if (g.alg < 6 && (long long)(g.Tp / 16) * ((g.Cout + 15) / 16) < 1024) return false;
   const long long fgroups = quad16_filter_count(g) / 16;
   const long long ybytes = 4ll * g.N * g.Cout * g.H * g.W;
   const long long vbytes = (long long)g.P * g.Tp * g.Cp;
@@ -60,6 +63,7 @@ hipError_t launch_repack_filter16(const Geometry& g, int filters, const void* U,
     case 3: hipLaunchKernelGGL(repack_filter16_kernel<3>, grid, dim3(64), 0, s, (const int8_t*)U, (int8_t*)U16, g); break;
     case 4: hipLaunchKernelGGL(repack_filter16_kernel<4>, grid, dim3(64), 0, s, (const int8_t*)U, (int8_t*)U16, g); break;
     case 5: hipLaunchKernelGGL(repack_filter16_kernel<5>, grid, dim3(64), 0, s, (const int8_t*)U, (int8_t*)U16, g); break;
+    case 8: hipLaunchKernelGGL(repack_filter16_kernel<8>, grid, dim3(64), 0, s, (const int8_t*)U, (int8_t*)U16, g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -110,8 +114,12 @@ static hipError_t launch_quad16_alg(int out, const Geometry& g, const void* V, c
 hipError_t launch_quad16(int out, const Geometry& g, const void* V, const FilterViews& f,
                          float x_scale, float inv_y, void* y, hipStream_t s, bool prepare) {
   if (!quad16_supported(g) || out == 1) return hipErrorNotSupported;
-  return g.alg == 4 ? launch_quad16_alg<4>(out, g, V, f, x_scale, inv_y, y, s, prepare)
-                    : launch_quad16_alg<5>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+  switch (g.alg) {
+    case 4: return launch_quad16_alg<4>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+    case 5: return launch_quad16_alg<5>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+    case 8: return launch_quad16_7tap(out, g, V, f, x_scale, inv_y, y, s, prepare);
+  }
+  return hipErrorNotSupported;
 }
 
 }  // namespace sfc

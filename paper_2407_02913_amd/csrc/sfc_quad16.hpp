@@ -1,5 +1,6 @@
-// Transform-domain products + output transform for the SFC-4(4x4,3x3) forms with no surplus
-// matrix work (gfx950): a wave owns 16 tiles x 16 filters, four (tile, filter) pairs per lane.
+// Transform-domain products + output transform with no surplus matrix work (gfx950), for the
+// SFC-4(4x4,3x3) forms and SFC-6(4x4,7x7) with 184 points: a wave owns 16 tiles x 16 filters,
+// four (tile, filter) pairs per lane.
 //
 // The int8 MFMA 16x16x64 gives lane l the four results D[4(l/16) + i][l%16], i = 0..3.  With
 // the A operand holding ONE point for 16 filters (row r = filter f0 + 4(r%4) + r/4) and the B
@@ -16,6 +17,7 @@
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
 #include "sfc_points.hpp"
+#include "sfc_stream_outputs.hpp"
 #include "sfc_store.hpp"
 
 namespace sfc {
@@ -54,6 +56,10 @@ template <>
 struct Half<f4> {
   static __device__ __forceinline__ f4 apply(const f4& a) { return a * f4(0.5f); }
 };
+template <>
+struct Third<f4> {
+  static __device__ __forceinline__ f4 apply(const f4& a) { return a * f4(1.0f / 3.0f); }
+};
 
 // Lane n of the reader's row of 16 lanes (its quarter of the wave), as a DPP row broadcast:
 // folds into the instruction that takes the value.
@@ -61,6 +67,9 @@ template <int N>
 __device__ __forceinline__ float row_lane(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xf, 0xf, false));
 }
+
+// waves per workgroup of the fused kernel = groups of 16 filters per workgroup
+constexpr int kQuad16Waves = 4;
 
 // V buffers of the fused kernel (groups of four points in LDS) and groups in flight in
 // registers behind them, by channel chunks: the load of a group is issued kVRegs groups
@@ -99,29 +108,33 @@ constexpr unsigned quad16_lds_layout(int what) {
 //                 buffers of the groups before pg
 // Software pipeline: call j issues the matrix instructions of position j + 1 and then converts
 // the sums of position j, so the matrix pipe works under the vector arithmetic of the output
-// transform.  Leaves z[b][o1] of the lane's four pairs (f4 element i: filter quad i).
-template <int ALG, int KC, int VB, int PS = KC * 1024, typename Sync>
-__device__ __forceinline__ void quad16_products(const unsigned char* vbuf, int lane,
-                                                __amdgpu_buffer_rsrc_t ures, unsigned a_wave,
-                                                __amdgpu_buffer_rsrc_t dres, unsigned d_wave,
-                                                Sync&& sync,
-                                                f4 (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M]) {
+// transform.
+//   consume(next) takes the products of the lane's four pairs (f4 element i: filter quad i) in
+//                 processing order, next(integral_constant<int, j>) being position j
+template <int ALG, int KC, int VB, int PS = KC * 1024, typename Sync, typename Consume>
+__device__ __forceinline__ void quad16_stream(const unsigned char* vbuf, int lane,
+                                              __amdgpu_buffer_rsrc_t ures, unsigned a_wave,
+                                              __amdgpu_buffer_rsrc_t dres, unsigned d_wave,
+                                              Sync&& sync, Consume&& consume) {
   constexpr int PP = Order<ALG>::PP;
   constexpr int GROUP_BYTES = 4 * PS;      // PS: bytes from one position's V to the next
   constexpr int STEPS = PP * KC;           // filter-operand blocks of the wave
   constexpr int RA = 8;                    // ... in flight
   constexpr int NDB = (PP + 15) / 16;      // blocks of 16 positions' factors
+  constexpr int DR = NDB > 4 ? 2 : NDB;    // ... held at a time
   const unsigned a_lane = (unsigned)lane * 16u;
   const unsigned d_lane = (unsigned)(lane & 15) * 64u + (unsigned)(lane >> 4) * 16u;
   v4i aring[RA];
-  v4f dblk[NDB];
+  v4f dblk[DR];
   auto load_a = [&](int s) {
     aring[s % RA] = __builtin_amdgcn_raw_buffer_load_b128(ures, a_lane, a_wave + (unsigned)s * 1024u, 0);
   };
-#pragma unroll
-  for (int m = 0; m < NDB; ++m)  // (a last block may reach past the wave's table: never used)
-    dblk[m] = __builtin_bit_cast(
+  auto load_d = [&](int m) {  // (a last block may reach past the wave's table: never used)
+    dblk[m % DR] = __builtin_bit_cast(
         v4f, __builtin_amdgcn_raw_buffer_load_b128(dres, d_lane, d_wave + (unsigned)m * 1024u, 0));
+  };
+#pragma unroll
+  for (int m = 0; m < DR; ++m) load_d(m);
 #pragma unroll
   for (int s = 0; s < RA && s < STEPS; ++s) load_a(s);
   const unsigned char* blane = vbuf + (lane & 15) * 64 + (lane >> 4) * 16;
@@ -172,17 +185,31 @@ __device__ __forceinline__ void quad16_products(const unsigned char* vbuf, int l
     f4 v;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float t = (float)acc_cur[i] * row_lane<j & 15>(dblk[j >> 4][i]);
+      float t = (float)acc_cur[i] * row_lane<j & 15>(dblk[(j >> 4) % DR][i]);
       // the scaled products are materialized here, the accumulator is not kept alive
       asm volatile("" : "+v"(t));
       v.v[i] = t;
     }
+    if constexpr ((j & 15) == 15 && (j >> 4) + DR < NDB) load_d((j >> 4) + DR);
     acc_cur = acc_new;
     __builtin_amdgcn_sched_barrier(0);
     return v;
   };
   // positions P .. PP-1 hold no point: their filter operand is zero, their products unused
-  stream_vertical<ALG, f4>(next, z);
+  consume(next);
+}
+
+// The same up to the vertical axis: leaves z[b][o1] of the lane's four pairs.
+template <int ALG, int KC, int VB, int PS = KC * 1024, typename Sync>
+__device__ __forceinline__ void quad16_products(const unsigned char* vbuf, int lane,
+                                                __amdgpu_buffer_rsrc_t ures, unsigned a_wave,
+                                                __amdgpu_buffer_rsrc_t dres, unsigned d_wave,
+                                                Sync&& sync,
+                                                f4 (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M]) {
+  quad16_stream<ALG, KC, VB, PS>(vbuf, lane, ures, a_wave, dres, d_wave, sync,
+                                 [&](auto& next) __attribute__((always_inline)) {
+                                   stream_vertical<ALG, f4>(next, z);
+                                 });
 }
 
 // y of the wave's 16 tiles x 16 filters from z (pair i of lane l: tile l%16, filter
@@ -365,14 +392,18 @@ __global__ __launch_bounds__(NW * 64, 2) void quad16_kernel(
   // group pg + 1 will take (VB >= 2; with VB = 3 the store may run a group earlier).
   constexpr int VB = quad16_vbufs(KC), VR = quad16_vregs(KC);
   v4i lreg[VR][NL];
+  // V offsets of the positions, 64 to a register: a piece takes the one of its point by its lane
+  // number.  (Selected among four constants instead, the loads of every group became branches
+  // with a copy of the load each, four to a piece: 516 loads and 400 branches in the code at
+  // 128 channels and 184 points, 1067 and 900 at 256.)
+  unsigned vofs[(PP + 63) / 64];
+#pragma unroll
+  for (int m = 0; m < (PP + 63) / 64; ++m) vofs[m] = (unsigned)max(order.pt[min(64 * m + lane, PP - 1)], 0) * vplane;
   auto load_regs = [&](int pg) {
-    const int p0 = max(order.pt[4 * pg], 0), p1 = max(order.pt[4 * pg + 1], 0),
-              p2 = max(order.pt[4 * pg + 2], 0), p3 = max(order.pt[4 * pg + 3], 0);
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const int r = rsel[i];
-      const int p = r == 0 ? p0 : r == 1 ? p1 : r == 2 ? p2 : p3;
-      lreg[pg % VR][i] = __builtin_amdgcn_raw_buffer_load_b128(vres, gsrc[i], (unsigned)p * vplane, 0);
+      const unsigned off = (unsigned)__builtin_amdgcn_readlane((int)vofs[pg >> 4], ((4 * pg) & 63) + rsel[i]);
+      lreg[pg % VR][i] = __builtin_amdgcn_raw_buffer_load_b128(vres, gsrc[i], off, 0);
     }
   };
   auto store_lds = [&](int pg) {
@@ -390,11 +421,30 @@ __global__ __launch_bounds__(NW * 64, 2) void quad16_kernel(
     if (pg + 1 + VR < PG) load_regs(pg + 1 + VR);
     __syncthreads();
   };
-  f4 z[NC][M];
-  quad16_products<ALG, KC, VB>(vbuf, lane, ures, (unsigned)fg * (unsigned)(PP * KC * 1024), dres,
-                           (unsigned)fg * (unsigned)(PP * 64), sync, z);
-  __syncthreads();  // the staging blocks take the place of the V buffers
-  quad16_store<ALG, OUT, EV>(z, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+  const unsigned a_wave = (unsigned)fg * (unsigned)(PP * KC * 1024), d_wave = (unsigned)fg * (unsigned)(PP * 64);
+  if constexpr (Tr::kFamily == 4) {
+    f4 z[NC][M];
+    quad16_products<ALG, KC, VB>(vbuf, lane, ures, a_wave, dres, d_wave, sync, z);
+    __syncthreads();  // the staging blocks take the place of the V buffers
+    quad16_store<ALG, OUT, EV>(z, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+  } else {
+    // (EV = 0: the width of a store is chosen here, the products are not compiled once for each)
+    static_assert(M == 4, "outputs kept: the 7x7-filter form");
+    f4 out[M][M];
+    quad16_stream<ALG, KC, VB>(vbuf, lane, ures, a_wave, dres, d_wave, sync,
+                               [&](auto& next) __attribute__((always_inline)) {
+                                 auto settle = [](f4& v) __attribute__((always_inline)) {
+#pragma unroll
+                                   for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(v.v[i]));
+                                 };
+                                 stream_outputs<ALG, f4>(next, settle, out);
+                               });
+    __syncthreads();
+    constexpr int COLS = kOutputColumns + M;
+    if (g.W % 4 == 0) quad16_store<COLS, OUT, 4>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+    else if (g.W % 2 == 0) quad16_store<COLS, OUT, 2>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+    else quad16_store<COLS, OUT, 1>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+  }
 }
 
 }  // namespace sfc

@@ -8,11 +8,13 @@
 //   A <alg> <p> <M*M ints>     output transform row p (times 36; times 16 for 4x4)
 //   S <alg> <p> <M*M ints>     the same row through the streaming form of the fused kernels
 //                              (products fed in processing order, stream_vertical + stream_row)
+//   O <alg> <p> <M*M ints>     8: the same through stream_outputs, which keeps the outputs
 #include <cmath>
 #include <cstdio>
 #include <vector>
 
 #include "../../paper_2407_02913_amd/csrc/sfc_points.hpp"
+#include "../../paper_2407_02913_amd/csrc/sfc_stream_outputs.hpp"
 
 using namespace sfc;
 
@@ -69,6 +71,22 @@ void dump() {
     }
     std::printf("\n");
     if (q == 0 && j != P) std::printf("S %d -1 %d\n", ALG, j);  // must consume exactly P products
+  }
+  if constexpr (ALG == 8) {
+    for (int q = 0; q < P; ++q) {
+      int j = 0;
+      auto next = [&]() -> float { return order.pt[j++] == q ? 3.0f : 0.0f; };
+      float y[M][M];
+      stream_outputs<ALG, float>(next, [](float&) {}, y);
+      std::printf("O %d %d", ALG, q);
+      for (int o1 = 0; o1 < M; ++o1) {
+        float out[M];
+        stream_row<kOutputColumns + M, float>(y, o1, out);
+        for (int o2 = 0; o2 < M; ++o2) std::printf(" %d", (int)std::lround(out[o2] / 3.0f));
+      }
+      std::printf("\n");
+      if (q == 0 && j != P) std::printf("O %d -1 %d\n", ALG, j);
+    }
   }
   for (int j = P; j < Order<ALG>::PP; ++j)
     if (order.pt[j] != -1) std::printf("S %d -2 %d\n", ALG, j);

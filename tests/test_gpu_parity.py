@@ -504,6 +504,29 @@ def test_5x5_fused_path_matches_oracle(binding, shape, alg):
     assert rel_err(y, y_ref) <= F32_TOL
 
 
+@pytest.mark.parametrize("shape", [
+    (1, 64, 64, 16, 16),    # one chunk, 16 tiles: exactly one block, rows of four outputs per store
+    (2, 128, 65, 9, 18),    # two chunks, one filter beyond a workgroup's 64, pairs per store
+    (3, 193, 16, 11, 13),   # four chunks, the last with one channel, single outputs per store
+    (17, 256, 130, 4, 4),   # one tile per image, a second block with one tile
+])
+def test_7x7_filters_four_pairs_per_lane(binding, shape):
+    """The 184-point products kernel that keeps the outputs: its store widths, chunk counts and
+    ragged blocks, float32 and int8, against the oracle."""
+    alg = "4x4_7x7_p184"
+    x, w, xs, ws = uniform_case(shape, 2600 + sum(shape), r=7)
+    print("case 7x7 four pairs", shape, flush=True)
+    xc, _, _, _ = uniform_case(shape, 2700 + sum(shape))
+    sx = oracle.calibrate_act_scales(xc // 2, alg)
+    sw = oracle.calibrate_filter_scales(w, alg)
+    y_ref = oracle.conv_requant(x, w, sx, sw, xs, ws, alg)
+    args = dict(mode="requant", alg=alg, path="fused", sx=sx, sw=sw)
+    assert rel_err(binding.conv2d(x, w, xs, ws, **args), y_ref) <= F32_TOL
+    y_scale = float(np.float32(max(y_ref.max(), 1e-6) / 127.0 * 0.8))
+    y8 = binding.conv2d(x, w, xs, ws, out="i8", y_scale=y_scale, **args)
+    assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
+
+
 SINGLE_SHAPES = [
     (1, 16, 16, 32, 32),
     (2, 3, 5, 14, 14),
