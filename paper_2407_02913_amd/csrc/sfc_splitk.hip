@@ -119,16 +119,18 @@ __global__ __launch_bounds__(kSplitWaves * 64, 1) void splitk_kernel(
     ldst[i] = (unsigned)(((r * KC + (ch >> 2)) * 16 + tile) * 64 + (ch & 3) * 16);
   }
   v4i lreg[NL];
+  // V offsets of the positions, 64 to a register: a piece takes the one of its point by its lane
+  // number (selected among four constants, the loads of every group became branches with a copy
+  // of the load each: 13-layer stack at batch 64 359.7 us, now 356.3).  Positions without a point (the tail of the last group of an SFC-4 form)
+  // re-read point 0; their filter operand is zero and their sums are never taken.
+  unsigned vofs[(PP + 63) / 64];
+#pragma unroll
+  for (int m = 0; m < (PP + 63) / 64; ++m) vofs[m] = (unsigned)max(order.pt[min(64 * m + lane, PP - 1)], 0) * vplane;
   auto load_regs = [&](int pg) {
-    // positions without a point (the tail of the last group of an SFC-4 form) re-read point 0;
-    // their filter operand is zero and their sums are never taken
-    const int p0 = max(order.pt[4 * pg], 0), p1 = max(order.pt[4 * pg + 1], 0),
-              p2 = max(order.pt[4 * pg + 2], 0), p3 = max(order.pt[4 * pg + 3], 0);
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const int r = rsel[i];
-      const int p = r == 0 ? p0 : r == 1 ? p1 : r == 2 ? p2 : p3;
-      lreg[i] = __builtin_amdgcn_raw_buffer_load_b128(vres, gsrc[i], (unsigned)p * vplane, 0);
+      const unsigned off = (unsigned)__builtin_amdgcn_readlane((int)vofs[pg >> 4], ((4 * pg) & 63) + rsel[i]);
+      lreg[i] = __builtin_amdgcn_raw_buffer_load_b128(vres, gsrc[i], off, 0);
     }
   };
   auto store_lds = [&](int pg) {
