@@ -31,9 +31,7 @@ struct sfc_plan_s {
   bool filter_ready;
   int quad_filters;  // filters covered by the regrouped filter operand (0: none)
   int dq_filters;    // filters in the [filter][processing position] dequantization table (0: none)
-  bool quad16;       // filter operand in groups of 16 filters (sfc_quad16.hpp, sfc_splitk.hip)
-  bool splitk;       // fused path: input channels split over the waves of a workgroup
-  bool small;        // single and fused paths: the kernels for small layers (sfc_small.hip)
+  sfc::Kernel kernel;  // fused and single paths: what runs, and with it the filter operand's layout
   float inv_y;  // 1 / output scale (SFC_OUT_I8_RELU), 0: not set
 };
 
@@ -214,19 +212,18 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
   p->off_dq_single = off;
   p->off_U_single = off;
   p->quad_filters = 0;
-  p->small = d.path == SFC_PATH_SINGLE  ? sfc::single_small_supported(g)
-             : d.path == SFC_PATH_FUSED ? sfc::product_small_supported(g)
-                                        : false;
-  const bool fused_large = d.path == SFC_PATH_FUSED && !p->small;
-  p->splitk = fused_large && !sfc::quad16_supported(g) && sfc::splitk_supported(g);
-  p->quad16 = p->splitk || (fused_large && sfc::quad16_supported(g)) ||
-              (d.path == SFC_PATH_SINGLE && (sfc::single16_supported(g) || sfc::single16k_supported(g)));
-  if (d.path == SFC_PATH_SINGLE) p->quad_filters = p->quad16 ? g.Kp : (g.Cout + 63) / 64 * 64;
-  if (d.path == SFC_PATH_FUSED)
-    p->quad_filters = p->small    ? sfc::product_small_filter_count(g)
-                      : p->splitk ? sfc::splitk_filter_count(g)
-                      : p->quad16 ? sfc::quad16_filter_count(g)
-                                  : sfc::quad_filter_count(g);
+  p->kernel = sfc::choose_kernel(d.path, g);
+  switch (p->kernel) {
+    case sfc::Kernel::kStaged: break;
+    case sfc::Kernel::kFusedQuad: p->quad_filters = sfc::quad_filter_count(g); break;
+    case sfc::Kernel::kQuad16: p->quad_filters = sfc::quad16_filter_count(g); break;
+    case sfc::Kernel::kSplitK: p->quad_filters = sfc::splitk_filter_count(g); break;
+    case sfc::Kernel::kProductSmall: p->quad_filters = sfc::product_small_filter_count(g); break;
+    case sfc::Kernel::kSingleConv: p->quad_filters = (g.Cout + 63) / 64 * 64; break;
+    case sfc::Kernel::kSingle16:
+    case sfc::Kernel::kSingle16K:
+    case sfc::Kernel::kSingleSmall: p->quad_filters = g.Kp; break;
+  }
   // the staged output transform reads the same [filter][position] table as the fused kernels
   p->dq_filters = p->quad_filters;
   if (d.path == SFC_PATH_STAGED && d.mode == SFC_MODE_REQUANT_I8) p->dq_filters = g.Kp;
@@ -398,7 +395,7 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
     std::vector<int> pt(pp, -1);
     sfc::single_point_order(plan->d.alg, pt.data());
     float* dqs = table(plan->off_dq_single);
-    if (plan->quad16) {
+    if (sfc::groups_of_16(plan->kernel)) {
       // [group of 16 filters][processing position][lane quarter q][i]: filter 16*fg + 4*i + q
       for (int k = 0; k < g.Cout; ++k) {
         const int fg = k >> 4, i = (k & 15) >> 2, q = k & 3;
@@ -426,9 +423,9 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   const FilterViews f = views(plan, filter_dev);
   if (sfc::launch_filter_transform(plan->d.mode, g, w_dev, f, s) != hipSuccess)
     return SFC_EHIP;
-  if (quad && (plan->quad16 ? sfc::launch_repack_filter16(g, plan->quad_filters, f.U, f.U_single, s)
-                            : sfc::launch_repack_filter(g, plan->quad_filters, f.U, f.U_single, s)) !=
-                  hipSuccess)
+  if (quad && (sfc::groups_of_16(plan->kernel)
+                   ? sfc::launch_repack_filter16(g, plan->quad_filters, f.U, f.U_single, s)
+                   : sfc::launch_repack_filter(g, plan->quad_filters, f.U, f.U_single, s)) != hipSuccess)
     return SFC_EHIP;
   plan->filter_dev = filter_dev;
   plan->filter_ready = true;
@@ -451,14 +448,18 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
     const FilterViews f = views(plan, plan->filter_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    if (plan->small)
-      e = sfc::launch_single_small(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
-    else if (!plan->quad16)
-      e = sfc::launch_single_conv(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
-    else if (plan->g.Cp <= 128)
-      e = sfc::launch_single16(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
-    else
-      e = sfc::launch_single16k(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
+    switch (plan->kernel) {
+      case sfc::Kernel::kSingleSmall:
+        e = sfc::launch_single_small(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
+        break;
+      case sfc::Kernel::kSingle16:
+        e = sfc::launch_single16(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
+        break;
+      case sfc::Kernel::kSingle16K:
+        e = sfc::launch_single16k(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
+        break;
+      default: e = sfc::launch_single_conv(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
+    }
     if (e != hipSuccess) return SFC_EHIP;
     return SFC_OK;
   }
@@ -475,13 +476,21 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
       return SFC_EHIP;
   }
   if (fused) {
-    if (tail &&
-        (plan->small    ? sfc::launch_product_small(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)
-         : plan->splitk ? sfc::launch_splitk(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)
-         : plan->quad16 ? sfc::launch_quad16(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)
-                        : sfc::launch_fused_quad(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s)) !=
-            hipSuccess)
-      return SFC_EHIP;
+    if (!tail) return SFC_OK;
+    hipError_t e;
+    switch (plan->kernel) {
+      case sfc::Kernel::kProductSmall:
+        e = sfc::launch_product_small(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
+        break;
+      case sfc::Kernel::kSplitK:
+        e = sfc::launch_splitk(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
+        break;
+      case sfc::Kernel::kQuad16:
+        e = sfc::launch_quad16(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
+        break;
+      default: e = sfc::launch_fused_quad(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
+    }
+    if (e != hipSuccess) return SFC_EHIP;
     return SFC_OK;
   }
   int32_t* M = reinterpret_cast<int32_t*>(ws + plan->off_M);

@@ -142,6 +142,26 @@ void single_point_order(int alg, int* pt /*[P]*/);
 hipError_t launch_single_conv(int out, const Geometry& g, const int8_t* x, const FilterViews& f,
                               float x_scale, float inv_y, void* y, hipStream_t s,
                               bool prepare = false);
+// The kernel that does the products of a requantized layer on `path` (sfc_path); what the plan
+// lays out for it and what a call launches both follow from this.
+enum class Kernel {
+  kStaged,        // sfc_gemm.hip
+  kFusedQuad,     // sfc_fused_quad.hpp
+  kQuad16,        // sfc_quad16.hpp
+  kSplitK,        // sfc_splitk.hip
+  kProductSmall,  // sfc_small.hip
+  kSingleConv,    // sfc_single.hip
+  kSingle16,      // sfc_single16.hip
+  kSingle16K,     // sfc_single16k.hip
+  kSingleSmall,   // sfc_small.hip
+};
+Kernel choose_kernel(int path, const Geometry& g);
+// whether it reads filter operand and factors in groups of 16 filters (launch_quad16), else one
+// block per four points and four filters
+inline bool groups_of_16(Kernel k) {
+  return k == Kernel::kQuad16 || k == Kernel::kSplitK || k == Kernel::kSingle16 || k == Kernel::kSingle16K ||
+         k == Kernel::kSingleSmall;
+}
 // Requantized mode: prepares every kernel that `path` (sfc_path) launches for this geometry
 // and output type.  Once per plan, from sfc_transform_filter.
 hipError_t prepare_kernels(int path, int out, const Geometry& g);

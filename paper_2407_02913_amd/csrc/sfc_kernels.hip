@@ -389,23 +389,39 @@ hipError_t launch_input_transform(int mode, const Geometry& g, const int8_t* x, 
   return launch_input_alg<0>(g, x, V, inv_sx, nullptr, s);
 }
 
+Kernel choose_kernel(int path, const Geometry& g) {
+  if (path == 2)
+    return single_small_supported(g) ? Kernel::kSingleSmall
+           : single16_supported(g)   ? Kernel::kSingle16
+           : single16k_supported(g)  ? Kernel::kSingle16K
+                                     : Kernel::kSingleConv;
+  if (path == 1)
+    return product_small_supported(g) ? Kernel::kProductSmall
+           : quad16_supported(g)      ? Kernel::kQuad16
+           : splitk_supported(g)      ? Kernel::kSplitK
+                                      : Kernel::kFusedQuad;
+  return Kernel::kStaged;
+}
+
 hipError_t prepare_kernels(int path, int out, const Geometry& g) {
   const FilterViews none{};
-  if (path == 2) {
-    if (single_small_supported(g)) return launch_single_small(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
-    if (single16_supported(g)) return launch_single16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
-    if (single16k_supported(g)) return launch_single16k(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
-    return launch_single_conv(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+  if (path != 2) {
+    // the generic input kernel (geometries the int8 one does not take) stays under 64 KB
+    const hipError_t e = launch_input_transform_i8(g, nullptr, nullptr, nullptr, nullptr, nullptr, true);
+    if (e != hipSuccess && e != hipErrorNotSupported) return e;
   }
-  // the generic input kernel (geometries the int8 one does not take) stays under 64 KB
-  hipError_t e = launch_input_transform_i8(g, nullptr, nullptr, nullptr, nullptr, nullptr, true);
-  if (e != hipSuccess && e != hipErrorNotSupported) return e;
-  if (path == 1 && product_small_supported(g)) return hipSuccess;  // static LDS only
-  if (path == 1)
-    return quad16_supported(g)   ? launch_quad16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true)
-           : splitk_supported(g) ? launch_splitk(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true)
-                                 : launch_fused_quad(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
-  return launch_output_sums(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+  switch (choose_kernel(path, g)) {
+    case Kernel::kStaged: return launch_output_sums(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kFusedQuad: return launch_fused_quad(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kQuad16: return launch_quad16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kSplitK: return launch_splitk(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kProductSmall: return hipSuccess;  // static LDS only
+    case Kernel::kSingleConv: return launch_single_conv(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kSingle16: return launch_single16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kSingle16K: return launch_single16k(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kSingleSmall: return launch_single_small(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_act_absmax(const Geometry& g, const int8_t* x, int32_t* maxima, hipStream_t s) {

@@ -591,6 +591,61 @@ def test_single_kernel_path_with_two_channel_chunks(binding, shape, alg):
     assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
 
 
+# 46 points, just past the layer sizes that the kernels for small layers take
+# (tests/test_host_logic.py asks the library that these are the kernels): the edges of the kernels
+# for larger layers, as the shapes above are theirs for 49 points.
+PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
+    ("single", "single16", (19, 33, 17, 56, 56)),    # two tile-column chunks per strip, two filter groups
+    ("single", "single16", (1030, 20, 8, 7, 7)),     # whole images, odd W, half a filter group
+    ("single", "single16", (259, 9, 8, 14, 14)),     # one image per workgroup, pairs per store
+    ("single", "single16", (430, 3, 4, 12, 12)),     # several strips per workgroup, the last ragged
+    ("single", "single16", (323, 2, 3, 13, 9)),
+    ("single", "single16", (4100, 1, 1, 1, 1)),      # one pixel: sixteen images per workgroup
+    ("single", "single16", (131, 5, 9, 6, 61)),      # wide and flat
+    ("single", "single16", (207, 7, 130, 7, 7)),     # three workgroups along Cout
+    ("single", "single16", (171, 64, 72, 11, 7)),
+    ("single", "single16", (75, 64, 16, 28, 28)),
+    ("single", "single16", (515, 65, 8, 7, 7)),      # from here two 64-channel chunks
+    ("single", "single16", (53, 128, 136, 11, 7)),   # nine groups of 16 filters
+    ("single", "single16", (37, 100, 24, 28, 28)),   # rectangles of two strips
+    ("single", "single16", (131, 128, 16, 14, 14)),
+    ("single", "single16", (65, 127, 5, 6, 61)),
+    ("single", "single16", (3, 96, 130, 56, 56)),    # one strip per workgroup
+    ("single", "single16", (43, 70, 40, 9, 20)),
+    ("fused", "quad16", (203, 33, 130, 12, 12)),     # one chunk, rows of four outputs per store
+    ("fused", "quad16", (81, 100, 264, 9, 13)),      # two chunks, single outputs per store
+    ("fused", "quad16", (115, 193, 136, 14, 14)),    # four chunks, the last with one channel; pairs per store
+    ("fused", "quad16", (549, 200, 72, 11, 7)),      # four chunks, odd W, a ragged last tile block
+    ("fused", "fused_quad", (41, 200, 72, 11, 7)),
+    ("fused", "fused_quad", (9, 193, 136, 14, 14)),
+    ("fused", "splitk", (171, 500, 24, 8, 8)),
+    ("fused", "splitk", (15, 460, 72, 14, 14)),      # three filter pairs of 32
+    ("fused", "splitk", (35, 512, 40, 9, 13)),       # odd W, a ragged last tile block
+]
+
+
+@pytest.mark.parametrize("path,kernel,shape", PAST_SMALL_LAYERS)
+def test_46_points_past_the_small_layers(binding, path, kernel, shape):
+    alg = "4x4_p46"
+    x, w, xs, ws = uniform_case(shape, 2800 + sum(shape))
+    print("case past small", path, kernel, shape, flush=True)
+    xc, _, _, _ = uniform_case((min(shape[0], 4), *shape[1:]), 2900 + sum(shape))
+    sx = oracle.calibrate_act_scales(xc // 2, alg)
+    sw = oracle.calibrate_filter_scales(w, alg)
+    y_ref, taps_ref = oracle.conv_requant(x, w, sx, sw, xs, ws, alg, return_taps=True)
+    args = dict(mode="requant", alg=alg, path=path, sx=sx, sw=sw)
+    y, taps = binding.conv2d(x, w, xs, ws, return_taps=True, **args)
+    for name in taps:
+        assert np.array_equal(taps[name].astype(np.int64), taps_ref[name]), name
+    assert rel_err(y, y_ref) <= F32_TOL
+    y_scale = float(np.float32(max(y_ref.max(), 1e-6) / 127.0 * 0.8))
+    y8 = binding.conv2d(x, w, xs, ws, out="i8", y_scale=y_scale, **args)
+    differ = check_i8_against_oracle(y8, y_ref, y_scale)  # (only ties of the rounding may)
+    # one channel, one pixel: y is j/127 of its maximum, j = -127 .. 127, or 1.25 j steps of the
+    # output: a tie for every second even j, each one 1/255 of the values
+    assert differ < (63 / 255 if shape[1:] == (1, 1, 1, 1) else 1e-3)
+
+
 def test_single_kernel_path_channel_limits(binding):
     with pytest.raises(binding.SfcError) as e:
         binding.Plan(1, 65, 16, 8, 8, path="single")  # 6x6 tiles: one chunk of 64 channels

@@ -248,6 +248,51 @@ def test_kernel_add_networks_realize_the_oracle_matrices(kernel_maps, alg_id, al
         assert np.array_equal(kernel_maps[("O", alg_id)], a2)
 
 
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    """(path, algorithm, shape) of layers -> the product kernels the built library picks for them."""
+    from paper_2407_02913_amd import binding
+
+    exe = tmp_path_factory.mktemp("host") / "route"
+    src = os.path.join(ROOT, "tests", "host", "route.cpp")
+    where = os.path.dirname(binding.LIB_PATH)
+    subprocess.run(["/opt/rocm/bin/hipcc", "--cuda-host-only", "-O1", "-std=c++17", src, "-L", where,
+                    "-l:" + os.path.basename(binding.LIB_PATH), "-Wl,-rpath," + where, "-o", str(exe)],
+                   check=True, capture_output=True)
+
+    def ask(layers):
+        text = "".join(f"{binding.PATH[path]} {binding.ALG[alg]} {' '.join(map(str, shape))}\n"
+                       for path, alg, shape in layers)
+        out = subprocess.run([str(exe)], input=text, check=True, capture_output=True, text=True).stdout
+        return out.splitlines()
+
+    return ask
+
+
+def test_kernels_of_the_shapes_past_the_small_layers(lib, routes):
+    """The shapes of the GPU parity test run the kernels they are there for; one image of the same
+    geometry runs a kernel for small layers where there is one."""
+    import test_gpu_parity as parity
+
+    cases = parity.PAST_SMALL_LAYERS
+    assert routes([(path, "4x4_p46", shape) for path, _, shape in cases]) == [kernel for _, kernel, _ in cases]
+    one = routes([(path, "4x4_p46", (1, *shape[1:])) for path, _, shape in cases])
+    for (path, _, shape), kernel in zip(cases, one):
+        small = "single_small" if path == "single" else "product_small" if shape[1] > 128 else "fused_quad"
+        assert kernel == small, shape
+
+
+def test_every_kernel_choice_fits_the_filter_layout(lib, routes):
+    """Single path: the kernel for small layers reads the operand of the 16-filter kernels, and is
+    only picked where one of those would be without it."""
+    shapes = [(n, cin, cout, h, w) for n in (1, 3, 40) for cin in (1, 16, 64, 65, 128) for cout in (1, 40, 300)
+              for h, w in ((1, 1), (7, 7), (13, 9), (56, 56), (9, 200), (300, 5), (4, 1024))]
+    for shape, kernel, kernel49 in zip(shapes, routes([("single", "4x4_p46", s) for s in shapes]),
+                                       routes([("single", "4x4_p49", s) for s in shapes])):
+        assert kernel in ("single_small", "single16"), (shape, kernel)
+        assert kernel49 == "single16", (shape, kernel49)
+
+
 def test_bench_operation_counts_match_the_add_networks(tmp_path):
     """bench.py's vector-ALU roofline counts: recounted from sfc_points.hpp with a counting type."""
     import bench
