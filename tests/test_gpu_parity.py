@@ -446,6 +446,51 @@ def test_full_size_exact_against_direct_conv(binding, name):
     assert np.array_equal(acc.astype(np.int64), ref)
 
 
+@pytest.mark.parametrize("alg,out", [("6x6_p88", "i32"), ("7x7_p132", "f32"), ("4x4_p46", "i32")])
+def test_exact_mode_beyond_32_bit_offsets(binding, alg, out):
+    """x, V and M of more than 2 GiB each: the input and output kernels with 64-bit offsets.  Images
+    are independent, so the result is that of the same batch in eight calls, whose tensors are
+    within 2 GiB and go through the matrix-core kernels; the first and the last image are compared
+    with the oracle as well."""
+    import torch
+
+    n, parts, cin, cout, h, w = 10752, 8, 64, 5, 56, 56
+    print("case exact large", alg, out, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    x = torch.randint(-128, 128, (n, cin, h, w), dtype=torch.int8, device="cuda", generator=gen)
+    assert x.numel() >= 2**31
+    wt = torch.randint(-128, 128, (cout, cin, 3, 3), dtype=torch.int8, device="cuda", generator=gen)
+    ws = np.linspace(0.005, 0.02, cout).astype(np.float32)
+    dtype = {"i32": torch.int32, "f32": torch.float32}[out]
+
+    def run(batch):
+        plan = binding.Plan(batch.shape[0], cin, cout, h, w, alg=alg, mode="exact", out=out)
+        fbuf = binding.device_buffer(plan.filter_bytes)
+        wbuf = binding.device_buffer(plan.workspace_bytes)
+        y = torch.full((batch.shape[0], cout, h, w), -7, dtype=dtype, device="cuda")
+        plan.transform_filter(wt, ws, fbuf)
+        plan.conv2d(batch, 0.02, y, wbuf)
+        torch.cuda.synchronize()
+        points, tiles = plan.P, plan.tiles
+        plan.close()
+        return y, 4 * points * tiles * 16  # (M holds 16 filters at least)
+
+    y, m_bytes = run(x)
+    assert m_bytes >= 2**31
+    for i in range(parts):
+        part = slice(i * n // parts, (i + 1) * n // parts)
+        y_part, m_bytes = run(x[part])
+        assert m_bytes < 2**31 and torch.equal(y[part], y_part)
+    for i in (0, n - 1):
+        acc = oracle.direct_conv(x[i : i + 1].cpu().numpy(), wt.cpu().numpy())
+        if out == "i32":
+            assert np.array_equal(y[i : i + 1].cpu().numpy().astype(np.int64), acc)
+        else:
+            assert rel_err(y[i : i + 1].cpu().numpy(), oracle.dequantize(acc, 0.02, ws)) <= F32_TOL
+    del x, y, y_part
+    torch.cuda.empty_cache()
+
+
 # ---- fused path: products never leave the chip, so only V, U and y can be compared ----
 
 FUSED_SHAPES = [
