@@ -123,21 +123,26 @@ def _nbytes(t) -> int:
     return int(t.numel() * t.element_size())
 
 
-_torch = None  # torch, once a call has needed it
+_raw_stream = _device = None  # raw handle of a device's current stream, the current device
 
 
 def _stream_ptr(stream):
     """hipStream_t of `stream`, or of the current stream.  The raw handle is asked for: a
     torch.cuda.Stream object takes 2.7 us to build, as long as the launch that follows, the
-    handle 0.1 us."""
-    global _torch
+    handle 0.1 us.  The names are torch's own (its compiled graphs ask the same way) and not
+    documented; without them the handle comes from the Stream object."""
+    global _raw_stream, _device
     if stream is not None:
         return stream.cuda_stream
-    if _torch is None:
+    if _raw_stream is None:
         import torch
 
-        _torch = torch
-    return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        if raw is None or device is None:
+            raw, device = (lambda d: torch.cuda.current_stream(d).cuda_stream), torch.cuda.current_device
+        _device, _raw_stream = device, raw
+    return _raw_stream(_device())
 
 
 class Plan:

@@ -56,6 +56,29 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
         binding.load()
 
 
+@pytest.mark.parametrize("missing", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",)])
+def test_current_stream_with_and_without_the_raw_handle(monkeypatch, missing):
+    """The handle of the current device's current stream, from torch's undocumented names where
+    it has them, else from the Stream object."""
+    from types import SimpleNamespace
+
+    import torch
+
+    from paper_2407_02913_amd import binding
+
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(binding, "_device", None)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 1000 + d, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: SimpleNamespace(cuda_stream=2000 + d))
+    for name in missing:
+        monkeypatch.delattr(torch._C, name)
+    want = 2003 if missing else 1003
+    assert [binding._stream_ptr(None) for _ in range(2)] == [want, want]
+    assert binding._stream_ptr(SimpleNamespace(cuda_stream=5)) == 5
+
+
 def make_desc(**kw):
     from paper_2407_02913_amd import binding
 
