@@ -392,17 +392,24 @@ __global__ __launch_bounds__(NW * 64, 2) void quad16_kernel(
   // group pg + 1 will take (VB >= 2; with VB = 3 the store may run a group earlier).
   constexpr int VB = quad16_vbufs(KC), VR = quad16_vregs(KC);
   v4i lreg[VR][NL];
-  // V offsets of the positions, 64 to a register: a piece takes the one of its point by its lane
-  // number.  (Selected among four constants instead, the loads of every group became branches
-  // with a copy of the load each, four to a piece: 516 loads and 400 branches in the code at
-  // 128 channels and 184 points, 1067 and 900 at 256.)
+  // V offset of a piece's point.  With as many waves as channel chunks (256 channels) piece i of
+  // every thread is point i of the group, a constant.  Else the offsets of the positions lie 64
+  // to a register and a piece takes the one of its point by its lane number.  (Selected among
+  // four constants, the loads of every group became branches with a copy of the load each, four
+  // to a piece: 516 loads and 400 branches in the code at 128 channels and 184 points, 1067 and
+  // 900 at 256.  256 channels on 14x14 maps, batch 128, layer: 38.4 us selected, 38.7 by lane,
+  // 38.3 constant; the 13-layer stack at batch 64 363.9, 356.2, 355.5; over 84 layers of 129 to
+  // 256 channels the constant takes 0.992 of the time of the selection, 0.93 to 1.03.)
+  constexpr bool kPieceIsPoint = NT == 64 * KC;
   unsigned vofs[(PP + 63) / 64];
 #pragma unroll
   for (int m = 0; m < (PP + 63) / 64; ++m) vofs[m] = (unsigned)max(order.pt[min(64 * m + lane, PP - 1)], 0) * vplane;
   auto load_regs = [&](int pg) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const unsigned off = (unsigned)__builtin_amdgcn_readlane((int)vofs[pg >> 4], ((4 * pg) & 63) + rsel[i]);
+      unsigned off;
+      if constexpr (kPieceIsPoint) off = (unsigned)max(order.pt[4 * pg + i], 0) * vplane;
+      else off = (unsigned)__builtin_amdgcn_readlane((int)vofs[pg >> 4], ((4 * pg) & 63) + rsel[i]);
       lreg[pg % VR][i] = __builtin_amdgcn_raw_buffer_load_b128(vres, gsrc[i], off, 0);
     }
   };
