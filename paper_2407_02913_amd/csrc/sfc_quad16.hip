@@ -7,6 +7,18 @@ namespace sfc {
 hipError_t launch_quad16_7tap(int out, const Geometry& g, const void* V, const FilterViews& f,
                               float x_scale, float inv_y, void* y, hipStream_t s, bool prepare);
 
+// Layers whose workgroups leave compute units idle, so that one workgroup's chain is the
+// duration, on maps of two tile columns and odd width (7x7): a wave stores its 16 filters one
+// element at a time, every instruction on pieces of many short rows, where a wave of the
+// one-pair-per-lane kernel stores four.  7x7 filters, 64 to 64 channels on 7x7 maps, batch 64: 33.0 us
+// here, 27.8 there (kernels 22.6 and 17.4); over 100 layers of at least 16 tiles and 64 filters 1.06 times
+// its time here (0.98 to 1.20).  With fewer tiles or filters (0.9), on wider maps (9x13 0.95 to
+// 1), and with several channel chunks from 128 tiles on (0.97), it is level or behind.
+static bool quad16_stores_bound(const Geometry& g) {
+  return g.W % 2 == 1 && g.tw == 2 && g.Cout >= 64 && g.T >= 16 && (g.Cp == 64 || g.T < 128) &&
+         (long long)(g.Tp / 16) * ((g.Cout + 63) / 64) < 128;
+}
+
 bool quad16_supported(const Geometry& g) {
   if (g.alg != 4 && g.alg != 5 && g.alg != 8) return false;
   const int kc = g.Cp / 64;
@@ -15,11 +27,12 @@ bool quad16_supported(const Geometry& g) {
   // those layers).
   if (kc != 1 && kc != 2 && kc != 4) return false;
   // A wave takes 256 (tile, filter) pairs: with fewer than one wave per SIMD of the chip the
-  // one-pair-per-lane kernel, whose waves take 64, fills it better.  Not so with 184 points,
-  // where that kernel's fourfold matrix work and operand reads outweigh it at every size (7x7
-  // filters, layer: 16 channels on one 32x32 map 30.3 us against 26.3 here, 128 channels on one
-  // 28x28 map 35.2 against 32.1, 256 channels on 14x14 maps at batch 32 67.3 against 59.5).
+  // one-pair-per-lane kernel, whose waves take 64, fills it better.  With 184 points its fourfold
+  // matrix work and operand reads outweigh that on most layers (7x7 filters, layer: 16 channels
+  // on one 32x32 map 30.3 us against 26.3 here, 128 channels on one 28x28 map 35.2 against 32.1,
+  // 256 channels on 14x14 maps at batch 32 67.3 against 59.5), not where quad16_stores_bound.
   if (g.alg < 6 && (long long)(g.Tp / 16) * ((g.Cout + 15) / 16) < 1024) return false;
+  if (g.alg == 8 && quad16_stores_bound(g)) return false;
   const long long fgroups = quad16_filter_count(g) / 16;
   const long long ybytes = 4ll * g.N * g.Cout * g.H * g.W;
   const long long vbytes = (long long)g.P * g.Tp * g.Cp;

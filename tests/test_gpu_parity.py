@@ -549,7 +549,25 @@ def test_5x5_fused_path_matches_oracle(binding, shape, alg):
     assert rel_err(y, y_ref) <= F32_TOL
 
 
-@pytest.mark.parametrize("shape", [
+# (kernel, shape): the layers with 184 points that the one-pair-per-lane kernel takes, and those
+# next to them (tests/test_host_logic.py asks the library)
+SHAPES_184 = [
+    ("fused_quad", (4, 16, 64, 7, 7)),      # 16 tiles
+    ("quad16", (3, 16, 64, 7, 7)),          # 12
+    ("quad16", (4, 16, 63, 7, 7)),
+    ("fused_quad", (31, 100, 72, 5, 7)),    # two chunks, 124 tiles
+    ("quad16", (32, 100, 72, 5, 7)),        # 128
+    ("fused_quad", (31, 200, 64, 7, 5)),    # four chunks
+    ("fused_quad", (5, 256, 130, 7, 7)),
+    ("quad16", (5, 33, 64, 9, 9)),          # three tile columns
+    ("quad16", (5, 33, 64, 7, 6)),          # even width
+    ("quad16", (5, 33, 64, 7, 3)),          # one tile column
+    ("fused_quad", (252, 9, 128, 7, 7)),    # 63 blocks of 16 tiles x two of 64 filters
+    ("quad16", (253, 9, 128, 7, 7)),        # 64 x two
+]
+
+
+@pytest.mark.parametrize("shape", [shape for _, shape in SHAPES_184] + [
     (1, 64, 64, 16, 16),    # one chunk, 16 tiles: exactly one block, rows of four outputs per store
     (2, 128, 65, 9, 18),    # two chunks, one filter beyond a workgroup's 64, pairs per store
     (3, 193, 16, 11, 13),   # four chunks, the last with one channel, single outputs per store
@@ -557,7 +575,7 @@ def test_5x5_fused_path_matches_oracle(binding, shape, alg):
 ])
 def test_7x7_filters_four_pairs_per_lane(binding, shape):
     """The 184-point products kernel that keeps the outputs: its store widths, chunk counts and
-    ragged blocks, float32 and int8, against the oracle."""
+    ragged blocks, and the layers around its line, float32 and int8, against the oracle."""
     alg = "4x4_7x7_p184"
     x, w, xs, ws = uniform_case(shape, 2600 + sum(shape), r=7)
     print("case 7x7 four pairs", shape, flush=True)

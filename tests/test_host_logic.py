@@ -305,6 +305,13 @@ def test_kernels_of_the_shapes_past_the_small_layers(lib, routes):
         assert kernel == small, shape
 
 
+def test_kernels_of_the_184_point_shapes(lib, routes):
+    import test_gpu_parity as parity
+
+    cases = parity.SHAPES_184
+    assert routes([("fused", "4x4_7x7_p184", shape) for _, shape in cases]) == [kernel for kernel, _ in cases]
+
+
 def test_every_kernel_choice_fits_the_filter_layout(lib, routes):
     """Single path: the kernel for small layers reads the operand of the 16-filter kernels, and is
     only picked where one of those would be without it."""
