@@ -270,9 +270,13 @@ __global__ __launch_bounds__(256) void input_transform_image16_kernel(const int8
 
 // Layers of a few images: up to one wave of 64 channels per SIMD (256 channels on 14x14 maps, us of
 // the kernel at 2 / 8 / 16 images, 4.0 / 5.0 / 7.9 against 7.9 / 8.7 / 9.0 of the kernel that
-// stages whole images; 32 images 12.2 against 8.7; 512 channels on 7x7 maps 3.0 / 4.6 / 4.7 against
-// 4.4 / 4.5 / 4.8 of input_transform_image_kernel, 32 images level, 64 behind).
-static bool image_input_few(const Geometry& g) { return g.alg == 4 && (long long)g.T * (g.Cp / 64) <= 1024; }
+// stages whole images; 32 images 12.2 against 8.7).  Maps of 64 samples have the other form of
+// this kernel, which is ahead a little earlier (512 channels on 7x7 maps 3.0 / 4.6 / 4.7 against
+// 4.4 / 4.5 / 4.8; layers of 256 and 512 channels on 7x7 and 8x8 maps, whole layer: 0.94 at 512 waves,
+// 0.99 at 768, 1.02 at 1024).
+static bool image_input_few(const Geometry& g) {
+  return g.alg == 4 && (long long)g.T * (g.Cp / 64) <= (g.H * g.W <= 64 ? 768 : 1024);
+}
 
 bool image_input_supported(const Geometry& g) {
   if (g.alg < 0 || g.alg > 5) return false;

@@ -500,12 +500,19 @@ int product_small_filter_count(const Geometry& g) { return (g.Cout + 3) / 4 * 4;
 // While the workgroups fit the chip in one round (us per layer, input transform included: 256
 // channels on 14x14 maps, 1 / 4 images, 9.3 / 12.4 against 20.2 / 21.6 with the kernels for larger
 // layers, 512 channels on 7x7 maps, 1 / 4 / 8 images, 12.3 / 14.1 / 18.0 against 22.2; in two rounds
-// level or behind: 6 images 20.7 against 21.8, 12 images 31.2 against 22.2).
+// level or behind: 6 images 20.7 against 21.8, 12 images 31.2 against 22.2).  Every filter quad reads
+// all of V, consecutive quads on different XCDs, so where V is not small next to an L2 the line
+// comes earlier (512 channels on 7x7 maps, 32 / 96 / 128 images, 128 / 32 / 32 filters: 22.2 / 22.2 /
+// 27.9 us against 20.5 / 19.7 / 23.5).  Time against the other kernels over 560 layers of 4 to 512
+// filters: 256 channels, V to 4 MB 0.47 to 0.95, else up to 160 workgroups 0.73 to 1.04, above 0.95
+// to 1.11; 512 channels, V to 2 MB 0.50 to 0.97, else up to 128 workgroups 0.65 to 1.04, above 0.92 to
+// 1.22.
 bool product_small_supported(const Geometry& g) {
   if (g.alg != kSmallAlg || (g.Cp != 256 && g.Cp != 512)) return false;
-  if ((long long)(g.Tp / 16) * (product_small_filter_count(g) / 4) > 256) return false;
-  const long long lim = 1ll << 31;
-  return 4ll * g.N * g.Cout * g.H * g.W < lim && (long long)g.P * g.Tp * g.Cp < lim;
+  const long long wgs = (long long)(g.Tp / 16) * (product_small_filter_count(g) / 4);
+  const long long vbytes = (long long)g.P * g.Tp * g.Cp;
+  const bool v_small = vbytes <= (g.Cp == 256 ? 4ll : 2ll) << 20;
+  return wgs <= (v_small ? 256 : g.Cp == 256 ? 160 : 128) && 4ll * g.N * g.Cout * g.H * g.W < (1ll << 31);
 }
 
 template <int KC, int OUT>

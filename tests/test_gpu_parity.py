@@ -656,7 +656,7 @@ def test_single_kernel_path_with_two_channel_chunks(binding, shape, alg):
 
 # 46 points, just past the layer sizes that the kernels for small layers take
 # (tests/test_host_logic.py asks the library that these are the kernels): the edges of the kernels
-# for larger layers, as the shapes above are theirs for 49 points.
+# for larger layers, as the shapes above are theirs for 49 points; the last ones on either side.
 PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
     ("single", "single16", (19, 33, 17, 56, 56)),    # two tile-column chunks per strip, two filter groups
     ("single", "single16", (1030, 20, 8, 7, 7)),     # whole images, odd W, half a filter group
@@ -684,6 +684,16 @@ PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
     ("fused", "splitk", (171, 500, 24, 8, 8)),
     ("fused", "splitk", (15, 460, 72, 14, 14)),      # three filter pairs of 32
     ("fused", "splitk", (35, 512, 40, 9, 13)),       # odd W, a ragged last tile block
+    ("fused", "product_small", (40, 256, 16, 14, 14)),  # 160 workgroups, V 7.5 MB
+    ("fused", "fused_quad", (41, 256, 16, 14, 14)),     # 164
+    ("fused", "product_small", (512, 512, 4, 7, 7)),    # 128 workgroups of one quad, V 48 MB
+    ("fused", "splitk", (513, 512, 4, 7, 7)),           # 129
+    ("fused", "product_small", (8, 512, 64, 14, 14)),   # 128 workgroups, V 3 MB
+    ("fused", "splitk", (9, 512, 64, 14, 14)),          # 144
+    ("fused", "product_small", (20, 512, 200, 7, 7)),   # 250 workgroups, V 1.9 MB
+    ("fused", "splitk", (21, 512, 100, 7, 7)),          # 150, V 2.3 MB
+    ("fused", "product_small", (24, 512, 40, 8, 8)),    # 16-channel waves of the input transform: 768 ...
+    ("fused", "product_small", (25, 512, 36, 7, 7)),    # ... and past them
 ]
 
 
