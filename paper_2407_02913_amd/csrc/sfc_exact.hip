@@ -376,10 +376,34 @@ static hipError_t launch_output_exact_alg(bool sums_out, const Geometry& g, cons
   return launch(output_exact_kernel<ALG, false>);
 }
 
+// Where the kernel above is ahead of the one-thread-per-pair one (output_transform_kernel,
+// sfc_kernels.hip), which asks for all sums of a pair at once and has few idle threads where
+// there are few filters.  A wave here keeps a ring of sums in flight: 14.4 us of a lone workgroup
+// with 88 points against 6.0 there.  The lines are in full waves of pairs, from 2158 layers (with
+// the better kernel each time 0.89 of the time with this one alone); us of a layer here against
+// there, waves: difference,
+//   64 filters and more, even widths (two outputs per store)   88 points 400: +0.5, 800: -0.5, 1152: -7;
+//       132 4: -0.3, 64: -1.2, 1024: -11; 46 392: +0.6, 512: -0.2, 1024: -1.8; 184 (5x5 filters)
+//       18: +1.4, 50: -1.5, 800: -6; 184 (7x7) 128: +0.8, 196: -0.8, 1024: -5
+//   odd widths   88 points 1024: +5.0, 1536: -7.7; 132 16: +0.5, 64: -0.1, 1024: -3.1; 46 512: +0.9, 768: +0.3,
+//       1024: -0.5; 184 (5x5) 512: +3.3, 768: -2.5; 184 (7x7) 512: +1.9, 768: -0.5
+//   16 to 63, where that kernel reads M in longer pieces   88 points 800: +3.8, 3200: -12; 132 576: +0.6,
+//       2048: -13; 46 512: +2.4, 1568: -0.8; 184 (5x5) 2000: +8, 3200: -16; 184 (7x7) 1568: +1.9, 6272: -24
+//   9 to 15   88 points 1200: +2, 2814: -2; 132 1800: +1, 3072: -4; 46 2520: +1, 5514: -3; 184 +0.6 to +53
+//   8 and less   that kernel (8 filters, 46 points, 6272: +7; 184 points +74)
+bool output_exact_ahead(const Geometry& g) {
+  constexpr int kNever = 1 << 30;
+  constexpr int kWaves[5][4] = {  // [alg / 2][9 to 15 filters; 16 to 63; more, even; more, odd width]
+      {2560, 1025, 768, 1200}, {2560, 768, 0, 48}, {4096, 1024, 512, 768}, {kNever, 2560, 48, 640}, {kNever, 4096, 160, 640}};
+  const long long pairs = (long long)g.T * ((g.Cout + 3) / 4 * 4);
+  return g.Cout > 8 && pairs >= 64ll * kWaves[g.alg >> 1][g.Cout < 16 ? 0 : g.Cout < 64 ? 1 : 2 + g.W % 2];
+}
+
 hipError_t launch_output_exact(bool sums_out, const Geometry& g, const int32_t* M, const float* wscale,
                                float x_scale, void* y, hipStream_t s) {
   const long long mbytes = 4ll * g.P * g.Tp * g.Kp, ybytes = 4ll * g.N * g.Cout * g.H * g.W;
   if (mbytes >= (1ll << 31) || ybytes >= (1ll << 31)) return hipErrorNotSupported;  // 32-bit offsets
+  if (!output_exact_ahead(g)) return hipErrorNotSupported;
   switch (g.alg) {
     case 0: return launch_output_exact_alg<0>(sums_out, g, M, wscale, x_scale, y, s);
     case 1: return launch_output_exact_alg<1>(sums_out, g, M, wscale, x_scale, y, s);

@@ -66,12 +66,13 @@ unsigned rows_table_offset(const Geometry& g);
 void build_image_input_table(const Geometry& g, const float* inv_sx, unsigned char* tab);
 hipError_t launch_input_image(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab,
                               hipStream_t s, bool prepare);
-// exact mode (sfc_exact.hip); hipErrorNotSupported beyond the 32-bit offset limits, where
-// the generic kernels of sfc_kernels.hip take over.  tab: kRowsTabBytes at
-// FilterViews::input_tab
+// exact mode (sfc_exact.hip); hipErrorNotSupported beyond the 32-bit offset limits, and of the
+// output transform where output_exact_ahead does not hold: the generic kernels of
+// sfc_kernels.hip take over.  tab: kRowsTabBytes at FilterViews::input_tab
 hipError_t launch_input_exact(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab,
                               hipStream_t s, bool prepare = false);
 hipError_t launch_product_exact(const Geometry& g, const void* V, const void* U, int32_t* M, hipStream_t s);
+bool output_exact_ahead(const Geometry& g);
 hipError_t launch_output_exact(bool sums_out, const Geometry& g, const int32_t* M, const float* wscale,
                                float x_scale, void* y, hipStream_t s);
 hipError_t launch_product(int mode, const Geometry& g, const void* V, const void* U, int32_t* M,

@@ -1,6 +1,7 @@
-// Which kernel the library picks: reads layers "path alg N Cin Cout H W" (path and alg as in
-// include/sfc.h) and prints the name of the product kernel of each.  Linked against the built
-// library, whose own rule it asks.
+// Which kernels the library picks: reads layers "path alg N Cin Cout H W" (path and alg as in
+// include/sfc.h) and prints the name of the product kernel of each and, for the exact mode of the
+// layer, which output transform is ahead.  Linked against the built library, whose own rules it
+// asks.
 #include <cstdio>
 
 #include "../../paper_2407_02913_amd/csrc/sfc_internal.hpp"
@@ -22,7 +23,7 @@ int main() {
     g.Kp = (g.Cout + 15) / 16 * 16;
     g.P = sfc::alg_points(g.alg);
     g.qmax = 127.0f;
-    std::printf("%s\n", kNames[(int)sfc::choose_kernel(path, g)]);
+    std::printf("%s %s\n", kNames[(int)sfc::choose_kernel(path, g)], sfc::output_exact_ahead(g) ? "waves" : "threads");
   }
   return 0;
 }

@@ -83,6 +83,40 @@ def test_exact_products_at_block_edges(binding, shape, alg):
     assert np.array_equal(acc.astype(np.int64), acc_ref)
 
 
+# exact mode, just past the line of the output transform that runs one pair per lane: odd and even
+# widths, filter counts that end inside a quad, a wave or a workgroup, a ragged last tile block
+EXACT_WAVE_SHAPES = [
+    ("6x6_p88", (48, 2, 66, 31, 19)),
+    ("6x6_p88", (513, 1, 15, 23, 30)),
+    ("6x6_p100", (83, 1, 130, 12, 14)),
+    ("7x7_p132", (1, 65, 70, 9, 20)),
+    ("7x7_p132", (8, 65, 70, 29, 15)),
+    ("7x7_p132", (165, 1, 17, 31, 20)),
+    ("7x7_p144", (13, 3, 129, 9, 13)),
+    ("4x4_p46", (55, 2, 69, 13, 14)),
+    ("4x4_p46", (122, 1, 35, 11, 18)),
+    ("4x4_p49", (33, 3, 70, 21, 17)),
+    ("6x6_5x5_p184", (3, 2, 70, 20, 26)),
+    ("6x6_5x5_p184", (31, 2, 66, 29, 23)),
+    ("6x6_5x5_p184", (51, 1, 50, 37, 50)),
+    ("6x6_5x5_p196", (34, 1, 65, 14, 31)),
+    ("4x4_7x7_p184", (11, 2, 67, 13, 22)),
+    ("4x4_7x7_p184", (130, 1, 62, 25, 23)),
+    ("4x4_7x7_p196", (26, 1, 130, 15, 9)),
+]
+
+
+@pytest.mark.parametrize("alg,shape", EXACT_WAVE_SHAPES)
+def test_exact_output_transform_past_its_line(binding, alg, shape):
+    x, w, xs, ws = uniform_case(shape, 160 + sum(shape), r=binding.KERNEL_SIZE[alg])
+    print("case exact waves", shape, alg, flush=True)
+    acc_ref = oracle.direct_conv(x, w)
+    acc = binding.conv2d(x, w, xs, ws, mode="exact", alg=alg, out="i32")
+    assert np.array_equal(acc.astype(np.int64), acc_ref)
+    y = binding.conv2d(x, w, xs, ws, mode="exact", alg=alg, out="f32")
+    assert rel_err(y, oracle.dequantize(acc_ref, xs, ws)) <= F32_TOL
+
+
 @pytest.mark.parametrize("alg", ALGS_STAGED)
 @pytest.mark.parametrize("shape", SMALL_SHAPES)
 def test_requant_mode_taps_bit_exact_and_output_close(binding, shape, alg):

@@ -273,7 +273,8 @@ def test_kernel_add_networks_realize_the_oracle_matrices(kernel_maps, alg_id, al
 
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
-    """(path, algorithm, shape) of layers -> the product kernels the built library picks for them."""
+    """(path, algorithm, shape) of layers -> the product kernels the built library picks for them, or
+    (column 1) the output transforms of their exact mode."""
     from paper_2407_02913_amd import binding
 
     exe = tmp_path_factory.mktemp("host") / "route"
@@ -283,11 +284,11 @@ def routes(tmp_path_factory):
                     "-l:" + os.path.basename(binding.LIB_PATH), "-Wl,-rpath," + where, "-o", str(exe)],
                    check=True, capture_output=True)
 
-    def ask(layers):
+    def ask(layers, column=0):
         text = "".join(f"{binding.PATH[path]} {binding.ALG[alg]} {' '.join(map(str, shape))}\n"
                        for path, alg, shape in layers)
         out = subprocess.run([str(exe)], input=text, check=True, capture_output=True, text=True).stdout
-        return out.splitlines()
+        return [line.split()[column] for line in out.splitlines()]
 
     return ask
 
@@ -310,6 +311,29 @@ def test_kernels_of_the_184_point_shapes(lib, routes):
 
     cases = parity.SHAPES_184
     assert routes([("fused", "4x4_7x7_p184", shape) for _, shape in cases]) == [kernel for kernel, _ in cases]
+
+
+def test_output_transforms_of_the_exact_shapes(lib, routes):
+    """Either output transform has the shapes of the GPU parity tests that are there for it."""
+    import test_gpu_parity as parity
+
+    cases = parity.EXACT_WAVE_SHAPES
+    assert set(routes([("staged", alg, shape) for alg, shape in cases], column=1)) == {"waves"}
+    small = [("staged", alg, shape) for alg in parity.ALGS_STAGED + parity.ALGS_5X5 for shape in parity.SMALL_SHAPES
+             if shape != (5, 64, 64, 12, 18)]
+    assert set(routes(small, column=1)) == {"threads"}
+    # the lines: 9 to 15 filters, 16 to 63, 64 and more with even and with odd width
+    for alg, *lines in (("6x6_p88", 2560, 1025, 768, 1200), ("7x7_p132", 2560, 768, 0, 48),
+                        ("4x4_p46", 4096, 1024, 512, 768), ("6x6_5x5_p184", None, 2560, 48, 640),
+                        ("4x4_7x7_p184", None, 4096, 160, 640)):
+        for cout, width, line in zip((9, 16, 63, 64, 300), (4, 4, 3, 4, 3), (*lines[:2], *lines[1:])):
+            if line is None:
+                assert routes([("staged", alg, (200000, 1, 15, 4, 4))], column=1) == ["threads"]
+                continue
+            images = max(1, -(-16 * line // -(-cout // 4)))  # one tile each
+            layers = [("staged", alg, (images - i, 1, cout, 4, width)) for i in (0, 1) if images > i]
+            assert routes(layers, column=1) == ["waves", "threads"][: len(layers)], (alg, cout)
+        assert routes([("staged", alg, (200000, 1, 8, 4, 4))], column=1) == ["threads"]
 
 
 def test_every_kernel_choice_fits_the_filter_layout(lib, routes):
