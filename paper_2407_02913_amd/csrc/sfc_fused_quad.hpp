@@ -1,5 +1,6 @@
-// Transform-domain products + output transform in one kernel for any number of input
-// channels (gfx950): V comes from the input-transform kernel, M never leaves the chip.
+// Transform-domain products + output transform in one kernel for 64, 128, 256 or 512 input
+// channels after padding (gfx950): V comes from the input-transform kernel, M never leaves the
+// chip.
 //
 // A workgroup owns 16 consecutive tiles and 4*NW filters (wave w: filters 4w..4w+3,
 // lane l: the pair (tile l%16, filter 4w + l/16)).  Points are taken in groups of four
@@ -252,10 +253,13 @@ inline hipError_t launch_quad_impl(const Geometry& g, const void* V, const Filte
 template <int ALG, int KC>
 inline hipError_t launch_quad_kc(int out, const Geometry& g, const void* V, const FilterViews& f,
                                  float x_scale, float inv_y, void* y, hipStream_t s, bool prepare) {
-  constexpr bool kPairs = AlgTraits<ALG>::M % 2 == 0;
+  // (SFC-6(4x4,7x7) with 184 points and up to four chunks comes here at odd widths only:
+  // quad16_supported)
+  constexpr bool kOddOnly = ALG == 8 && KC <= 4;
+  constexpr bool kPairs = AlgTraits<ALG>::M % 2 == 0 && !kOddOnly;
   // 7x7 tiles on 7x7, 14x14, 28x28 ... maps, 4x4 tiles on 4x4, 8x8, 16x16 ...: a wave's
   // pairs are whole planes of y
-  if constexpr (AlgTraits<ALG>::M == 7 || AlgTraits<ALG>::M == 4) {
+  if constexpr (!kOddOnly && (AlgTraits<ALG>::M == 7 || AlgTraits<ALG>::M == 4)) {
     if (whole_image_tiles(AlgTraits<ALG>::M, g.H, g.W, g.th, g.tw, g.Cout))
       return out == 2 ? launch_quad_impl<ALG, KC, 2, false, true>(g, V, f, x_scale, inv_y, y, s, prepare)
                       : launch_quad_impl<ALG, KC, 0, false, true>(g, V, f, x_scale, inv_y, y, s, prepare);
