@@ -116,6 +116,8 @@ __global__ __launch_bounds__(kExactWaves * 64) void input_transform_i16_kernel(
   }
 }
 
+// (48 KB take the rows of one strip, so waves stay without a tile: of eight, 5 have one with 6x6
+// tiles on 56x56 and 28x28 maps, 3 on 14x14 and 2 on 7x7; 7, 7, 4 and 2 with 4x4 tiles.)
 static bool make_exact_input_plan(const Geometry& g, ExactInputPlan* ip) {
   if ((long long)g.N * g.Cin * g.H * g.W >= (1ll << 31)) return false;  // 32-bit offsets into x
   if (!make_tile_rect(g, 48u * 1024u, &ip->tr, kExactWaves, true, false)) return false;
@@ -157,7 +159,8 @@ hipError_t launch_input_exact(const Geometry& g, const int8_t* x, void* V, const
 
 // ---------------------------------------------------------------------------------------
 // Products.  A 16-bit operand is v = 256 h + l with l its low byte taken as a signed one and
-// h = (v - l) / 256, |h| <= 18 for the transforms of this library; a sum of products is then
+// h = (v - l) / 256, |h| <= 25 for the transforms of this library (49 * 128 at the all-taps point
+// of a 7x7 filter); a sum of products is then
 // 65536 S(hh) + 256 S(hl + lh) + S(ll), three int32 accumulators and four int8 MFMA 16x16x64,
 // exact (|S(ll)| <= 2^14 Cin; the combination is taken modulo 2^32 like everything behind it).
 // A workgroup of four waves owns 64 filters x 64 tiles of one point, each wave 32 x 32; per

@@ -73,7 +73,8 @@ SFC_HD void hermitian_components(const T& uo0, const T& uo1, const T& vo0, const
 // Consumes the products in processing order (as stream_vertical does) and leaves
 // y[o2][o1] = 36 times output (o1, o2).  settle(v) is called on every value that stays until a
 // later product: it keeps the compiler from putting the additions off and the products in
-// registers instead (500 spilled registers without it).
+// registers instead (quad16_kernel at 64 / 128 / 256 channels: 188 / 214 / 253 vector registers,
+// 196 / 218 / 253 without it, none spilled).
 template <int ALG, typename T, typename F, typename Settle>
 SFC_HD void stream_outputs(F&& next, Settle&& settle, T (&y)[AlgTraits<ALG>::M][AlgTraits<ALG>::M]) {
   using Tr = AlgTraits<ALG>;
