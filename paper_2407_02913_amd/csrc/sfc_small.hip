@@ -313,10 +313,14 @@ __global__ __launch_bounds__(kSmallWaves * 64) void single_small_kernel(
 }
 
 // Tiles and filter groups of a workgroup: of the combinations whose workgroups all run at once
-// (one per compute unit) the one with the least estimated time in us.  The estimate is a fit to
-// timings of one 56x56 image with 64 and one 28x28 image with 128 channels over all
-// combinations: a fixed part, 16-channel patches, a second filter group, and workgroups (each
-// fetches the filter operand of its groups).
+// (one per compute unit) the one with the least estimated time in us, less what all of them
+// share.  The estimate is a fit to 2514 timings, every combination of 688 layers (16 to 128
+// channels, 16 to 256 filters, maps from 5x5 to 224x224, 200x16 and 6x61, one image to the most that
+// the kernel takes): 16-channel patches, a second filter group, workgroups (each fetches the
+// filter operand of its groups), and the staging of whole images or strips, byte by byte where
+// rows are not whole dwords.  The picked combination takes 1.004 times as long as the best one (at most
+// 1.14); without the staging in the estimate, fitted to 56x56 and 28x28 maps, it was 1.036 (at most
+// 1.68; 31x45 maps, 16 channels, ten images: 12.6 us against 8.5 with four tiles).
 static bool make_small_plan(const Geometry& g, SmallPlan* best) {
   if (g.alg != kSmallAlg || g.Cp > 128) return false;
   const long long lim = 1ll << 31;
@@ -341,8 +345,10 @@ static bool make_small_plan(const Geometry& g, SmallPlan* best) {
       if (sp.lds_bytes > lds_max) continue;
       const long long wgs = (long long)tile_rect_groups(g, sp.tr) * ((sp.fgroups + sp.fper - 1) / sp.fper);
       if (wgs > 256) continue;
-      sp.cost = 4.2 + 1.4 * kc + (0.03 + 0.0075 * kc) * sp.tr.ntiles * sp.cgroups + 1.3 * (sp.fper - 1) +
-                0.0055 * (double)wgs;
+      const bool dwords = g.W % 4 == 0;
+      sp.cost = 0.045 * sp.tr.ntiles * sp.cgroups + (1.0 + 0.5 * kc) * (sp.fper - 1) + 0.006 * (double)wgs +
+                (sp.tr.whole ? 3.5 + kc * (dwords ? 0.3 : 0.55) * sp.tr.ipw
+                             : kc * (0.6 * sp.tr.S + (dwords ? 0.0 : 2.0)));
       if (!found || sp.cost < best->cost - 1e-9) {
         *best = sp;
         found = true;
@@ -354,8 +360,10 @@ static bool make_small_plan(const Geometry& g, SmallPlan* best) {
 
 // Where its workgroups fit the chip in one round, the kernel is ahead of single16_kernel (us per
 // layer: 64 channels on 56x56 maps, 1 / 4 / 8 images, 6.9 / 7.6 / 8.8 against 9.7 / 10.0 / 9.9; 128
-// channels on 28x28 maps 7.2 / 8.8 / 10.6 against 17.1 / 17.5 / 17.6); in two rounds it is behind
-// (12 images: 16.0 against 10.2 and 19.6 against 17.7).
+// channels on 28x28 maps 7.2 / 8.8 / 10.6 against 17.1 / 17.5 / 17.6; 0.28 to 0.96 of its time, 0.58 on
+// average, over 547 layers of 16 to 128 channels on maps from 7x7 to 224x224, 200x16 and 6x61, up to
+// the most images that fit); in two rounds it is behind (12 images: 16.0 against 10.2 and 19.6
+// against 17.7).
 bool single_small_supported(const Geometry& g) {
   SmallPlan sp;
   return make_small_plan(g, &sp);

@@ -728,6 +728,23 @@ PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
     ("fused", "splitk", (21, 512, 100, 7, 7)),          # 150, V 2.3 MB
     ("fused", "product_small", (24, 512, 40, 8, 8)),    # 16-channel waves of the input transform: 768 ...
     ("fused", "product_small", (25, 512, 36, 7, 7)),    # ... and past them
+    ("single", "single_small", (181, 9, 17, 14, 10)),  # 16 tiles and two filter groups to a workgroup, strips
+    ("single", "single_small", (129, 9, 130, 5, 6)),  # ... whole images
+    ("single", "single_small", (71, 9, 20, 5, 6)),  # two tiles, two groups
+    ("single", "single_small", (51, 23, 37, 4, 30)),  # four
+    ("single", "single_small", (336, 33, 20, 3, 5)),  # ... whole images
+    ("single", "single_small", (67, 9, 20, 13, 9)),  # eight
+    ("single", "single_small", (282, 23, 17, 5, 6)),  # ... whole images
+    ("single", "single_small", (46, 9, 5, 11, 20)),  # sixteen tiles, one group, strips
+    ("single", "single_small", (288, 9, 17, 3, 5)),  # eight tiles, one group, whole images
+    ("single", "single_small", (166, 70, 5, 14, 10)),  # from here two chunks
+    ("single", "single_small", (1, 100, 5, 3, 5)),
+    ("single", "single_small", (69, 70, 37, 13, 9)),
+    ("single", "single_small", (44, 70, 37, 8, 8)),
+    ("single", "single_small", (33, 119, 20, 13, 9)),
+    ("single", "single_small", (155, 70, 17, 5, 6)),
+    ("single", "single_small", (47, 70, 17, 11, 20)),
+    ("single", "single_small", (299, 70, 20, 5, 6)),
 ]
 
 
