@@ -57,8 +57,8 @@ typedef enum {
 /* Which 2-D point set realizes the element-wise product of Eq. (1), Appendix A. */
 typedef enum {
   /* sfc_plan picks the tile size for 3x3 filters from the layer shape (sfc_plan_choice tells
-   * which).  Requantized mode: SFC-4's 4x4 tiles, except 7x7 tiles on 14x14 and 7x7 maps
-   * with many (tile, filter) pairs; exact mode: 6x6 tiles; always the Hermitian point set. */
+   * which).  Requantized mode: SFC-4's 4x4 tiles, except 7x7 tiles on 7x7 maps with
+   * many (tile, filter) pairs; exact mode: 6x6 tiles; always the Hermitian point set. */
   SFC_ALG_AUTO = -1,
   SFC_ALG_6X6_P88 = 0,  /* SFC-6(6x6,3x3), Hermitian symmetry fully used: 88 multiplications per tile */
   SFC_ALG_6X6_P100 = 1, /* SFC-6(6x6,3x3), nested (Kronecker) form: 100 multiplications */

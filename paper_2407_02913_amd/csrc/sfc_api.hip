@@ -1,6 +1,6 @@
 // C ABI of the SFC library: plans, argument checks, buffer layout, stage sequencing.
-// Every numeric step runs in the kernels of sfc_kernels.hip; this file only
-// validates, lays out buffers and launches.
+// Every numeric step runs in the kernels; this file only validates, lays out buffers and
+// launches.
 #include <cmath>
 #include <cstdlib>
 #include <cstring>

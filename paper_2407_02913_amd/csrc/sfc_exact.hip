@@ -7,8 +7,8 @@
 //
 // M is kept as in requantized mode, in blocks of 16 tiles x 4 filters (sfc_gemm.hip).  The
 // three kernels move V (2 bytes a value) and M (4) to memory and back and are bound by that.
-// 64 channels on 56x56 maps, batch 32, 6x6 tiles (V 36 MB, M 72 MB, y 26 MB): 13.1 + 22.6 +
-// 25.6 us (3.3, 4.8 and 3.8 TB/s); with the transforms and products on the vector ALU, one
+// 64 channels on 56x56 maps, batch 32, 6x6 tiles (V 36 MB, M 72 MB, y 26 MB): 12.1 + 17.9 +
+// 25.1 us (3.5, 6.1 and 3.9 TB/s); with the transforms and products on the vector ALU, one
 // thread per (tile, channel), sum and (tile, filter), 31 + 133 + 47 us.
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
