@@ -397,7 +397,8 @@ static hipError_t launch_output_exact_alg(bool sums_out, const Geometry& g, cons
 bool output_exact_ahead(const Geometry& g) {
   constexpr int kNever = 1 << 30;
   constexpr int kWaves[5][4] = {  // [alg / 2][9 to 15 filters; 16 to 63; more, even; more, odd width]
-      {2560, 1025, 768, 1200}, {2560, 768, 0, 48}, {4096, 1024, 512, 768}, {kNever, 2560, 48, 640}, {kNever, 4096, 160, 640}};
+      {2560, 1025, 768, 1200}, {2560, 768, 0, 48}, {4096, 1024, 512, 768},
+      {kNever, 2560, 48, 640}, {kNever, 4096, 160, 640}};
   const long long pairs = (long long)g.T * ((g.Cout + 3) / 4 * 4);
   return g.Cout > 8 && pairs >= 64ll * kWaves[g.alg >> 1][g.Cout < 16 ? 0 : g.Cout < 64 ? 1 : 2 + g.W % 2];
 }
