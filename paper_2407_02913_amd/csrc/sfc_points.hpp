@@ -132,9 +132,9 @@ SFC_HD constexpr int kept_index4(int r1, int r2) {
 }
 
 // Processing order of the fused kernels: canonical point indices grouped by
-// horizontal class (first the real columns with all their vertical rows, then the
-// complex column groups), so that each group can be collapsed as soon as its
-// products exist.  pt[j] = canonical index of the j-th point, pos = its inverse.
+// horizontal class (the real columns with all their vertical rows, then the complex column
+// groups; SFC-4 the other way round, so that the group with the most values on the way comes
+// while nothing else is kept), so that each group can be collapsed as soon as its products exist.  pt[j] = canonical index of the j-th point, pos = its inverse.
 // The kernels take points in groups of four: PP is P rounded up to a multiple of four,
 // positions P .. PP-1 hold no point (pt = -1; only the SFC-4 forms have any).
 template <int ALG>
@@ -147,19 +147,20 @@ struct Order {
   constexpr Order() : pt{}, pos{} {
     int n = 0;
     if constexpr (Tr::kFamily == 4) {
-      // real columns 0, 1, 5, 6: all seven vertical rows
-      for (int j = 0; j < NREAL; ++j)
-        for (int r1 = 0; r1 < NR; ++r1)
-          pt[n++] = Tr::kHermitian ? kept_index4(r1, real_row4(j)) : NR * r1 + real_row4(j);
-      // the complex column group: rows 2, 3, 4 = (a0 + a1, a1, a0)
+      // the complex column group: rows 2, 3, 4 = (a0 + a1, a1, a0); Hermitian form: the points
+      // of the complex x complex block, then those kept against each real row
       if (!Tr::kHermitian) {
         for (int r1 = 0; r1 < NR; ++r1)
           for (int i = 0; i < 3; ++i) pt[n++] = NR * r1 + 2 + i;
       } else {
+        for (int i = 0; i < 6; ++i) pt[n++] = (NR * NR - 9) + i;
         for (int j = 0; j < NREAL; ++j)
           for (int i = 0; i < 3; ++i) pt[n++] = kept_index4(real_row4(j), 2 + i);
-        for (int i = 0; i < 6; ++i) pt[n++] = (NR * NR - 9) + i;
       }
+      // real columns 0, 1, 5, 6: all seven vertical rows
+      for (int j = 0; j < NREAL; ++j)
+        for (int r1 = 0; r1 < NR; ++r1)
+          pt[n++] = Tr::kHermitian ? kept_index4(r1, real_row4(j)) : NR * r1 + real_row4(j);
     } else {
       // real columns: all vertical rows
       for (int j = 0; j < NREAL; ++j)
@@ -705,63 +706,108 @@ SFC_HD auto take_product(F&& next) {
 // z[b][o1]: horizontal component b, vertical output o1, times 6.  Each group
 // collapses at once: product-rule post-additions, Hermitian recombination, inverse
 // symbolic DFT-6 with the corrections along the vertical axis.
-// SFC-4, first part: the products of the four real columns (7 each, processing positions
-// 0 .. 27) give z[0], z[1], z[4], z[5].
-template <int ALG, typename T, typename F>
-SFC_HD void stream_vertical4_real(F&& next, T (&z)[6][4]) {
-  constexpr int NR = 7, NC = 6;
-  static_for<4>([&](auto jc) {
-    constexpr int j = decltype(jc)::value;
-    T col[NR], cc[NC];
-    static_for<NR>([&](auto rc) {
+// SFC-4: the vertical outputs of one column (inv4_outputs of collapse4_rows) from its products,
+// row by row: feed<0>, ..., feed<6>, four values at any time.
+template <typename T>
+struct Vertical4 {
+  T v[4];
+  template <int R>
+  SFC_HD void feed(const T& m) {
+    if constexpr (R == 0) {
+      v[0] = m;
+    } else if constexpr (R == 1) {
+      v[1] = v[0] - m;
+      v[0] = v[0] + m;
+    } else if constexpr (R == 2) {
+      v[2] = m;
+    } else if constexpr (R == 3) {
+      v[2] = v[2] - m;
+      v[3] = m;
+    } else if constexpr (R == 4) {
+      const T re = m - v[3], im = v[2] - m;
+      complex(re + re, im + im);
+    } else {
+      T& o = v[R == 5 ? 0 : 3];
+      o = o + T(4) * m;
+    }
+  }
+  // rows 2, 3, 4 by twice the components 2 and 3
+  SFC_HD void complex(const T& re2, const T& im2) {
+    v[2] = v[0] + re2;
+    v[0] = v[0] - re2;
+    v[3] = v[1] - im2;
+    v[1] = v[1] + im2;
+  }
+};
+
+// SFC-4: positions of the complex column group, the first ones, and of the real columns behind them
+template <int ALG>
+SFC_HD constexpr int complex4_positions() { return AlgTraits<ALG>::kHermitian ? 18 : 21; }
+
+// SFC-4, first part: the products of the complex column group (Eq. DFT4M) give the vertical
+// outputs of components 2 and 3.  settle(v) as in stream_outputs (sfc_stream_outputs.hpp).
+template <int ALG, typename T, typename F, typename Settle>
+SFC_HD void stream_complex4(F&& next, Settle&& settle, Vertical4<T>& va, Vertical4<T>& vb) {
+  auto settle_all = [&](Vertical4<T>& v) {
+#pragma unroll
+    for (int o = 0; o < 4; ++o) settle(v.v[o]);
+  };
+  if constexpr (!AlgTraits<ALG>::kHermitian) {
+    static_for<7>([&](auto rc) {
       constexpr int r1 = decltype(rc)::value;
-      col[r1] = take_product<NR * j + r1>(next);
+      const T m2 = take_product<3 * r1>(next), m1 = take_product<3 * r1 + 1>(next),
+              m0 = take_product<3 * r1 + 2>(next);  // rows a0 + a1, a1, a0
+      va.template feed<r1>(m0 - m1);
+      vb.template feed<r1>(m2 - m0 - m1);
     });
-    collapse4_rows(col, cc);
-    inv4_outputs(cc, z[real_comp4(j)]);
-  });
+  } else {
+    T re_a, im_a, re_b, im_b;  // twice components 2 and 3 of both columns
+    {
+      const T m0 = take_product<0>(next), m1 = take_product<1>(next), m2 = take_product<2>(next);
+      T uo0 = m0 - m1, uo1 = m2 - m0 - m1;
+      settle(uo0);
+      settle(uo1);
+      const T m3 = take_product<3>(next), m4 = take_product<4>(next), m5 = take_product<5>(next);
+      const T vo0 = m3 - m4, vo1 = m5 - m3 - m4;
+      re_a = uo0 + vo0;
+      im_a = uo1 + vo1;
+      re_b = uo1 - vo1;
+      im_b = vo0 - uo0;
+      settle(re_a);
+      settle(im_a);
+      settle(re_b);
+      settle(im_b);
+    }
+    static_for<4>([&](auto jc) {
+      constexpr int j = decltype(jc)::value, r1 = real_row4(j);
+      const T m2 = take_product<6 + 3 * j>(next), m1 = take_product<6 + 3 * j + 1>(next),
+              m0 = take_product<6 + 3 * j + 2>(next);
+      va.template feed<r1>(m0 - m1);
+      vb.template feed<r1>(m2 - m0 - m1);
+      if constexpr (j == 0) {
+        settle(va.v[0]);
+        settle(vb.v[0]);
+      } else {
+        if constexpr (j == 1) {
+          va.complex(re_a, im_a);
+          vb.complex(re_b, im_b);
+        }
+        settle_all(va);
+        settle_all(vb);
+      }
+    });
+  }
 }
 
-// SFC-4, second part: the products of the complex column group (positions 28 on; Eq. DFT4M)
-// give z[2], z[3].
-template <int ALG, typename T, typename F>
-SFC_HD void stream_vertical4_complex(F&& next, T (&z)[6][4]) {
-  constexpr int NR = 7, NC = 6, NREAL = 4;
-  constexpr int J0 = NR * NREAL;  // positions of the real columns come first
-  T c0[NC], c1[NC];
-  if constexpr (!AlgTraits<ALG>::kHermitian) {
-    T h0[NR], h1[NR];
-    static_for<NR>([&](auto rc) {
-      constexpr int r1 = decltype(rc)::value;
-      const T m2 = take_product<J0 + 3 * r1>(next), m1 = take_product<J0 + 3 * r1 + 1>(next),
-              m0 = take_product<J0 + 3 * r1 + 2>(next);  // rows a0 + a1, a1, a0
-      h0[r1] = m0 - m1;
-      h1[r1] = m2 - m0 - m1;
-    });
-    collapse4_rows(h0, c0);
-    collapse4_rows(h1, c1);
-  } else {
-    static_for<NREAL>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      const T m2 = take_product<J0 + 3 * j>(next), m1 = take_product<J0 + 3 * j + 1>(next),
-              m0 = take_product<J0 + 3 * j + 2>(next);
-      c0[real_comp4(j)] = m0 - m1;
-      c1[real_comp4(j)] = m2 - m0 - m1;
-    });
-    T m[6];
-    static_for<6>([&](auto ic) {
-      constexpr int i = decltype(ic)::value;
-      m[i] = take_product<J0 + 3 * NREAL + i>(next);
-    });
-    const T uo0 = m[0] - m[1], uo1 = m[2] - m[0] - m[1];
-    const T vo0 = m[3] - m[4], vo1 = m[5] - m[3] - m[4];
-    c0[2] = Half<T>::apply(uo0 + vo0);  // o00
-    c0[3] = Half<T>::apply(uo1 + vo1);  // o10
-    c1[2] = Half<T>::apply(uo1 - vo1);  // o01
-    c1[3] = Half<T>::apply(vo0 - uo0);  // o11
-  }
-  inv4_outputs(c0, z[2]);
-  inv4_outputs(c1, z[3]);
+// SFC-4, the other part: the products of real column J (7 positions) give its vertical outputs.
+template <int ALG, int J, typename T, typename F, typename Settle>
+SFC_HD void stream_real4(F&& next, Settle&& settle, Vertical4<T>& v) {
+  static_for<7>([&](auto rc) {
+    constexpr int r1 = decltype(rc)::value;
+    v.template feed<r1>(take_product<complex4_positions<ALG>() + 7 * J + r1>(next));
+#pragma unroll
+    for (int o = 0; o < (r1 < 4 ? r1 + 1 : 4); ++o) settle(v.v[o]);
+  });
 }
 
 template <int ALG, typename T, typename F>
@@ -769,9 +815,22 @@ SFC_HD void stream_vertical(F&& next, T (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>:
   using Tr = AlgTraits<ALG>;
   constexpr int NR = Tr::NR, NC = Tr::NC, NREAL = Tr::NREAL;
   if constexpr (Tr::kFamily == 4) {
-    // SFC-4: four real columns, then the one complex column group
-    stream_vertical4_real<ALG, T>(next, z);
-    stream_vertical4_complex<ALG, T>(next, z);
+    // SFC-4: the one complex column group, then four real columns
+    auto keep = [](T&) {};
+    Vertical4<T> va, vb;
+    stream_complex4<ALG, T>(next, keep, va, vb);
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      z[2][o] = va.v[o];
+      z[3][o] = vb.v[o];
+    }
+    static_for<4>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      Vertical4<T> v;
+      stream_real4<ALG, j, T>(next, keep, v);
+#pragma unroll
+      for (int o = 0; o < 4; ++o) z[real_comp4(j)][o] = v.v[o];
+    });
     return;
   } else {
   static_for<NREAL>([&](auto jc) {

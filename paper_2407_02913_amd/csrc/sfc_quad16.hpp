@@ -6,9 +6,9 @@
 // the A operand holding ONE point for 16 filters (row r = filter f0 + 4(r%4) + r/4) and the B
 // operand V of the same point for 16 tiles, every accumulator element is a wanted product:
 // lane l gets, for tile l%16, the filters f0 + 4i + l/16 -- filter l/16 of the four filter
-// quads f0/4 + i.  The 46 / 49 points of SFC-4 leave 6 x 4 partial outputs per pair, so four
-// pairs fit a lane's registers and the streaming output transform runs on four-element
-// vectors.  Per product that is a quarter of the matrix instructions, LDS reads of V and
+// quads f0/4 + i.  The 16 outputs of a pair are all that is kept from one product to the next
+// (sfc_stream_outputs.hpp), so four pairs fit a lane's registers and the streaming output transform
+// runs on four-element vectors.  Per product that is a quarter of the matrix instructions, LDS reads of V and
 // filter-operand bytes of the one-pair-per-lane form (sfc_fused_quad.hpp), which spends three
 // of four accumulator elements on mixed points.
 #pragma once
@@ -90,6 +90,12 @@ constexpr unsigned quad16_lds_layout(int what) {
   return what == 0 ? 0u : what == 1 ? tab_off : tab_off + 256u;
 }
 
+// Filter-operand blocks that are on the way or held when block s is multiplied, s included.
+template <int N>
+struct ConstantAhead {
+  static constexpr int at(int) { return N; }
+};
+
 // The products and the output transform of one wave: 16 tiles (V in LDS, groups of four
 // points in a ring of buffers kept filled by `sync`) x 16 filters (operand and dequantization
 // factors from global memory, a ring of loads ahead).
@@ -109,34 +115,48 @@ constexpr unsigned quad16_lds_layout(int what) {
 // Software pipeline: call j issues the matrix instructions of position j + 1 and then converts
 // the sums of position j, so the matrix pipe works under the vector arithmetic of the output
 // transform.
+//   ready()       called once, when the first loads from memory are under way and before V is read
+//   Ahead         filter-operand blocks asked for by position: constant, or fewer while more partial
+//                 outputs are kept
+//   J0, J1        the positions asked for
 //   consume(next) takes the products of the lane's four pairs (f4 element i: filter quad i) in
 //                 processing order, next(integral_constant<int, j>) being position j
-template <int ALG, int KC, int VB, int PS = KC * 1024, typename Sync, typename Consume>
+template <int ALG, int KC, int VB, int PS = KC * 1024, typename Ahead = ConstantAhead<8>, int J0 = 0,
+          int J1 = Order<ALG>::PP, typename Ready, typename Sync, typename Consume>
 __device__ __forceinline__ void quad16_stream(const unsigned char* vbuf, int lane,
                                               __amdgpu_buffer_rsrc_t ures, unsigned a_wave,
                                               __amdgpu_buffer_rsrc_t dres, unsigned d_wave,
-                                              Sync&& sync, Consume&& consume) {
-  constexpr int PP = Order<ALG>::PP;
+                                              Ready&& ready, Sync&& sync, Consume&& consume) {
   constexpr int GROUP_BYTES = 4 * PS;      // PS: bytes from one position's V to the next
-  constexpr int STEPS = PP * KC;           // filter-operand blocks of the wave
-  constexpr int RA = 8;                    // ... in flight
-  constexpr int NDB = (PP + 15) / 16;      // blocks of 16 positions' factors
-  constexpr int DR = NDB > 4 ? 2 : NDB;    // ... held at a time
+  constexpr int STEP0 = J0 * KC, STEPS = J1 * KC;  // filter-operand blocks of the wave
+  constexpr int ND0 = J0 / 16, NDB = (J1 + 15) / 16;  // blocks of 16 positions' factors
+  constexpr int DR = NDB - ND0 > 4 ? 2 : NDB - ND0;   // ... held at a time
   const unsigned a_lane = (unsigned)lane * 16u;
   const unsigned d_lane = (unsigned)(lane & 15) * 64u + (unsigned)(lane >> 4) * 16u;
-  v4i aring[RA];
+  v4i aop[STEPS];  // (every index is a constant: a block lives from its load to its products)
   v4f dblk[DR];
   auto load_a = [&](int s) {
-    aring[s % RA] = __builtin_amdgcn_raw_buffer_load_b128(ures, a_lane, a_wave + (unsigned)s * 1024u, 0);
+    aop[s] = __builtin_amdgcn_raw_buffer_load_b128(ures, a_lane, a_wave + (unsigned)s * 1024u, 0);
+  };
+  // blocks asked for by the time block s is multiplied: no fewer than before
+  auto asked = [](int s) constexpr {
+    int n = 0;
+    for (int i = STEP0; i <= s; ++i) {
+      int m = i + Ahead::at(i);
+      if (m > STEPS) m = STEPS;
+      if (m > n) n = m;
+    }
+    return n;
   };
   auto load_d = [&](int m) {  // (a last block may reach past the wave's table: never used)
     dblk[m % DR] = __builtin_bit_cast(
         v4f, __builtin_amdgcn_raw_buffer_load_b128(dres, d_lane, d_wave + (unsigned)m * 1024u, 0));
   };
 #pragma unroll
-  for (int m = 0; m < DR; ++m) load_d(m);
+  for (int m = ND0; m < ND0 + DR; ++m) load_d(m);
 #pragma unroll
-  for (int s = 0; s < RA && s < STEPS; ++s) load_a(s);
+  for (int s = STEP0; s < asked(STEP0); ++s) load_a(s);
+  ready();
   const unsigned char* blane = vbuf + (lane & 15) * 64 + (lane >> 4) * 16;
   // V of position jj for the lane's tile: KC reads of 16 bytes.  Up to two chunks they are
   // issued a call ahead of the matrix instructions that take them (PREB); with more the
@@ -150,36 +170,37 @@ __device__ __forceinline__ void quad16_stream(const unsigned char* vbuf, int lan
     for (int kc = 0; kc < NB; ++kc) breg[kc] = *(const v4i*)(bsrc + kc * 1024);
   };
   // the sums of position jj: KC chained matrix instructions
-  auto products = [&](int jj) -> v4i {
+  auto products = [&](auto position) __attribute__((always_inline)) -> v4i {
+    constexpr int jj = decltype(position)::value;
     v4i acc = {0, 0, 0, 0};
     const unsigned char* bsrc = blane + ((jj >> 2) % VB) * GROUP_BYTES + (jj & 3) * PS;
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      const int s = jj * KC + kc;
+    static_for<KC>([&](auto kcc) __attribute__((always_inline)) {
+      constexpr int kc = decltype(kcc)::value, s = jj * KC + kc;
       v4i b;
       if constexpr (PREB) b = breg[kc];
       else b = *(const v4i*)(bsrc + kc * 1024);
-      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(aring[s % RA], b, acc, 0, 0, 0);
-      if (s + RA < STEPS) load_a(s + RA);
-    }
+      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop[s], b, acc, 0, 0, 0);
+      constexpr int from = asked(s), to = s + 1 < STEPS ? asked(s + 1) : from;
+      static_for<to - from>([&](auto n) __attribute__((always_inline)) { load_a(from + decltype(n)::value); });
+    });
     return acc;
   };
-  if constexpr (PREB) read_b(0);
-  v4i acc_cur = products(0);
-  if constexpr (PREB) read_b(1);
+  if constexpr (PREB) read_b(J0);
+  v4i acc_cur = products(std::integral_constant<int, J0>{});
+  if constexpr (PREB) read_b(J0 + 1);
   // (the streaming output transform asks for the products in order and names the position)
   auto next = [&](auto position) __attribute__((always_inline)) -> f4 {
     constexpr int j = decltype(position)::value;
     v4i acc_new = acc_cur;
     if constexpr (PREB) {
-      if (j + 1 < PP) acc_new = products(j + 1);
-      if (j + 2 < PP) {
+      if constexpr (j + 1 < J1) acc_new = products(std::integral_constant<int, j + 1>{});
+      if (j + 2 < J1) {
         if (((j + 2) & 3) == 0) sync((j + 2) / 4 - 1);
         read_b(j + 2);
       }
-    } else if (j + 1 < PP) {
+    } else if constexpr (j + 1 < J1) {
       if (((j + 1) & 3) == 0) sync((j + 1) / 4 - 1);
-      acc_new = products(j + 1);
+      acc_new = products(std::integral_constant<int, j + 1>{});
     }
     __builtin_amdgcn_sched_barrier(0);  // the matrix instructions go first
     f4 v;
@@ -199,17 +220,71 @@ __device__ __forceinline__ void quad16_stream(const unsigned char* vbuf, int lan
   consume(next);
 }
 
-// The same up to the vertical axis: leaves z[b][o1] of the lane's four pairs.
-template <int ALG, int KC, int VB, int PS = KC * 1024, typename Sync>
-__device__ __forceinline__ void quad16_products(const unsigned char* vbuf, int lane,
-                                                __amdgpu_buffer_rsrc_t ures, unsigned a_wave,
-                                                __amdgpu_buffer_rsrc_t dres, unsigned d_wave,
-                                                Sync&& sync,
-                                                f4 (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M]) {
-  quad16_stream<ALG, KC, VB, PS>(vbuf, lane, ures, a_wave, dres, d_wave, sync,
-                                 [&](auto& next) __attribute__((always_inline)) {
-                                   stream_vertical<ALG, f4>(next, z);
-                                 });
+// keeps the compiler from putting additions off and the products in registers instead
+// (stream_outputs)
+struct SettleF4 {
+  __device__ __forceinline__ void operator()(f4& v) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(v.v[i]));
+  }
+};
+
+// Two waves for one block of 16 tiles x 16 filters (SFC-4), cut by horizontal class: wave HALF = 0
+// takes the complex column group and column 0 (components 2, 3, 0), HALF = 1 columns 1, 4 and 5.
+// Together they do the work of one wave, each with half of its chain and half of its partial outputs
+// (12 values of four pairs instead of 24).
+template <int ALG, int HALF>
+struct Quad16Half {
+  static constexpr int kCut = complex4_positions<ALG>() + 7;
+  static constexpr int J0 = HALF == 0 ? 0 : kCut, J1 = HALF == 0 ? kCut : AlgTraits<ALG>::P;
+  static constexpr int comp(int i) { return HALF == 0 ? (i < 2 ? 2 + i : 0) : (i == 0 ? 1 : 3 + i); }
+};
+constexpr int kQuad16HalfBytes = 6 * 1024;  // what a wave hands to the other one
+
+// The products of one half, its partial outputs exchanged: leaves z of the pairs 2 HALF, 2 HALF + 1
+// (as elements 0 and 1) with all their components.  give, take: LDS blocks of kQuad16HalfBytes that
+// this wave writes and the other one reads, and the other way round; meet() is called twice, all V
+// read before the first and every block written before the second.
+template <int ALG, int KC, int VB, int PS, int HALF, typename Ahead, typename Ready, typename Sync, typename Meet>
+__device__ __forceinline__ void quad16_half(const unsigned char* vbuf, int lane, __amdgpu_buffer_rsrc_t ures,
+                                            unsigned a_wave, __amdgpu_buffer_rsrc_t dres, unsigned d_wave,
+                                            Ready&& ready, Sync&& sync, Meet&& meet, unsigned char* give,
+                                            const unsigned char* take, f4 (&zz)[6][4]) {
+  using Mine = Quad16Half<ALG, HALF>;
+  using Other = Quad16Half<ALG, 1 - HALF>;
+  Vertical4<f4> v[3];
+  quad16_stream<ALG, KC, VB, PS, Ahead, Mine::J0, Mine::J1>(
+      vbuf, lane, ures, a_wave, dres, d_wave, ready, sync, [&](auto& next) __attribute__((always_inline)) {
+        SettleF4 settle;
+        if constexpr (HALF == 0) {
+          stream_complex4<ALG, f4>(next, settle, v[0], v[1]);
+          stream_real4<ALG, 0, f4>(next, settle, v[2]);
+        } else {
+          stream_real4<ALG, 1, f4>(next, settle, v[0]);
+          stream_real4<ALG, 2, f4>(next, settle, v[1]);
+          stream_real4<ALG, 3, f4>(next, settle, v[2]);
+        }
+      });
+  meet();
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int e = 2 * (1 - HALF) + i;
+      *(v4f*)(give + ((c * 2 + i) * 64 + lane) * 16) =
+          v4f{v[c].v[0].v[e], v[c].v[1].v[e], v[c].v[2].v[e], v[c].v[3].v[e]};
+#pragma unroll
+      for (int o = 0; o < 4; ++o) zz[Mine::comp(c)][o].v[i] = v[c].v[o].v[2 * HALF + i];
+    }
+  meet();
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const v4f t = *(const v4f*)(take + ((c * 2 + i) * 64 + lane) * 16);
+#pragma unroll
+      for (int o = 0; o < 4; ++o) zz[Other::comp(c)][o].v[i] = t[o];
+    }
 }
 
 // y of the wave's 16 tiles x 16 filters from z (pair i of lane l: tile l%16, filter
@@ -218,15 +293,16 @@ __device__ __forceinline__ void quad16_products(const unsigned char* vbuf, int l
 // in the wave's block as [filter 16][tile 16][row 4][4 outputs]; then lane l takes row l/16 of
 // tile l%16 for one filter after the other, so that a store instruction writes, for one
 // filter, four image rows of 16 neighbouring tiles: consecutive lanes hold consecutive
-// pieces of an image row.  No branches: a piece outside the image, or of a filter beyond
-// Cout, gets an offset outside the buffer and is dropped by the bounds check.
+// pieces of an image row.  A piece outside the image gets an offset outside the buffer and is
+// dropped by the bounds check; filters beyond Cout end the loop.
+// NP, i0: pairs i0 .. i0 + NP - 1 of z alone, filters from 4 kq0 on (a block of 4 NP filters).
 // EV: elements per store instruction, 4 when W is a multiple of 4 (a tile row never crosses
 // the end of an image row), else 2 (W even) or 1.
-template <int ALG, int OUT, int EV>
+template <int ALG, int OUT, int EV, int NP = 4>
 __device__ __forceinline__ void quad16_store(const f4 (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M],
                                              unsigned char* stage, const int* tile_tab, int lane,
                                              int kq0, float x_scale, float inv_y,
-                                             __amdgpu_buffer_rsrc_t yres, const Geometry& g) {
+                                             __amdgpu_buffer_rsrc_t yres, const Geometry& g, int i0 = 0) {
   constexpr int NC = AlgTraits<ALG>::NC, M = AlgTraits<ALG>::M;
   static_assert(M == 4, "tiles of 4 x 4 outputs");
   constexpr unsigned esz = OUT == 2 ? 1u : 4u;
@@ -234,16 +310,18 @@ __device__ __forceinline__ void quad16_store(const f4 (&z)[AlgTraits<ALG>::NC][A
   constexpr float kMagic = 12582912.0f;
   const int tl = lane & 15, q = lane >> 4;
   const float act = x_scale * inv_y;  // int8 output: activation scale over output scale
+  // this lane's piece: row q of tile tl (asked for here, waited for behind the transform)
+  const int tile_off = tile_tab[tl], tile_rows = tile_tab[16 + tl], tile_cols = tile_tab[32 + tl];
   // float32 staging: 16-byte slots, slot (tile, row) of a filter moved round by tile/4 so
   // that the 16 lanes of a quarter wave fall into different banks, writing and reading
   auto slot = [](int tile, int row) { return tile * 4 + ((row + (tile >> 2)) & 3); };
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < NP; ++i) {
     float zi[NC][M];
 #pragma unroll
     for (int b = 0; b < NC; ++b)
 #pragma unroll
-      for (int o = 0; o < M; ++o) zi[b][o] = z[b][o].v[i];
+      for (int o = 0; o < M; ++o) zi[b][o] = z[b][o].v[i0 + i];
     const int f = 4 * i + q;
 #pragma unroll
     for (int o1 = 0; o1 < M; ++o1) {
@@ -269,54 +347,67 @@ __device__ __forceinline__ void quad16_store(const f4 (&z)[AlgTraits<ALG>::NC][A
     }
   }
   __builtin_amdgcn_wave_barrier();  // LDS accesses of one wave complete in order
-  // this lane's piece: row q of tile tl
   const int HW = g.H * g.W;
-  const bool row_ok = q < tile_tab[16 + tl];
-  const int cols = row_ok ? tile_tab[32 + tl] : 0;
-  const unsigned base = (unsigned)(tile_tab[tl] + q * g.W);  // elements, filter 0
+  const int cols = q < tile_rows ? tile_cols : 0;
+  const unsigned base = esz * (unsigned)(tile_off + q * g.W);  // filter 0
+  // byte offsets of the lane's store pieces (filter 0; outside the buffer: dropped); a filter's
+  // plane is the scalar offset of the store
+  constexpr int NE = EV == 4 ? 1 : EV == 2 ? 2 : 4;
+  unsigned piece[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) piece[e] = cols > EV * e ? base + esz * (unsigned)(EV * e) : kOutOfRange;
   const bool stream = g.W >= 48;  // whole long rows per workgroup: past the L2
-  auto run = [&](auto policy) {
-  constexpr bool kStream = decltype(policy)::value;
+  const int nk = min(4 * NP, g.Cout - 4 * kq0);  // filters of the wave that exist
+  auto put = [&](auto policy, auto full) {
+  constexpr int kPolicy = decltype(policy)::value ? kStreamStore : 0;
+  constexpr int KB = OUT == 2 ? 4 * NP : 4;  // filters read from the block before the first is stored
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int kc = 4 * kq0 + k;
-    const unsigned off = esz * (base + (unsigned)kc * (unsigned)HW);
-    const int ncol = kc < g.Cout ? cols : 0;
-    if constexpr (OUT == 2) {
-      const unsigned word = *(const unsigned*)(stage + ((k * 16 + tl) * 4 + ((q + k) & 3)) * 4);
-      if constexpr (EV == 4) {
-        const unsigned o = ncol > 0 ? off : kOutOfRange;
-        if constexpr (kStream) __builtin_amdgcn_raw_buffer_store_b32(word, yres, o, 0, kStreamStore);
-        else __builtin_amdgcn_raw_buffer_store_b32(word, yres, o, 0, 0);
-      } else if constexpr (EV == 2) {
-        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)word, yres, ncol > 0 ? off : kOutOfRange, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(word >> 16), yres,
-                                              ncol > 2 ? off + 2u : kOutOfRange, 0, 0);
+  for (int k0 = 0; k0 < 4 * NP; k0 += KB) {
+    unsigned word[OUT == 2 ? KB : 1];
+    v4f quad[OUT == 2 ? 1 : KB];
+#pragma unroll
+    for (int kk = 0; kk < KB; ++kk) {
+      const int k = k0 + kk;
+      if constexpr (OUT == 2) word[kk] = *(const unsigned*)(stage + ((k * 16 + tl) * 4 + ((q + k) & 3)) * 4);
+      else quad[kk] = *(const v4f*)(stage + (k * 64 + slot(tl, q)) * 16);
+    }
+#pragma unroll
+    for (int kk = 0; kk < KB; ++kk) {
+      const int k = k0 + kk;
+      if (!decltype(full)::value && k >= nk) break;
+      const unsigned plane = esz * (unsigned)(4 * kq0 + k) * (unsigned)HW;
+      if constexpr (OUT == 2) {
+        const unsigned w = word[kk];
+        if constexpr (EV == 4) {
+          __builtin_amdgcn_raw_buffer_store_b32(w, yres, piece[0], plane, kPolicy);
+        } else if constexpr (EV == 2) {
+          __builtin_amdgcn_raw_buffer_store_b16((unsigned short)w, yres, piece[0], plane, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(w >> 16), yres, piece[1], plane, 0);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(w >> (8 * e)), yres, piece[e], plane, 0);
+        }
       } else {
+        const v4f v = quad[kk];
+        if constexpr (EV == 4) {
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), yres, piece[0], plane, kPolicy);
+        } else if constexpr (EV == 2) {
+          __builtin_amdgcn_raw_buffer_store_b64(v2f{v[0], v[1]}, yres, piece[0], plane, 0);
+          __builtin_amdgcn_raw_buffer_store_b64(v2f{v[2], v[3]}, yres, piece[1], plane, 0);
+        } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(word >> (8 * e)), yres,
-                                               ncol > e ? off + (unsigned)e : kOutOfRange, 0, 0);
-      }
-    } else {
-      const v4f v = *(const v4f*)(stage + (k * 64 + slot(tl, q)) * 16);
-      if constexpr (EV == 4) {
-        const unsigned o = ncol > 0 ? off : kOutOfRange;
-        if constexpr (kStream) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), yres, o, 0, kStreamStore);
-        else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), yres, o, 0, 0);
-      } else if constexpr (EV == 2) {
-        __builtin_amdgcn_raw_buffer_store_b64(v2f{v[0], v[1]}, yres, ncol > 0 ? off : kOutOfRange, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b64(v2f{v[2], v[3]}, yres, ncol > 2 ? off + 8u : kOutOfRange, 0, 0);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[e]), yres,
-                                                ncol > e ? off + 4u * (unsigned)e : kOutOfRange, 0, 0);
+          for (int e = 0; e < 4; ++e) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[e]), yres, piece[e], plane, 0);
+        }
       }
     }
   }
   };
-  if (stream) run(std::true_type{});
+  auto run = [&](auto policy) {
+    if (nk >= 4 * NP) put(policy, std::true_type{});
+    else if (nk > 0) put(policy, std::false_type{});
+  };
+  if (EV == 4 && stream) run(std::true_type{});
   else run(std::false_type{});
 }
 
@@ -329,7 +420,7 @@ __global__ __launch_bounds__(NW * 64, 2) void quad16_kernel(
     const int8_t* __restrict__ V, const int8_t* __restrict__ U16, const float* __restrict__ dq16,
     float x_scale, float inv_y, void* __restrict__ y, Geometry g, int fgroups) {
   using Tr = AlgTraits<ALG>;
-  constexpr int P = Tr::P, M = Tr::M, NC = Tr::NC;
+  constexpr int P = Tr::P, M = Tr::M;
   constexpr int PP = Order<ALG>::PP, PG = PP / 4;
   constexpr int CP = KC * 64;
   constexpr int GROUP_BYTES = 4 * 16 * CP;
@@ -429,25 +520,18 @@ __global__ __launch_bounds__(NW * 64, 2) void quad16_kernel(
     __syncthreads();
   };
   const unsigned a_wave = (unsigned)fg * (unsigned)(PP * KC * 1024), d_wave = (unsigned)fg * (unsigned)(PP * 64);
-  if constexpr (Tr::kFamily == 4) {
-    f4 z[NC][M];
-    quad16_products<ALG, KC, VB>(vbuf, lane, ures, a_wave, dres, d_wave, sync, z);
-    __syncthreads();  // the staging blocks take the place of the V buffers
-    quad16_store<ALG, OUT, EV>(z, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
-  } else {
-    // (EV = 0: the width of a store is chosen here, the products are not compiled once for each)
-    static_assert(M == 4, "outputs kept: the 7x7-filter form");
-    f4 out[M][M];
-    quad16_stream<ALG, KC, VB>(vbuf, lane, ures, a_wave, dres, d_wave, sync,
-                               [&](auto& next) __attribute__((always_inline)) {
-                                 auto settle = [](f4& v) __attribute__((always_inline)) {
-#pragma unroll
-                                   for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(v.v[i]));
-                                 };
-                                 stream_outputs<ALG, f4>(next, settle, out);
-                               });
-    __syncthreads();
-    constexpr int COLS = kOutputColumns + M;
+  static_assert(M == 4, "tiles of 4 x 4 outputs");
+  constexpr int COLS = kOutputColumns + M;
+  f4 out[M][M];
+  quad16_stream<ALG, KC, VB>(vbuf, lane, ures, a_wave, dres, d_wave, [] {}, sync,
+                             [&](auto& next) __attribute__((always_inline)) {
+                               if constexpr (Tr::kFamily == 4) stream_outputs4<ALG, f4>(next, SettleF4{}, out);
+                               else stream_outputs<ALG, f4>(next, SettleF4{}, out);
+                             });
+  __syncthreads();  // the staging blocks take the place of the V buffers
+  if constexpr (EV != 0) {
+    quad16_store<COLS, OUT, EV>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+  } else {  // (the width of a store is chosen here, the products are not compiled once for each)
     if (g.W % 4 == 0) quad16_store<COLS, OUT, 4>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
     else if (g.W % 2 == 0) quad16_store<COLS, OUT, 2>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
     else quad16_store<COLS, OUT, 1>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);

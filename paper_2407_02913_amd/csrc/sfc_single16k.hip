@@ -68,8 +68,9 @@ __global__ __launch_bounds__(512, 2) void single16k_kernel(
   constexpr int M = Tr::M, NC = Tr::NC, PAD = Tr::PAD;
   constexpr int PP = Order<ALG>::PP;
   constexpr int NW = 8, SPW = 16 / NW;
-  constexpr int JR = 28;             // positions of the real columns (4 x 7)
-  constexpr int JC = PP - JR;        // ... of the complex column group, padded (20 / 24)
+  constexpr int JR = 28;             // positions of the real columns (4 x 7), from J0R on
+  constexpr int J0R = complex4_positions<ALG>();
+  constexpr int JC = (J0R + 3) / 4 * 4;  // ... of the complex column group, padded (20 / 24)
   constexpr int VS = 1024 + 16;      // bytes of V per position (16 positions written at once: banks)
   constexpr int NPB = MfmaInput<ALG>::NPB;
   constexpr int RA = 4, RD = 4;
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(512, 2) void single16k_kernel(
   static_assert(JC <= JR, "one accumulator array serves both roles");
   v4i acc[JR];  // the complex waves use the first JC
 #pragma unroll
-  for (int j = 0; j < RA; ++j) load_a((role == 0 ? 0 : JR) + j, 0, j);
+  for (int j = 0; j < RA; ++j) load_a((role == 0 ? J0R : 0) + j, 0, j);
 #pragma unroll
   for (int j = 0; j < JR; ++j) acc[j] = v4i{0, 0, 0, 0};
   MfmaInput<ALG> mi;
@@ -162,8 +163,8 @@ __global__ __launch_bounds__(512, 2) void single16k_kernel(
       }
     }
     __syncthreads();
-    if (role == 0) chunk_products<0, JR, JR, RA, VS>(blane, acc, aring, kc, load_a);
-    else chunk_products<JR, PP, JR, RA, VS>(blane, acc, aring, kc, load_a);
+    if (role == 0) chunk_products<J0R, J0R + JR, JR, RA, VS>(blane, acc, aring, kc, load_a);
+    else chunk_products<0, JC, JR, RA, VS>(blane, acc, aring, kc, load_a);
   }
 
   // ---- 3. output transform from the accumulators, hand-over, store ------------------------------
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(512, 2) void single16k_kernel(
   f4* xchg = (f4*)lds + (wave & 3) * (2 * M * 64);
   if (role == 0) {
 #pragma unroll
-    for (int j = 0; j < RD; ++j) load_d(j, j);
+    for (int j = 0; j < RD; ++j) load_d(J0R + j, j);
     int j = 0;  // folds to a constant after unrolling
     auto next = [&]() -> f4 {
       f4 v;
@@ -190,14 +191,20 @@ __global__ __launch_bounds__(512, 2) void single16k_kernel(
         asm volatile("" : "+v"(t));  // the accumulator's registers are free from here on
         v.v[i] = t;
       }
-      if (j + RD < JR) load_d(j + RD, j % RD);
+      if (j + RD < JR) load_d(J0R + j + RD, j % RD);
       ++j;
       return v;
     };
-    stream_vertical4_real<ALG, f4>(next, z);
+    static_for<4>([&](auto jc) __attribute__((always_inline)) {
+      constexpr int jj = decltype(jc)::value;
+      Vertical4<f4> v;
+      stream_real4<ALG, jj, f4>(next, [](f4&) {}, v);
+#pragma unroll
+      for (int o = 0; o < M; ++o) z[real_comp4(jj)][o] = v.v[o];
+    });
   } else {
 #pragma unroll
-    for (int j = 0; j < RD; ++j) load_d(JR + j, j);
+    for (int j = 0; j < RD; ++j) load_d(j, j);
     int j = 0;
     auto next = [&]() -> f4 {
       f4 v;
@@ -208,11 +215,17 @@ __global__ __launch_bounds__(512, 2) void single16k_kernel(
         asm volatile("" : "+v"(t));
         v.v[i] = t;
       }
-      if (j + RD < JC) load_d(JR + j + RD, j % RD);
+      if (j + RD < JC) load_d(j + RD, j % RD);
       ++j;
       return v;
     };
-    stream_vertical4_complex<ALG, f4>(next, z);
+    Vertical4<f4> va, vb;
+    stream_complex4<ALG, f4>(next, [](f4&) {}, va, vb);
+#pragma unroll
+    for (int o = 0; o < M; ++o) {
+      z[2][o] = va.v[o];
+      z[3][o] = vb.v[o];
+    }
   }
   __syncthreads();  // every wave is done with V and the staged planes: hand-over and staging blocks
   if (role == 1) {

@@ -12,9 +12,9 @@
 //   product_small_kernel  products + output transform from V, 256 and 512 input channels
 //
 // The first cuts the 46 positions of the processing order by horizontal class into seven parts
-// of at most seven: the four real columns (positions 0..27), and of the complex column group the
-// points kept from the nested form against real rows 0, 1 (28..33) and 5, 6 (34..39) and the
-// Hermitian ones (40..45).  Every part leaves four partial outputs per (tile, filter) pair.
+// of at most seven: the four real columns (positions 18..45), and of the complex column group the
+// points kept from the nested form against real rows 0, 1 (6..11) and 5, 6 (12..17) and the
+// Hermitian ones (0..5).  Every part leaves four partial outputs per (tile, filter) pair.
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
 #include "sfc_mfma_input.hpp"
@@ -31,7 +31,7 @@ constexpr int kSmallAlg = 4;    // SFC_ALG_4X4_P46
 constexpr int kParts = 7;
 constexpr int kPartSlots = 7;  // positions of the largest part
 
-__host__ __device__ constexpr int part_first(int part) { return part < 4 ? 7 * part : 28 + 6 * (part - 4); }
+__host__ __device__ constexpr int part_first(int part) { return part < 4 ? 18 + 7 * part : part == 6 ? 0 : 6 * (part - 3); }
 __host__ __device__ constexpr int part_count(int part) { return part < 4 ? 7 : 6; }
 
 // The products m[0..6] of one part -> four values: the vertical outputs of a real column (parts
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void single_small_kernel(
       constexpr int jj = decltype(jc)::value;
       v4i acc = {0, 0, 0, 0};
 #pragma unroll
-      for (int kc = 0; kc < KC; ++kc)  // (position 46 of a last part of six: V of a position without a point)
+      for (int kc = 0; kc < KC; ++kc)  // (the seventh of a part of six is not used)
         acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[jj * KC + kc], *(const v4i*)(bsrc + jj * VS + kc * 1024), acc, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) m[jj].v[i] = (float)acc[i] * row_lane<jj>(dq[i]);

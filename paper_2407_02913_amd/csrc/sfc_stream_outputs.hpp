@@ -1,4 +1,4 @@
-// Streaming output transform that keeps the outputs themselves (SFC-6(4x4,7x7), 184 points).
+// Streaming output transform that keeps the outputs themselves (SFC-6(4x4,7x7), 184 points; SFC-4).
 //
 // stream_vertical (sfc_points.hpp) leaves NC x M values per pair for the inverse along the
 // horizontal axis; with the 12 components of this form that is 48 registers a pair.  Here a
@@ -181,6 +181,44 @@ SFC_HD void stream_outputs(F&& next, Settle&& settle, T (&y)[AlgTraits<ALG>::M][
         y[c][o] = col[c];
         settle(y[c][o]);
       }
+    }
+  });
+}
+
+// The same for SFC-4: y[o2][o1] = 16 times output (o1, o2).  The complex column group comes first, so
+// at most 21 values of a pair are kept at any time (8 of the group, 4 of column 0, column 1 on the
+// way; from then on the 16 outputs and one column) where stream_vertical ends with 24.
+template <int ALG, typename T, typename F, typename Settle>
+SFC_HD void stream_outputs4(F&& next, Settle&& settle, T (&y)[4][4]) {
+  static_assert(AlgTraits<ALG>::kFamily == 4, "SFC-4");
+  Vertical4<T> va, vb, v0;
+  stream_complex4<ALG, T>(next, settle, va, vb);
+  stream_real4<ALG, 0, T>(next, settle, v0);
+  {
+    Vertical4<T> v1;
+    stream_real4<ALG, 1, T>(next, settle, v1);
+#pragma unroll
+    for (int o1 = 0; o1 < 4; ++o1) {
+      Vertical4<T> row;  // the same inverse along the row
+      row.v[0] = v0.v[o1] + v1.v[o1];
+      row.v[1] = v0.v[o1] - v1.v[o1];
+      row.complex(va.v[o1] + va.v[o1], vb.v[o1] + vb.v[o1]);
+#pragma unroll
+      for (int o2 = 0; o2 < 4; ++o2) {
+        y[o2][o1] = row.v[o2];
+        settle(y[o2][o1]);
+      }
+    }
+  }
+  static_for<2>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    Vertical4<T> v;
+    stream_real4<ALG, 2 + j, T>(next, settle, v);
+#pragma unroll
+    for (int o1 = 0; o1 < 4; ++o1) {
+      T& o = y[j == 0 ? 0 : 3][o1];
+      o = o + T(4) * v.v[o1];
+      settle(o);
     }
   });
 }

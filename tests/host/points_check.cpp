@@ -8,7 +8,8 @@
 //   A <alg> <p> <M*M ints>     output transform row p (times 36; times 16 for 4x4)
 //   S <alg> <p> <M*M ints>     the same row through the streaming form of the fused kernels
 //                              (products fed in processing order, stream_vertical + stream_row)
-//   O <alg> <p> <M*M ints>     8: the same through stream_outputs, which keeps the outputs
+//   O <alg> <p> <M*M ints>     4, 5, 8: the same through stream_outputs4 and stream_outputs, which
+//                              keep the outputs
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -72,12 +73,13 @@ void dump() {
     std::printf("\n");
     if (q == 0 && j != P) std::printf("S %d -1 %d\n", ALG, j);  // must consume exactly P products
   }
-  if constexpr (ALG == 8) {
+  if constexpr (ALG == 8 || Tr::kFamily == 4) {
     for (int q = 0; q < P; ++q) {
       int j = 0;
       auto next = [&]() -> float { return order.pt[j++] == q ? 3.0f : 0.0f; };
       float y[M][M];
-      stream_outputs<ALG, float>(next, [](float&) {}, y);
+      if constexpr (Tr::kFamily == 4) stream_outputs4<ALG, float>(next, [](float&) {}, y);
+      else stream_outputs<ALG, float>(next, [](float&) {}, y);
       std::printf("O %d %d", ALG, q);
       for (int o1 = 0; o1 < M; ++o1) {
         float out[M];

@@ -712,6 +712,16 @@ PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
     ("fused", "quad16", (203, 33, 130, 12, 12)),     # one chunk, rows of four outputs per store
     ("fused", "quad16", (81, 100, 264, 9, 13)),      # two chunks, single outputs per store
     ("fused", "quad16", (115, 193, 136, 14, 14)),    # four chunks, the last with one channel; pairs per store
+    ("single", "single16", (37, 33, 17, 56, 56)),    # from here more than 512 workgroups of one chunk
+    ("single", "single16", (513, 9, 8, 14, 14)),
+    ("single", "single16", (2060, 20, 8, 7, 7)),
+    ("single", "single16", (646, 2, 3, 13, 9)),
+    ("single", "single16", (74, 17, 70, 28, 28)),    # two workgroups along the filters
+    ("single", "single16", (19, 70, 17, 56, 56)),    # from here more than 256 of two chunks
+    ("single", "single16", (260, 70, 40, 14, 14)),
+    ("single", "single16", (323, 127, 5, 13, 9)),
+    ("single", "single16", (38, 100, 130, 28, 28)),
+    ("single", "single16", (38, 128, 16, 28, 28)),   # 133 of two chunks
     ("fused", "quad16", (549, 200, 72, 11, 7)),      # four chunks, odd W, a ragged last tile block
     ("fused", "fused_quad", (41, 200, 72, 11, 7)),
     ("fused", "fused_quad", (9, 193, 136, 14, 14)),

@@ -267,7 +267,7 @@ def test_kernel_add_networks_realize_the_oracle_matrices(kernel_maps, alg_id, al
     assert np.array_equal(kernel_maps[("A", alg_id)], a2)
     # the streaming form of the fused kernels (processing order + per-group collapse)
     assert np.array_equal(kernel_maps[("S", alg_id)], a2)
-    if alg_id == 8:  # the form that keeps the outputs instead of the horizontal components
+    if alg_id in (4, 5, 8):  # the form that keeps the outputs instead of the horizontal components
         assert np.array_equal(kernel_maps[("O", alg_id)], a2)
 
 
