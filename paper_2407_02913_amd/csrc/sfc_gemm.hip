@@ -187,13 +187,20 @@ hipError_t launch_product_gemm_i8(const Geometry& g, const void* V, const void* 
 // (whole_image_tiles); y is then written image by image (store_planes) from a staging
 // block of M*M floats per pair.
 // ---------------------------------------------------------------------------------------
-// Points in flight per lane: 12 where a compute unit holds many waves; 32 for the forms
+// Points in flight per lane.  The SFC-4 forms ask for all of them at once: what bounds the kernel on
+// any layer but the largest is how often a wave waits for memory, and 24 partial outputs leave the
+// registers (68 in all).  With 12 ahead a wave waited four times; with sixteen waves to a workgroup, as
+// that needed, small layers left compute units idle.  us per layer before and after, 160 channels, 46
+// points: 64 filters on one 28x28 map 19.6 -> 14.1, 136 filters on one 31x45 map 25.3 -> 20.2, on 36 of
+// them 83.6 -> 80.1, 184 filters on 213 9x13 maps 81.5 -> 76.8; over 259 layers from 3 to 800 of the
+// larger workgroups 0.70 to 1.01 of the time, so there is no second form.
+// 12 for the 6x6 forms, whose compute units hold many waves; 32 for the forms
 // whose partial outputs allow few (7x7 tiles, 5x5 and 7x7 filters: four-wave workgroups), so
 // that the eight waves a compute unit has on a small layer keep some 64 KB of M on the way
 // (512 channels on 7x7 maps, 256 images: the same 23 us either way when measured alone; the
 // kernel there is bound by the bytes of M, see m_sum_bytes).
 template <int ALG>
-constexpr int sum_ring() { return AlgTraits<ALG>::NC <= 8 ? 12 : 32; }
+constexpr int sum_ring() { return AlgTraits<ALG>::NC <= 6 ? Order<ALG>::PP : AlgTraits<ALG>::NC <= 8 ? 12 : 32; }
 
 template <int ALG, bool PLANES, int NW>
 constexpr unsigned sums_stage_bytes() {
@@ -287,8 +294,9 @@ static hipError_t launch_sums_impl(const Geometry& g, const int32_t* M, const Fi
   // 12x4: they need the 256-register budget; four waves per workgroup, so that a small layer
   // still has several workgroups per compute unit, reading M and writing y out of phase (512
   // channels on 7x7 maps at batch 64, 7x7 tiles: staged path 38.9 us against 47.3 with eight).
-  // The 6x6 forms (8x6 partial outputs) take eight waves: with sixteen, 128 registers, they spill.
-  constexpr int NW = AlgTraits<ALG>::NC <= 6 ? 16 : AlgTraits<ALG>::NC <= 8 ? 8 : 4;
+  // The SFC-4 forms take four as well (sum_ring); the 6x6 forms (8x6 partial outputs) eight: with
+  // sixteen, 128 registers, they spill.
+  constexpr int NW = AlgTraits<ALG>::NC == 8 ? 8 : 4;
   constexpr unsigned lds_bytes = sums_stage_bytes<ALG, PLANES, NW>() + 256;
   static_assert(lds_bytes <= 160u * 1024u, "staging blocks exceed the LDS of a compute unit");
   auto kernel = output_sums_kernel<ALG, OUT, VEC2, NW, PLANES>;

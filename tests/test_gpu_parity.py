@@ -755,6 +755,10 @@ PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
     ("single", "single_small", (155, 70, 17, 5, 6)),
     ("single", "single_small", (47, 70, 17, 11, 20)),
     ("single", "single_small", (299, 70, 20, 5, 6)),
+    ("staged", "output_sums", (1, 130, 1, 1, 1)),    # one pair
+    ("staged", "output_sums", (7, 184, 17, 31, 45)),  # single outputs per store, a second workgroup of one filter
+    ("staged", "output_sums", (3, 150, 66, 30, 46)),  # pairs per store
+    ("staged", "output_sums", (5, 129, 16, 16, 16)),  # whole images
 ]
 
 
