@@ -755,10 +755,6 @@ PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
     ("single", "single_small", (155, 70, 17, 5, 6)),
     ("single", "single_small", (47, 70, 17, 11, 20)),
     ("single", "single_small", (299, 70, 20, 5, 6)),
-    ("staged", "output_sums", (1, 130, 1, 1, 1)),    # one pair
-    ("staged", "output_sums", (7, 184, 17, 31, 45)),  # single outputs per store, a second workgroup of one filter
-    ("staged", "output_sums", (3, 150, 66, 30, 46)),  # pairs per store
-    ("staged", "output_sums", (5, 129, 16, 16, 16)),  # whole images
 ]
 
 
@@ -782,6 +778,16 @@ def test_46_points_past_the_small_layers(binding, path, kernel, shape):
     # one channel, one pixel: y is j/127 of its maximum, j = -127 .. 127, or 1.25 j steps of the
     # output: a tie for every second even j, each one 1/255 of the values
     assert differ < (63 / 255 if shape[1:] == (1, 1, 1, 1) else 1e-3)
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 130, 1, 1, 1),     # one pair
+    (7, 184, 17, 31, 45),  # single outputs per store, a second workgroup of one filter
+    (3, 150, 66, 30, 46),  # pairs per store
+    (5, 129, 16, 16, 16),  # whole images
+])
+def test_46_points_staged_output_transform(binding, shape):
+    test_46_points_past_the_small_layers(binding, "staged", "staged", shape)
 
 
 def test_single_kernel_path_channel_limits(binding):
