@@ -721,10 +721,11 @@ struct Vertical4 {
     } else if constexpr (R == 2) {
       v[2] = m;
     } else if constexpr (R == 3) {
-      v[2] = v[2] - m;
       v[3] = m;
     } else if constexpr (R == 4) {
-      const T re = m - v[3], im = v[2] - m;
+      // (in the order of collapse4_rows: float32 sums, and int8 outputs at a tie of their rounding,
+      // are those of every other form of this transform)
+      const T re = m - v[3], im = v[2] - m - v[3];
       complex(re + re, im + im);
     } else {
       T& o = v[R == 5 ? 0 : 3];

@@ -10,14 +10,87 @@
 //                              (products fed in processing order, stream_vertical + stream_row)
 //   O <alg> <p> <M*M ints>     4, 5, 8: the same through stream_outputs4 and stream_outputs, which
 //                              keep the outputs
+//   F <alg> <0> <2 ints>       4, 5: outputs of both streaming forms, of all that were compared, whose
+//                              float32 sums are not those of collapse4_rows and inv4_outputs bit for bit
 #include <cmath>
 #include <cstdio>
+#include <cstring>
+#include <random>
 #include <vector>
 
 #include "../../paper_2407_02913_amd/csrc/sfc_points.hpp"
 #include "../../paper_2407_02913_amd/csrc/sfc_stream_outputs.hpp"
 
 using namespace sfc;
+
+// SFC-4: the outputs of products m (canonical order) from collapse4_rows and inv4_outputs alone, the
+// vertical axis first, as the kernels for small layers add them.
+template <int ALG>
+void rounded_outputs4(const std::vector<float>& m, float (&y)[4][4]) {
+  constexpr bool kHermitian = AlgTraits<ALG>::kHermitian;
+  auto at = [&](int r1, int r2) { return m[kHermitian ? kept_index4(r1, r2) : 7 * r1 + r2]; };
+  float z[6][4], c0[6], c1[6];
+  for (int j = 0; j < 4; ++j) {
+    float col[7], cc[6];
+    for (int r1 = 0; r1 < 7; ++r1) col[r1] = at(r1, real_row4(j));
+    collapse4_rows(col, cc);
+    inv4_outputs(cc, z[real_comp4(j)]);
+  }
+  float h0[7] = {}, h1[7] = {};
+  for (int r1 = 0; r1 < 7; ++r1)
+    if (!kHermitian || !row4_is_complex(r1)) {
+      h0[r1] = at(r1, 4) - at(r1, 3);
+      h1[r1] = at(r1, 2) - at(r1, 4) - at(r1, 3);
+    }
+  collapse4_rows(h0, c0);
+  collapse4_rows(h1, c1);
+  if (kHermitian) {
+    const float* b = &m[AlgTraits<ALG>::P - 6];
+    const float uo0 = b[0] - b[1], uo1 = b[2] - b[0] - b[1];
+    const float vo0 = b[3] - b[4], vo1 = b[5] - b[3] - b[4];
+    c0[2] = 0.5f * (uo0 + vo0);
+    c0[3] = 0.5f * (uo1 + vo1);
+    c1[2] = 0.5f * (uo1 - vo1);
+    c1[3] = 0.5f * (vo0 - uo0);
+  }
+  inv4_outputs(c0, z[2]);
+  inv4_outputs(c1, z[3]);
+  for (int o1 = 0; o1 < 4; ++o1) {
+    float zc[6];
+    for (int b = 0; b < 6; ++b) zc[b] = z[b][o1];
+    inv4_outputs(zc, y[o1]);
+  }
+}
+
+template <int ALG>
+void compare_rounding() {
+  constexpr Order<ALG> order{};
+  std::mt19937 gen(7);
+  std::uniform_real_distribution<float> uniform(-1.0f, 1.0f);
+  int differ = 0, compared = 0;
+  for (int trial = 0; trial < 500; ++trial) {
+    std::vector<float> m(AlgTraits<ALG>::P);
+    for (float& v : m) v = std::ldexp(uniform(gen), (int)(gen() % 8));
+    float want[4][4], z[6][4], columns[4][4];
+    rounded_outputs4<ALG>(m, want);
+    int j = 0;
+    auto next = [&]() -> float { return m[order.pt[j++]]; };
+    stream_vertical<ALG, float>(next, z);
+    j = 0;
+    stream_outputs4<ALG, float>(next, [](float&) {}, columns);
+    for (int o1 = 0; o1 < 4; ++o1) {
+      float out[4], kept[4];
+      stream_row<ALG, float>(z, o1, out);
+      stream_row<kOutputColumns + 4, float>(columns, o1, kept);
+      for (int o2 = 0; o2 < 4; ++o2) {
+        differ += std::memcmp(&out[o2], &want[o1][o2], 4) != 0;
+        differ += std::memcmp(&kept[o2], &want[o1][o2], 4) != 0;
+        compared += 2;
+      }
+    }
+  }
+  std::printf("F %d 0 %d %d\n", ALG, differ, compared);
+}
 
 template <int ALG>
 void dump() {
@@ -114,5 +187,7 @@ int main() {
   dump<7>();
   dump<8>();
   dump<9>();
+  compare_rounding<4>();
+  compare_rounding<5>();
   return 0;
 }

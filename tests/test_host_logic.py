@@ -271,6 +271,13 @@ def test_kernel_add_networks_realize_the_oracle_matrices(kernel_maps, alg_id, al
         assert np.array_equal(kernel_maps[("O", alg_id)], a2)
 
 
+@pytest.mark.parametrize("alg_id", [4, 5])
+def test_sfc4_output_transforms_round_alike(kernel_maps, alg_id):
+    """Every form of the SFC-4 output transform adds its float32 values in one order: outputs, and
+    int8 activations at a tie of their rounding, do not depend on the kernel that a layer runs."""
+    assert kernel_maps[("F", alg_id)][0].tolist() == [0, 16000]
+
+
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
     """(path, algorithm, shape) of layers -> the product kernels the built library picks for them, or
