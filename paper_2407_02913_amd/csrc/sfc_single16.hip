@@ -26,8 +26,9 @@
 // a compute unit; with all 46 positions in LDS, 24 partial outputs a pair and 150 registers it were
 // three (one).  us per layer before and after: 64 channels on 56x56 maps, batch 64, int8 21.9 ->
 // 19.6, float32 26.0 -> 20.6; on 224x224 maps, batch 32, 177 -> 161; 128 channels on 28x28 maps,
-// batch 128, 34.1 -> 27.4, 112x112 maps, batch 16, 63.8 -> 51.6.  Layers of few workgroups:
-// single16_few.
+// batch 128, 34.1 -> 27.4, 112x112 maps, batch 16, 63.8 -> 51.6.  With 49 points, which need more
+// registers (single16_waves), three (one): int8 25.1 -> 23.3, float32 26.8 -> 24.9; 184 -> 148; 37.6 -> 33.1, 70.1 -> 66.0.
+// Layers of few workgroups: single16_few.
 #include <cstring>
 
 #include "sfc_device.hpp"
@@ -50,13 +51,28 @@ __host__ __device__ constexpr unsigned single16_wave_bytes(int nh, int out) {
 // the first have been multiplied; with two waves per filter group all of them
 __host__ __device__ constexpr int single16_ring(int nh, int pp) { return nh == 1 ? 32 : pp; }
 
+// Waves per SIMD that the registers are cut for.  49 points take 30 to 50 registers more than 46 (the
+// complex column group leaves three products a row, 52 positions of V one block more): cut for four waves
+// they spilled 86 to 115.  One chunk fits three workgroups to a compute unit, 168 registers, or one of
+// eight waves (FEW); two chunks one, as more than 128 registers leave two waves.
+__host__ __device__ constexpr int single16_waves(int alg, int kc, bool few) {
+  return alg == 5 ? (kc == 1 && !few ? 3 : 2) : few && kc == 2 ? 2 : 4;
+}
+
 // Filter-operand blocks ahead (quad16_stream) with 128 registers: as many as the partial outputs of
 // the moment leave room for.  (A constant 4: 64 channels on 56x56 maps, batch 32, float32 13.5 us a
-// layer against 13.3; 8 to 10 ahead until position 32 spilled, 14.4.)
+// layer against 13.3; 8 to 10 ahead until position 32 spilled, 14.4.)  Two chunks put 6 to 10 values in
+// scratch however few blocks are ahead: two from the start, the others, outputs, where the late V is
+// written, each stored and loaded once in some 12000 instructions; with 256 registers there are none, and
+// 128 channels on 28x28 maps, batch 128, took 30.4 us against 27.4.
 template <int KC>
 struct Single16Ahead {
   static constexpr int at(int s) { return KC == 1 ? (s < 25 ? 8 : s < 32 ? 6 : 4) : (s < 36 ? 4 : s < 50 ? 6 : s < 64 ? 4 : 3); }
 };
+// (49 points, one chunk: 6; 8 spilled 8 to 10 registers)
+template <int ALG, int KC, bool FEW>
+using Single16Blocks = std::conditional_t<(ALG == 5 && KC == 1), ConstantAhead<6>,
+                                          std::conditional_t<(ALG == 5 || FEW), ConstantAhead<16>, Single16Ahead<KC>>>;
 
 struct Single16Plan {
   TileRect tr;
@@ -196,7 +212,7 @@ __device__ __forceinline__ void stage_planes(const int8_t* __restrict__ x, unsig
 // chunk: two waves to a group of 16 filters, and of 16 channels.  Two chunks: 256 registers and the
 // filter operand further ahead, one workgroup to a compute unit instead of two.
 template <int ALG, int KC, int OUT, int EV, bool FEW>
-__global__ __launch_bounds__(single16_halves(KC, FEW) * KC * 256, FEW && KC == 2 ? 2 : 4) void single16_kernel(
+__global__ __launch_bounds__(single16_halves(KC, FEW) * KC * 256, single16_waves(ALG, KC, FEW)) void single16_kernel(
     const int8_t* __restrict__ x, const int8_t* __restrict__ U16, const float* __restrict__ dq16,
     const unsigned char* __restrict__ intab, float x_scale, float inv_y, void* __restrict__ y,
     Geometry g, Single16Plan sp) {
@@ -355,7 +371,7 @@ __global__ __launch_bounds__(single16_halves(KC, FEW) * KC * 256, FEW && KC == 2
   if constexpr (NH == 1) {
     f4 out[M][M];
     constexpr int kLate = (PP - RING) / 4;  // groups of four positions behind the ring's
-    quad16_stream<ALG, KC, RING / 4, VS, std::conditional_t<FEW, ConstantAhead<16>, Single16Ahead<KC>>>(
+    quad16_stream<ALG, KC, RING / 4, VS, Single16Blocks<ALG, KC, FEW>>(
         lds, lane, ures, a_wave, dres, d_wave, ready,
         [&](int pg) __attribute__((always_inline)) {
           if (pg == kLate - 1) {  // every wave has read the positions whose place the late ones take
@@ -484,11 +500,15 @@ static unsigned single16_stage_bytes(const TileRect& tr) {
 
 // Few workgroups (the kernel's FEW): one chunk while all of them are resident with eight waves each
 // (64 channels on 56x56 maps, 16 / 32 / 40 / 64 images, 224 / 448 / 560 / 896 workgroups: 8.7 / 11.9 /
-// 16.8 / 21.6 us a layer against 10.1 / 13.1 / 15.9 / 19.6 with four); two chunks while every one has a
-// compute unit to itself (128 channels on 28x28 maps, 32 / 64 / 80 / 128 images, 112 / 224 / 280 / 448
-// workgroups: 15.6 / 16.1 / 30.0 / 30.4 us against 16.5 / 17.5 / 25.4 / 27.4 with 128 registers).
+// 16.8 / 21.6 us a layer against 10.1 / 13.1 / 15.9 / 19.6 with four), with 49 points, in whose registers
+// two such workgroups do not share a compute unit, while every one has its own (float32, 2 / 12 images, 28 /
+// 168 workgroups: 9.2 / 9.9 against 10.6 / 11.0; 32 images, 448 workgroups, cut for 128 registers 16.0
+// against 14.8); two chunks likewise (46 points, 128 channels on 28x28 maps, 32 / 64 / 80 / 128 images,
+// 112 / 224 / 280 / 448 workgroups: 15.6 / 16.1 / 30.0 / 30.4 us against 16.5 / 17.5 / 25.4 / 27.4 with 128
+// registers; 49 points have one form).
 static bool single16_few(const Geometry& g, long long workgroups) {
-  return g.alg == 4 && workgroups <= (g.Cp == 64 ? 512 : 256);
+  if (g.alg == 5 && g.Cp > 64) return false;
+  return workgroups <= (g.alg == 4 && g.Cp == 64 ? 512 : 256);
 }
 
 static bool make_single16_plan(const Geometry& g, int out, Single16Plan* sp) {
@@ -544,7 +564,7 @@ template <int ALG, int KC, int OUT>
 static hipError_t launch_single16_out(const Geometry& g, const Single16Plan& sp, const int8_t* x,
                                       const FilterViews& f, float x_scale, float inv_y, void* y,
                                       hipStream_t s, bool prepare) {
-  if constexpr (ALG == 4) {
+  if constexpr (ALG == 4 || KC == 1) {
     if (sp.few) return launch_single16_impl<ALG, KC, OUT, 0, true>(g, sp, x, f, x_scale, inv_y, y, s, prepare);
   }
   if (g.W % 4 == 0) return launch_single16_impl<ALG, KC, OUT, 4, false>(g, sp, x, f, x_scale, inv_y, y, s, prepare);

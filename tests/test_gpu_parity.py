@@ -759,8 +759,7 @@ PAST_SMALL_LAYERS = [  # (path, kernel, (N, Cin, Cout, H, W))
 
 
 @pytest.mark.parametrize("path,kernel,shape", PAST_SMALL_LAYERS)
-def test_46_points_past_the_small_layers(binding, path, kernel, shape):
-    alg = "4x4_p46"
+def test_46_points_past_the_small_layers(binding, path, kernel, shape, alg="4x4_p46"):
     x, w, xs, ws = uniform_case(shape, 2800 + sum(shape))
     print("case past small", path, kernel, shape, flush=True)
     xc, _, _, _ = uniform_case((min(shape[0], 4), *shape[1:]), 2900 + sum(shape))
@@ -788,6 +787,26 @@ def test_46_points_past_the_small_layers(binding, path, kernel, shape):
 ])
 def test_46_points_staged_output_transform(binding, shape):
     test_46_points_past_the_small_layers(binding, "staged", "staged", shape)
+
+
+SINGLE16_49 = [  # 49 points in one kernel
+    (18, 33, 17, 56, 56),    # 252 workgroups of one chunk: two waves to a filter group
+    (256, 9, 40, 14, 14),    # 256: whole images, pairs per store
+    (112, 2, 3, 13, 9),      # strips, single outputs per store
+    (7, 50, 130, 30, 31),    # three workgroups along the filters
+    (19, 33, 17, 56, 56),    # 266: one wave, the late positions of V
+    (257, 9, 40, 14, 14),
+    (646, 2, 3, 13, 9),
+    (1100, 20, 8, 7, 7),
+    (19, 70, 17, 56, 56),    # two chunks
+    (53, 128, 136, 11, 7),
+    (260, 70, 40, 14, 14),
+]
+
+
+@pytest.mark.parametrize("shape", SINGLE16_49)
+def test_49_points_single_kernel_forms(binding, shape):
+    test_46_points_past_the_small_layers(binding, "single", "single16", shape, "4x4_p49")
 
 
 def test_single_kernel_path_channel_limits(binding):

@@ -4,6 +4,7 @@ networks (compiled for the host) realize the oracle's matrices."""
 import ctypes as C
 import os
 import re
+import struct
 import subprocess
 
 import numpy as np
@@ -352,6 +353,45 @@ def test_every_kernel_choice_fits_the_filter_layout(lib, routes):
                                        routes([("single", "4x4_p49", s) for s in shapes])):
         assert kernel in ("single_small", "single16"), (shape, kernel)
         assert kernel49 == "single16", (shape, kernel49)
+
+
+def kernel_resources(path):
+    """(kernel, scratch bytes of a lane, spilled vector registers) of every gfx950 kernel in a library,
+    from the metadata notes of its code objects."""
+    readelf = "/opt/rocm/llvm/bin/llvm-readelf"
+    data = open(path, "rb").read()
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    start, found = data.find(magic), []
+    while start >= 0:
+        count, = struct.unpack_from("<Q", data, start + len(magic))
+        at = start + len(magic) + 8
+        for _ in range(count):
+            offset, size, name = struct.unpack_from("<QQQ", data, at)
+            target = data[at + 24 : at + 24 + name].decode()
+            at += 24 + name
+            if size and "gfx950" in target:
+                notes = subprocess.run([readelf, "--notes", "-"], input=data[start + offset : start + offset + size],
+                                       check=True, capture_output=True).stdout.decode()
+                # (a kernel's keys are sorted, .name before .private_segment_fixed_size)
+                found += re.findall(r"\n    \.name: +(\S+)\n.*?\.private_segment_fixed_size: (\d+)\n.*?"
+                                    r"\.vgpr_spill_count: (\d+)", notes, flags=re.S)
+        start = data.find(magic, at)
+    names = subprocess.run(["c++filt"], input="\n".join(k for k, _, _ in found), check=True, capture_output=True,
+                           text=True).stdout.splitlines()
+    return [(name, int(scratch), int(spilled)) for name, (_, scratch, spilled) in zip(names, found)]
+
+
+def test_single16_keeps_its_values_in_registers(lib):
+    """No form of single16_kernel works in scratch memory; the one for 46 points, two chunks and many
+    workgroups keeps a few values there, each written and read once (Single16Ahead)."""
+    from paper_2407_02913_amd import binding
+
+    kernels = {name[: name.index("(")]: rest for name, *rest in kernel_resources(binding.LIB_PATH)
+               if "single16_kernel<" in name}
+    assert {name.split("<")[1][:4] for name in kernels} == {"4, 1", "4, 2", "5, 1", "5, 2"}
+    for name, (scratch, spilled) in kernels.items():
+        few = "single16_kernel<4, 2," in name and name.endswith("false>")
+        assert scratch <= (48 if few else 0) and spilled <= (12 if few else 0), (name, scratch, spilled)
 
 
 def test_bench_operation_counts_match_the_add_networks(tmp_path):
