@@ -121,8 +121,9 @@ __global__ __launch_bounds__(NW * 64) void input_transform_i8_kernel(
     // from the table, the next block's under way) serve the four channel groups.  The rounded
     // bytes of a block are turned round in a piece of LDS that only this wave uses and written
     // to V with 16-byte lanes, 64 contiguous bytes per (position, tile): V never lies in LDS
-    // as a whole, so three workgroups share a compute unit and overlap their phases (5x5
-    // filters, 128 channels on 28x28 maps, batch 64: 29.1 us with V collected in LDS).
+    // as a whole, so two workgroups share a compute unit and overlap their phases (5x5
+    // filters, 128 channels on 28x28 maps, batch 64: 29.1 us with V collected in LDS).  The LDS
+    // holds three; 96 to 98 registers leave four or five waves to a SIMD, and a workgroup takes two.
     using Tr = AlgTraits<ALG>;
     static_assert(TPW == 1, "one tile per wave");
     constexpr int PP = Order<ALG>::PP, NPB = (PP + 15) / 16, CS = stage_channel_bytes(Tr::NI);
@@ -376,8 +377,8 @@ static bool make_input_plan(const Geometry& g, InputPlan* ip) {
   if (xb >= (1ll << 31) || vb >= (1ll << 31)) return false;
   if (g.alg < 4 || g.alg >= 6) {
     // SFC-6 forms: staged rows of one strip (rectangles only), then a block of 16
-    // positions per wave; a third of the LDS, so that three workgroups share a compute unit.  (Of
-    // the eight waves 5 have a tile with 6x6 tiles of the 5x5-filter form on 56x56 and 28x28 maps,
+    // positions per wave; at most a third of the LDS, of which the registers let two workgroups to a
+    // compute unit use two.  (Of the eight waves 5 have a tile with 6x6 tiles of the 5x5-filter form on 56x56 and 28x28 maps,
     // 7 with 4x4 tiles of the 7x7-filter form.)
     const int waves = input_waves(g.alg);  // one tile slot each
     if (!make_tile_rect(g, 48u * 1024u, &ip->tr, waves, true, false)) return false;
