@@ -377,9 +377,9 @@ static bool make_input_plan(const Geometry& g, InputPlan* ip) {
   if (xb >= (1ll << 31) || vb >= (1ll << 31)) return false;
   if (g.alg < 4 || g.alg >= 6) {
     // SFC-6 forms: staged rows of one strip (rectangles only), then a block of 16
-    // positions per wave; at most a third of the LDS, of which the registers let two workgroups to a
-    // compute unit use two.  (Of the eight waves 5 have a tile with 6x6 tiles of the 5x5-filter form on 56x56 and 28x28 maps,
-    // 7 with 4x4 tiles of the 7x7-filter form.)
+    // positions per wave; a third of the LDS at most (the registers let two workgroups share a
+    // compute unit).  (Of the eight waves 5 have a tile with 6x6 tiles of the 5x5-filter form on
+    // 56x56 and 28x28 maps, 7 with 4x4 tiles of the 7x7-filter form.)
     const int waves = input_waves(g.alg);  // one tile slot each
     if (!make_tile_rect(g, 48u * 1024u, &ip->tr, waves, true, false)) return false;
     const unsigned xbytes = tile_rect_stage_bytes(g, ip->tr) + 32u;  // (patch reads reach 8 bytes past a row)
