@@ -90,6 +90,14 @@ constexpr unsigned quad16_lds_layout(int what) {
   return what == 0 ? 0u : what == 1 ? tab_off : tab_off + 256u;
 }
 
+// Between LDS accesses of different lanes of one wave.  The hardware completes them in order; the
+// compiler follows one lane at a time and may swap a write and a read that it can tell apart for
+// that lane.  Emits nothing.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Filter-operand blocks that are on the way or held when block s is multiplied, s included.
 template <int N>
 struct ConstantAhead {
@@ -312,6 +320,7 @@ __device__ __forceinline__ void quad16_store(const f4 (&z)[AlgTraits<ALG>::NC][A
   const float act = x_scale * inv_y;  // int8 output: activation scale over output scale
   // this lane's piece: row q of tile tl (asked for here, waited for behind the transform)
   const int tile_off = tile_tab[tl], tile_rows = tile_tab[16 + tl], tile_cols = tile_tab[32 + tl];
+  wave_lds_order();  // (the block may have been read a moment ago: a store of other pairs, a hand-over)
   // float32 staging: 16-byte slots, slot (tile, row) of a filter moved round by tile/4 so
   // that the 16 lanes of a quarter wave fall into different banks, writing and reading
   auto slot = [](int tile, int row) { return tile * 4 + ((row + (tile >> 2)) & 3); };
@@ -346,7 +355,7 @@ __device__ __forceinline__ void quad16_store(const f4 (&z)[AlgTraits<ALG>::NC][A
       }
     }
   }
-  __builtin_amdgcn_wave_barrier();  // LDS accesses of one wave complete in order
+  wave_lds_order();
   const int HW = g.H * g.W;
   const int cols = q < tile_rows ? tile_cols : 0;
   const unsigned base = esz * (unsigned)(tile_off + q * g.W);  // filter 0

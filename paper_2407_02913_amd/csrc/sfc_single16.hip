@@ -259,6 +259,7 @@ __global__ __launch_bounds__(single16_halves(KC, FEW) * KC * 256, single16_waves
     write_tile_entry<M>(tile_tab, threadIdx.x, tc.live, tc.n, tc.ti, tc.tj, g.Cout, g.H, g.W);
   }
   if constexpr (NH > 1) __syncthreads();
+  else wave_lds_order();  // a patch was staged by other lanes of its wave
 
   // ---- 2. input transform (sfc_mfma_input.hpp) --------------------------------------------
   // A patch is (tile, group of 16 channels); the waves of a group take every NH-th tile.  All
