@@ -92,11 +92,9 @@ constexpr unsigned quad16_lds_layout(int what) {
 
 // Between LDS accesses of different lanes of one wave.  The hardware completes them in order; the
 // compiler follows one lane at a time and may swap a write and a read that it can tell apart for
-// that lane.  Emits nothing.
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-}
+// that lane.  Emits nothing.  (A wave barrier holds back the arithmetic too: at the head of quad16_store
+// it made the float32 form of single16_kernel with two waves to a filter group spill 32 registers.)
+__device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
 
 // Filter-operand blocks that are on the way or held when block s is multiplied, s included.
 template <int N>
