@@ -116,6 +116,7 @@ hipError_t launch_splitk(int out, const Geometry& g, const void* V, const Filter
 // single-kernel path of the SFC-4 forms, up to 128 input channels (sfc_single16.hip), on the
 // same filter operand and factor table as launch_quad16
 bool single16_supported(const Geometry& g);
+bool single16_few_workgroups(const Geometry& g);  // whether it takes its form for few workgroups
 hipError_t launch_single16(int out, const Geometry& g, const int8_t* x, const FilterViews& f,
                            float x_scale, float inv_y, void* y, hipStream_t s, bool prepare = false);
 // the same for 129 to 512 input channels on feature maps of at most 16 tiles, the products

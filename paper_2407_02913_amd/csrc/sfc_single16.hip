@@ -549,6 +549,11 @@ bool single16_supported(const Geometry& g) {
   return make_single16_plan(g, 0, &sp);
 }
 
+bool single16_few_workgroups(const Geometry& g) {
+  Single16Plan sp;
+  return make_single16_plan(g, 0, &sp) && sp.few;
+}
+
 template <int ALG, int KC, int OUT, int EV, bool FEW>
 static hipError_t launch_single16_impl(const Geometry& g, const Single16Plan& sp, const int8_t* x,
                                        const FilterViews& f, float x_scale, float inv_y, void* y,

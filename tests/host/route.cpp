@@ -1,6 +1,6 @@
 // Which kernels the library picks: reads layers "path alg N Cin Cout H W" (path and alg as in
-// include/sfc.h) and prints the name of the product kernel of each and, for the exact mode of the
-// layer, which output transform is ahead.  Linked against the built library, whose own rules it
+// include/sfc.h) and prints the name of the product kernel of each, for the exact mode of the
+// layer which output transform is ahead, and the form of single16_kernel that it would take.  Linked against the built library, whose own rules it
 // asks.
 #include <cstdio>
 
@@ -23,7 +23,8 @@ int main() {
     g.Kp = (g.Cout + 15) / 16 * 16;
     g.P = sfc::alg_points(g.alg);
     g.qmax = 127.0f;
-    std::printf("%s %s\n", kNames[(int)sfc::choose_kernel(path, g)], sfc::output_exact_ahead(g) ? "waves" : "threads");
+    std::printf("%s %s %s\n", kNames[(int)sfc::choose_kernel(path, g)], sfc::output_exact_ahead(g) ? "waves" : "threads",
+                sfc::single16_few_workgroups(g) ? "few" : "many");
   }
   return 0;
 }

@@ -282,7 +282,7 @@ def test_sfc4_output_transforms_round_alike(kernel_maps, alg_id):
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
     """(path, algorithm, shape) of layers -> the product kernels the built library picks for them, or
-    (column 1) the output transforms of their exact mode."""
+    (column 1) the output transforms of their exact mode, or (2) the forms of single16_kernel."""
     from paper_2407_02913_amd import binding
 
     exe = tmp_path_factory.mktemp("host") / "route"
@@ -312,6 +312,25 @@ def test_kernels_of_the_shapes_past_the_small_layers(lib, routes):
     for (path, _, shape), kernel in zip(cases, one):
         small = "single_small" if path == "single" else "product_small" if shape[1] > 128 else "fused_quad"
         assert kernel == small, shape
+
+
+def test_single16_forms_of_the_parity_shapes(lib, routes):
+    """Both forms of single16_kernel, for few workgroups and for many, have shapes of the GPU parity
+    tests with one chunk of 64 channels and with two; the lines between them."""
+    import test_gpu_parity as parity
+
+    for alg, shapes in (("4x4_p46", [s for _, kernel, s in parity.PAST_SMALL_LAYERS if kernel == "single16"]),
+                        ("4x4_p49", parity.SINGLE16_49)):
+        forms = routes([("single", alg, s) for s in shapes], column=2)
+        seen = {(1 if s[1] <= 64 else 2, form) for s, form in zip(shapes, forms)}
+        assert seen == {(1, "few"), (1, "many"), (2, "many")} | ({(2, "few")} if alg == "4x4_p46" else set()), alg
+        assert sum(f == "many" for f in forms) >= 5 and len({s[4] % 4 for s, f in zip(shapes, forms) if f == "many"}) >= 3
+        # images of 16 tiles: one workgroup each and 64 filters a chunk
+        for cin, line in ((64, 512 if alg == "4x4_p46" else 256), (128, 256)):
+            layers = [("single", alg, (n, cin, c, 16, 16)) for n, c in
+                      ((line, cin), (line // 2, cin + 1), (line + 1, cin), (line // 2 + 1, cin + 1))]
+            few = "many" if (alg, cin) == ("4x4_p49", 128) else "few"  # (one form)
+            assert routes(layers, column=2) == [few, few, "many", "many"], (alg, cin)
 
 
 def test_kernels_of_the_184_point_shapes(lib, routes):
