@@ -24,10 +24,11 @@
 // time; so what counts is the number of workgroups side by side and the length of the chain.
 // 34 KB of LDS and 128 registers let four workgroups of one chunk (two of two chunks, 67 KB) share
 // a compute unit; with all 46 positions in LDS, 24 partial outputs a pair and 150 registers it were
-// three (one).  us per layer before and after: 64 channels on 56x56 maps, batch 64, int8 21.9 ->
-// 19.6, float32 26.0 -> 20.6; on 224x224 maps, batch 32, 177 -> 161; 128 channels on 28x28 maps,
-// batch 128, 34.1 -> 27.4, 112x112 maps, batch 16, 63.8 -> 51.6.  With 49 points, which need more
-// registers (single16_waves), three (one): int8 25.1 -> 23.3, float32 26.8 -> 24.9; 184 -> 148; 37.6 -> 33.1, 70.1 -> 66.0.
+// three (one).  us per layer before and after: 64 channels on 56x56 maps, batch 64, int8 21.0 ->
+// 19.3, float32 25.1 -> 20.8; on 224x224 maps, batch 32, int8 151 -> 142; 128 channels on 28x28 maps,
+// batch 128, int8 34.5 -> 26.1, 112x112 maps, batch 16, 63.8 -> 51.3.  With 49 points, which need more
+// registers (single16_waves), three (one) instead of two (one): 25.1 -> 22.9, 26.9 -> 24.4; 175 -> 146;
+// 37.0 -> 32.9, 68.9 -> 64.6.
 // Layers of few workgroups: single16_few.
 #include <cstring>
 
@@ -64,7 +65,7 @@ __host__ __device__ constexpr int single16_waves(int alg, int kc, bool few) {
 // layer against 13.3; 8 to 10 ahead until position 32 spilled, 14.4.)  Two chunks put 6 to 10 values in
 // scratch however few blocks are ahead: two from the start, the others, outputs, where the late V is
 // written, each stored and loaded once in some 12000 instructions; with 256 registers there are none, and
-// 128 channels on 28x28 maps, batch 128, took 30.4 us against 27.4.
+// 128 channels on 28x28 maps, batch 128, int8, took 30.1 us against 26.1.
 template <int KC>
 struct Single16Ahead {
   static constexpr int at(int s) { return KC == 1 ? (s < 25 ? 8 : s < 32 ? 6 : 4) : (s < 36 ? 4 : s < 50 ? 6 : s < 64 ? 4 : 3); }
@@ -500,13 +501,12 @@ static unsigned single16_stage_bytes(const TileRect& tr) {
 }
 
 // Few workgroups (the kernel's FEW): one chunk while all of them are resident with eight waves each
-// (64 channels on 56x56 maps, 16 / 32 / 40 / 64 images, 224 / 448 / 560 / 896 workgroups: 8.7 / 11.9 /
-// 16.8 / 21.6 us a layer against 10.1 / 13.1 / 15.9 / 19.6 with four), with 49 points, in whose registers
-// two such workgroups do not share a compute unit, while every one has its own (float32, 2 / 12 images, 28 /
-// 168 workgroups: 9.2 / 9.9 against 10.6 / 11.0; 32 images, 448 workgroups, cut for 128 registers 16.0
-// against 14.8); two chunks likewise (46 points, 128 channels on 28x28 maps, 32 / 64 / 80 / 128 images,
-// 112 / 224 / 280 / 448 workgroups: 15.6 / 16.1 / 30.0 / 30.4 us against 16.5 / 17.5 / 25.4 / 27.4 with 128
-// registers; 49 points have one form).
+// (int8, 64 channels on 56x56 maps, 16 / 32 / 40 / 64 images, 224 / 448 / 560 / 896 workgroups: 8.9 /
+// 12.0 / 16.8 / 21.4 us a layer against 10.2 / 13.2 / 15.8 / 19.6 with four), with 49 points, in whose
+// registers two such workgroups do not share a compute unit, while every one has its own (2 / 16 / 32
+// images, 28 / 224 / 448 workgroups: 9.2 / 9.5 / 17.0 against 10.8 / 11.1 / 14.4); two chunks likewise (46
+// points, 128 channels on 28x28 maps, 32 / 64 / 80 / 128 images, 112 / 224 / 280 / 448 workgroups: 15.7 /
+// 16.2 / 29.8 / 30.1 us against 16.3 / 17.3 / 24.8 / 26.2 with 128 registers; 49 points have one form).
 static bool single16_few(const Geometry& g, long long workgroups) {
   if (g.alg == 5 && g.Cp > 64) return false;
   return workgroups <= (g.alg == 4 && g.Cp == 64 ? 512 : 256);

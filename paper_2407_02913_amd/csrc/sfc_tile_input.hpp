@@ -48,6 +48,9 @@ __host__ __device__ constexpr int plane_stride_bytes(int hw) {
 // max_tiles: tile slots of a workgroup (16, or 8 for workgroups of eight one-tile waves).
 // partial_images: take whole images even if they leave tile slots empty, when the
 // alternative is a rectangle whose rows are not whole dwords (byte-wise staging).
+// Strips are counted with the 64-byte rows above.  single16_kernel stages 4 (tlw + 2) bytes a row and
+// would hold more of them on narrow maps: with two chunks it gets three strips at most, 9 of 16 tile
+// slots on maps of three tile columns.
 // whole_images: false keeps to rectangles whatever the size of the feature map.
 inline bool make_tile_rect(const Geometry& g, unsigned stage_budget, TileRect* tr,
                            int max_tiles = 16, bool partial_images = false, bool whole_images = true) {
