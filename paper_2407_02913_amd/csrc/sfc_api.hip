@@ -413,6 +413,10 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the kernels of this plan's path that need more than the default 64 KB of dynamic LDS
   if (requant && sfc::prepare_kernels(plan->d.path, plan->d.out, g) != hipSuccess) return SFC_EHIP;
+  if (!requant) {  // (a layer beyond its limits takes the generic kernel)
+    const hipError_t e = sfc::launch_input_exact(g, nullptr, nullptr, nullptr, nullptr, true);
+    if (e != hipSuccess && e != hipErrorNotSupported) return SFC_EHIP;
+  }
   if (!requant) {
     const hipError_t e = sfc::launch_input_exact(g, nullptr, nullptr, nullptr, nullptr, true);
     if (e != hipSuccess && e != hipErrorNotSupported) return SFC_EHIP;

@@ -1,7 +1,7 @@
 // Exact mode on the matrix cores (gfx950): transform-domain operands kept as 16-bit integers,
 // sums as 32-bit ones, so that the result equals direct convolution bit for bit.
 //
-//   input_transform_i16_kernel   V = B^T x B            (NCHW int8 -> int16 [P][Tp][Cp])
+//   input_rows_kernel            V = B^T x B            (sfc_input_rows.hip; NCHW int8 -> int16 [P][Tp][Cp])
 //   product_gemm_i16_kernel      M_p = V_p . U_p^T      (int16 operands as pairs of int8 ones)
 //   output_exact_kernel          y = A^T M A / kDen, corrections, NCHW store
 //
@@ -18,144 +18,6 @@
 #include "sfc_tile_input.hpp"
 
 namespace sfc {
-
-// ---------------------------------------------------------------------------------------
-// Input transform: as the row form of input_transform_i8_kernel (sfc_input.hip), every
-// algorithm, without the rounding.  A workgroup stages the rows of up to NW tiles of one strip
-// for 64 channels; wave = tile.  Per block of 16 positions the sums of four groups of 16
-// channels are taken as int8 matrix instructions against the coefficient table, packed to
-// int16, turned round in LDS of the wave's own and written with 16-byte lanes, 128 contiguous
-// bytes per (position, tile).
-// ---------------------------------------------------------------------------------------
-constexpr int kExactWaves = 8;       // waves, and tile slots, per workgroup
-constexpr int kExactRowBytes = 144;  // LDS bytes per position in a wave's block (128 + padding)
-
-struct ExactInputPlan {
-  TileRect tr;
-  unsigned blk_off;  // LDS byte offset of the waves' blocks
-  unsigned tab_off;  // ... of the tile -> V row table
-  unsigned lds_bytes;
-};
-
-template <int ALG>
-__global__ __launch_bounds__(kExactWaves * 64) void input_transform_i16_kernel(
-    const int8_t* __restrict__ x, int16_t* __restrict__ V, const unsigned char* __restrict__ tab,
-    Geometry g, ExactInputPlan ip) {
-  using Tr = AlgTraits<ALG>;
-  constexpr int NW = kExactWaves;
-  constexpr int PP = Order<ALG>::PP, NPB = (PP + 15) / 16, CS = stage_channel_bytes(Tr::NI);
-  static_assert(16 * NPB <= kRowsTabRows && Tr::NI <= 12, "table rows, three steps of four patch rows");
-  constexpr int KST = (Tr::NI + 3) / 4;
-  extern __shared__ __align__(16) unsigned char lds[];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const TileRect& tr = ip.tr;
-  const int cgn = g.Cp >> 6;
-  const int pos = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int bx = pos / cgn;
-  const int c0 = (pos - bx * cgn) * 64;
-  int* row_tab = (int*)(lds + ip.tab_off);
-  if (threadIdx.x < 16) {
-    const int tl = threadIdx.x;
-    const TileCoord tc = tile_coord(g, tr, bx, tl);
-    row_tab[tl] = tc.live ? (tc.n * g.th + tc.ti) * g.tw + tc.tj : -1;
-  }
-  stage_input<ALG, NW>(x, lds, g, tr, bx, c0, wave, lane);
-  __syncthreads();
-  const int t = wave < tr.ntiles ? row_tab[wave] : -1;  // the same for the whole wave
-  if (t < 0) return;  // (no workgroup barrier after this point)
-  const int tj0 = (bx % tr.chunks) * tr.tlw;
-  const int halo = Tr::M * tj0 - Tr::PAD - ((Tr::M * tj0) & ~3) + 4;
-  const int s = wave / tr.tlw, tjl = wave - s * tr.tlw;
-  const int o = s * 64 * CS + halo + Tr::M * tjl;
-  v4i a[4][KST];
-#pragma unroll
-  for (int cg = 0; cg < 4; ++cg)
-#pragma unroll
-    for (int st = 0; st < KST; ++st) a[cg][st] = operand_rows16<CS, Tr::NI>(lds, 16 * cg, o, lane, st);
-  const int* point = (const int*)(tab + kRowsTabPoint);
-  const unsigned char* ctab = tab + kRowsTabCoeff;
-  const size_t vplane = (size_t)g.Tp * g.Cp;
-  int16_t* vrow = V + (size_t)t * g.Cp + c0 + 8 * (lane & 7);
-  unsigned char* blk = lds + ip.blk_off + wave * (16 * kExactRowBytes);
-  v4i c_cur[KST], c_nxt[KST];
-  int pt_cur[2], pt_nxt[2] = {-1, -1};
-  auto load_block = [&](int m, v4i (&c)[KST], int (&pt)[2]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) pt[h] = point[16 * m + 8 * h + (lane >> 3)];
-#pragma unroll
-    for (int st = 0; st < KST; ++st)
-      c[st] = *(const v4i*)(ctab + (16 * m + (lane & 15)) * 192 + 64 * st + 16 * (lane >> 4));
-  };
-  load_block(0, c_cur, pt_cur);
-#pragma unroll
-  for (int m = 0; m < NPB; ++m) {
-    if (m + 1 < NPB) load_block(m + 1, c_nxt, pt_nxt);
-#pragma unroll
-    for (int cg = 0; cg < 4; ++cg) {
-      v4i d = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[cg][0], c_cur[0], v4i{0, 0, 0, 0}, 0, 0, 0);
-#pragma unroll
-      for (int st = 1; st < KST; ++st) d = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[cg][st], c_cur[st], d, 0, 0, 0);
-      // channels 16 cg + 4 (lane / 16) .. + 3 of position lane % 16
-      v2i w;
-      w[0] = (int)__builtin_amdgcn_perm((unsigned)d[1], (unsigned)d[0], 0x05040100u);
-      w[1] = (int)__builtin_amdgcn_perm((unsigned)d[3], (unsigned)d[2], 0x05040100u);
-      *(v2i*)(blk + (lane & 15) * kExactRowBytes + 32 * cg + 8 * (lane >> 4)) = w;
-    }
-    __builtin_amdgcn_wave_barrier();  // LDS accesses of one wave complete in order
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const v4i d = *(const v4i*)(blk + (8 * h + (lane >> 3)) * kExactRowBytes + 16 * (lane & 7));
-      if (pt_cur[h] >= 0) *(v4i*)(vrow + (size_t)pt_cur[h] * vplane) = d;
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int st = 0; st < KST; ++st) c_cur[st] = c_nxt[st];
-    pt_cur[0] = pt_nxt[0];
-    pt_cur[1] = pt_nxt[1];
-  }
-}
-
-// (48 KB take the rows of one strip, so waves stay without a tile: of eight, 5 have one with 6x6
-// tiles on 56x56 and 28x28 maps, 3 on 14x14 and 2 on 7x7; 7, 7, 4 and 2 with 4x4 tiles.)
-static bool make_exact_input_plan(const Geometry& g, ExactInputPlan* ip) {
-  if ((long long)g.N * g.Cin * g.H * g.W >= (1ll << 31)) return false;  // 32-bit offsets into x
-  if (!make_tile_rect(g, 48u * 1024u, &ip->tr, kExactWaves, true, false)) return false;
-  // (patch reads reach 8 bytes past a row)
-  ip->blk_off = (tile_rect_stage_bytes(g, ip->tr) + 32u + 15u) & ~15u;
-  ip->tab_off = ip->blk_off + (unsigned)kExactWaves * 16u * (unsigned)kExactRowBytes;
-  ip->lds_bytes = ip->tab_off + 64u;
-  return ip->lds_bytes <= 160u * 1024u;
-}
-
-template <int ALG>
-static hipError_t launch_input_exact_alg(const Geometry& g, const ExactInputPlan& ip, const int8_t* x,
-                                         void* V, const unsigned char* tab, hipStream_t s, bool prepare) {
-  auto kernel = input_transform_i16_kernel<ALG>;
-  if (prepare) return raise_lds_limit(reinterpret_cast<const void*>(kernel));
-  const dim3 grid(tile_rect_groups(g, ip.tr) * (unsigned)(g.Cp / 64));
-  hipLaunchKernelGGL(kernel, grid, dim3(kExactWaves * 64), ip.lds_bytes, s, x, (int16_t*)V, tab, g, ip);
-  return hipGetLastError();
-}
-
-hipError_t launch_input_exact(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab,
-                              hipStream_t s, bool prepare) {
-  ExactInputPlan ip;
-  if (!make_exact_input_plan(g, &ip)) return hipErrorNotSupported;
-  switch (g.alg) {
-    case 0: return launch_input_exact_alg<0>(g, ip, x, V, tab, s, prepare);
-    case 1: return launch_input_exact_alg<1>(g, ip, x, V, tab, s, prepare);
-    case 2: return launch_input_exact_alg<2>(g, ip, x, V, tab, s, prepare);
-    case 3: return launch_input_exact_alg<3>(g, ip, x, V, tab, s, prepare);
-    case 4: return launch_input_exact_alg<4>(g, ip, x, V, tab, s, prepare);
-    case 5: return launch_input_exact_alg<5>(g, ip, x, V, tab, s, prepare);
-    case 6: return launch_input_exact_alg<6>(g, ip, x, V, tab, s, prepare);
-    case 7: return launch_input_exact_alg<7>(g, ip, x, V, tab, s, prepare);
-    case 8: return launch_input_exact_alg<8>(g, ip, x, V, tab, s, prepare);
-    case 9: return launch_input_exact_alg<9>(g, ip, x, V, tab, s, prepare);
-  }
-  return hipErrorInvalidValue;
-}
 
 // ---------------------------------------------------------------------------------------
 // Products.  A 16-bit operand is v = 256 h + l with l its low byte taken as a signed one and

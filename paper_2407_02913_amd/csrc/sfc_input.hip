@@ -1,15 +1,14 @@
 // Input-tile transform V = B^T x B with transform-domain requantization to int8,
-// the HBM-facing first stage of the two-kernel paths (gfx950), every algorithm, on the
-// matrix cores (sfc_mfma_input.hpp; small feature maps: sfc_input_image.hip).
+// the HBM-facing first stage of the two-kernel paths (gfx950), SFC-4 forms, on the
+// matrix cores (sfc_mfma_input.hpp; 7x7 maps: sfc_input_image.hip; SFC-6 forms: sfc_input_rows.hip).
 //
 // A workgroup owns up to NW tiles (a rectangle of S strips x tlw tile columns, or whole
 // images of a small feature map), one per wave, and 64 input channels:
 //  1. stage the input rows of every (strip, channel) in LDS (coalesced dword loads),
 //  2. transform: wave = tile, four groups of 16 channels, lane = (position, four channels);
-//  3. SFC-4 forms: the rounded points land in LDS as [processing position][tile][channel],
-//     over the staging area, and are copied out with 16-byte lanes, 64 contiguous bytes per
-//     (point, tile) and NW tiles in a row; SFC-6 forms: every wave turns blocks of 16
-//     positions round in LDS of its own and stores them directly.
+//  3. the rounded points land in LDS as [processing position][tile][channel], over the staging
+//     area, and are copied out with 16-byte lanes, 64 contiguous bytes per (point, tile) and NW
+//     tiles in a row.
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
 #include "sfc_mfma_input.hpp"
@@ -28,18 +27,18 @@ struct InputPlan {
 
 // VS: bytes of V per point in LDS, 64 per tile slot (512 for the 8-tile workgroups: half the
 // LDS, so that more workgroups share a compute unit and overlap their phases).
-// TPW: tiles per wave (SFC-4 forms: 2 when the workgroup takes whole images of 9 to 16 tiles,
+// TPW: tiles per wave (2 when the workgroup takes whole images of 9 to 16 tiles,
 // whose planes it copies as they lie in memory instead of staging sparse 64-byte row windows).
 template <int ALG, int NW, int VS, int TPW = 1>
 __global__ __launch_bounds__(NW * 64) void input_transform_i8_kernel(
-    const int8_t* __restrict__ x, int8_t* __restrict__ V, const float* __restrict__ inv_sx,
-    const unsigned char* __restrict__ intab, Geometry g, InputPlan ip) {
+    const int8_t* __restrict__ x, int8_t* __restrict__ V, const unsigned char* __restrict__ intab, Geometry g,
+    InputPlan ip) {
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int P = AlgTraits<ALG>::P;
-  // LDS bytes from one position's V to the next: the SFC-4 forms write 16 positions per
-  // instruction (sfc_mfma_input.hpp) and need them in different banks
-  constexpr bool kRows16 = AlgTraits<ALG>::kFamily == 6;  // 8x8 to 10x10 patches on the matrix cores, below
-  constexpr int VSP = AlgTraits<ALG>::kFamily == 4 ? VS + 16 : VS;
+  // LDS bytes from one position's V to the next: 16 positions are written per instruction
+  // (sfc_mfma_input.hpp) and lie in different banks
+  static_assert(AlgTraits<ALG>::kFamily == 4, "the SFC-4 forms");
+  constexpr int VSP = VS + 16;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const TileRect& tr = ip.tr;
@@ -61,140 +60,56 @@ __global__ __launch_bounds__(NW * 64) void input_transform_i8_kernel(
     row_tab[tl] = tc.live ? (tc.n * g.th + tc.ti) * g.tw + tc.tj : -1;
   }
 
-  // (the SFC-4 forms stage 16 bytes into the LDS: plane patches are read from up to 4 bytes early)
-  unsigned char* in = lds + (AlgTraits<ALG>::kFamily == 4 ? 16 : 0);
+  unsigned char* in = lds + 16;  // (plane patches are read from up to 4 bytes early)
   stage_input<ALG, NW>(x, in, g, tr, bx, c0, wave, lane);
   __syncthreads();
-  if constexpr (AlgTraits<ALG>::kFamily == 4) {
-    // on the matrix cores: wave = tile, four groups of 16 channels; rounded and packed in
-    // registers before V is written over the staged rows
-    using Tr = AlgTraits<ALG>;
-    constexpr int NPB = MfmaInput<ALG>::NPB, PP = Order<ALG>::PP;
-    MfmaInput<ALG> mi;
-    mi.load(intab, lane);
-    unsigned packed[TPW][4][NPB];
+  // on the matrix cores: wave = tile, four groups of 16 channels; rounded and packed in
+  // registers before V is written over the staged rows
+  using Tr = AlgTraits<ALG>;
+  constexpr int NPB = MfmaInput<ALG>::NPB, PP = Order<ALG>::PP;
+  MfmaInput<ALG> mi;
+  mi.load(intab, lane);
+  unsigned packed[TPW][4][NPB];
 #pragma unroll
-    for (int it = 0; it < TPW; ++it) {
-      const int tile = wave + NW * it;
-      if (tile < tr.ntiles) {
-        if (tr.whole) {
-          const int tpi = g.th * g.tw;
-          const int slot = tile / tpi, rem = tile - slot * tpi;
-          const int ti = rem / g.tw, tj = rem - ti * g.tw;
-#pragma unroll
-          for (int cg = 0; cg < 4; ++cg)
-            mi.transform(MfmaInput<ALG>::operand_plane(in + slot * 64 * tr.cs, tr.cs, 16 * cg,
-                                                       Tr::M * ti - Tr::PAD, Tr::M * tj - Tr::PAD, g.H,
-                                                       g.W, lane),
-                         g.qmax, packed[it][cg]);
-        } else {
-          const int tj0 = (bx % tr.chunks) * tr.tlw;
-          const int halo = Tr::M * tj0 - Tr::PAD - ((Tr::M * tj0) & ~3) + 4;
-          const int s = tile / tr.tlw, tjl = tile - s * tr.tlw;
-#pragma unroll
-          for (int cg = 0; cg < 4; ++cg)
-            mi.transform(MfmaInput<ALG>::template operand_rect<stage_channel_bytes(Tr::NI)>(
-                             in, s, 16 * cg, halo + Tr::M * tjl, lane),
-                         g.qmax, packed[it][cg]);
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < TPW; ++it) {
-      const int tile = wave + NW * it;
-      if (tile < tr.ntiles) {
+  for (int it = 0; it < TPW; ++it) {
+    const int tile = wave + NW * it;
+    if (tile < tr.ntiles) {
+      if (tr.whole) {
+        const int tpi = g.th * g.tw;
+        const int slot = tile / tpi, rem = tile - slot * tpi;
+        const int ti = rem / g.tw, tj = rem - ti * g.tw;
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg)
+          mi.transform(MfmaInput<ALG>::operand_plane(in + slot * 64 * tr.cs, tr.cs, 16 * cg,
+                                                     Tr::M * ti - Tr::PAD, Tr::M * tj - Tr::PAD, g.H,
+                                                     g.W, lane),
+                       g.qmax, packed[it][cg]);
+      } else {
+        const int tj0 = (bx % tr.chunks) * tr.tlw;
+        const int halo = Tr::M * tj0 - Tr::PAD - ((Tr::M * tj0) & ~3) + 4;
+        const int s = tile / tr.tlw, tjl = tile - s * tr.tlw;
 #pragma unroll
-          for (int m = 0; m < NPB; ++m) {
-            const int pos = 16 * m + (lane & 15);
-            if (pos < PP)
-              *(unsigned*)(lds + pos * VSP + tile * 64 + 16 * cg + 4 * (lane >> 4)) = packed[it][cg][m];
-          }
+        for (int cg = 0; cg < 4; ++cg)
+          mi.transform(MfmaInput<ALG>::template operand_rect<stage_channel_bytes(Tr::NI)>(
+                           in, s, 16 * cg, halo + Tr::M * tjl, lane),
+                       g.qmax, packed[it][cg]);
       }
     }
-  } else if constexpr (kRows16) {
-    // SFC-6 forms: the sums of an 8x8, 9x9 or 10x10 patch as int8 matrix instructions, wave =
-    // tile, four groups of 16 channels; per block of 16 positions two or three steps of 64
-    // k-bytes (sfc_mfma_input.hpp).  The coefficients of a block (16-byte loads per lane
-    // from the table, the next block's under way) serve the four channel groups.  The rounded
-    // bytes of a block are turned round in a piece of LDS that only this wave uses and written
-    // to V with 16-byte lanes, 64 contiguous bytes per (position, tile): V never lies in LDS
-    // as a whole, so two workgroups share a compute unit and overlap their phases (5x5
-    // filters, 128 channels on 28x28 maps, batch 64: 29.1 us with V collected in LDS).  The LDS
-    // holds three; 96 to 98 registers leave four or five waves to a SIMD, and a workgroup takes two.
-    using Tr = AlgTraits<ALG>;
-    static_assert(TPW == 1, "one tile per wave");
-    constexpr int PP = Order<ALG>::PP, NPB = (PP + 15) / 16, CS = stage_channel_bytes(Tr::NI);
-    static_assert(16 * NPB <= kRowsTabRows && Tr::NI <= 12, "table rows, three steps of four patch rows");
-    constexpr int KST = (Tr::NI + 3) / 4;  // steps that carry patch rows
-    const float* inv_pos = (const float*)intab;
-    const int* point = (const int*)(intab + kRowsTabPoint);
-    const unsigned char* ctab = intab + kRowsTabCoeff;
-    const int t = wave < tr.ntiles ? row_tab[wave] : -1;  // the same for the whole wave
-    if (t >= 0) {
-      const int tj0 = (bx % tr.chunks) * tr.tlw;
-      const int halo = Tr::M * tj0 - Tr::PAD - ((Tr::M * tj0) & ~3) + 4;
-      const int s = wave / tr.tlw, tjl = wave - s * tr.tlw;
-      const int o = s * 64 * CS + halo + Tr::M * tjl;
-      v4i a[4][KST];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < TPW; ++it) {
+    const int tile = wave + NW * it;
+    if (tile < tr.ntiles) {
 #pragma unroll
       for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
-        for (int st = 0; st < KST; ++st) a[cg][st] = operand_rows16<CS, Tr::NI>(in, 16 * cg, o, lane, st);
-      // this lane's part of a store: position 16 m + lane / 4, channels c0 + 16 (lane % 4) ..
-      const unsigned vplane = (unsigned)g.Tp * (unsigned)g.Cp;
-      const __amdgpu_buffer_rsrc_t vres =
-          __builtin_amdgcn_make_buffer_rsrc((void*)V, 0, (int)(vplane * (unsigned)P), kBufferFlags);
-      const unsigned trow = (unsigned)t * (unsigned)g.Cp;
-      unsigned char* blk = lds + ip.tab_off - (NW - wave) * (16 * kWaveRowBytes);
-      constexpr float kMagic = 12582912.0f;
-      const float lo = kMagic - g.qmax, hi = kMagic + g.qmax;
-      v4i c_cur[KST], c_nxt[KST];
-      float inv_cur, inv_nxt = 0.0f;
-      int pt_cur, pt_nxt = -1;
-      auto load_block = [&](int m, v4i (&c)[KST], float& inv, int& pt) __attribute__((always_inline)) {
-        const int pos = 16 * m + (lane & 15);
-        inv = inv_pos[pos];
-        pt = point[16 * m + (lane >> 2)];
-#pragma unroll
-        for (int st = 0; st < KST; ++st) c[st] = *(const v4i*)(ctab + pos * 192 + 64 * st + 16 * (lane >> 4));
-      };
-      load_block(0, c_cur, inv_cur, pt_cur);
-#pragma unroll
-      for (int m = 0; m < NPB; ++m) {
-        if (m + 1 < NPB) load_block(m + 1, c_nxt, inv_nxt, pt_nxt);
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg) {
-          v4i d = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[cg][0], c_cur[0], v4i{0, 0, 0, 0}, 0, 0, 0);
-#pragma unroll
-          for (int st = 1; st < KST; ++st) d = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[cg][st], c_cur[st], d, 0, 0, 0);
-          unsigned b[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float v = __fmaf_rn((float)d[i], inv_cur, kMagic);
-            v = __builtin_amdgcn_fmed3f(v, lo, hi);
-            b[i] = __float_as_uint(v);
-          }
-          const unsigned w = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) | __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
-          *(unsigned*)(blk + (lane & 15) * kWaveRowBytes + 16 * cg + 4 * (lane >> 4)) = w;
+        for (int m = 0; m < NPB; ++m) {
+          const int pos = 16 * m + (lane & 15);
+          if (pos < PP)
+            *(unsigned*)(lds + pos * VSP + tile * 64 + 16 * cg + 4 * (lane >> 4)) = packed[it][cg][m];
         }
-        __builtin_amdgcn_wave_barrier();  // LDS accesses of one wave complete in order
-        const v4i d = *(const v4i*)(blk + (lane >> 2) * kWaveRowBytes + 16 * (lane & 3));
-        const unsigned pofs =
-            pt_cur >= 0 ? (unsigned)pt_cur * vplane + (unsigned)(c0 + 16 * (lane & 3)) : 0x80000000u;
-        __builtin_amdgcn_raw_buffer_store_b128(d, vres, pofs, trow, 0);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int st = 0; st < KST; ++st) c_cur[st] = c_nxt[st];
-        inv_cur = inv_nxt;
-        pt_cur = pt_nxt;
-      }
     }
-    return;  // (no workgroup barrier after this point on this path)
-  } else {
-    static_assert(AlgTraits<ALG>::kFamily == 4 || kRows16, "every form has its matrix-core transform");
   }
   __syncthreads();
 
@@ -352,22 +267,18 @@ static hipError_t launch_input_waves_alg(const Geometry& g, const WaveInputPlan&
                          : launch(input_transform_waves_kernel<ALG, 8, 1>);
 }
 
-// waves per workgroup = tiles per workgroup: 16 for the 6x6 forms (rectangles of 16 tiles
-// fit their feature maps best); 8 for the 7x7 forms (a 9x10 half-transformed patch per tile
-// needs the registers, the 10x12 one of the 5x5-filter forms all the more) and the 4x4
-// forms, with half the LDS per workgroup
-static int input_waves(int alg) { return alg < 2 ? 16 : 8; }
-// tile slots of a workgroup: one per wave, or two per wave for the SFC-4 forms on feature
+constexpr int kInputWaves = 8;
+// tile slots of a workgroup: one per wave, or two per wave on feature
 // maps of 9 to 16 tiles when these then go through whole-image staging: the 64 channel planes
 // of an image are one contiguous run, against sparse 64-byte row windows for the 8-tile
 // rectangles of two strips (256 channels on 14x14 maps, 128 images: 23.0 -> 14.1 us)
 static int input_tile_slots(const Geometry& g) {
   const int tpi = g.th * g.tw;
-  if ((g.alg == 4 || g.alg == 5) && tpi > 8 && tpi <= 16) {
+  if (tpi > 8 && tpi <= 16) {
     TileRect tr;
     if (make_tile_rect(g, 160u * 1024u - 32u - 64u, &tr, 16, true) && tr.whole) return 16;
   }
-  return input_waves(g.alg);
+  return kInputWaves;
 }
 
 static bool make_input_plan(const Geometry& g, InputPlan* ip) {
@@ -375,19 +286,7 @@ static bool make_input_plan(const Geometry& g, InputPlan* ip) {
   const long long xb = (long long)g.N * g.Cin * g.H * g.W;
   const long long vb = (long long)g.P * g.Tp * g.Cp;
   if (xb >= (1ll << 31) || vb >= (1ll << 31)) return false;
-  if (g.alg < 4 || g.alg >= 6) {
-    // SFC-6 forms: staged rows of one strip (rectangles only), then a block of 16
-    // positions per wave; a third of the LDS at most (the registers let two workgroups share a
-    // compute unit).  (Of the eight waves 5 have a tile with 6x6 tiles of the 5x5-filter form on
-    // 56x56 and 28x28 maps, 7 with 4x4 tiles of the 7x7-filter form.)
-    const int waves = input_waves(g.alg);  // one tile slot each
-    if (!make_tile_rect(g, 48u * 1024u, &ip->tr, waves, true, false)) return false;
-    const unsigned xbytes = tile_rect_stage_bytes(g, ip->tr) + 32u;  // (patch reads reach 8 bytes past a row)
-    ip->tab_off = ((xbytes + 15u) & ~15u) + (unsigned)waves * 16u * (unsigned)kWaveRowBytes;
-    ip->lds_bytes = ip->tab_off + 64u;
-    return ip->lds_bytes <= lds_max;
-  }
-  // (16 more bytes per position for the SFC-4 forms, whose points are padded to 48 / 52)
+  // (points padded to 48 / 52)
   const int slots = input_tile_slots(g);
   const unsigned vbytes = (unsigned)((g.P + 3) / 4 * 4) * ((slots == 8 ? 512u : 1024u) + 16u);
   if (vbytes + 16u + 64u > lds_max) return false;
@@ -405,25 +304,16 @@ unsigned rows_table_offset(const Geometry& g) {
 
 template <int ALG>
 static hipError_t launch_input_i8_alg(const Geometry& g, const InputPlan& ip, const int8_t* x,
-                                      void* V, const float* inv_sx, const unsigned char* intab,
-                                      hipStream_t s, bool prepare) {
-  constexpr int NW = ALG < 2 ? 16 : 8;
+                                      void* V, const unsigned char* intab, hipStream_t s, bool prepare) {
+  constexpr int NW = kInputWaves;
   const dim3 grid(tile_rect_groups(g, ip.tr) * (unsigned)(g.Cp / 64));
-  if constexpr (AlgTraits<ALG>::kFamily == 4) {
-    if (input_tile_slots(g) == 16) {  // two tiles per wave
-      auto kernel2 = input_transform_i8_kernel<ALG, NW, 1024, 2>;
-      if (prepare) return raise_lds_limit(reinterpret_cast<const void*>(kernel2));
-      hipLaunchKernelGGL(kernel2, grid, dim3(NW * 64), ip.lds_bytes, s, x, (int8_t*)V, inv_sx, intab, g, ip);
-      return hipGetLastError();
-    }
-  }
-  auto kernel = input_transform_i8_kernel<ALG, NW, NW == 8 ? 512 : 1024>;
-  if (prepare) return raise_lds_limit(reinterpret_cast<const void*>(kernel));
-  // (the SFC-6 forms read the table of the row-form transform)
-  const unsigned toff = rows_table_offset(g);
-  const unsigned char* tab = intab && toff != ~0u ? intab + toff : intab;
-  hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), ip.lds_bytes, s, x, (int8_t*)V, inv_sx, tab, g, ip);
-  return hipGetLastError();
+  auto launch = [&](auto kernel) {
+    if (prepare) return raise_lds_limit(reinterpret_cast<const void*>(kernel));
+    hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), ip.lds_bytes, s, x, (int8_t*)V, intab, g, ip);
+    return hipGetLastError();
+  };
+  return input_tile_slots(g) == 16 ? launch(input_transform_i8_kernel<ALG, NW, 1024, 2>)
+                                   : launch(input_transform_i8_kernel<ALG, NW, 512>);
 }
 
 // Returns hipErrorNotSupported when the geometry is outside this kernel's limits;
@@ -433,25 +323,16 @@ hipError_t launch_input_transform_i8(const Geometry& g, const int8_t* x, void* V
                                      hipStream_t s, bool prepare) {
   if (image_input_supported(g))
     return launch_input_image(g, x, V, intab ? intab + image_table_offset(g) : nullptr, s, prepare);
+  if (g.alg != 4 && g.alg != 5)
+    return launch_input_rows(g, x, V, intab ? intab + rows_table_offset(g) : nullptr, s, prepare);
   WaveInputPlan wp;
   if (make_wave_input_plan(g, &wp))
     return g.alg == 4 ? launch_input_waves_alg<4>(g, wp, x, V, intab, s, prepare)
                       : launch_input_waves_alg<5>(g, wp, x, V, intab, s, prepare);
   InputPlan ip;
   if (!make_input_plan(g, &ip)) return hipErrorNotSupported;
-  switch (g.alg) {
-    case 0: return launch_input_i8_alg<0>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 1: return launch_input_i8_alg<1>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 2: return launch_input_i8_alg<2>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 3: return launch_input_i8_alg<3>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 4: return launch_input_i8_alg<4>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 5: return launch_input_i8_alg<5>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 6: return launch_input_i8_alg<6>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 7: return launch_input_i8_alg<7>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 8: return launch_input_i8_alg<8>(g, ip, x, V, inv_sx, intab, s, prepare);
-    case 9: return launch_input_i8_alg<9>(g, ip, x, V, inv_sx, intab, s, prepare);
-  }
-  return hipErrorInvalidValue;
+  return g.alg == 4 ? launch_input_i8_alg<4>(g, ip, x, V, intab, s, prepare)
+                    : launch_input_i8_alg<5>(g, ip, x, V, intab, s, prepare);
 }
 
 }  // namespace sfc

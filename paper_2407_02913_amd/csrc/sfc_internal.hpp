@@ -66,7 +66,10 @@ unsigned rows_table_offset(const Geometry& g);
 void build_image_input_table(const Geometry& g, const float* inv_sx, unsigned char* tab);
 hipError_t launch_input_image(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab,
                               hipStream_t s, bool prepare);
-// exact mode (sfc_exact.hip); hipErrorNotSupported beyond the 32-bit offset limits, and of the
+// the SFC-6 forms elsewhere, from the table at rows_table_offset (sfc_input_rows.hip)
+hipError_t launch_input_rows(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab,
+                             hipStream_t s, bool prepare = false);
+// exact mode (input transform: sfc_input_rows.hip; sfc_exact.hip); hipErrorNotSupported beyond the 32-bit offset limits, and of the
 // output transform where output_exact_ahead does not hold: the generic kernels of
 // sfc_kernels.hip take over.  tab: kRowsTabBytes at FilterViews::input_tab
 hipError_t launch_input_exact(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab,

@@ -418,6 +418,29 @@ def test_wide_rows_exact_calibration_and_requant(binding, shape, alg):
     assert rel_err(y, y_ref) <= F32_TOL
 
 
+ROWS_SHAPES = [  # rectangles of up to eight tiles (512 workgroups and more) of the row-form input transform
+    (601, 3, 2, 13, 17),  # several strips to a rectangle, the last one short; fewer columns than tile groups
+    (32, 3, 2, 50, 58),   # two chunks of tile columns, the second starting inside a dword
+    (16, 70, 2, 50, 59),  # rows that are not whole dwords, two ranges of 64 channels
+]
+
+
+@pytest.mark.parametrize("alg", ["6x6_p88", "6x6_p100", "7x7_p132", "6x6_5x5_p184", "4x4_7x7_p184", "4x4_7x7_p196"])
+@pytest.mark.parametrize("shape", ROWS_SHAPES)
+def test_row_form_rectangles(binding, shape, alg):
+    x, w, xs, ws = uniform_case(shape, 1900 + len(alg) + sum(shape), r=binding.KERNEL_SIZE[alg])
+    print("case rows", shape, alg, flush=True)
+    _, taps_ref = oracle.conv_exact(x, w, alg, return_taps=True)
+    _, taps = binding.conv2d(x, w, xs, ws, mode="exact", alg=alg, out="i32", return_taps=True)
+    assert np.array_equal(taps["V"].astype(np.int64), taps_ref["V"])
+    sx = oracle.calibrate_act_scales(x // 2, alg)
+    sw = oracle.calibrate_filter_scales(w, alg)
+    y_ref, taps_ref = oracle.conv_requant(x, w, sx, sw, xs, ws, alg, return_taps=True)
+    y, taps = binding.conv2d(x, w, xs, ws, mode="requant", alg=alg, sx=sx, sw=sw, return_taps=True)
+    assert np.array_equal(taps["V"].astype(np.int64), taps_ref["V"])
+    assert rel_err(y, y_ref) <= F32_TOL
+
+
 FULL = ["resnet56", "resnet28", "resnet14", "resnet7"]
 
 
