@@ -417,10 +417,6 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
     const hipError_t e = sfc::launch_input_exact(g, nullptr, nullptr, nullptr, nullptr, true);
     if (e != hipSuccess && e != hipErrorNotSupported) return SFC_EHIP;
   }
-  if (!requant) {
-    const hipError_t e = sfc::launch_input_exact(g, nullptr, nullptr, nullptr, nullptr, true);
-    if (e != hipSuccess && e != hipErrorNotSupported) return SFC_EHIP;
-  }
   if (hipMemcpyAsync(static_cast<char*>(filter_dev) + plan->off_dequant, plan->staging.data(),
                      table_bytes, hipMemcpyHostToDevice, s) != hipSuccess)
     return SFC_EHIP;
