@@ -217,6 +217,7 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
     case sfc::Kernel::kStaged: break;
     case sfc::Kernel::kFusedQuad: p->quad_filters = sfc::quad_filter_count(g); break;
     case sfc::Kernel::kQuad16: p->quad_filters = sfc::quad16_filter_count(g); break;
+    case sfc::Kernel::kPair16: p->quad_filters = sfc::pair16_filter_count(g); break;
     case sfc::Kernel::kSplitK: p->quad_filters = sfc::splitk_filter_count(g); break;
     case sfc::Kernel::kProductSmall: p->quad_filters = sfc::product_small_filter_count(g); break;
     case sfc::Kernel::kSingleConv: p->quad_filters = (g.Cout + 63) / 64 * 64; break;
@@ -403,6 +404,11 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
           dqs[((size_t)fg * pp + j) * 16 + 4 * q + i] =
               pt[j] < 0 ? 0.0f : dequant[(size_t)pt[j] * g.Kp + k];
       }
+    } else if (plan->kernel == sfc::Kernel::kPair16) {
+      // [group of 8 filters][processing position][lane quarter q][i]: filter 8*fg + 4*i + q
+      for (int k = 0; k < g.Cout; ++k)
+        for (int j = 0; j < pp; ++j)
+          dqs[((size_t)(k >> 3) * pp + j) * 8 + 2 * (k & 3) + ((k & 7) >> 2)] = dequant[(size_t)pt[j] * g.Kp + k];
     } else {
       // [filter][processing position]; filters beyond Cout stay zero
       for (int k = 0; k < g.Cout; ++k)
@@ -423,7 +429,8 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   const FilterViews f = views(plan, filter_dev);
   if (sfc::launch_filter_transform(plan->d.mode, g, w_dev, f, s) != hipSuccess)
     return SFC_EHIP;
-  if (quad && (sfc::groups_of_16(plan->kernel)
+  if (quad && (plan->kernel == sfc::Kernel::kPair16 ? sfc::launch_repack_filter8(g, plan->quad_filters, f.U, f.U_single, s)
+               : sfc::groups_of_16(plan->kernel)
                    ? sfc::launch_repack_filter16(g, plan->quad_filters, f.U, f.U_single, s)
                    : sfc::launch_repack_filter(g, plan->quad_filters, f.U, f.U_single, s)) != hipSuccess)
     return SFC_EHIP;
@@ -487,6 +494,9 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
         break;
       case sfc::Kernel::kQuad16:
         e = sfc::launch_quad16(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
+        break;
+      case sfc::Kernel::kPair16:
+        e = sfc::launch_pair16(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
         break;
       default: e = sfc::launch_fused_quad(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
     }

@@ -35,7 +35,6 @@ hipError_t launch_fused_quad(int out, const Geometry& g, const void* V, const Fi
     case 3: return launch_quad_alg<3>(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 4: return launch_quad_alg<4>(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 5: return launch_quad_alg<5>(out, g, V, f, x_scale, inv_y, y, s, prepare);
-    case 6:
     case 7: return launch_fused_quad_5tap(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 8:
     case 9: return launch_fused_quad_7tap(out, g, V, f, x_scale, inv_y, y, s, prepare);

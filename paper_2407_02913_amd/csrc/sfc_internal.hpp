@@ -109,6 +109,13 @@ hipError_t launch_repack_filter16(const Geometry& g, int filters, const void* U,
                                   hipStream_t s);
 hipError_t launch_quad16(int out, const Geometry& g, const void* V, const FilterViews& f,
                          float x_scale, float inv_y, void* y, hipStream_t s, bool prepare = false);
+// the same for SFC-6(6x6,5x5) with 184 points, 8 filters per wave and two pairs per lane
+// (sfc_pair16.hip): dequant_single holds the factors as [group of 8 filters][position][lane quarter][2]
+bool pair16_supported(const Geometry& g);
+int pair16_filter_count(const Geometry& g);
+hipError_t launch_repack_filter8(const Geometry& g, int filters, const void* U, void* U8, hipStream_t s);
+hipError_t launch_pair16(int out, const Geometry& g, const void* V, const FilterViews& f,
+                         float x_scale, float inv_y, void* y, hipStream_t s, bool prepare = false);
 // products + output transform with the input channels split over the waves of a workgroup
 // (sfc_splitk.hip: 512 channels, 7x7 and 4x4 tiles), on the filter operand and factor table
 // of launch_quad16
@@ -159,6 +166,7 @@ enum class Kernel {
   kSingle16,      // sfc_single16.hip
   kSingle16K,     // sfc_single16k.hip
   kSingleSmall,   // sfc_small.hip
+  kPair16,        // sfc_pair16.hip
 };
 Kernel choose_kernel(int path, const Geometry& g);
 // whether it reads filter operand and factors in groups of 16 filters (launch_quad16), else one

@@ -401,6 +401,7 @@ Kernel choose_kernel(int path, const Geometry& g) {
   if (path == 1)
     return product_small_supported(g) ? Kernel::kProductSmall
            : quad16_supported(g)      ? Kernel::kQuad16
+           : pair16_supported(g)      ? Kernel::kPair16
            : splitk_supported(g)      ? Kernel::kSplitK
                                       : Kernel::kFusedQuad;
   return Kernel::kStaged;
@@ -417,6 +418,7 @@ hipError_t prepare_kernels(int path, int out, const Geometry& g) {
     case Kernel::kStaged: return launch_output_sums(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
     case Kernel::kFusedQuad: return launch_fused_quad(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
     case Kernel::kQuad16: return launch_quad16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
+    case Kernel::kPair16: return launch_pair16(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
     case Kernel::kSplitK: return launch_splitk(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);
     case Kernel::kProductSmall: return hipSuccess;  // static LDS only
     case Kernel::kSingleConv: return launch_single_conv(out, g, nullptr, none, 1.0f, 1.0f, nullptr, nullptr, true);

@@ -1,11 +1,12 @@
-// Streaming output transform that keeps the outputs themselves (SFC-6(4x4,7x7), 184 points; SFC-4).
+// Streaming output transform that keeps the outputs themselves (SFC-6(4x4,7x7) and SFC-6(6x6,5x5),
+// 184 points; SFC-4).
 //
 // stream_vertical (sfc_points.hpp) leaves NC x M values per pair for the inverse along the
 // horizontal axis; with the 12 components of this form that is 48 registers a pair.  Here a
 // component is added to the M output columns as soon as its vertical outputs exist: 16
 // registers a pair, with as many additions, which is what lets a lane own four pairs
 // (sfc_quad16.hpp).  (The 36 outputs of a 6x6 tile do not leave a lane the registers for four:
-// SFC-6(6x6,5x5) spilled 55 this way and took as long as with one pair per lane.)
+// SFC-6(6x6,5x5) spilled 55 this way; a lane owns two, sfc_pair16.hip.)
 #pragma once
 #include "sfc_points.hpp"
 
@@ -23,9 +24,19 @@ SFC_HD void stream_row<kOutputColumns + 4, float>(const float (&z)[4][4], int o1
 #pragma unroll
   for (int o = 0; o < 4; ++o) out[o] = z[o][o1];
 }
+template <>
+struct AlgTraits<kOutputColumns + 6> {
+  static constexpr int NC = 6, M = 6;
+};
+template <>
+SFC_HD void stream_row<kOutputColumns + 6, float>(const float (&z)[6][6], int o1, float (&out)[6]) {
+#pragma unroll
+  for (int o = 0; o < 6; ++o) out[o] = z[o][o1];
+}
 
 // The inverse along one axis (inv_outputs of 12 components), one component after the other.
-// Outputs, e and d as in inv_outputs: e0 - d0, e1 - d1, e2 - d2, e0 + d0.
+// Outputs, e and d as in inv_outputs: e0 - d0, e1 - d1, e2 - d2, e0 + d0 with four of them, with six
+// e1 + d1, e2 + d2 and then these four.
 
 // components 0 and 5 (d0, d1, d2 take component 5 as -, +, -)
 template <int M, typename T>
@@ -47,11 +58,16 @@ SFC_HD void add_complex(const T& a, const T& b, T (&v)[M]) {
     w1 = b - a;
     w2 = a + a + b;
   }
-  static_assert(M == 4, "outputs of SFC-6(4x4,7x7)");
-  v[0] = G == 0 ? v[0] - w0 : v[0] + w0;
-  v[1] = G == 0 ? v[1] - w1 : v[1] + w1;
-  v[2] = G == 0 ? v[2] - w2 : v[2] + w2;
-  v[3] = v[3] + w0;
+  static_assert(M == 4 || M == 6, "outputs of SFC-6(4x4,7x7) and SFC-6(6x6,5x5)");
+  constexpr int F = M - 4;  // the first of the last four
+  if constexpr (M == 6) {
+    v[0] = v[0] + w1;
+    v[1] = v[1] + w2;
+  }
+  v[F] = G == 0 ? v[F] - w0 : v[F] + w0;
+  v[F + 1] = G == 0 ? v[F + 1] - w1 : v[F + 1] + w1;
+  v[F + 2] = G == 0 ? v[F + 2] - w2 : v[F + 2] + w2;
+  v[F + 3] = v[F + 3] + w0;
 }
 // the output that correction component B (6 ... 11) is added to, six times
 template <int B, int M>
@@ -78,7 +94,7 @@ SFC_HD void hermitian_components(const T& uo0, const T& uo1, const T& vo0, const
 template <int ALG, typename T, typename F, typename Settle>
 SFC_HD void stream_outputs(F&& next, Settle&& settle, T (&y)[AlgTraits<ALG>::M][AlgTraits<ALG>::M]) {
   using Tr = AlgTraits<ALG>;
-  static_assert(Tr::NC == 12 && Tr::M == 4 && Tr::kHermitian, "SFC-6(4x4,7x7), 184 points");
+  static_assert(Tr::NC == 12 && Tr::kHermitian, "the forms with 184 points");
   constexpr int NR = Tr::NR, NREAL = Tr::NREAL, M = Tr::M;
   auto settle_all = [&](T (&v)[M]) {
 #pragma unroll

@@ -8,7 +8,7 @@
 //   A <alg> <p> <M*M ints>     output transform row p (times 36; times 16 for 4x4)
 //   S <alg> <p> <M*M ints>     the same row through the streaming form of the fused kernels
 //                              (products fed in processing order, stream_vertical + stream_row)
-//   O <alg> <p> <M*M ints>     4, 5, 8: the same through stream_outputs4 and stream_outputs, which
+//   O <alg> <p> <M*M ints>     4, 5, 6, 8: the same through stream_outputs4 and stream_outputs, which
 //                              keep the outputs
 //   F <alg> <0> <2 ints>       4, 5: outputs of both streaming forms, of all that were compared, whose
 //                              float32 sums are not those of collapse4_rows and inv4_outputs bit for bit
@@ -146,7 +146,7 @@ void dump() {
     std::printf("\n");
     if (q == 0 && j != P) std::printf("S %d -1 %d\n", ALG, j);  // must consume exactly P products
   }
-  if constexpr (ALG == 8 || Tr::kFamily == 4) {
+  if constexpr (ALG == 6 || ALG == 8 || Tr::kFamily == 4) {
     for (int q = 0; q < P; ++q) {
       int j = 0;
       auto next = [&]() -> float { return order.pt[j++] == q ? 3.0f : 0.0f; };

@@ -9,7 +9,7 @@
 
 int main() {
   static const char* const kNames[] = {"staged",      "fused_quad", "quad16",     "splitk",      "product_small",
-                                       "single_conv", "single16",   "single16k", "single_small"};
+                                       "single_conv", "single16",   "single16k", "single_small", "pair16"};
   int path;
   sfc::Geometry g{};
   while (std::scanf("%d %d %d %d %d %d %d", &path, &g.alg, &g.N, &g.Cin, &g.Cout, &g.H, &g.W) == 7) {

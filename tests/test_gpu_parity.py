@@ -647,6 +647,34 @@ def test_7x7_filters_four_pairs_per_lane(binding, shape):
     assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
 
 
+PAIR16_SHAPES = [  # SFC-6(6x6,5x5), 184 points, two pairs per lane
+    (1, 1, 1, 1, 1),        # one pixel
+    (1, 64, 32, 24, 24),    # one chunk, exactly one block of 16 tiles, four full waves
+    (3, 70, 33, 13, 20),    # two chunks, the second with six channels; eight waves, four without a filter
+    (2, 128, 65, 31, 29),   # odd width; a workgroup with one filter
+    (5, 193, 16, 11, 14),   # four chunks, the last with one channel; half the waves empty
+    (1, 256, 130, 6, 6),    # one tile
+    (2, 449, 40, 7, 9),     # eight chunks, the last with one channel
+]
+
+
+@pytest.mark.parametrize("shape", PAIR16_SHAPES)
+def test_5x5_filters_two_pairs_per_lane(binding, shape):
+    """The products kernel of the 5x5 filters at the edges of its blocks, float32 and int8, against the oracle."""
+    alg = "6x6_5x5_p184"
+    x, w, xs, ws = uniform_case(shape, 3600 + sum(shape), r=5)
+    print("case 5x5 two pairs", shape, flush=True)
+    xc, _, _, _ = uniform_case(shape, 3700 + sum(shape))
+    sx = oracle.calibrate_act_scales(xc // 2, alg)
+    sw = oracle.calibrate_filter_scales(w, alg)
+    y_ref = oracle.conv_requant(x, w, sx, sw, xs, ws, alg)
+    args = dict(mode="requant", alg=alg, path="fused", sx=sx, sw=sw)
+    assert rel_err(binding.conv2d(x, w, xs, ws, **args), y_ref) <= F32_TOL
+    y_scale = float(np.float32(max(y_ref.max(), 1e-6) / 127.0 * 0.8))
+    y8 = binding.conv2d(x, w, xs, ws, out="i8", y_scale=y_scale, **args)
+    assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
+
+
 SINGLE_SHAPES = [
     (1, 16, 16, 32, 32),
     (2, 3, 5, 14, 14),

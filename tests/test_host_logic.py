@@ -272,6 +272,11 @@ def test_kernel_add_networks_realize_the_oracle_matrices(kernel_maps, alg_id, al
         assert np.array_equal(kernel_maps[("O", alg_id)], a2)
 
 
+def test_kept_outputs_of_the_5x5_form(kernel_maps):
+    """The form with six outputs an axis that keeps the outputs (two pairs per lane)."""
+    assert np.array_equal(kernel_maps[("O", 6)], oracle.algorithm("6x6_5x5_p184")[2])
+
+
 @pytest.mark.parametrize("alg_id", [4, 5])
 def test_sfc4_output_transforms_round_alike(kernel_maps, alg_id):
     """Every form of the SFC-4 output transform adds its float32 values in one order: outputs, and
@@ -338,6 +343,13 @@ def test_kernels_of_the_184_point_shapes(lib, routes):
 
     cases = parity.SHAPES_184
     assert routes([("fused", "4x4_7x7_p184", shape) for _, shape in cases]) == [kernel for kernel, _ in cases]
+
+
+def test_kernels_of_the_5x5_shapes(lib, routes):
+    import test_gpu_parity as parity
+
+    assert set(routes([("fused", "6x6_5x5_p184", shape) for shape in parity.PAIR16_SHAPES])) == {"pair16"}
+    assert set(routes([("fused", "6x6_5x5_p196", shape) for shape in parity.PAIR16_SHAPES])) == {"fused_quad"}
 
 
 def test_output_transforms_of_the_exact_shapes(lib, routes):
