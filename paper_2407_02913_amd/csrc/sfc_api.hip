@@ -29,6 +29,7 @@ struct sfc_plan_s {
   std::vector<float> staging;  // host image of the float tables of the filter buffer
   void* filter_dev;
   bool filter_ready;
+  bool staged_instead;  // the library's choice of the staged path for a layer that the fused path takes
   int quad_filters;  // filters covered by the regrouped filter operand (0: none)
   int dq_filters;    // filters in the [filter][processing position] dequantization table (0: none)
   sfc::Kernel kernel;  // fused and single paths: what runs, and with it the filter operand's layout
@@ -104,6 +105,11 @@ bool make_geometry(const sfc_conv_desc& d, Geometry* out) {
   return true;
 }
 
+// Workspace of the sums of nf filters.  (The output transform reads three-byte sums as dwords: a byte past the last.)
+size_t sums_bytes(const Geometry& g, int nf, int bytes) {
+  return align_up((size_t)g.P * g.Tp * nf * bytes + (bytes == 3 ? 1 : 0), 256);
+}
+
 // SFC_ALG_AUTO (3x3 filters), from per-layer timings of the ResNet shapes on one MI355X.
 // Requantized mode: SFC-4's 4x4 tiles -- 46 points per tile keep two or three workgroups on a
 // compute unit and the filter operand small, which outweighs even the ragged tiles of 14x14
@@ -125,10 +131,39 @@ int choose_alg(const sfc_conv_desc& d) {
   return SFC_ALG_4X4_P46;
 }
 
+// Staged path in passes over the filters: how many of them a pass may take for V and the pass's sums to fit
+// `bytes` (at least 16; 0: not even those fit).
+int filters_that_fit(const Geometry& g, size_t bytes) {
+  const size_t v = align_up((size_t)g.P * g.Tp * g.Cp, 256);
+  int nf = g.Kp;
+  while (nf > 0 && v + sums_bytes(g, nf, sfc::m_sum_bytes(g)) > bytes) nf -= 16;
+  return nf;
+}
+
+// The 5x5- and 7x7-filter forms with 184 points: whether three kernels are ahead of the fused path.  A
+// workgroup there is one chain of 184 positions, as many matrix instructions to each as there are
+// chunks of 64 channels, whatever the layer's size (5x5 filters: 23 to 88 us, 7x7: 21 to 87); the three kernels of a small layer
+// take 20 to 30 us and grow with M.  The lines are in workgroups of 16 tiles x 64 filters, by channel
+// chunks, from 920 layers on both paths; us staged against fused there, workgroups: ratio of staged,
+//   5x5   1 chunk  16: 0.79, 32: 0.93-1.02, 54: 1.0, 72: 1.3; 32 filters and less 8: 1.0, 19: 1.1;  2  17: 0.95, 38: 0.85, 76: 1.15;
+//         3  54: 0.75, 76: 0.95, 120: 1.0-1.16, 168: 1.35;  4  69: 0.71, 92: 0.83-1.03, 120: 1.03, 140: 1.3;
+//         5  96: 0.81, 118: 0.94, 165: 1.27;  6  56: 0.49, 119: 0.90;  7  92: 0.88;  8  56: 0.43, 112: 0.69, 181: 0.91
+//   7x7   1 chunk  10: 0.81-0.89, 16: 0.96, 25: 1.05;  2  30: 0.83, 50: 0.89, 72: 1.16;  4  64: 0.64, 84: 0.85,
+//         100: 1.03, 136: 1.24;  8 (one pair per lane)  64: 0.45, 124: 0.86, 174: 0.72
+bool staged_ahead(const Geometry& g) {
+  constexpr int kLines[2][8] = {{36, 64, 92, 104, 130, 140, 150, 170}, {18, 60, 80, 100, 0, 0, 0, 200}};
+  constexpr int kFewFilters[8] = {8, 30, 75, 85, 130, 150, 200, 300};  // 5x5, up to 32 filters
+  const int kc = g.Cp / 64;
+  if ((g.alg != SFC_ALG_6X6_5X5_P184 && g.alg != SFC_ALG_4X4_7X7_P184) || kc > 8) return false;
+  const long long workgroups = (long long)(g.Tp / 16) * ((g.Cout + 63) / 64);
+  const int line = g.alg == SFC_ALG_4X4_7X7_P184 ? kLines[1][kc - 1] : g.Cout > 32 ? kLines[0][kc - 1] : kFewFilters[kc - 1];
+  return workgroups < line;
+}
+
 // SFC_PATH_AUTO: one kernel where the layer allows it, else input transform + fused
 // product/output kernel, else the staged path (exact mode, channel counts the fused
-// kernel does not take).
-int choose_path(const sfc_conv_desc& d, const Geometry& g) {
+// kernel does not take).  *instead: the staged path of a layer that the fused path would take.
+int choose_path(const sfc_conv_desc& d, const Geometry& g, bool* instead) {
   if (d.mode != SFC_MODE_REQUANT_I8) return SFC_PATH_STAGED;
   // (with more than 128 channels the single-kernel path repeats the input transform for
   // every 64 filters and is slower than two kernels: 51 against 30 us for 256 channels on
@@ -138,7 +173,17 @@ int choose_path(const sfc_conv_desc& d, const Geometry& g) {
   // operands from L2 eight times over; the products as batched GEMMs through HBM are faster
   // (64.0 against 77.0 us at batch 256)
   const bool gemm = alg_is_7x7(d.alg) && d.H < 14 && d.Cin >= 512;
-  if (!gemm && sfc::fused_quad_supported(g)) return SFC_PATH_FUSED;
+  if (gemm) return SFC_PATH_STAGED;
+  if (sfc::fused_quad_supported(g)) {
+    // (a layer whose V fits the static workspace runs from there as well, in passes)
+    const bool in_static = (size_t)g.P * g.Tp * g.Cp > SFC_STATIC_WORKSPACE_BYTES ||
+                           filters_that_fit(g, SFC_STATIC_WORKSPACE_BYTES) > 0;
+    *instead = staged_ahead(g) && in_static;
+    return *instead ? SFC_PATH_STAGED : SFC_PATH_FUSED;
+  }
+  // chunk counts that the fused path does not take on request: its 184-point kernels do
+  if ((sfc::pair16_supported(g) || (g.alg == SFC_ALG_4X4_7X7_P184 && sfc::quad16_supported(g))) && !staged_ahead(g))
+    return SFC_PATH_FUSED;
   return SFC_PATH_STAGED;
 }
 
@@ -185,8 +230,9 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
 
   Geometry g;
   if (!make_geometry(d, &g)) return SFC_EUNSUPPORTED;
-  if (d.path == SFC_PATH_AUTO) d.path = choose_path(d, g);
-  if (d.path == SFC_PATH_FUSED && !sfc::fused_quad_supported(g)) return SFC_EUNSUPPORTED;
+  bool instead = false;
+  if (d.path == SFC_PATH_AUTO) d.path = choose_path(d, g, &instead);
+  else if (d.path == SFC_PATH_FUSED && !sfc::fused_quad_supported(g)) return SFC_EUNSUPPORTED;
   if (d.path == SFC_PATH_SINGLE && !sfc::single_supported(g)) return SFC_EUNSUPPORTED;
 
   sfc_plan_s* p = new (std::nothrow) sfc_plan_s();
@@ -194,6 +240,7 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
   p->d = d;
   p->g = g;
   p->esz = d.mode == SFC_MODE_EXACT ? 2 : 1;
+  p->staged_instead = instead;
   const size_t PK = (size_t)g.P * g.Kp;
   size_t off = 0;
   p->off_U = off;        off = align_up(off + PK * g.Cp * p->esz, 256);
@@ -241,7 +288,7 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
   // the single-kernel path keeps V on chip; its workspace only serves calibration
   if (d.path != SFC_PATH_SINGLE) off = align_up(off + (size_t)g.P * g.Tp * g.Cp * p->esz, 256);
   p->off_M = off;
-  if (d.path == SFC_PATH_STAGED) off = align_up(off + (size_t)g.P * g.Tp * g.Kp * 4, 256);
+  if (d.path == SFC_PATH_STAGED) off += sums_bytes(g, g.Kp, instead ? sfc::m_sum_bytes(g) : 4);
   // calibration scratch (abs-max tables) must fit as well
   const size_t calib = align_up((size_t)g.P * (size_t)(g.Cout > 1 ? g.Cout : 1) * 4, 256);
   p->workspace_bytes = off > calib ? off : calib;
@@ -439,14 +486,16 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   return SFC_OK;
 }
 
-sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale,
-                             void* y_dev, void* workspace_dev, size_t workspace_bytes, void* stream,
-                             int32_t stage_mask) {
+// sfc_conv2d_stages.  pass: 0, or the filters of a pass over products and output transform (all stages, workspace
+// for V and the sums of a pass).
+static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale, void* y_dev,
+                             void* workspace_dev, void* stream, int32_t stage_mask, size_t workspace_bytes,
+                             int pass) {
   if (!plan || !x_dev || !y_dev || !workspace_dev) return SFC_EINVAL;
   if (!aligned16(x_dev) || !aligned16(y_dev) || !aligned16(workspace_dev)) return SFC_EINVAL;
   if (!(x_scale > 0.0f) || !std::isfinite(x_scale)) return SFC_EINVAL;
   if (stage_mask <= 0 || stage_mask > SFC_STAGE_ALL) return SFC_EINVAL;
-  if (workspace_bytes < plan->workspace_bytes) return SFC_EWORKSPACE;
+  if (pass == 0 && workspace_bytes < plan->workspace_bytes) return SFC_EWORKSPACE;
   if (!plan->filter_ready) return SFC_ENOTREADY;
   if (plan->d.out == SFC_OUT_I8_RELU && plan->inv_y == 0.0f) return SFC_ENOTREADY;
   const bool fused = plan->d.path == SFC_PATH_FUSED;
@@ -504,6 +553,12 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
     return SFC_OK;
   }
   int32_t* M = reinterpret_cast<int32_t*>(ws + plan->off_M);
+  for (int f0 = 0; pass > 0 && f0 < g.Cout; f0 += pass) {
+    if (sfc::launch_product_gemm_i8(g, V, f.U, M, s, f0, pass) != hipSuccess ||
+        sfc::launch_output_sums(plan->d.out, g, M, f, x_scale, plan->inv_y, y_dev, s, false, f0, pass) != hipSuccess)
+      return SFC_EHIP;
+  }
+  if (pass > 0) return SFC_OK;
   if (stage_mask & SFC_STAGE_PRODUCT) {
     if (sfc::launch_product(plan->d.mode, g, V, f.U, M, s) != hipSuccess) return SFC_EHIP;
   }
@@ -515,6 +570,12 @@ sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
   return SFC_OK;
 }
 
+sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale,
+                             void* y_dev, void* workspace_dev, size_t workspace_bytes, void* stream,
+                             int32_t stage_mask) {
+  return run_stages(plan, x_dev, x_scale, y_dev, workspace_dev, stream, stage_mask, workspace_bytes, 0);
+}
+
 sfc_status sfc_conv2d_nchw(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale, void* y_dev,
                            void* workspace_dev, size_t workspace_bytes, void* stream) {
   return sfc_conv2d_stages(plan, x_dev, x_scale, y_dev, workspace_dev, workspace_bytes, stream,
@@ -524,11 +585,13 @@ sfc_status sfc_conv2d_nchw(const sfc_plan_t* plan, const int8_t* x_dev, float x_
 sfc_status sfc_conv2d_nchw_static(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale,
                                   void* y_dev, void* stream) {
   if (!plan) return SFC_EINVAL;
-  if (plan->workspace_bytes > SFC_STATIC_WORKSPACE_BYTES) return SFC_EWORKSPACE;
+  // (a layer that the library sends through M of its own accord: as many filters at a time as fit)
+  const bool passes = plan->staged_instead && plan->workspace_bytes > SFC_STATIC_WORKSPACE_BYTES;
+  const int nf = passes ? filters_that_fit(plan->g, SFC_STATIC_WORKSPACE_BYTES) : 0;
+  if (plan->workspace_bytes > SFC_STATIC_WORKSPACE_BYTES && nf == 0) return SFC_EWORKSPACE;
   void* ws = static_workspace();
   if (!ws) return SFC_EHIP;
-  return sfc_conv2d_stages(plan, x_dev, x_scale, y_dev, ws, SFC_STATIC_WORKSPACE_BYTES, stream,
-                           SFC_STAGE_ALL);
+  return run_stages(plan, x_dev, x_scale, y_dev, ws, stream, SFC_STAGE_ALL, SFC_STATIC_WORKSPACE_BYTES, nf);
 }
 
 sfc_status sfc_tap_info(const sfc_plan_t* plan, const void* workspace_dev, int32_t which,

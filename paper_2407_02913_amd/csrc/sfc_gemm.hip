@@ -10,10 +10,13 @@
 // M is kept in blocks of 16 tiles x 4 filters, M[p][t/16][k/4][t%16][k%4]: the 64 sums
 // (256 contiguous bytes) that one wave of the output transform needs per point, and that
 // a quarter wave of the GEMM holds in one accumulator register quad.
+#include <algorithm>
+
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
 #include "sfc_points.hpp"
 #include "sfc_store.hpp"
+#include "sfc_stream_outputs.hpp"
 
 namespace sfc {
 
@@ -25,6 +28,7 @@ namespace sfc {
 // LDS through registers, the next chunk's loads in flight while the current one is
 // multiplied.  LDS rows are 80 bytes apart: the 16 rows a quarter wave reads as one MFMA
 // operand (16 bytes each) then fall into different banks.
+// f0, nf: the filters of the launch, f0 .. f0 + nf - 1; M holds those alone.
 // ---------------------------------------------------------------------------------------
 constexpr int kGemmBlock = 128;  // filters and tiles per workgroup
 constexpr int kGemmPitch = 80;   // LDS bytes per operand row (64 + padding)
@@ -33,7 +37,7 @@ __global__ __launch_bounds__(256) void product_gemm_i8_kernel(const int8_t* __re
                                                               const int8_t* __restrict__ U,
                                                               int32_t* __restrict__ M, Geometry g,
                                                               int nbt, int nbf, int stream_m,
-                                                              int m_bytes) {
+                                                              int m_bytes, int f0, int nf) {
   constexpr int BL = kGemmBlock, PITCH = kGemmPitch;
   constexpr int TILE_BYTES = BL * PITCH;  // one staged operand
   __shared__ __align__(16) unsigned char lds[4 * TILE_BYTES];  // [buffer][U, V]
@@ -61,7 +65,7 @@ __global__ __launch_bounds__(256) void product_gemm_i8_kernel(const int8_t* __re
   for (int i = 0; i < 2; ++i) {
     const int q = (int)threadIdx.x + 256 * i;
     const int row = q >> 2, seg = q & 3;
-    const int k = bf * BL + row, t = bt * BL + row;
+    const int k = f0 + bf * BL + row, t = bt * BL + row;
     usrc[i] = k < g.Kp ? (unsigned)(k * g.Cp + seg * 16) : kOutOfRange;
     vsrc[i] = t < g.Tp ? (unsigned)(t * g.Cp + seg * 16) : kOutOfRange;
     ldst[i] = (unsigned)(row * PITCH + seg * 16);
@@ -115,11 +119,11 @@ __global__ __launch_bounds__(256) void product_gemm_i8_kernel(const int8_t* __re
   // lane: filter quad (k0 + 16*i)/4 + lane/16, tile block (t0 + 16*j)/16, tile lane%16 of it:
   // the four sums of an accumulator are 16 contiguous bytes of M (12 when the sums are kept
   // in three bytes each, m_sum_bytes), a wave writes 1 KiB (768 bytes)
-  const size_t plane = (size_t)g.Tp * g.Kp * (size_t)m_bytes;
+  const size_t plane = (size_t)g.Tp * nf * (size_t)m_bytes;
   const __amdgpu_buffer_rsrc_t mres = __builtin_amdgcn_make_buffer_rsrc(
       (void*)((unsigned char*)M + (size_t)p * plane), 0, (int)plane, kBufferFlags);
   const int k0 = bf * BL + wm * 64, t0 = bt * BL + wn * 64;
-  const int kquads = g.Kp >> 2;
+  const int kquads = nf >> 2;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int tb = (t0 >> 4) + j;
@@ -158,8 +162,9 @@ int m_sum_bytes(const Geometry& g) {
 }
 
 hipError_t launch_product_gemm_i8(const Geometry& g, const void* V, const void* U, int32_t* M,
-                                  hipStream_t s) {
-  const int nbt = (g.Tp + kGemmBlock - 1) / kGemmBlock, nbf = (g.Kp + kGemmBlock - 1) / kGemmBlock;
+                                  hipStream_t s, int f0, int nf) {
+  if (nf == 0) nf = g.Kp;
+  const int nbt = (g.Tp + kGemmBlock - 1) / kGemmBlock, nbf = (nf + kGemmBlock - 1) / kGemmBlock;
   const long long total = (long long)g.P * nbt * nbf;
   // 32-bit byte offsets inside one point's V, U and M
   if (total > 0x7fffffffll || (long long)g.Tp * g.Cp >= (1ll << 31) ||
@@ -170,9 +175,9 @@ hipError_t launch_product_gemm_i8(const Geometry& g, const void* V, const void* 
   // channels on 7x7 maps, 256 images, M = 69 MB: 23.4 instead of 27.6 us; the output
   // transform that follows reads M from memory either way once several batches are in flight).
   const int m_bytes = m_sum_bytes(g);
-  const int stream_m = (long long)g.P * g.Tp * g.Kp * m_bytes > (48ll << 20) ? 1 : 0;
+  const int stream_m = (long long)g.P * g.Tp * nf * m_bytes > (48ll << 20) ? 1 : 0;
   hipLaunchKernelGGL(product_gemm_i8_kernel, dim3((unsigned)total), dim3(256), 0, s,
-                     (const int8_t*)V, (const int8_t*)U, M, g, nbt, nbf, stream_m, m_bytes);
+                     (const int8_t*)V, (const int8_t*)U, M, g, nbt, nbf, stream_m, m_bytes, f0, nf);
   return hipGetLastError();
 }
 
@@ -195,12 +200,19 @@ hipError_t launch_product_gemm_i8(const Geometry& g, const void* V, const void* 
 // them 83.6 -> 80.1, 184 filters on 213 9x13 maps 81.5 -> 76.8; over 259 layers from 3 to 800 of the
 // larger workgroups 0.70 to 1.01 of the time, so there is no second form.
 // 12 for the 6x6 forms, whose compute units hold many waves; 32 for the forms
-// whose partial outputs allow few (7x7 tiles, 5x5 and 7x7 filters: four-wave workgroups), so
+// whose partial outputs allow few (7x7 tiles, nested 5x5- and 7x7-filter forms: four-wave workgroups), so
 // that the eight waves a compute unit has on a small layer keep some 64 KB of M on the way
 // (512 channels on 7x7 maps, 256 images: the same 23 us either way when measured alone; the
 // kernel there is bound by the bytes of M, see m_sum_bytes).
+// The forms with 184 points keep their outputs (36 or 16 registers, 24 to 72 with the components) and
+// have room for more: us a layer with 32 / 48 / 64 / 92 in flight, 5x5 filters, 98 channels, 60 7x7 maps
+// 30.6 / 29.7 / 30.0 / 29.3, twelve 28x28 maps 31.2 / 30.3 / 30.5 / 29.8; 7x7 filters, 512 channels, two
+// 14x14 maps 32.1 / 32.1 / 32.4 / 32.3.
 template <int ALG>
-constexpr int sum_ring() { return AlgTraits<ALG>::NC <= 6 ? Order<ALG>::PP : AlgTraits<ALG>::NC <= 8 ? 12 : 32; }
+constexpr int sum_ring() {
+  using Tr = AlgTraits<ALG>;
+  return Tr::NC <= 6 ? Order<ALG>::PP : Tr::NC <= 8 ? 12 : Tr::NC < 12 || !Tr::kHermitian ? 32 : Tr::M == 6 ? 92 : 48;
+}
 
 template <int ALG, bool PLANES, int NW>
 constexpr unsigned sums_stage_bytes() {
@@ -212,7 +224,7 @@ __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __r
                                                               const float* __restrict__ dequant,
                                                               float x_scale, float inv_y,
                                                               void* __restrict__ y, Geometry g,
-                                                              int m_bytes) {
+                                                              int m_bytes, int f0, int nf) {
   using Tr = AlgTraits<ALG>;
   constexpr int P = Tr::P, Mo = Tr::M, NC = Tr::NC, D = sum_ring<ALG>();
   constexpr Order<ALG> order{};
@@ -222,7 +234,8 @@ __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __r
   float* stage = (float*)lds + wave * (64 * Mo * (PLANES ? Mo : 1));
   int* tile_tab = (int*)(lds + sums_stage_bytes<ALG, PLANES, NW>());
   const int t0 = blockIdx.x * 16;
-  const int kq = blockIdx.y * NW + wave;
+  const int mq = blockIdx.y * NW + wave;  // filter quad in M
+  const int kq = (f0 >> 2) + mq;
   const int kcol = kq * 4 + (lane >> 4);
   if (threadIdx.x < 16) {
     const int tl = threadIdx.x, t = t0 + tl;
@@ -235,7 +248,7 @@ __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __r
 
   // bytes of one point of M; three-byte sums are read as the low bytes of a dword (the last
   // one reaches a byte past the tensor, inside the 256-byte rounding of its buffer)
-  const unsigned mplane = (unsigned)g.Tp * (unsigned)g.Kp * (unsigned)m_bytes;
+  const unsigned mplane = (unsigned)g.Tp * (unsigned)nf * (unsigned)m_bytes;
   const unsigned msh = m_bytes == 3 ? 8u : 0u;
   const __amdgpu_buffer_rsrc_t mres = __builtin_amdgcn_make_buffer_rsrc(
       (void*)M, 0, (int)(mplane * (unsigned)P + (4u - (unsigned)m_bytes)), kBufferFlags);
@@ -245,9 +258,9 @@ __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __r
   const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
       y, 0, (int)(esz * (unsigned)(g.N * g.Cout) * (unsigned)(g.H * g.W)), kBufferFlags);
   // filters beyond the padded count read nothing (zeros) and store nothing
-  const bool kvalid = kcol < g.Kp;
+  const bool kvalid = kcol < g.Kp && 4 * mq < nf;
   const unsigned m_lane =
-      kvalid ? (unsigned)((blockIdx.x * (g.Kp >> 2) + kq) * 64 + (lane & 15) * 4 + (lane >> 4)) *
+      kvalid ? (unsigned)((blockIdx.x * (nf >> 2) + mq) * 64 + (lane & 15) * 4 + (lane >> 4)) *
                    (unsigned)m_bytes
              : 0x80000000u;
   // dequantization factors: [filter][processing position], one 16-byte load per four points
@@ -278,18 +291,22 @@ __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __r
     ++j;
     return v;
   };
-  float z[NC][Mo];
-  stream_vertical<ALG, float>(next, z);
+  // The forms with 184 points keep the outputs, as their fused kernels do (the same sums in the same order).
+  constexpr bool kOutputs = NC == 12 && Tr::kHermitian;
+  constexpr int STORE = kOutputs ? kOutputColumns + Mo : ALG;
+  float z[kOutputs ? Mo : NC][Mo];
+  if constexpr (kOutputs) stream_outputs<ALG, float>(next, [](float& v) { asm volatile("" : "+v"(v)); }, z);
+  else stream_vertical<ALG, float>(next, z);
   if constexpr (PLANES)
-    store_planes<ALG, OUT>(z, stage, tile_tab, lane, kq, x_scale, inv_y, yres, g.Cout, g.th, g.tw);
+    store_planes<STORE, OUT>(z, stage, tile_tab, lane, kq, x_scale, inv_y, yres, g.Cout, g.th, g.tw);
   else
-    store_pairs<ALG, OUT, VEC2>(z, stage, tile_tab, lane, kq, x_scale, inv_y, yres, g.Cout, g.H, g.W);
+    store_pairs<STORE, OUT, VEC2>(z, stage, tile_tab, lane, kq, x_scale, inv_y, yres, g.Cout, g.H, g.W);
 }
 
 template <int ALG, int OUT, bool VEC2, bool PLANES = false>
 static hipError_t launch_sums_impl(const Geometry& g, const int32_t* M, const FilterViews& f,
                                    float x_scale, float inv_y, void* y, hipStream_t s,
-                                   bool prepare) {
+                                   bool prepare, int f0, int nf) {
   // the 7x7 forms carry 10x7 partial outputs per pair, the 5x5- and 7x7-filter forms 12x6 or
   // 12x4: they need the 256-register budget; four waves per workgroup, so that a small layer
   // still has several workgroups per compute unit, reading M and writing y out of phase (512
@@ -303,49 +320,51 @@ static hipError_t launch_sums_impl(const Geometry& g, const int32_t* M, const Fi
   if (prepare)
     return lds_bytes > 64u * 1024u ? raise_lds_limit(reinterpret_cast<const void*>(kernel))
                                    : hipSuccess;
-  const dim3 grid((unsigned)(g.Tp / 16), (unsigned)((g.Cout + 4 * NW - 1) / (4 * NW)));
+  const dim3 grid((unsigned)(g.Tp / 16), (unsigned)((std::min(g.Cout - f0, nf) + 4 * NW - 1) / (4 * NW)));
   hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), lds_bytes, s, M, f.dequant_single, x_scale,
-                     inv_y, y, g, m_sum_bytes(g));
+                     inv_y, y, g, m_sum_bytes(g), f0, nf);
   return hipGetLastError();
 }
 
 template <int ALG>
 static hipError_t launch_sums_alg(int out, const Geometry& g, const int32_t* M,
                                   const FilterViews& f, float x_scale, float inv_y, void* y,
-                                  hipStream_t s, bool prepare) {
+                                  hipStream_t s, bool prepare, int f0, int nf) {
   constexpr bool kPairs = AlgTraits<ALG>::M % 2 == 0;
   // 7x7 tiles on 7x7, 14x14, 28x28 ... maps, 4x4 tiles on 4x4, 8x8, 16x16 ...: a wave's
   // pairs are whole planes of y
   if constexpr (AlgTraits<ALG>::M == 7 || AlgTraits<ALG>::M == 4) {
     if (whole_image_tiles(AlgTraits<ALG>::M, g.H, g.W, g.th, g.tw, g.Cout))
-      return out == 2 ? launch_sums_impl<ALG, 2, false, true>(g, M, f, x_scale, inv_y, y, s, prepare)
-                      : launch_sums_impl<ALG, 0, false, true>(g, M, f, x_scale, inv_y, y, s, prepare);
+      return out == 2 ? launch_sums_impl<ALG, 2, false, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                      : launch_sums_impl<ALG, 0, false, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
   }
   if constexpr (kPairs) {
     if (g.W % 2 == 0)
-      return out == 2 ? launch_sums_impl<ALG, 2, true>(g, M, f, x_scale, inv_y, y, s, prepare)
-                      : launch_sums_impl<ALG, 0, true>(g, M, f, x_scale, inv_y, y, s, prepare);
+      return out == 2 ? launch_sums_impl<ALG, 2, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                      : launch_sums_impl<ALG, 0, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
   }
-  return out == 2 ? launch_sums_impl<ALG, 2, false>(g, M, f, x_scale, inv_y, y, s, prepare)
-                  : launch_sums_impl<ALG, 0, false>(g, M, f, x_scale, inv_y, y, s, prepare);
+  return out == 2 ? launch_sums_impl<ALG, 2, false>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                  : launch_sums_impl<ALG, 0, false>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
 }
 
 // out: 0 float32, 2 int8 with ReLU.  hipErrorNotSupported beyond the 32-bit offset limits.
 hipError_t launch_output_sums(int out, const Geometry& g, const int32_t* M, const FilterViews& f,
-                              float x_scale, float inv_y, void* y, hipStream_t s, bool prepare) {
-  const long long mbytes = 4ll * g.P * g.Tp * g.Kp, ybytes = 4ll * g.N * g.Cout * g.H * g.W;
+                              float x_scale, float inv_y, void* y, hipStream_t s, bool prepare, int f0,
+                              int nf) {
+  if (nf == 0) nf = g.Kp;
+  const long long mbytes = 4ll * g.P * g.Tp * nf, ybytes = 4ll * g.N * g.Cout * g.H * g.W;
   if (mbytes >= (1ll << 31) || ybytes >= (1ll << 31) || out == 1) return hipErrorNotSupported;
   switch (g.alg) {
-    case 0: return launch_sums_alg<0>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 1: return launch_sums_alg<1>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 2: return launch_sums_alg<2>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 3: return launch_sums_alg<3>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 4: return launch_sums_alg<4>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 5: return launch_sums_alg<5>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 6: return launch_sums_alg<6>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 7: return launch_sums_alg<7>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 8: return launch_sums_alg<8>(out, g, M, f, x_scale, inv_y, y, s, prepare);
-    case 9: return launch_sums_alg<9>(out, g, M, f, x_scale, inv_y, y, s, prepare);
+    case 0: return launch_sums_alg<0>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 1: return launch_sums_alg<1>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 2: return launch_sums_alg<2>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 3: return launch_sums_alg<3>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 4: return launch_sums_alg<4>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 5: return launch_sums_alg<5>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 6: return launch_sums_alg<6>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 7: return launch_sums_alg<7>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 8: return launch_sums_alg<8>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 9: return launch_sums_alg<9>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
   }
   return hipErrorInvalidValue;
 }

@@ -11,7 +11,7 @@ hipError_t launch_pair16_wide(int out, const Geometry& g, const void* V, const F
 bool pair16_supported(const Geometry& g) {
   if (g.alg != kAlg5Tap) return false;
   const int kc = g.Cp / 64;
-  if (kc != 1 && kc != 2 && kc != 4 && kc != 8) return false;
+  if (kc > 8) return false;
   const long long filters = pair16_filter_count(g);
   const long long ybytes = 4ll * g.N * g.Cout * g.H * g.W, vbytes = (long long)g.P * g.Tp * g.Cp;
   const long long lim = 1ll << 31;
@@ -54,10 +54,10 @@ hipError_t launch_pair16(int out, const Geometry& g, const void* V, const Filter
   switch (g.Cp / 64) {
     case 1: return launch_pair16_kc<1>(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 2: return launch_pair16_kc<2>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+    case 3: return launch_pair16_kc<3>(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 4: return launch_pair16_kc<4>(out, g, V, f, x_scale, inv_y, y, s, prepare);
-    case 8: return launch_pair16_wide(out, g, V, f, x_scale, inv_y, y, s, prepare);
   }
-  return hipErrorNotSupported;
+  return launch_pair16_wide(out, g, V, f, x_scale, inv_y, y, s, prepare);
 }
 
 }  // namespace sfc

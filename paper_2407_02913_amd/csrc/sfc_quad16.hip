@@ -22,10 +22,10 @@ static bool quad16_stores_bound(const Geometry& g) {
 bool quad16_supported(const Geometry& g) {
   if (g.alg != 4 && g.alg != 5 && g.alg != 8) return false;
   const int kc = g.Cp / 64;
-  // Up to four channel chunks: with eight a wave's filter operand stream (8 KiB per point) is
+  // Up to four channel chunks (three with 184 points): with eight a wave's filter operand stream (8 KiB per point) is
   // not hidden behind its own arithmetic (sfc_splitk.hip and the one-pair-per-lane kernel take
   // those layers).
-  if (kc != 1 && kc != 2 && kc != 4) return false;
+  if (kc > 4 || (kc == 3 && g.alg != 8)) return false;
   // A wave takes 256 (tile, filter) pairs: with fewer than one wave per SIMD of the chip the
   // one-pair-per-lane kernel, whose waves take 64, fills it better.  With 184 points its fourfold
   // matrix work and operand reads outweigh that on most layers (7x7 filters, layer: 16 channels

@@ -30,6 +30,8 @@ hipError_t launch_quad16_7tap(int out, const Geometry& g, const void* V, const F
                             : launch_quad16_7tap_impl<1, 0>(g, V, f, x_scale, inv_y, y, s, prepare);
     case 2: return out == 2 ? launch_quad16_7tap_impl<2, 2>(g, V, f, x_scale, inv_y, y, s, prepare)
                             : launch_quad16_7tap_impl<2, 0>(g, V, f, x_scale, inv_y, y, s, prepare);
+    case 3: return out == 2 ? launch_quad16_7tap_impl<3, 2>(g, V, f, x_scale, inv_y, y, s, prepare)
+                            : launch_quad16_7tap_impl<3, 0>(g, V, f, x_scale, inv_y, y, s, prepare);
     case 4: return out == 2 ? launch_quad16_7tap_impl<4, 2>(g, V, f, x_scale, inv_y, y, s, prepare)
                             : launch_quad16_7tap_impl<4, 0>(g, V, f, x_scale, inv_y, y, s, prepare);
   }

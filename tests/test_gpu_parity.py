@@ -675,6 +675,56 @@ def test_5x5_filters_two_pairs_per_lane(binding, shape):
     assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
 
 
+@pytest.mark.parametrize("alg,shape", [
+    ("6x6_5x5_p184", (2300, 130, 24, 5, 6)),   # three chunks of channels on the fused path
+    ("6x6_5x5_p184", (2400, 300, 60, 3, 5)),   # five
+    ("6x6_5x5_p184", (1205, 390, 65, 6, 2)),   # seven
+    ("4x4_7x7_p184", (1290, 192, 65, 4, 3)),   # three
+])
+def test_odd_chunk_counts_of_the_184_point_kernels(binding, alg, shape):
+    x, w, xs, ws = uniform_case(shape, 3900 + sum(shape), r=binding.KERNEL_SIZE[alg])
+    print("case odd chunks", alg, shape, flush=True)
+    plan = binding.Plan(*shape, alg=alg, mode="requant", path="auto")
+    assert plan.path == "fused"
+    plan.close()
+    sx = oracle.calibrate_act_scales(x[:8] // 2, alg)
+    sw = oracle.calibrate_filter_scales(w, alg)
+    y_ref = oracle.conv_requant(x, w, sx, sw, xs, ws, alg)
+    args = dict(mode="requant", alg=alg, path="auto", sx=sx, sw=sw)
+    assert rel_err(binding.conv2d(x, w, xs, ws, **args), y_ref) <= F32_TOL
+    y_scale = float(np.float32(max(y_ref.max(), 1e-6) / 127.0 * 0.8))
+    y8 = binding.conv2d(x, w, xs, ws, out="i8", y_scale=y_scale, **args)
+    assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
+
+
+@pytest.mark.parametrize("alg,shape,out", [
+    ("6x6_5x5_p184", (20, 512, 500, 13, 12), "f32"),  # 120 tiles: 11 MB of V, two passes
+    ("4x4_7x7_p184", (20, 512, 130, 14, 16), "i8"),   # 320 tiles: 30 MB of V, passes of 16 filters, the last with two
+])
+def test_static_workspace_in_passes(binding, alg, shape, out):
+    """A layer that the library sends through M although the fused path takes it: from the static workspace
+    its filters run in passes, with the outputs of the one pass of a caller's workspace."""
+    import torch
+
+    x, w, xs, ws = uniform_case(shape, 4100 + sum(shape), r=binding.KERNEL_SIZE[alg])
+    print("case static passes", alg, shape, flush=True)
+    plan = binding.Plan(*shape, alg=alg, mode="requant", path="auto", out=out)
+    assert plan.path == "staged" and plan.workspace_bytes > binding.STATIC_WORKSPACE_BYTES
+    plan.set_point_scales(oracle.calibrate_act_scales(x[:2], alg), oracle.calibrate_filter_scales(w, alg))
+    if out == "i8":
+        plan.set_output_scale(30.0)
+    fbuf, wbuf = binding.device_buffer(plan.filter_bytes), binding.device_buffer(plan.workspace_bytes)
+    plan.transform_filter(torch.from_numpy(w).cuda(), ws, fbuf)
+    xd = torch.from_numpy(x).cuda()
+    ys = [torch.full((shape[0], shape[2], *shape[3:]), 77, dtype=torch.int8 if out == "i8" else torch.float32,
+                     device="cuda") for _ in range(2)]
+    plan.conv2d(xd, xs, ys[0], wbuf)
+    plan.conv2d_static(xd, xs, ys[1])
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1]) and ys[0].float().std() > 0
+    plan.close()
+
+
 SINGLE_SHAPES = [
     (1, 16, 16, 32, 32),
     (2, 3, 5, 14, 14),

@@ -352,6 +352,29 @@ def test_kernels_of_the_5x5_shapes(lib, routes):
     assert set(routes([("fused", "6x6_5x5_p196", shape) for shape in parity.PAIR16_SHAPES])) == {"fused_quad"}
 
 
+@pytest.mark.parametrize("alg,cin,cout,line", [
+    ("6x6_5x5_p184", 64, 64, 36), ("6x6_5x5_p184", 64, 32, 8), ("6x6_5x5_p184", 100, 128, 64),
+    ("6x6_5x5_p184", 129, 64, 92), ("6x6_5x5_p184", 257, 300, 130), ("6x6_5x5_p184", 512, 64, 170),
+    ("4x4_7x7_p184", 30, 64, 18), ("4x4_7x7_p184", 128, 40, 60), ("4x4_7x7_p184", 150, 64, 80),
+    ("4x4_7x7_p184", 256, 128, 100), ("4x4_7x7_p184", 512, 256, 200)])
+def test_auto_path_on_both_sides_of_its_line(lib, alg, cin, cout, line):
+    """Layers with 184 points: three kernels below a number of workgroups, the fused path from there on;
+    the chunk counts that the fused path refuses on request stay refused."""
+    from paper_2407_02913_amd import binding
+
+    edge, groups = int(alg[0]), -(-cout // 64)
+    for blocks, path in ((-(-line // groups) - 1, "staged"), (-(-line // groups), "fused")):
+        plan = binding.Plan(16 * blocks, cin, cout, edge, edge, alg=alg, mode="requant", path="auto")
+        assert plan.path == path, blocks
+        plan.close()
+    if -(-cin // 64) in (1, 2, 4, 8):
+        binding.Plan(1, cin, cout, edge, edge, alg=alg, mode="requant", path="fused").close()
+    else:
+        with pytest.raises(binding.SfcError) as e:
+            binding.Plan(1, cin, cout, edge, edge, alg=alg, mode="requant", path="fused")
+        assert e.value.code == 2
+
+
 def test_output_transforms_of_the_exact_shapes(lib, routes):
     """Either output transform has the shapes of the GPU parity tests that are there for it."""
     import test_gpu_parity as parity
