@@ -1,14 +1,7 @@
 // Input-tile transform V = B^T x B with transform-domain requantization to int8,
-// the HBM-facing first stage of the two-kernel paths (gfx950), SFC-4 forms, on the
-// matrix cores (sfc_mfma_input.hpp; 7x7 maps: sfc_input_image.hip; SFC-6 forms: sfc_input_rows.hip).
-//
-// A workgroup owns up to NW tiles (a rectangle of S strips x tlw tile columns, or whole
-// images of a small feature map), one per wave, and 64 input channels:
-//  1. stage the input rows of every (strip, channel) in LDS (coalesced dword loads),
-//  2. transform: wave = tile, four groups of 16 channels, lane = (position, four channels);
-//  3. the rounded points land in LDS as [processing position][tile][channel], over the staging
-//     area, and are copied out with 16-byte lanes, 64 contiguous bytes per (point, tile) and NW
-//     tiles in a row.
+// the HBM-facing first stage of the two-kernel paths (gfx950): choice of its kernel, and the one of
+// the SFC-4 forms on small feature maps, on the matrix cores (sfc_mfma_input.hpp; 7x7 maps:
+// sfc_input_image.hip; SFC-6 forms and larger maps: sfc_input_rows.hip).
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
 #include "sfc_mfma_input.hpp"
@@ -18,111 +11,6 @@
 namespace sfc {
 
 constexpr int kWaveRowBytes = 80;  // LDS bytes per position in a wave's block (conflict-free dword writes)
-
-struct InputPlan {
-  TileRect tr;
-  unsigned tab_off;  // LDS byte offset of the tile -> V row table
-  unsigned lds_bytes;
-};
-
-// VS: bytes of V per point in LDS, 64 per tile slot (512 for the 8-tile workgroups: half the
-// LDS, so that more workgroups share a compute unit and overlap their phases).
-// TPW: tiles per wave (2 when the workgroup takes whole images of 9 to 16 tiles,
-// whose planes it copies as they lie in memory instead of staging sparse 64-byte row windows).
-template <int ALG, int NW, int VS, int TPW = 1>
-__global__ __launch_bounds__(NW * 64) void input_transform_i8_kernel(
-    const int8_t* __restrict__ x, int8_t* __restrict__ V, const unsigned char* __restrict__ intab, Geometry g,
-    InputPlan ip) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  constexpr int P = AlgTraits<ALG>::P;
-  // LDS bytes from one position's V to the next: 16 positions are written per instruction
-  // (sfc_mfma_input.hpp) and lie in different banks
-  static_assert(AlgTraits<ALG>::kFamily == 4, "the SFC-4 forms");
-  constexpr int VSP = VS + 16;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const TileRect& tr = ip.tr;
-  // Workgroups are dealt to the 8 XCDs round-robin by id; remap so that each XCD (each
-  // L2) gets a contiguous range of rectangles: neighbours share halo rows and columns.
-  // Position = (tile group, 64-channel group), the channel group varying fastest: the
-  // workgroups that write the two 64-byte halves of a line of V (Cp = 128) run next to
-  // each other on one XCD.
-  const int cgn = g.Cp >> 6;
-  const int pos = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int bx = pos / cgn;
-  const int c0 = (pos - bx * cgn) * 64;
-
-  // tile slot -> row of V (-1: no such tile)
-  int* row_tab = (int*)(lds + ip.tab_off);
-  if (threadIdx.x < 16) {
-    const int tl = threadIdx.x;
-    const TileCoord tc = tile_coord(g, tr, bx, tl);
-    row_tab[tl] = tc.live ? (tc.n * g.th + tc.ti) * g.tw + tc.tj : -1;
-  }
-
-  unsigned char* in = lds + 16;  // (plane patches are read from up to 4 bytes early)
-  stage_input<ALG, NW>(x, in, g, tr, bx, c0, wave, lane);
-  __syncthreads();
-  // on the matrix cores: wave = tile, four groups of 16 channels; rounded and packed in
-  // registers before V is written over the staged rows
-  using Tr = AlgTraits<ALG>;
-  constexpr int NPB = MfmaInput<ALG>::NPB, PP = Order<ALG>::PP;
-  MfmaInput<ALG> mi;
-  mi.load(intab, lane);
-  unsigned packed[TPW][4][NPB];
-#pragma unroll
-  for (int it = 0; it < TPW; ++it) {
-    const int tile = wave + NW * it;
-    if (tile < tr.ntiles) {
-      if (tr.whole) {
-        const int tpi = g.th * g.tw;
-        const int slot = tile / tpi, rem = tile - slot * tpi;
-        const int ti = rem / g.tw, tj = rem - ti * g.tw;
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg)
-          mi.transform(MfmaInput<ALG>::operand_plane(in + slot * 64 * tr.cs, tr.cs, 16 * cg,
-                                                     Tr::M * ti - Tr::PAD, Tr::M * tj - Tr::PAD, g.H,
-                                                     g.W, lane),
-                       g.qmax, packed[it][cg]);
-      } else {
-        const int tj0 = (bx % tr.chunks) * tr.tlw;
-        const int halo = Tr::M * tj0 - Tr::PAD - ((Tr::M * tj0) & ~3) + 4;
-        const int s = tile / tr.tlw, tjl = tile - s * tr.tlw;
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg)
-          mi.transform(MfmaInput<ALG>::template operand_rect<stage_channel_bytes(Tr::NI)>(
-                           in, s, 16 * cg, halo + Tr::M * tjl, lane),
-                       g.qmax, packed[it][cg]);
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int it = 0; it < TPW; ++it) {
-    const int tile = wave + NW * it;
-    if (tile < tr.ntiles) {
-#pragma unroll
-      for (int cg = 0; cg < 4; ++cg)
-#pragma unroll
-        for (int m = 0; m < NPB; ++m) {
-          const int pos = 16 * m + (lane & 15);
-          if (pos < PP)
-            *(unsigned*)(lds + pos * VSP + tile * 64 + 16 * cg + 4 * (lane >> 4)) = packed[it][cg][m];
-        }
-    }
-  }
-  __syncthreads();
-
-  // ---- copy out: wave w takes positions w, w+NW, ...; lane = (tile, 16-byte quarter) ---
-  const unsigned vplane = (unsigned)g.Tp * (unsigned)g.Cp;
-  const __amdgpu_buffer_rsrc_t vres =
-      __builtin_amdgcn_make_buffer_rsrc((void*)V, 0, (int)(vplane * (unsigned)P), kBufferFlags);
-  const int t = row_tab[VS == 512 ? (lane >> 2) & 7 : lane >> 2];
-  const unsigned lane_off = (unsigned)t * (unsigned)g.Cp + (unsigned)(c0 + 16 * (lane & 3));
-  if (t >= 0) {
-    copy_out_points<ALG, NW, VS, VSP>(lds, vres, lane_off, vplane, wave, lane);
-  }
-}
 
 // SFC-4 forms on small feature maps (whole images staged as they lie in memory): after the
 // one barrier that follows the staging every wave works on its own.  It transforms its tiles on
@@ -267,53 +155,10 @@ static hipError_t launch_input_waves_alg(const Geometry& g, const WaveInputPlan&
                          : launch(input_transform_waves_kernel<ALG, 8, 1>);
 }
 
-constexpr int kInputWaves = 8;
-// tile slots of a workgroup: one per wave, or two per wave on feature
-// maps of 9 to 16 tiles when these then go through whole-image staging: the 64 channel planes
-// of an image are one contiguous run, against sparse 64-byte row windows for the 8-tile
-// rectangles of two strips (256 channels on 14x14 maps, 128 images: 23.0 -> 14.1 us)
-static int input_tile_slots(const Geometry& g) {
-  const int tpi = g.th * g.tw;
-  if (tpi > 8 && tpi <= 16) {
-    TileRect tr;
-    if (make_tile_rect(g, 160u * 1024u - 32u - 64u, &tr, 16, true) && tr.whole) return 16;
-  }
-  return kInputWaves;
-}
-
-static bool make_input_plan(const Geometry& g, InputPlan* ip) {
-  const unsigned lds_max = 160u * 1024u;
-  const long long xb = (long long)g.N * g.Cin * g.H * g.W;
-  const long long vb = (long long)g.P * g.Tp * g.Cp;
-  if (xb >= (1ll << 31) || vb >= (1ll << 31)) return false;
-  // (points padded to 48 / 52)
-  const int slots = input_tile_slots(g);
-  const unsigned vbytes = (unsigned)((g.P + 3) / 4 * 4) * ((slots == 8 ? 512u : 1024u) + 16u);
-  if (vbytes + 16u + 64u > lds_max) return false;
-  if (!make_tile_rect(g, lds_max - 32u - 64u, &ip->tr, slots, true)) return false;
-  const unsigned xbytes = tile_rect_stage_bytes(g, ip->tr) + 16u;
-  ip->tab_off = ((xbytes > vbytes ? xbytes : vbytes) + 15u) & ~15u;
-  ip->lds_bytes = ip->tab_off + 64u;
-  return ip->lds_bytes <= lds_max;
-}
-
 unsigned rows_table_offset(const Geometry& g) {
-  if (g.alg == 4 || g.alg == 5) return ~0u;
-  return (image_table_bytes(g) + 255u) & ~255u;
-}
-
-template <int ALG>
-static hipError_t launch_input_i8_alg(const Geometry& g, const InputPlan& ip, const int8_t* x,
-                                      void* V, const unsigned char* intab, hipStream_t s, bool prepare) {
-  constexpr int NW = kInputWaves;
-  const dim3 grid(tile_rect_groups(g, ip.tr) * (unsigned)(g.Cp / 64));
-  auto launch = [&](auto kernel) {
-    if (prepare) return raise_lds_limit(reinterpret_cast<const void*>(kernel));
-    hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), ip.lds_bytes, s, x, (int8_t*)V, intab, g, ip);
-    return hipGetLastError();
-  };
-  return input_tile_slots(g) == 16 ? launch(input_transform_i8_kernel<ALG, NW, 1024, 2>)
-                                   : launch(input_transform_i8_kernel<ALG, NW, 512>);
+  WaveInputPlan wp;
+  if (image_input_supported(g) || make_wave_input_plan(g, &wp)) return ~0u;
+  return (image_table_offset(g) + 255u) & ~255u;
 }
 
 // Returns hipErrorNotSupported when the geometry is outside this kernel's limits;
@@ -323,16 +168,11 @@ hipError_t launch_input_transform_i8(const Geometry& g, const int8_t* x, void* V
                                      hipStream_t s, bool prepare) {
   if (image_input_supported(g))
     return launch_input_image(g, x, V, intab ? intab + image_table_offset(g) : nullptr, s, prepare);
-  if (g.alg != 4 && g.alg != 5)
-    return launch_input_rows(g, x, V, intab ? intab + rows_table_offset(g) : nullptr, s, prepare);
   WaveInputPlan wp;
   if (make_wave_input_plan(g, &wp))
     return g.alg == 4 ? launch_input_waves_alg<4>(g, wp, x, V, intab, s, prepare)
                       : launch_input_waves_alg<5>(g, wp, x, V, intab, s, prepare);
-  InputPlan ip;
-  if (!make_input_plan(g, &ip)) return hipErrorNotSupported;
-  return g.alg == 4 ? launch_input_i8_alg<4>(g, ip, x, V, intab, s, prepare)
-                    : launch_input_i8_alg<5>(g, ip, x, V, intab, s, prepare);
+  return launch_input_rows(g, x, V, intab ? intab + rows_table_offset(g) : nullptr, s, prepare);
 }
 
 }  // namespace sfc

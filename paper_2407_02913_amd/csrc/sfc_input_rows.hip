@@ -1,6 +1,5 @@
-// Input-tile transform V = B^T x B in row form on the matrix cores (gfx950): the SFC-6 forms of
-// requantized mode outside small feature maps (rounded to int8, [P][Tp][Cp]) and every form of
-// exact mode (kept as int16).
+// Input-tile transform V = B^T x B in row form on the matrix cores (gfx950): requantized mode
+// outside small feature maps (rounded to int8, [P][Tp][Cp]) and exact mode (kept as int16).
 //
 // A workgroup stages the input rows of a rectangle of tiles (S strips x tlw tile columns) for 64
 // channels in LDS.  A patch row is up to 16 bytes, k = 16 i + j, so the sums of 16 channels at 16
@@ -21,6 +20,10 @@
 // batch 32, 13.8 -> 13.6; layers drawn over the range of the 5x5 and 7x7 filters 0.93 of the time (60, 0.80 to
 // 1.06), of exact mode 0.97 (40, 0.88 to 1.07).  Two, three and six position groups for 184 points instead of
 // four: 35.0, 30.4 and 34.5 us for the first layer.
+// The SFC-4 forms had a wave to a tile, 64-byte rows staged whatever the width (a byte at a time where 4 does
+// not divide it) and V collected in LDS: 192 to 64 channels on 107 35x35 maps, three kernels, 349 -> 137 us, 350 to
+// 40 on 256 53x25 maps 613 -> 485, 256 to 256 on 16 56x56 maps 56.3 -> 54.4; over 138 layers of more than 128 channels
+// 0.39 to 1.05 of the time, 0.93 in the middle (above 1.02 with 350 to 650 tiles).
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
 #include "sfc_mfma_input.hpp"
@@ -318,8 +321,11 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
   tr.th_magic = ((1ull << 32) + (unsigned long long)g.th - 1) / (unsigned long long)g.th;
   constexpr unsigned kBlocks = (unsigned)Form::NW * (unsigned)Form::kBlockBytes;
   constexpr unsigned kBudget = 80u * 1024u;  // two workgroups to a compute unit at least
+  // (4x4 tiles, int8: a wave owns every position of its tile columns, with fewer than four tiles some waves
+  // would have none)
+  constexpr int kLeast = !EXACT && Form::PG == 1 ? Form::TG : 1;
   bool found = false;
-  for (int tiles = 8; tiles >= 1; tiles >>= 1) {
+  for (int tiles = 8; tiles >= kLeast; tiles >>= 1) {
     RowsPlan c = *rp;
     c.tr.chunks = (g.tw + tiles - 1) / tiles;
     c.tr.tlw = (g.tw + c.tr.chunks - 1) / c.tr.chunks;
@@ -364,6 +370,8 @@ hipError_t launch_input_rows(const Geometry& g, const int8_t* x, void* V, const 
     case 1: return launch_rows_alg<1, false>(g, x, V, tab, s, prepare);
     case 2: return launch_rows_alg<2, false>(g, x, V, tab, s, prepare);
     case 3: return launch_rows_alg<3, false>(g, x, V, tab, s, prepare);
+    case 4: return launch_rows_alg<4, false>(g, x, V, tab, s, prepare);
+    case 5: return launch_rows_alg<5, false>(g, x, V, tab, s, prepare);
     case 6: return launch_rows_alg<6, false>(g, x, V, tab, s, prepare);
     case 7: return launch_rows_alg<7, false>(g, x, V, tab, s, prepare);
     case 8: return launch_rows_alg<8, false>(g, x, V, tab, s, prepare);

@@ -27,9 +27,9 @@ constexpr unsigned kInputTabBytes = kInputTabPoints + kInputTabRows * 4;
 void build_input_table(int alg, const float* inv_sx, unsigned char* tab);
 
 
-// The SFC-6 forms (8x8, 9x9 and 10x10 patches) outside small feature maps: k = 16 i + j over
+// Row form (sfc_input_rows.hip; 6x6 to 10x10 patches outside small feature maps, exact mode): k = 16 i + j over
 // two or three matrix steps of 64 (patch rows 4 s .. 4 s + 3 in step s; columns and rows past
-// the patch carry no coefficient; exact mode: every form).  Table, in FilterViews::input_tab:
+// the patch carry no coefficient).  Table, in FilterViews::input_tab:
 // float inv_pos[208], int point[208], int8 coeff[208][192] ([position][k]).
 constexpr int kRowsTabRows = 208;
 constexpr unsigned kRowsTabPoint = kRowsTabRows * 4;
@@ -59,15 +59,8 @@ struct MfmaInput {
 
   // Operand A from the staged rows of a tile rectangle (sfc_tile_input.hpp: 64 bytes per
   // image row, six rows per channel, CS bytes per channel): lane = (channel l%16 of the group
-  // of 16 starting at ch0, patch rows 2(l/16), 2(l/16)+1); o = LDS byte of the tile's first
-  // patch column.  Lanes 48..63 (k >= 48, coefficients zero) repeat rows 4, 5.
-  template <int CS>
-  static __device__ __forceinline__ v4i operand_rect(const unsigned char* in, int s, int ch0, int o,
-                                                     int lane) {
-    return operand_rect<CS>(in, ch0, s * 64 * CS + o, lane);
-  }
-  // (the same with the strip folded into the offset: o = strip * 64 * CS + LDS byte of the
-  // tile's first patch column, which lies in the first 64 bytes)
+  // of 16 starting at ch0, patch rows 2(l/16), 2(l/16)+1); o = strip * 64 * CS + LDS byte of the
+  // tile's first patch column, which lies in the first 64 bytes.  Lanes 48..63 (k >= 48, coefficients zero) repeat rows 4, 5.
   template <int CS>
   static __device__ __forceinline__ v4i operand_rect(const unsigned char* in, int ch0, int o, int lane) {
     const int ch = ch0 + (lane & 15), rp = min(lane >> 4, 2);

@@ -407,56 +407,6 @@ __device__ __forceinline__ void transform_tiles(unsigned char* lds, const float*
   }
 }
 
-// Copies the rounded points of the rectangle from LDS ([position][tile][channel]) to
-// V: wave w takes positions w, w+NW, ...; lane = (tile, 16-byte quarter of its 64
-// channels); lane_off is the lane's byte offset inside a point's plane of V.
-// VS = 512 (eight tiles per workgroup): a wave takes two positions at a time, lanes 0..31
-// the first, lanes 32..63 the second.
-// VSP: LDS bytes from one position to the next (VS, or more when the points are padded).
-template <int ALG, int NW, int VS = 1024, int VSP = VS>
-__device__ __forceinline__ void copy_out_points(const unsigned char* lds,
-                                                __amdgpu_buffer_rsrc_t vres, unsigned lane_off,
-                                                unsigned vplane, int wave, int lane) {
-  constexpr int P = AlgTraits<ALG>::P;
-  constexpr Order<ALG> order{};
-  if constexpr (VS == 512) {
-    const int hi = lane >> 5;  // which of the wave's two positions
-#pragma unroll
-    for (int jj = 0; jj < (P + 2 * NW - 1) / (2 * NW); ++jj) {
-      // positions 2*(jj*NW + wave) and the next one: compile-time candidates selected by
-      // the uniform wave index and the half of the wave
-      int p = -1;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const int j0 = 2 * (jj * NW + w);
-        if (w == wave) {
-          const int pa = j0 < P ? order.pt[j0 < P ? j0 : 0] : -1;
-          const int pb = j0 + 1 < P ? order.pt[j0 + 1 < P ? j0 + 1 : 0] : -1;
-          p = hi ? pb : pa;
-        }
-      }
-      if (p >= 0) {
-        const v4i d = *(const v4i*)(lds + (2 * (jj * NW + wave) + hi) * VSP + (lane & 31) * 16);
-        __builtin_amdgcn_raw_buffer_store_b128(d, vres, lane_off + (unsigned)p * vplane, 0, 0);
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int jj = 0; jj < (P + NW - 1) / NW; ++jj) {
-    // the position is one of NW compile-time values chosen by the uniform wave index,
-    // so the canonical point index, and with it the plane offset, stays scalar
-    int p = -1;
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-      if (w == wave && jj * NW + w < P) p = order.pt[jj * NW + w];
-    if (p >= 0) {
-      const v4i d = *(const v4i*)(lds + (jj * NW + wave) * VSP + lane * 16);
-      __builtin_amdgcn_raw_buffer_store_b128(d, vres, lane_off, (unsigned)p * vplane, 0);
-    }
-  }
-}
-
 #endif  // __HIPCC__
 
 }  // namespace sfc

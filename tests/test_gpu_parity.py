@@ -890,6 +890,19 @@ def test_46_points_staged_output_transform(binding, shape):
     test_46_points_past_the_small_layers(binding, "staged", "staged", shape)
 
 
+@pytest.mark.parametrize("alg", ["4x4_p46", "4x4_p49"])
+@pytest.mark.parametrize("shape", [  # the last rows and columns of tiles ragged
+    (3, 130, 5, 17, 17),   # five tile columns, rows of 17 bytes
+    (2, 70, 4, 18, 22),    # two workgroups of three columns to a strip
+    (1, 66, 3, 5, 203),    # wide: 13 workgroups of four columns
+    (5, 65, 4, 66, 5),     # two strips of two columns: half of the waves have none
+    (46, 65, 2, 19, 35),   # past 512 workgroups: rectangles of five and four columns
+    (43, 129, 2, 20, 32),  # rows of whole dwords
+])
+def test_4x4_tiles_on_larger_maps(binding, shape, alg):
+    test_46_points_past_the_small_layers(binding, "staged", "staged", shape, alg)
+
+
 SINGLE16_49 = [  # 49 points in one kernel
     (18, 33, 17, 56, 56),    # 252 workgroups of one chunk: two waves to a filter group
     (256, 9, 40, 14, 14),    # 256: whole images, pairs per store
