@@ -181,9 +181,9 @@ int choose_path(const sfc_conv_desc& d, const Geometry& g, bool* instead) {
     *instead = staged_ahead(g) && in_static;
     return *instead ? SFC_PATH_STAGED : SFC_PATH_FUSED;
   }
-  // chunk counts that the fused path does not take on request: its 184-point kernels do
-  if ((sfc::pair16_supported(g) || (g.alg == SFC_ALG_4X4_7X7_P184 && sfc::quad16_supported(g))) && !staged_ahead(g))
-    return SFC_PATH_FUSED;
+  // chunk counts that the fused path does not take on request: its 184-point kernels do, and quad16_kernel
+  // with 46 points (192 channels on 56x56 maps, batch 32: 161 us with three kernels, 75 there)
+  if ((sfc::pair16_supported(g) || sfc::quad16_supported(g)) && !staged_ahead(g)) return SFC_PATH_FUSED;
   return SFC_PATH_STAGED;
 }
 

@@ -19,19 +19,43 @@ static bool quad16_stores_bound(const Geometry& g) {
          (long long)(g.Tp / 16) * ((g.Cout + 63) / 64) < 128;
 }
 
+// SFC-4 with 46 points and three to eight channel chunks: whether the layer has enough workgroups of 16 tiles x
+// 64 filters.  A workgroup is one chain, 14 to 30 us with its input transform whatever the layer's size; below the line three kernels
+// (three, five to seven chunks), the one-pair-per-lane kernel (four) or the split of the channels (eight)
+// are ahead.  us here over us there from 187 layers, workgroups: ratio,
+//   3   24: 1.02-1.2, 32: 0.97, 48: 0.90-1.0, 80: 0.84, 126: 0.83, 516: 0.79, 1200: 0.61
+//   4   39-48: 0.87, 62-98: 0.89-0.98, 125-150: 0.82-0.92, 152-200: 0.77-0.91
+//   5   80-108: 0.98-1.07, 124: 0.98-1.0, 147-216: 0.79-0.98, 1143: 0.71
+//   6   104-144: 1.05-1.1, 160: 1.0, 174-233: 0.91, 304: 1.03, 378-672: 0.75-0.85
+//   7   133-172: 0.98-1.03, 205-225: 0.71-0.88, 264: 1.0, 396-602: 0.66-0.86
+//   8   66-158: 1.15-1.23, 180: 0.88, 212-384: 0.75-0.91, 512-576: 0.71-0.77
+// Two tile columns and odd width (7x7): the stores of quad16_stores_bound; 56: 1.1, 128: 1.07-1.18, 189: 1.09, 232: 0.97,
+// 368: 0.91.  From six chunks on no less than 5/8 of the filters must exist (16, 24, 40 and 72 of 64 or 128: 0.83 to 1.2,
+// 1.0 in the middle).
+static bool quad16_workgroups_enough(const Geometry& g) {
+  constexpr int kLines[9] = {0, 0, 0, 40, 48, 140, 165, 200, 180};
+  const int kc = g.Cp / 64;
+  const int groups = (g.Cout + 63) / 64;
+  if (kc >= 6 && g.Cout * 8ll < groups * 64ll * 5) return false;
+  const int line = kLines[kc] + (g.W % 2 == 1 && g.tw == 2 ? 120 : 0);
+  return (long long)(g.Tp / 16) * groups >= line;
+}
+
 bool quad16_supported(const Geometry& g) {
   if (g.alg != 4 && g.alg != 5 && g.alg != 8) return false;
   const int kc = g.Cp / 64;
-  // Up to four channel chunks (three with 184 points): with eight a wave's filter operand stream (8 KiB per point) is
-  // not hidden behind its own arithmetic (sfc_splitk.hip and the one-pair-per-lane kernel take
-  // those layers).
-  if (kc > 4 || (kc == 3 && g.alg != 8)) return false;
+  // Up to four channel chunks (three with 184 points), with 46 points eight.
+  if (kc > (g.alg == 4 ? 8 : 4) || (kc == 3 && g.alg == 5)) return false;
   // A wave takes 256 (tile, filter) pairs: with fewer than one wave per SIMD of the chip the
   // one-pair-per-lane kernel, whose waves take 64, fills it better.  With 184 points its fourfold
   // matrix work and operand reads outweigh that on most layers (7x7 filters, layer: 16 channels
   // on one 32x32 map 30.3 us against 26.3 here, 128 channels on one 28x28 map 35.2 against 32.1,
   // 256 channels on 14x14 maps at batch 32 67.3 against 59.5), not where quad16_stores_bound.
-  if (g.alg < 6 && (long long)(g.Tp / 16) * ((g.Cout + 15) / 16) < 1024) return false;
+  if (g.alg == 4 && kc >= 3) {
+    if (!quad16_workgroups_enough(g)) return false;
+  } else if (g.alg < 6 && (long long)(g.Tp / 16) * ((g.Cout + 15) / 16) < 1024) {
+    return false;
+  }
   if (g.alg == 8 && quad16_stores_bound(g)) return false;
   const long long fgroups = quad16_filter_count(g) / 16;
   const long long ybytes = 4ll * g.N * g.Cout * g.H * g.W;
@@ -113,6 +137,14 @@ static hipError_t launch_quad16_kc(int out, const Geometry& g, const void* V, co
                   : launch_quad16_impl<ALG, KC, 0, 1>(g, V, f, x_scale, inv_y, y, s, prepare);
 }
 
+// (the store's width chosen in the kernel)
+template <int ALG, int KC>
+static hipError_t launch_quad16_any_width(int out, const Geometry& g, const void* V, const FilterViews& f,
+                                          float x_scale, float inv_y, void* y, hipStream_t s, bool prepare) {
+  return out == 2 ? launch_quad16_impl<ALG, KC, 2, 0>(g, V, f, x_scale, inv_y, y, s, prepare)
+                  : launch_quad16_impl<ALG, KC, 0, 0>(g, V, f, x_scale, inv_y, y, s, prepare);
+}
+
 template <int ALG>
 static hipError_t launch_quad16_alg(int out, const Geometry& g, const void* V, const FilterViews& f,
                                     float x_scale, float inv_y, void* y, hipStream_t s, bool prepare) {
@@ -120,6 +152,15 @@ static hipError_t launch_quad16_alg(int out, const Geometry& g, const void* V, c
     case 1: return launch_quad16_kc<ALG, 1>(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 2: return launch_quad16_kc<ALG, 2>(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 4: return launch_quad16_kc<ALG, 4>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+  }
+  if constexpr (ALG == 4) {
+    switch (g.Cp / 64) {
+      case 3: return launch_quad16_any_width<ALG, 3>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+      case 5: return launch_quad16_any_width<ALG, 5>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+      case 6: return launch_quad16_any_width<ALG, 6>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+      case 7: return launch_quad16_any_width<ALG, 7>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+      case 8: return launch_quad16_any_width<ALG, 8>(out, g, V, f, x_scale, inv_y, y, s, prepare);
+    }
   }
   return hipErrorNotSupported;
 }

@@ -74,7 +74,8 @@ constexpr int kQuad16Waves = 4;
 // V buffers of the fused kernel (groups of four points in LDS) and groups in flight in
 // registers behind them, by channel chunks: the load of a group is issued kVRegs groups
 // before its products
-constexpr int quad16_vbufs(int kc) { return kc >= 8 ? 2 : 3; }
+// (seven chunks: two buffers, 56 KB, leave room for a second workgroup on the compute unit)
+constexpr int quad16_vbufs(int kc) { return kc >= 7 ? 2 : 3; }
 // (four chunks: three groups ahead, 256 channels on 14x14 maps at batch 128 38.2 us per layer
 // against 39.8 with one; eight chunks leave no registers for more than one)
 constexpr int quad16_vregs(int kc) { return kc >= 8 ? 1 : kc == 4 ? 3 : 2; }

@@ -903,6 +903,29 @@ def test_4x4_tiles_on_larger_maps(binding, shape, alg):
     test_46_points_past_the_small_layers(binding, "staged", "staged", shape, alg)
 
 
+QUAD16_WIDE = [  # 46 points, three to eight chunks of channels, where the library chooses the fused path
+    (8, 150, 257, 14, 14),   # three chunks, 40 workgroups; a fifth workgroup of one filter
+    (80, 192, 64, 8, 30),    # pairs per store
+    (640, 129, 40, 7, 7),    # single outputs per store
+    (12, 250, 200, 18, 14),  # four, 60
+    (71, 320, 128, 14, 14),  # five
+    (77, 300, 40, 13, 31),
+    (56, 384, 190, 14, 14),  # six
+    (45, 321, 64, 29, 31),
+    (51, 448, 250, 13, 16),  # seven
+    (45, 512, 250, 14, 14),  # eight: the last tile block whole
+    (91, 449, 128, 9, 31),
+]
+
+
+@pytest.mark.parametrize("shape", QUAD16_WIDE)
+def test_46_points_fused_by_choice(binding, shape):
+    plan = binding.Plan(*shape, alg="4x4_p46", mode="requant", path="auto")
+    assert plan.path == "fused"
+    plan.close()
+    test_46_points_past_the_small_layers(binding, "auto", "quad16", shape)
+
+
 SINGLE16_49 = [  # 49 points in one kernel
     (18, 33, 17, 56, 56),    # 252 workgroups of one chunk: two waves to a filter group
     (256, 9, 40, 14, 14),    # 256: whole images, pairs per store

@@ -338,6 +338,36 @@ def test_single16_forms_of_the_parity_shapes(lib, routes):
             assert routes(layers, column=2) == [few, few, "many", "many"], (alg, cin)
 
 
+@pytest.mark.parametrize("cin,edge,cout,line", [
+    (129, 8, 64, 40), (192, 8, 16, 40), (160, 7, 64, 160), (256, 8, 64, 48), (200, 7, 128, 168), (320, 8, 72, 140),
+    (384, 8, 64, 165), (330, 7, 64, 285), (448, 8, 200, 200), (512, 8, 128, 180), (500, 7, 64, 300)])
+def test_46_points_quad16_on_both_sides_of_its_line(lib, routes, cin, edge, cout, line):
+    """Three to eight chunks of channels: the fused path from a number of workgroups on where its other
+    kernels do not take the chunk count, which stays refused on request; quad16_kernel there in any case."""
+    from paper_2407_02913_amd import binding
+
+    groups = -(-cout // 64)
+    for blocks, here in ((-(-line // groups) - 1, False), (-(-line // groups), True)):
+        shape = (4 * blocks, cin, cout, edge, edge)
+        assert (routes([("fused", "4x4_p46", shape)]) == ["quad16"]) == here, blocks
+        plan = binding.Plan(*shape, alg="4x4_p46", mode="requant", path="auto")
+        odd = -(-cin // 64) in (3, 5, 6, 7)
+        assert plan.path == ("fused" if here or not odd else "staged"), blocks
+        plan.close()
+        if odd:
+            with pytest.raises(binding.SfcError) as e:
+                binding.Plan(*shape, alg="4x4_p46", mode="requant", path="fused")
+            assert e.value.code == 2
+    few = (4 * 600, cin, 39, edge, edge)  # fewer than 5/8 of a workgroup's filters
+    assert (routes([("fused", "4x4_p46", few)]) == ["quad16"]) == (cin <= 320)
+
+
+def test_kernels_of_the_wide_46_point_shapes(lib, routes):
+    import test_gpu_parity as parity
+
+    assert set(routes([("fused", "4x4_p46", shape) for shape in parity.QUAD16_WIDE])) == {"quad16"}
+
+
 def test_kernels_of_the_184_point_shapes(lib, routes):
     import test_gpu_parity as parity
 
