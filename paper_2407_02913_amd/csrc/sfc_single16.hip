@@ -442,7 +442,7 @@ static void fill_input_table(const float* inv_sx, unsigned char* tab) {
     }
 }
 
-// The same for the row form (8x8 to 10x10 patches of the SFC-6 forms, every patch in exact mode): k = 16 i + j.
+// The same for the row form (sfc_input_rows.hip): k = 16 i + j.
 template <int ALG>
 static void fill_rows_table(const float* inv_sx, unsigned char* tab) {
   using Tr = AlgTraits<ALG>;
