@@ -80,6 +80,11 @@ constexpr int quad16_vbufs(int kc) { return kc >= 7 ? 2 : 3; }
 // against 39.8 with one; eight chunks leave no registers for more than one)
 constexpr int quad16_vregs(int kc) { return kc >= 8 ? 1 : kc == 4 ? 3 : 2; }
 
+// filter-operand blocks asked for ahead (SFC-4), where three and five chunks leave registers for more (209 and
+// 228 of them): 184 to 136 channels, seven 31x45 maps, 25.7 us with eight, 25.3; 320 to 192 on 31 20x20 maps 25.8
+// and 25.1; 0.97 to 1.01 of the time over 14 such layers.  Fourteen at four chunks: level (0.99 to 1.006)
+constexpr int quad16_ahead(int kc) { return kc == 3 ? 16 : kc == 5 ? 12 : 8; }
+
 // LDS of the products + output kernel: the V buffers, which the per-wave store staging
 // blocks (16 filters x 16 tiles x 16 outputs, float32 or int8) take over once the last
 // products are done, then the tile table.
@@ -531,7 +536,8 @@ __global__ __launch_bounds__(NW * 64, 2) void quad16_kernel(
   static_assert(M == 4, "tiles of 4 x 4 outputs");
   constexpr int COLS = kOutputColumns + M;
   f4 out[M][M];
-  quad16_stream<ALG, KC, VB>(vbuf, lane, ures, a_wave, dres, d_wave, [] {}, sync,
+  using Ahead = ConstantAhead<Tr::kFamily == 4 ? quad16_ahead(KC) : 8>;
+  quad16_stream<ALG, KC, VB, KC * 1024, Ahead>(vbuf, lane, ures, a_wave, dres, d_wave, [] {}, sync,
                              [&](auto& next) __attribute__((always_inline)) {
                                if constexpr (Tr::kFamily == 4) stream_outputs4<ALG, f4>(next, SettleF4{}, out);
                                else stream_outputs<ALG, f4>(next, SettleF4{}, out);
