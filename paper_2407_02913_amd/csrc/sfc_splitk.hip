@@ -259,7 +259,8 @@ bool splitk_supported(const Geometry& g) {
   // Small layers only (at most two workgroups per compute unit): there it is ahead of the
   // one-pair-per-lane kernel (512 channels on 7x7 maps, batch 64, 4x4 tiles: 27.3 against
   // 30.7 us per layer; 7x7 tiles at batch 256: 67.3 against 74.7), on larger ones level or
-  // behind (4x4 tiles at batch 256: 85 to 91 against 85.9).
+  // behind (4x4 tiles at batch 256: 85 to 91 against 85.9).  With 46 points quad16_kernel goes first, from
+  // its own line on (sfc_quad16.hip).
   if ((long long)(g.Tp / 16) * (fgroups / 2) > 512) return false;
   const long long ybytes = 4ll * g.N * g.Cout * g.H * g.W;
   const long long vbytes = (long long)g.P * g.Tp * g.Cp;
