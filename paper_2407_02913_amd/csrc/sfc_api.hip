@@ -553,9 +553,16 @@ static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
     return SFC_OK;
   }
   int32_t* M = reinterpret_cast<int32_t*>(ws + plan->off_M);
+  float inv_y = plan->inv_y;
+  // (int8 ties as the fused kernel of the layer rounds them: launch_quad16's product of the two scales)
+  if (plan->staged_instead && plan->d.out == SFC_OUT_I8_RELU &&
+      sfc::choose_kernel(SFC_PATH_FUSED, g) == sfc::Kernel::kQuad16) {
+    inv_y *= x_scale;
+    x_scale = 1.0f;
+  }
   for (int f0 = 0; pass > 0 && f0 < g.Cout; f0 += pass) {
     if (sfc::launch_product_gemm_i8(g, V, f.U, M, s, f0, pass) != hipSuccess ||
-        sfc::launch_output_sums(plan->d.out, g, M, f, x_scale, plan->inv_y, y_dev, s, false, f0, pass) != hipSuccess)
+        sfc::launch_output_sums(plan->d.out, g, M, f, x_scale, inv_y, y_dev, s, false, f0, pass) != hipSuccess)
       return SFC_EHIP;
   }
   if (pass > 0) return SFC_OK;
@@ -563,8 +570,7 @@ static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
     if (sfc::launch_product(plan->d.mode, g, V, f.U, M, s) != hipSuccess) return SFC_EHIP;
   }
   if (stage_mask & SFC_STAGE_OUTPUT) {
-    if (sfc::launch_output_transform(plan->d.mode, plan->d.out, g, M, f, x_scale,
-                                     plan->inv_y, y_dev, s) != hipSuccess)
+    if (sfc::launch_output_transform(plan->d.mode, plan->d.out, g, M, f, x_scale, inv_y, y_dev, s) != hipSuccess)
       return SFC_EHIP;
   }
   return SFC_OK;

@@ -41,19 +41,22 @@ static bool quad16_workgroups_enough(const Geometry& g) {
   return (long long)(g.Tp / 16) * groups >= line;
 }
 
+// a wave takes 256 (tile, filter) pairs
+static bool one_wave_per_simd(const Geometry& g) { return (long long)(g.Tp / 16) * ((g.Cout + 15) / 16) >= 1024; }
+
 bool quad16_supported(const Geometry& g) {
   if (g.alg != 4 && g.alg != 5 && g.alg != 8) return false;
   const int kc = g.Cp / 64;
   // Up to four channel chunks (three with 184 points), with 46 points eight.
   if (kc > (g.alg == 4 ? 8 : 4) || (kc == 3 && g.alg == 5)) return false;
-  // A wave takes 256 (tile, filter) pairs: with fewer than one wave per SIMD of the chip the
+  // With fewer than one wave per SIMD of the chip the
   // one-pair-per-lane kernel, whose waves take 64, fills it better.  With 184 points its fourfold
   // matrix work and operand reads outweigh that on most layers (7x7 filters, layer: 16 channels
   // on one 32x32 map 30.3 us against 26.3 here, 128 channels on one 28x28 map 35.2 against 32.1,
   // 256 channels on 14x14 maps at batch 32 67.3 against 59.5), not where quad16_stores_bound.
   if (g.alg == 4 && kc >= 3) {
     if (!quad16_workgroups_enough(g)) return false;
-  } else if (g.alg < 6 && (long long)(g.Tp / 16) * ((g.Cout + 15) / 16) < 1024) {
+  } else if (g.alg < 6 && !one_wave_per_simd(g)) {
     return false;
   }
   if (g.alg == 8 && quad16_stores_bound(g)) return false;
@@ -168,6 +171,14 @@ static hipError_t launch_quad16_alg(int out, const Geometry& g, const void* V, c
 hipError_t launch_quad16(int out, const Geometry& g, const void* V, const FilterViews& f,
                          float x_scale, float inv_y, void* y, hipStream_t s, bool prepare) {
   if (!quad16_supported(g) || out == 1) return hipErrorNotSupported;
+  // int8 outputs at a tie of their rounding: the staged path, the one-pair-per-lane kernel and the split of the
+  // channels scale twice (store_pairs), this kernel up to two chunks once.  From three chunks on it scales twice,
+  // so that a layer's bytes are the same on either side of the lines above; but for four chunks and a wave for
+  // every SIMD, layers that no other kernel takes (1 * (x_scale inv_y): the product again).
+  if (out == 2 && g.alg == 4 && g.Cp == 256 && one_wave_per_simd(g)) {
+    inv_y *= x_scale;
+    x_scale = 1.0f;
+  }
   switch (g.alg) {
     case 4: return launch_quad16_alg<4>(out, g, V, f, x_scale, inv_y, y, s, prepare);
     case 5: return launch_quad16_alg<5>(out, g, V, f, x_scale, inv_y, y, s, prepare);

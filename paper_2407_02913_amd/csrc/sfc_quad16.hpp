@@ -85,6 +85,9 @@ constexpr int quad16_vregs(int kc) { return kc >= 8 ? 1 : kc == 4 ? 3 : 2; }
 // and 25.1; 0.97 to 1.01 of the time over 14 such layers.  Fourteen at four chunks: level (0.99 to 1.006)
 constexpr int quad16_ahead(int kc) { return kc == 3 ? 16 : kc == 5 ? 12 : 8; }
 
+// the int8 outputs take two scales (quad16_store's TWO; launch_quad16 says which two)
+constexpr bool quad16_two_scales(int alg, int kc) { return alg == 4 && kc >= 3; }
+
 // LDS of the products + output kernel: the V buffers, which the per-wave store staging
 // blocks (16 filters x 16 tiles x 16 outputs, float32 or int8) take over once the last
 // products are done, then the tile table.
@@ -310,7 +313,9 @@ __device__ __forceinline__ void quad16_half(const unsigned char* vbuf, int lane,
 // NP, i0: pairs i0 .. i0 + NP - 1 of z alone, filters from 4 kq0 on (a block of 4 NP filters).
 // EV: elements per store instruction, 4 when W is a multiple of 4 (a tile row never crosses
 // the end of an image row), else 2 (W even) or 1.
-template <int ALG, int OUT, int EV, int NP = 4>
+// TWO (OUT = 2): an output takes x_scale and then inv_y, each with a rounding of its own, as
+// store_pairs does; else their product.  The two round a tie of the int8 output differently.
+template <int ALG, int OUT, int EV, int NP = 4, bool TWO = false>
 __device__ __forceinline__ void quad16_store(const f4 (&z)[AlgTraits<ALG>::NC][AlgTraits<ALG>::M],
                                              unsigned char* stage, const int* tile_tab, int lane,
                                              int kq0, float x_scale, float inv_y,
@@ -345,7 +350,7 @@ __device__ __forceinline__ void quad16_store(const f4 (&z)[AlgTraits<ALG>::NC][A
 #pragma unroll
         for (int o2 = 0; o2 < M; ++o2) {
           // next layer's activation: ReLU, round half to even, clamp to [0, 127]
-          float t = __fmaf_rn(out[o2], act, kMagic);
+          float t = TWO ? __fmaf_rn(out[o2] * x_scale, inv_y, kMagic) : __fmaf_rn(out[o2], act, kMagic);
           t = __builtin_amdgcn_fmed3f(t, kMagic, kMagic + 127.0f);
           b[o2] = __float_as_uint(t);
         }
@@ -543,12 +548,13 @@ __global__ __launch_bounds__(NW * 64, 2) void quad16_kernel(
                                else stream_outputs<ALG, f4>(next, SettleF4{}, out);
                              });
   __syncthreads();  // the staging blocks take the place of the V buffers
+  constexpr bool TWO = quad16_two_scales(ALG, KC);
   if constexpr (EV != 0) {
-    quad16_store<COLS, OUT, EV>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+    quad16_store<COLS, OUT, EV, 4, TWO>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
   } else {  // (the width of a store is chosen here, the products are not compiled once for each)
-    if (g.W % 4 == 0) quad16_store<COLS, OUT, 4>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
-    else if (g.W % 2 == 0) quad16_store<COLS, OUT, 2>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
-    else quad16_store<COLS, OUT, 1>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+    if (g.W % 4 == 0) quad16_store<COLS, OUT, 4, 4, TWO>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+    else if (g.W % 2 == 0) quad16_store<COLS, OUT, 2, 4, TWO>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
+    else quad16_store<COLS, OUT, 1, 4, TWO>(out, stage, tile_tab, lane, fg * 4, x_scale, inv_y, yres, g);
   }
 }
 

@@ -926,6 +926,62 @@ def test_46_points_fused_by_choice(binding, shape):
     test_46_points_past_the_small_layers(binding, "auto", "quad16", shape)
 
 
+TIE_SHAPES = [  # (N, Cin, Cout, H, W), whether an int8 output is scaled once
+    ((203, 33, 130, 12, 12), True),    # quad16_kernel: one chunk
+    ((115, 193, 136, 14, 14), True),   # four, a wave for every SIMD
+    ((16, 256, 256, 14, 14), False),   # four, fewer
+    ((12, 250, 200, 18, 14), False),
+    ((41, 200, 72, 11, 7), False),     # the one-pair-per-lane kernel
+    ((40, 192, 64, 16, 16), False),    # three (whole images)
+    ((71, 320, 128, 14, 14), False),
+    ((56, 384, 190, 14, 14), False),
+    ((51, 448, 250, 13, 16), False),
+    ((45, 512, 250, 14, 14), False),
+    ((64, 512, 128, 7, 7), False),     # the split of the channels
+]
+
+
+@pytest.mark.parametrize("shape,once", TIE_SHAPES)
+def test_int8_ties_do_not_depend_on_the_kernel(binding, shape, once):
+    """Every sixth output lies on a tie of its rounding but for the rounding of the scales themselves: one after
+    the other they round some of those ties otherwise than their product, whichever kernel a layer runs."""
+    rng = np.random.default_rng(4300 + sum(shape))
+    n, c, k, h, w = shape
+    x = rng.integers(0, 2, size=(n, c, h, w)).astype(np.int8)
+    wt = rng.integers(-1, 2, size=(k, c, 3, 3)).astype(np.int8)
+    p = oracle.multiplications_per_tile("4x4_p46")
+    xs, y_scale = np.float32(0.05), np.float32(0.3)
+    print("case ties", shape, flush=True)
+    y8 = binding.conv2d(x, wt, float(xs), np.float32([1.0]), mode="requant", alg="4x4_p46", path="auto", out="i8",
+                        sx=np.ones(p, np.float32), sw=np.ones((p, k), np.float32), y_scale=float(y_scale))
+    sums = oracle.direct_conv(x, wt)  # (no transform value leaves the range of an int8)
+    inv_y = np.float32(1.0) / y_scale
+    if once:
+        scaled = sums * np.float64(xs * inv_y)
+    else:
+        scaled = (sums.astype(np.float32) * xs) * np.float64(inv_y)
+    assert np.array_equal(y8, np.clip(np.rint(scaled), 0, 127).astype(np.int8))
+
+
+@pytest.mark.parametrize("shape", [(4, 128, 64, 21, 24), (2, 256, 66, 28, 28), (9, 30, 64, 8, 8)])
+def test_int8_ties_of_small_7x7_layers(binding, shape):
+    """A layer that the library sends through M has the bytes of the fused kernel that takes it on request."""
+    alg = "4x4_7x7_p184"
+    rng = np.random.default_rng(4400 + sum(shape))
+    n, c, k, h, w = shape
+    x = rng.integers(0, 2, size=(n, c, h, w)).astype(np.int8)
+    wt = rng.integers(-1, 2, size=(k, c, 7, 7)).astype(np.int8)
+    p = oracle.multiplications_per_tile(alg)
+    plan = binding.Plan(*shape, alg=alg, mode="requant", path="auto")
+    assert plan.path == "staged"
+    plan.close()
+    print("case ties 7x7", shape, flush=True)
+    y8 = [binding.conv2d(x, wt, 0.02, np.float32([1.0]), mode="requant", alg=alg, path=path, out="i8",
+                         sx=np.ones(p, np.float32), sw=np.ones((p, k), np.float32), y_scale=0.12)
+          for path in ("auto", "fused")]
+    assert np.array_equal(*y8)
+
+
 SINGLE16_49 = [  # 49 points in one kernel
     (18, 33, 17, 56, 56),    # 252 workgroups of one chunk: two waves to a filter group
     (256, 9, 40, 14, 14),    # 256: whole images, pairs per store
