@@ -134,6 +134,32 @@ def test_requant_mode_taps_bit_exact_and_output_close(binding, shape, alg):
     assert rel_err(y, y_ref) <= F32_TOL
 
 
+@pytest.mark.parametrize("alg", ALGS_STAGED + ["6x6_5x5_p184", "6x6_5x5_p196", "4x4_7x7_p184", "4x4_7x7_p196"])
+@pytest.mark.parametrize("shape", [(1, 3, 4, 1, 1), (5, 2, 4, 1, 1), (1, 5, 3, 2, 1), (2, 66, 2, 1, 2), (3, 1, 2, 1, 1), (1, 4, 2, 1, 3)])
+def test_maps_of_a_few_samples(binding, shape, alg):
+    """A dword at the end of the tensor holds several channels, or images."""
+    r = binding.KERNEL_SIZE[alg]
+    x, w, xs, ws = uniform_case(shape, 4600 + sum(shape), r=r)
+    print("case few samples", shape, alg, flush=True)
+    acc_ref, taps_ref = oracle.conv_exact(x, w, alg, return_taps=True)
+    acc, taps = binding.conv2d(x, w, xs, ws, mode="exact", alg=alg, out="i32", return_taps=True)
+    assert np.array_equal(taps["V"].astype(np.int64), taps_ref["V"])
+    assert np.array_equal(acc.astype(np.int64), acc_ref)
+    sx = oracle.calibrate_act_scales(x, alg)
+    sw = oracle.calibrate_filter_scales(w, alg)
+    y_ref, taps_ref = oracle.conv_requant(x, w, sx, sw, xs, ws, alg, return_taps=True)
+    y_ref_max = max(np.abs(y_ref).max(), 1e-30)
+    for path in ("staged", "fused") + (("single",) if r == 3 else ()):
+        try:
+            y, taps = binding.conv2d(x, w, xs, ws, mode="requant", alg=alg, path=path, sx=sx, sw=sw, return_taps=True)
+        except binding.SfcError as e:
+            assert path == "single" and shape[1] > 64 and e.code == 2
+            continue
+        if path != "single":
+            assert np.array_equal(taps["V"].astype(np.int64), taps_ref["V"]), path
+        assert np.abs(y.astype(np.float64) - y_ref).max() <= F32_TOL * y_ref_max, path
+
+
 IMAGE_SHAPES = [  # small feature maps (a patch within 128 bytes of a plane): the input transform reads planes as they lie
     (1, 3, 4, 7, 7),      # 147 bytes: the last dwords of the tensor are fetched byte by byte
     (5, 70, 24, 7, 7),    # channels padded to 128, the last 58 zero
