@@ -155,6 +155,13 @@ static hipError_t launch_input_waves_alg(const Geometry& g, const WaveInputPlan&
                          : launch(input_transform_waves_kernel<ALG, 8, 1>);
 }
 
+InputKernel choose_input_kernel(bool exact, const Geometry& g) {
+  WaveInputPlan wp;
+  if (!exact && image_input_supported(g)) return InputKernel::kImage;
+  if (!exact && make_wave_input_plan(g, &wp)) return InputKernel::kWaves;
+  return input_rows_supported(g, exact) ? InputKernel::kRows : InputKernel::kGeneric;
+}
+
 unsigned rows_table_offset(const Geometry& g) {
   WaveInputPlan wp;
   if (image_input_supported(g) || make_wave_input_plan(g, &wp)) return ~0u;

@@ -321,11 +321,12 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
   tr.whole = tr.ipw = tr.cs = 0;
   tr.th_magic = ((1ull << 32) + (unsigned long long)g.th - 1) / (unsigned long long)g.th;
   constexpr unsigned kBlocks = (unsigned)Form::NW * (unsigned)Form::kBlockBytes;
-  constexpr unsigned kBudget = 80u * 1024u;  // two workgroups to a compute unit at least
   // (4x4 tiles, int8: a wave owns every position of its tile columns, with fewer than four tiles some waves
   // would have none)
   constexpr int kLeast = !EXACT && Form::PG == 1 ? Form::TG : 1;
   bool found = false;
+  // (two workgroups to a compute unit; one where the waves' blocks alone exceed that, 7x7 tiles and 196 points in int16)
+  for (unsigned budget = 80u * 1024u; !found && budget <= 160u * 1024u; budget *= 2)
   for (int tiles = 8; tiles >= kLeast; tiles >>= 1) {
     RowsPlan c = *rp;
     c.tr.chunks = (g.tw + tiles - 1) / tiles;
@@ -341,7 +342,7 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
     if (c.tr.S < 1) c.tr.S = 1;
     auto bytes = [&](int S) { return (((unsigned)S * 64u * c.cs + 32u + 15u) & ~15u) + kBlocks; };
     while (c.tr.S > 1 && bytes(c.tr.S) > 40u * 1024u) --c.tr.S;
-    if (bytes(c.tr.S) > kBudget) continue;
+    if (bytes(c.tr.S) > budget) continue;
     c.tr.ntiles = c.tr.S * c.tr.tlw;
     c.blk_off = bytes(c.tr.S) - kBlocks;
     c.lds_bytes = bytes(c.tr.S);
@@ -362,6 +363,27 @@ static hipError_t launch_rows_alg(const Geometry& g, const int8_t* x, void* V, c
   const dim3 grid(tile_rect_groups(g, rp.tr) * (unsigned)(g.Cp / 64));
   hipLaunchKernelGGL(kernel, grid, dim3(RowsForm<ALG, EXACT>::NW * 64), rp.lds_bytes, s, x, V, tab, g, rp);
   return hipGetLastError();
+}
+
+bool input_rows_supported(const Geometry& g, bool exact) {
+  RowsPlan rp{};
+  auto plan = [&](auto alg) {
+    constexpr int ALG = decltype(alg)::value;
+    return exact ? make_rows_plan<ALG, true>(g, &rp) : make_rows_plan<ALG, false>(g, &rp);
+  };
+  switch (g.alg) {
+    case 0: return plan(std::integral_constant<int, 0>{});
+    case 1: return plan(std::integral_constant<int, 1>{});
+    case 2: return plan(std::integral_constant<int, 2>{});
+    case 3: return plan(std::integral_constant<int, 3>{});
+    case 4: return plan(std::integral_constant<int, 4>{});
+    case 5: return plan(std::integral_constant<int, 5>{});
+    case 6: return plan(std::integral_constant<int, 6>{});
+    case 7: return plan(std::integral_constant<int, 7>{});
+    case 8: return plan(std::integral_constant<int, 8>{});
+    case 9: return plan(std::integral_constant<int, 9>{});
+  }
+  return false;
 }
 
 hipError_t launch_input_rows(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab, hipStream_t s,

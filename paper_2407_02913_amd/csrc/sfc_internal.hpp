@@ -69,6 +69,15 @@ hipError_t launch_input_image(const Geometry& g, const int8_t* x, void* V, const
 // every form elsewhere, from the table at rows_table_offset (sfc_input_rows.hip)
 hipError_t launch_input_rows(const Geometry& g, const int8_t* x, void* V, const unsigned char* tab,
                              hipStream_t s, bool prepare = false);
+bool input_rows_supported(const Geometry& g, bool exact);
+// The kernel that transforms a layer's input, exact or requantized.
+enum class InputKernel {
+  kImage,    // sfc_input_image.hip
+  kWaves,    // sfc_input.hip
+  kRows,     // sfc_input_rows.hip
+  kGeneric,  // input_transform_kernel (sfc_kernels.hip)
+};
+InputKernel choose_input_kernel(bool exact, const Geometry& g);
 // exact mode (input transform: sfc_input_rows.hip; sfc_exact.hip); hipErrorNotSupported beyond the 32-bit offset limits, and of the
 // output transform where output_exact_ahead does not hold: the generic kernels of
 // sfc_kernels.hip take over.  tab: kRowsTabBytes at FilterViews::input_tab

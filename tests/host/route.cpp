@@ -1,7 +1,7 @@
 // Which kernels the library picks: reads layers "path alg N Cin Cout H W" (path and alg as in
 // include/sfc.h) and prints the name of the product kernel of each, for the exact mode of the
-// layer which output transform is ahead, and the form of single16_kernel that it would take.  Linked against the built library, whose own rules it
-// asks.
+// layer which output transform is ahead, the form of single16_kernel that it would take, and the kernels of its
+// input transform, requantized and exact.  Linked against the built library, whose own rules it asks.
 #include <cstdio>
 
 #include "../../paper_2407_02913_amd/csrc/sfc_internal.hpp"
@@ -10,6 +10,7 @@
 int main() {
   static const char* const kNames[] = {"staged",      "fused_quad", "quad16",     "splitk",      "product_small",
                                        "single_conv", "single16",   "single16k", "single_small", "pair16"};
+  static const char* const kInputs[] = {"image", "waves", "rows", "generic"};
   int path;
   sfc::Geometry g{};
   while (std::scanf("%d %d %d %d %d %d %d", &path, &g.alg, &g.N, &g.Cin, &g.Cout, &g.H, &g.W) == 7) {
@@ -23,8 +24,9 @@ int main() {
     g.Kp = (g.Cout + 15) / 16 * 16;
     g.P = sfc::alg_points(g.alg);
     g.qmax = 127.0f;
-    std::printf("%s %s %s\n", kNames[(int)sfc::choose_kernel(path, g)], sfc::output_exact_ahead(g) ? "waves" : "threads",
-                sfc::single16_few_workgroups(g) ? "few" : "many");
+    std::printf("%s %s %s %s %s\n", kNames[(int)sfc::choose_kernel(path, g)], sfc::output_exact_ahead(g) ? "waves" : "threads",
+                sfc::single16_few_workgroups(g) ? "few" : "many", kInputs[(int)sfc::choose_input_kernel(false, g)],
+                kInputs[(int)sfc::choose_input_kernel(true, g)]);
   }
   return 0;
 }

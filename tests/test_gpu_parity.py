@@ -467,6 +467,17 @@ def test_row_form_rectangles(binding, shape, alg):
     assert rel_err(y, y_ref) <= F32_TOL
 
 
+@pytest.mark.parametrize("alg", ["7x7_p132", "7x7_p144", "6x6_5x5_p196", "6x6_p100", "4x4_p49"])
+@pytest.mark.parametrize("shape", [(2, 65, 2, 31, 45), (9, 3, 2, 7, 7), (1, 2, 3, 224, 100)])
+def test_row_form_exact(binding, shape, alg):
+    x, w, xs, ws = uniform_case(shape, 2000 + len(alg) + sum(shape), r=binding.KERNEL_SIZE[alg])
+    print("case rows exact", shape, alg, flush=True)
+    acc_ref, taps_ref = oracle.conv_exact(x, w, alg, return_taps=True)
+    acc, taps = binding.conv2d(x, w, xs, ws, mode="exact", alg=alg, out="i32", return_taps=True)
+    assert np.array_equal(taps["V"].astype(np.int64), taps_ref["V"])
+    assert np.array_equal(acc.astype(np.int64), acc_ref)
+
+
 FULL = ["resnet56", "resnet28", "resnet14", "resnet7"]
 
 

@@ -287,7 +287,8 @@ def test_sfc4_output_transforms_round_alike(kernel_maps, alg_id):
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
     """(path, algorithm, shape) of layers -> the product kernels the built library picks for them, or
-    (column 1) the output transforms of their exact mode, or (2) the forms of single16_kernel."""
+    (column 1) the output transforms of their exact mode, (2) the forms of single16_kernel, or the input
+    kernels, (3) requantized and (4) exact."""
     from paper_2407_02913_amd import binding
 
     exe = tmp_path_factory.mktemp("host") / "route"
@@ -426,6 +427,20 @@ def test_output_transforms_of_the_exact_shapes(lib, routes):
             layers = [("staged", alg, (images - i, 1, cout, 4, width)) for i in (0, 1) if images > i]
             assert routes(layers, column=1) == ["waves", "threads"][: len(layers)], (alg, cout)
         assert routes([("staged", alg, (200000, 1, 8, 4, 4))], column=1) == ["threads"]
+
+
+def test_row_form_takes_every_algorithm(lib, routes):
+    """The row-form input transform, whose GPU test compares V: exact mode on any map, requantized mode
+    outside small ones."""
+    import test_gpu_parity as parity
+
+    algs = parity.ALGS_STAGED + parity.ALGS_5X5
+    large = parity.ROWS_SHAPES[1:] + [(2, 64, 3, 224, 224), (1, 512, 3, 40, 1024)]
+    small = parity.ROWS_SHAPES[:1] + [(256, 64, 3, 7, 7), (1, 1, 1, 1, 1), (64, 256, 3, 14, 14)]
+    assert set(routes([("staged", alg, shape) for alg in algs for shape in large + small], column=4)) == {"rows"}
+    assert set(routes([("staged", alg, shape) for alg in algs for shape in large], column=3)) == {"rows"}
+    assert routes([("staged", alg, (64, 256, 3, 14, 14)) for alg in ("6x6_p88", "4x4_p46", "4x4_7x7_p184")],
+                  column=3) == ["image", "waves", "rows"]
 
 
 def test_every_kernel_choice_fits_the_filter_layout(lib, routes):
