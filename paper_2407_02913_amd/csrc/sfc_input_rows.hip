@@ -13,17 +13,18 @@
 // clocks of every SIMD are vector instructions, 15 of 20 the rounding of four values, 14.6 k matrix
 // instructions) and, while V is larger than the caches, its way to memory.  With a wave to a tile every
 // wave read the whole coefficient table (36 KB at 184 positions) and its rounding waited for the matrix
-// instructions just before it.  Staged rows are as long as the rectangle needs (64 bytes each before),
-// so that four workgroups share a compute unit; and a wave's tiles all start at the same byte of a
-// dword, so the coefficients are shifted once instead of every patch row.  us before and after, V 74, 37 and (int16) 36 MB: 7x7
-// filters on that layer 39.5 -> 28.8, 5x5 filters 21.2 -> 19.3, exact mode, 64 channels on 56x56 maps,
-// batch 32, 13.8 -> 13.6; layers drawn over the range of the 5x5 and 7x7 filters 0.93 of the time (60, 0.80 to
-// 1.06), of exact mode 0.97 (40, 0.88 to 1.07).  Two, three and six position groups for 184 points instead of
-// four: 35.0, 30.4 and 34.5 us for the first layer.
+// instructions just before it.  Staged rows are as long as the rectangle needs (64 bytes each before): 20 to 40 KB
+// to a workgroup of four waves, three or four of which share a compute unit; one of twelve waves, 64 to 86 KB, with 7x7 tiles.  A
+// wave's tiles all start at the same byte of a dword, so the coefficients are shifted once instead of every patch
+// row.  us before and after, V 74, 37 and (int16) 36 MB: 7x7 filters on that layer 39.5 -> 28.8, 5x5 filters 21.2 -> 19.3,
+// exact mode, 64 channels on 56x56 maps, batch 32, 13.8 -> 13.6.  Two, three and six position groups for 184 points instead
+// of four: 35.0, 30.4 and 34.5 us for the first layer.
 // The SFC-4 forms had a wave to a tile, 64-byte rows staged whatever the width (a byte at a time where 4 does
 // not divide it) and V collected in LDS: 192 to 64 channels on 107 35x35 maps, three kernels, 349 -> 137 us, 350 to
-// 40 on 256 53x25 maps 613 -> 485, 256 to 256 on 16 56x56 maps 56.3 -> 54.4; over 138 layers of more than 128 channels
-// 0.39 to 1.05 of the time, 0.93 in the middle (above 1.02 with 350 to 650 tiles).
+// 40 on 256 53x25 maps 613 -> 485, 256 to 256 on 16 56x56 maps 56.3 -> 54.4; over 60 layers of more than 128 channels with
+// 350 to 650 tiles 0.48 to 1.04 of the time, 0.93 in the middle.
+#include <algorithm>
+
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
 #include "sfc_mfma_input.hpp"
@@ -36,7 +37,14 @@ template <int ALG, bool EXACT>
 struct RowsForm {
   using Tr = AlgTraits<ALG>;
   static constexpr int NPB = (Order<ALG>::PP + 15) / 16;  // blocks of 16 positions
-  static constexpr int PG = NPB <= 4 ? 1 : NPB <= 7 ? 2 : NPB <= 9 ? 3 : 4;  // position groups
+  // Position groups.  More of them, fewer blocks and registers to a wave and more waves to a workgroup; a last group that
+  // is not full works for nothing.  The kernel's time over 16 layers, geometric mean: 100 points with four groups
+  // 0.87 of that with two (int8 and int16), 88 points with three 0.95 in int8 (int16 0.94, but 12.6 for 11.8 us
+  // where V of 64 channels on 56x56 maps, batch 32, is written), 196 points in int16 with five and (4x4 tiles) seven
+  // 0.94 and 0.89 of that with four; in int8 1.04 and 0.97, 0.8 to 1.2.  52 positions with two 0.93, four 1.0;
+  // 48 with two 1.02; 184 points with five and six 1.04 to 1.19.
+  static constexpr int PG = NPB <= 3 ? 1 : NPB <= 4 ? 2 : NPB <= 6 ? (EXACT ? 2 : 3) : NPB <= 7 ? 4 : NPB <= 9 ? 3
+                            : NPB <= 12 || !EXACT ? 4 : Tr::M == 6 ? 5 : 7;
   static constexpr int BPW = (NPB + PG - 1) / PG;                           // blocks of a wave
   // tile groups: tile columns j, j + TG, ... of a rectangle, whose patches start at the same byte of a
   // dword (tile edges 4, 6, 7: every, every second, every fourth column)
@@ -307,9 +315,15 @@ __global__ __launch_bounds__((RowsForm<ALG, EXACT>::NW * 64), 4) void input_rows
 
 // ---------------------------------------------------------------------------------------
 
-// Tiles of a rectangle: eight where the layer has workgroups enough, fewer where it has not (a
-// workgroup's time is the staging plus so many tiles).  Four everywhere: 7x7 filters on the layer
-// above 33.7 us, 5x5 23.1; up to sixteen: the same as eight.
+// The rectangle of a workgroup.  What a layer takes goes by rounds: compute units times the workgroups that share
+// one are served at a time, and a workgroup costs its staging and so many tiles.  Of rectangles of up to eight, four, two
+// and one tiles, as many strips as fit in 40, 80 or 160 KB of LDS, the one with the least of
+//   6 rounds + tiles of a compute unit
+// is taken; at a tie more tiles (four, where a wave takes every tile of its workgroup), then less LDS.  The kernel alone
+// against one wave to a tile, geometric mean over 16 layers of every algorithm, int8 and int16 (320): 0.87; eight tiles,
+// else four, two, one until there are 512 workgroups: 1.00 (272 that had a plan).  Of the fixed choices the rule misses
+// the best by 1 % in the mean.  Left behind, layers with many tiles: 7x7 tiles in int8, 64 channels on 56x56 maps, batch 32,
+// 10.0 -> 11.6 us (sixteen 29x31 maps of 70 channels 12.6 -> 9.6), 196 points of the 5x5 filters in int16 22.5 -> 27.4.
 template <int ALG, bool EXACT>
 static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
   using Form = RowsForm<ALG, EXACT>;
@@ -317,18 +331,15 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
   const long long xb = (long long)g.N * g.Cin * g.H * g.W, vb = (long long)g.P * g.Tp * g.Cp;
   if (xb >= (1ll << 31) || (!EXACT && vb >= (1ll << 31))) return false;  // 32-bit offsets
   if ((long long)g.strips * g.th >= (1ll << 32)) return false;  // strip_image's reciprocal
-  TileRect& tr = rp->tr;
-  tr.whole = tr.ipw = tr.cs = 0;
-  tr.th_magic = ((1ull << 32) + (unsigned long long)g.th - 1) / (unsigned long long)g.th;
-  constexpr unsigned kBlocks = (unsigned)Form::NW * (unsigned)Form::kBlockBytes;
-  // (4x4 tiles, int8: a wave owns every position of its tile columns, with fewer than four tiles some waves
+  constexpr unsigned kBlocks = (unsigned)Form::NW * (unsigned)Form::kBlockBytes, kLds = 160u * 1024u;
+  constexpr int kUnits = 256, kWaves = 16;  // compute units, waves that share one (128 registers)
+  RowsPlan c{};
+  c.tr.th_magic = ((1ull << 32) + (unsigned long long)g.th - 1) / (unsigned long long)g.th;
+  long long best = -1;
+  // (4x4 tiles, 46 points: a wave owns every position of its tile columns, with fewer than four tiles some waves
   // would have none)
-  constexpr int kLeast = !EXACT && Form::PG == 1 ? Form::TG : 1;
-  bool found = false;
-  // (two workgroups to a compute unit; one where the waves' blocks alone exceed that, 7x7 tiles and 196 points in int16)
-  for (unsigned budget = 80u * 1024u; !found && budget <= 160u * 1024u; budget *= 2)
+  constexpr int kLeast = Form::PG == 1 ? Form::TG : 1;
   for (int tiles = 8; tiles >= kLeast; tiles >>= 1) {
-    RowsPlan c = *rp;
     c.tr.chunks = (g.tw + tiles - 1) / tiles;
     c.tr.tlw = (g.tw + c.tr.chunks - 1) / c.tr.chunks;
     const int h = (c.tr.chunks > 1 && (M * c.tr.tlw) % 4 != 0 ? 2 + M % 2 : 0) + 4 - PAD;
@@ -337,20 +348,26 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
     c.ndw = (h + M * c.tr.tlw + R - 1 + 3) / 4 | 1;
     c.rcp_ndw = (65536u + (unsigned)c.ndw - 1u) / (unsigned)c.ndw;
     c.cs = 16u * ((unsigned)(NI * c.ndw + 3) / 4u | 1u);
-    c.tr.S = tiles / c.tr.tlw;
-    if (c.tr.S > g.strips) c.tr.S = g.strips;
-    if (c.tr.S < 1) c.tr.S = 1;
     auto bytes = [&](int S) { return (((unsigned)S * 64u * c.cs + 32u + 15u) & ~15u) + kBlocks; };
-    while (c.tr.S > 1 && bytes(c.tr.S) > 40u * 1024u) --c.tr.S;
-    if (bytes(c.tr.S) > budget) continue;
-    c.tr.ntiles = c.tr.S * c.tr.tlw;
-    c.blk_off = bytes(c.tr.S) - kBlocks;
-    c.lds_bytes = bytes(c.tr.S);
-    *rp = c;
-    found = true;
-    if ((long long)tile_rect_groups(g, c.tr) * (g.Cp / 64) >= 512) break;
+    const int strips = std::max(1, std::min(tiles / c.tr.tlw, g.strips));
+    c.tr.S = 0;
+    for (unsigned most = kLds / 4; most <= kLds && c.tr.S < strips; most *= 2) {
+      c.tr.S = strips;
+      while (c.tr.S > 1 && bytes(c.tr.S) > most) --c.tr.S;
+      c.tr.ntiles = c.tr.S * c.tr.tlw;
+      c.lds_bytes = bytes(c.tr.S);
+      c.blk_off = c.lds_bytes - kBlocks;
+      if (c.lds_bytes > kLds) continue;
+      const long long of_unit = ((long long)tile_rect_groups(g, c.tr) * (g.Cp / 64) + kUnits - 1) / kUnits;
+      const int shared = std::max(1, std::min((int)(kLds / c.lds_bytes), kWaves / Form::NW));
+      const long long cost = 6 * ((of_unit + shared - 1) / shared) + of_unit * c.tr.ntiles;
+      if (best < 0 || cost < best || (cost == best && Form::TG == 1 && tiles == 4)) {
+        best = cost;
+        *rp = c;
+      }
+    }
   }
-  return found;
+  return best >= 0;
 }
 
 template <int ALG, bool EXACT>
