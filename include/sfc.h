@@ -241,8 +241,9 @@ sfc_status sfc_conv2d_nchw(const sfc_plan_t* plan, const int8_t* x_dev, float x_
  * is part of the library's code object, one copy per GPU, held until the process ends.  The
  * call allocates and frees nothing.  Plans whose workspace is larger are refused with
  * SFC_EWORKSPACE before any launch, except where sfc_plan chose SFC_PATH_STAGED for a layer that
- * SFC_PATH_FUSED takes: its products and output transform then run in passes of as many filters as
- * fit beside V.  Every call on a GPU shares that GPU's buffer: calls that
+ * SFC_PATH_FUSED takes and V fits: its products and output transform then run in two or three passes over
+ * the filters, or as the fused kernel, whose filter operand such a plan's filter buffer holds as
+ * well (sfc_plan_sizes).  Every call on a GPU shares that GPU's buffer: calls that
  * overlap on one GPU (different streams, or threads) race; calls queued on one stream do
  * not.  V (and M) of the previous call are overwritten, nothing needs clearing. */
 #define SFC_STATIC_WORKSPACE_BYTES ((size_t)32 << 20)

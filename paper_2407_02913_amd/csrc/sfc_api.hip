@@ -1,6 +1,7 @@
 // C ABI of the SFC library: plans, argument checks, buffer layout, stage sequencing.
 // Every numeric step runs in the kernels; this file only validates, lays out buffers and
 // launches.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -15,13 +16,20 @@
 using sfc::FilterViews;
 using sfc::Geometry;
 
+// The filter operand as a product kernel reads it, and its dequantization factors.
+struct Regrouped {
+  sfc::Kernel kernel;  // which kernel, and with it the layout of both
+  int filters;         // filters covered by the operand (0: none)
+  int dq_filters;      // ... by the factors (0: none)
+  size_t off_dq, off_U;
+};
+
 struct sfc_plan_s {
   sfc_conv_desc d;
   Geometry g;
   int esz;  // bytes per transform-domain operand: 2 exact, 1 requantized
   // filter buffer layout (byte offsets)
-  size_t off_U, off_dequant, off_inv_sw, off_inv_sx, off_wscale, off_input_tab, off_dq_single, off_U_single,
-      filter_bytes;
+  size_t off_U, off_dequant, off_inv_sw, off_inv_sx, off_wscale, off_input_tab, off_tables_end, filter_bytes;
   // workspace layout
   size_t off_V, off_M, workspace_bytes;
   std::vector<float> sx, sw;  // [P], [P][Cout]
@@ -29,10 +37,12 @@ struct sfc_plan_s {
   std::vector<float> staging;  // host image of the float tables of the filter buffer
   void* filter_dev;
   bool filter_ready;
-  bool staged_instead;  // the library's choice of the staged path for a layer that the fused path takes
-  int quad_filters;  // filters covered by the regrouped filter operand (0: none)
-  int dq_filters;    // filters in the [filter][processing position] dequantization table (0: none)
-  sfc::Kernel kernel;  // fused and single paths: what runs, and with it the filter operand's layout
+  Regrouped op;     // of the plan's path (staged: the factors alone)
+  // The library's choice of the staged path for a layer that the fused path takes: the kernel of the latter
+  // (kStaged: no such choice).  Where V and M exceed the static workspace, a call from there runs the products in
+  // passes of so many filters, or (0) that kernel, whose operand the plan then holds as well.
+  Regrouped fused;
+  int static_pass;
   float inv_y;  // 1 / output scale (SFC_OUT_I8_RELU), 0: not set
 };
 
@@ -66,7 +76,7 @@ void* static_workspace() {
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-FilterViews views(const sfc_plan_s* p, void* filter_dev) {
+FilterViews views(const sfc_plan_s* p, const Regrouped& op, void* filter_dev) {
   char* b = static_cast<char*>(filter_dev);
   FilterViews f;
   f.U = b + p->off_U;
@@ -75,9 +85,56 @@ FilterViews views(const sfc_plan_s* p, void* filter_dev) {
   f.inv_sx = reinterpret_cast<float*>(b + p->off_inv_sx);
   f.wscale = reinterpret_cast<float*>(b + p->off_wscale);
   f.input_tab = reinterpret_cast<unsigned char*>(b + p->off_input_tab);
-  f.dequant_single = reinterpret_cast<float*>(b + p->off_dq_single);
-  f.U_single = b + p->off_U_single;
+  f.dequant_single = reinterpret_cast<float*>(b + op.off_dq);
+  f.U_single = b + op.off_U;
   return f;
+}
+
+// filters covered by a kernel's regrouped operand
+int regrouped_filters(sfc::Kernel kernel, const Geometry& g) {
+  switch (kernel) {
+    case sfc::Kernel::kStaged: return 0;
+    case sfc::Kernel::kFusedQuad: return sfc::quad_filter_count(g);
+    case sfc::Kernel::kQuad16: return sfc::quad16_filter_count(g);
+    case sfc::Kernel::kPair16: return sfc::pair16_filter_count(g);
+    case sfc::Kernel::kSplitK: return sfc::splitk_filter_count(g);
+    case sfc::Kernel::kProductSmall: return sfc::product_small_filter_count(g);
+    case sfc::Kernel::kSingleConv: return (g.Cout + 63) / 64 * 64;
+    case sfc::Kernel::kSingle16:
+    case sfc::Kernel::kSingle16K:
+    case sfc::Kernel::kSingleSmall: return g.Kp;
+  }
+  return 0;
+}
+
+// The factors of a kernel from those of the points, dequant[p][k].  pt: canonical points by processing position.
+void regroup_factors(sfc::Kernel kernel, const Geometry& g, const std::vector<int>& pt, const float* dequant, float* dqs) {
+  const int pp = (int)pt.size();
+  if (sfc::groups_of_16(kernel)) {
+    // [group of 16 filters][processing position][lane quarter q][i]: filter 16*fg + 4*i + q
+    for (int k = 0; k < g.Cout; ++k) {
+      const int fg = k >> 4, i = (k & 15) >> 2, q = k & 3;
+      for (int j = 0; j < pp; ++j)
+        dqs[((size_t)fg * pp + j) * 16 + 4 * q + i] = pt[j] < 0 ? 0.0f : dequant[(size_t)pt[j] * g.Kp + k];
+    }
+  } else if (kernel == sfc::Kernel::kPair16) {
+    // [group of 8 filters][processing position][lane quarter q][i]: filter 8*fg + 4*i + q
+    for (int k = 0; k < g.Cout; ++k)
+      for (int j = 0; j < pp; ++j)
+        dqs[((size_t)(k >> 3) * pp + j) * 8 + 2 * (k & 3) + ((k & 7) >> 2)] = dequant[(size_t)pt[j] * g.Kp + k];
+  } else {
+    // [filter][processing position]; filters beyond Cout stay zero
+    for (int k = 0; k < g.Cout; ++k)
+      for (int j = 0; j < pp; ++j)
+        dqs[(size_t)k * pp + j] = pt[j] < 0 ? 0.0f : dequant[(size_t)pt[j] * g.Kp + k];
+  }
+}
+
+hipError_t launch_repack(const Regrouped& op, const Geometry& g, const FilterViews& f, hipStream_t s) {
+  if (op.filters == 0) return hipSuccess;
+  if (op.kernel == sfc::Kernel::kPair16) return sfc::launch_repack_filter8(g, op.filters, f.U, f.U_single, s);
+  return sfc::groups_of_16(op.kernel) ? sfc::launch_repack_filter16(g, op.filters, f.U, f.U_single, s)
+                                      : sfc::launch_repack_filter(g, op.filters, f.U, f.U_single, s);
 }
 
 bool alg_is_7x7(int alg) { return alg == SFC_ALG_7X7_P132 || alg == SFC_ALG_7X7_P144; }
@@ -131,13 +188,20 @@ int choose_alg(const sfc_conv_desc& d) {
   return SFC_ALG_4X4_P46;
 }
 
-// Staged path in passes over the filters: how many of them a pass may take for V and the pass's sums to fit
-// `bytes` (at least 16; 0: not even those fit).
-int filters_that_fit(const Geometry& g, size_t bytes) {
+// Staged path from the static workspace, where V and M together exceed it: filters of a pass over products and
+// output transform, V and the pass's sums within the workspace; 0: the fused kernel instead.  A pass takes some 20 us
+// whatever its filters, the fused kernel 30 to 40, 50 to 60 and 90 to 100 with two, four and eight chunks.  Passes against
+// the fused kernel, 5x5 and 7x7 filters: eight chunks two 0.58-0.64, three 0.79-0.89, four 1.0-1.1; four chunks two
+// 0.96-1.13, three 1.4-1.5; two chunks two 1.4-1.7.  (Equal passes: 256 filters as 128 and 128 57.3 us, as 144 and 112,
+// three blocks of 128 in the product, 61.8.)
+int static_pass_filters(const Geometry& g) {
   const size_t v = align_up((size_t)g.P * g.Tp * g.Cp, 256);
   int nf = g.Kp;
-  while (nf > 0 && v + sums_bytes(g, nf, sfc::m_sum_bytes(g)) > bytes) nf -= 16;
-  return nf;
+  while (nf > 0 && v + sums_bytes(g, nf, sfc::m_sum_bytes(g)) > SFC_STATIC_WORKSPACE_BYTES) nf -= 16;
+  const int most = g.Cp >= 512 ? 3 : 1;
+  if (nf * most < g.Kp) return 0;
+  const int passes = (g.Kp + nf - 1) / nf;
+  return ((g.Kp + passes - 1) / passes + 15) / 16 * 16;
 }
 
 // The 5x5- and 7x7-filter forms with 184 points: whether three kernels are ahead of the fused path.  A
@@ -175,10 +239,7 @@ int choose_path(const sfc_conv_desc& d, const Geometry& g, bool* instead) {
   const bool gemm = alg_is_7x7(d.alg) && d.H < 14 && d.Cin >= 512;
   if (gemm) return SFC_PATH_STAGED;
   if (sfc::fused_quad_supported(g)) {
-    // (a layer whose V fits the static workspace runs from there as well, in passes)
-    const bool in_static = (size_t)g.P * g.Tp * g.Cp > SFC_STATIC_WORKSPACE_BYTES ||
-                           filters_that_fit(g, SFC_STATIC_WORKSPACE_BYTES) > 0;
-    *instead = staged_ahead(g) && in_static;
+    *instead = staged_ahead(g);
     return *instead ? SFC_PATH_STAGED : SFC_PATH_FUSED;
   }
   // chunk counts that the fused path does not take on request: its 184-point kernels do, and quad16_kernel
@@ -240,7 +301,6 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
   p->d = d;
   p->g = g;
   p->esz = d.mode == SFC_MODE_EXACT ? 2 : 1;
-  p->staged_instead = instead;
   const size_t PK = (size_t)g.P * g.Kp;
   size_t off = 0;
   p->off_U = off;        off = align_up(off + PK * g.Cp * p->esz, 256);
@@ -256,42 +316,38 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out) {
   if (d.mode == SFC_MODE_REQUANT_I8 && d.path != SFC_PATH_SINGLE && sfc::rows_table_offset(g) != ~0u)
     off = align_up(off + sfc::kRowsTabBytes, 256);
   if (d.mode == SFC_MODE_EXACT) off = align_up(off + sfc::kRowsTabBytes, 256);  // every algorithm
-  p->off_dq_single = off;
-  p->off_U_single = off;
-  p->quad_filters = 0;
-  p->kernel = sfc::choose_kernel(d.path, g);
-  switch (p->kernel) {
-    case sfc::Kernel::kStaged: break;
-    case sfc::Kernel::kFusedQuad: p->quad_filters = sfc::quad_filter_count(g); break;
-    case sfc::Kernel::kQuad16: p->quad_filters = sfc::quad16_filter_count(g); break;
-    case sfc::Kernel::kPair16: p->quad_filters = sfc::pair16_filter_count(g); break;
-    case sfc::Kernel::kSplitK: p->quad_filters = sfc::splitk_filter_count(g); break;
-    case sfc::Kernel::kProductSmall: p->quad_filters = sfc::product_small_filter_count(g); break;
-    case sfc::Kernel::kSingleConv: p->quad_filters = (g.Cout + 63) / 64 * 64; break;
-    case sfc::Kernel::kSingle16:
-    case sfc::Kernel::kSingle16K:
-    case sfc::Kernel::kSingleSmall: p->quad_filters = g.Kp; break;
-  }
-  // the staged output transform reads the same [filter][position] table as the fused kernels
-  p->dq_filters = p->quad_filters;
-  if (d.path == SFC_PATH_STAGED && d.mode == SFC_MODE_REQUANT_I8) p->dq_filters = g.Kp;
+  p->op.kernel = sfc::choose_kernel(d.path, g);
+  p->fused.kernel = instead ? sfc::choose_kernel(SFC_PATH_FUSED, g) : sfc::Kernel::kStaged;
+  const size_t m_bytes = d.path != SFC_PATH_STAGED ? 0 : sums_bytes(g, g.Kp, instead ? sfc::m_sum_bytes(g) : 4);
+  const size_t v_bytes = align_up((size_t)g.P * g.Tp * g.Cp * p->esz, 256);
+  // calibration scratch (abs-max tables)
+  const size_t calib = align_up((size_t)g.P * (size_t)(g.Cout > 1 ? g.Cout : 1) * 4, 256);
+  const bool exceeds_static = instead && std::max(v_bytes + m_bytes, calib) > SFC_STATIC_WORKSPACE_BYTES;
+  p->static_pass = exceeds_static ? static_pass_filters(g) : 0;
+  p->op.filters = p->op.dq_filters = regrouped_filters(p->op.kernel, g);
+  // the staged output transform reads the same [filter][position] table as fused_quad_kernel
+  if (d.path == SFC_PATH_STAGED && d.mode == SFC_MODE_REQUANT_I8) p->op.dq_filters = g.Kp;
+  p->fused.filters = p->fused.dq_filters =
+      exceeds_static && p->static_pass == 0 && v_bytes <= SFC_STATIC_WORKSPACE_BYTES ? regrouped_filters(p->fused.kernel, g) : 0;
   // the kernels take the points in groups of four: positions up to a multiple of 4
   const size_t pp = (size_t)(g.P + 3) / 4 * 4;
-  if (p->dq_filters > 0) {
-    off = align_up(off + (size_t)p->dq_filters * pp * sizeof(float), 256);
-    p->off_U_single = off;
+  for (Regrouped* op : {&p->op, &p->fused}) {
+    op->off_dq = off;
+    off = align_up(off + (size_t)op->dq_filters * pp * sizeof(float), 256);
   }
-  if (p->quad_filters > 0) off = align_up(off + (size_t)p->quad_filters * pp * g.Cp, 256);
+  p->off_tables_end = off;
+  for (Regrouped* op : {&p->op, &p->fused}) {
+    op->off_U = off;
+    off = align_up(off + (size_t)op->filters * pp * g.Cp, 256);
+  }
   p->filter_bytes = off;
   off = 0;
   p->off_V = off;
   // the single-kernel path keeps V on chip; its workspace only serves calibration
-  if (d.path != SFC_PATH_SINGLE) off = align_up(off + (size_t)g.P * g.Tp * g.Cp * p->esz, 256);
+  if (d.path != SFC_PATH_SINGLE) off += v_bytes;
   p->off_M = off;
-  if (d.path == SFC_PATH_STAGED) off += sums_bytes(g, g.Kp, instead ? sfc::m_sum_bytes(g) : 4);
-  // calibration scratch (abs-max tables) must fit as well
-  const size_t calib = align_up((size_t)g.P * (size_t)(g.Cout > 1 ? g.Cout : 1) * 4, 256);
-  p->workspace_bytes = off > calib ? off : calib;
+  off += m_bytes;
+  p->workspace_bytes = std::max(off, calib);
   p->scales_set = false;
   p->filter_dev = nullptr;
   p->filter_ready = false;
@@ -394,11 +450,8 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   for (int k = 0; k < (plan->d.per_channel_wscale ? g.Cout : 1); ++k)
     if (!(wscale_host[k] > 0.0f) || !std::isfinite(wscale_host[k])) return SFC_EINVAL;
 
-  // host image of the float tables: [dequant | inv_sw | inv_sx | wscale], contiguous
-  // from off_dequant to filter_bytes
-  const bool quad = plan->quad_filters > 0;
-  const size_t table_bytes =
-      (plan->dq_filters > 0 ? plan->off_U_single : plan->filter_bytes) - plan->off_dequant;
+  // host image of the float tables: [dequant | inv_sw | inv_sx | wscale | input | factors], contiguous
+  const size_t table_bytes = plan->off_tables_end - plan->off_dequant;
   try {
     plan->staging.assign(table_bytes / sizeof(float), 0.0f);
   } catch (...) {
@@ -426,7 +479,7 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
       inv_sw[(size_t)p * g.Kp + k] = inv;
     }
   }
-  if (plan->off_dq_single > plan->off_input_tab) {
+  if (plan->op.off_dq > plan->off_input_tab) {
     unsigned char* tab = reinterpret_cast<unsigned char*>(table(plan->off_input_tab));
     if (!requant) {
       sfc::build_rows_table(g.alg, inv_sx, tab);
@@ -438,34 +491,16 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
         sfc::build_rows_table(g.alg, inv_sx, tab + sfc::rows_table_offset(g));
     }
   }
-  if (plan->dq_filters > 0) {
-    const int pp = (g.P + 3) / 4 * 4;
-    std::vector<int> pt(pp, -1);
+  if (plan->op.dq_filters > 0) {
+    std::vector<int> pt((g.P + 3) / 4 * 4, -1);
     sfc::single_point_order(plan->d.alg, pt.data());
-    float* dqs = table(plan->off_dq_single);
-    if (sfc::groups_of_16(plan->kernel)) {
-      // [group of 16 filters][processing position][lane quarter q][i]: filter 16*fg + 4*i + q
-      for (int k = 0; k < g.Cout; ++k) {
-        const int fg = k >> 4, i = (k & 15) >> 2, q = k & 3;
-        for (int j = 0; j < pp; ++j)
-          dqs[((size_t)fg * pp + j) * 16 + 4 * q + i] =
-              pt[j] < 0 ? 0.0f : dequant[(size_t)pt[j] * g.Kp + k];
-      }
-    } else if (plan->kernel == sfc::Kernel::kPair16) {
-      // [group of 8 filters][processing position][lane quarter q][i]: filter 8*fg + 4*i + q
-      for (int k = 0; k < g.Cout; ++k)
-        for (int j = 0; j < pp; ++j)
-          dqs[((size_t)(k >> 3) * pp + j) * 8 + 2 * (k & 3) + ((k & 7) >> 2)] = dequant[(size_t)pt[j] * g.Kp + k];
-    } else {
-      // [filter][processing position]; filters beyond Cout stay zero
-      for (int k = 0; k < g.Cout; ++k)
-        for (int j = 0; j < pp; ++j)
-          dqs[(size_t)k * pp + j] = pt[j] < 0 ? 0.0f : dequant[(size_t)pt[j] * g.Kp + k];
-    }
+    for (const Regrouped* op : {&plan->op, &plan->fused})
+      if (op->dq_filters > 0) regroup_factors(op->kernel, g, pt, dequant, table(op->off_dq));
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the kernels of this plan's path that need more than the default 64 KB of dynamic LDS
   if (requant && sfc::prepare_kernels(plan->d.path, plan->d.out, g) != hipSuccess) return SFC_EHIP;
+  if (plan->fused.filters > 0 && sfc::prepare_kernels(SFC_PATH_FUSED, plan->d.out, g) != hipSuccess) return SFC_EHIP;
   if (!requant) {  // (a layer beyond its limits takes the generic kernel)
     const hipError_t e = sfc::launch_input_exact(g, nullptr, nullptr, nullptr, nullptr, true);
     if (e != hipSuccess && e != hipErrorNotSupported) return SFC_EHIP;
@@ -473,38 +508,35 @@ sfc_status sfc_transform_filter(sfc_plan_t* plan, const int8_t* w_dev, const flo
   if (hipMemcpyAsync(static_cast<char*>(filter_dev) + plan->off_dequant, plan->staging.data(),
                      table_bytes, hipMemcpyHostToDevice, s) != hipSuccess)
     return SFC_EHIP;
-  const FilterViews f = views(plan, filter_dev);
-  if (sfc::launch_filter_transform(plan->d.mode, g, w_dev, f, s) != hipSuccess)
+  if (sfc::launch_filter_transform(plan->d.mode, g, w_dev, views(plan, plan->op, filter_dev), s) != hipSuccess)
     return SFC_EHIP;
-  if (quad && (plan->kernel == sfc::Kernel::kPair16 ? sfc::launch_repack_filter8(g, plan->quad_filters, f.U, f.U_single, s)
-               : sfc::groups_of_16(plan->kernel)
-                   ? sfc::launch_repack_filter16(g, plan->quad_filters, f.U, f.U_single, s)
-                   : sfc::launch_repack_filter(g, plan->quad_filters, f.U, f.U_single, s)) != hipSuccess)
-    return SFC_EHIP;
+  for (const Regrouped* op : {&plan->op, &plan->fused})
+    if (launch_repack(*op, g, views(plan, *op, filter_dev), s) != hipSuccess) return SFC_EHIP;
   plan->filter_dev = filter_dev;
   plan->filter_ready = true;
   return SFC_OK;
 }
 
-// sfc_conv2d_stages.  pass: 0, or the filters of a pass over products and output transform (all stages, workspace
-// for V and the sums of a pass).
+// sfc_conv2d_stages.  statically: sfc_conv2d_nchw_static with a plan whose workspace exceeds the static one, in
+// passes or with the fused kernel (all stages).
 static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale, void* y_dev,
                              void* workspace_dev, void* stream, int32_t stage_mask, size_t workspace_bytes,
-                             int pass) {
+                             bool statically) {
   if (!plan || !x_dev || !y_dev || !workspace_dev) return SFC_EINVAL;
   if (!aligned16(x_dev) || !aligned16(y_dev) || !aligned16(workspace_dev)) return SFC_EINVAL;
   if (!(x_scale > 0.0f) || !std::isfinite(x_scale)) return SFC_EINVAL;
   if (stage_mask <= 0 || stage_mask > SFC_STAGE_ALL) return SFC_EINVAL;
-  if (pass == 0 && workspace_bytes < plan->workspace_bytes) return SFC_EWORKSPACE;
+  if (!statically && workspace_bytes < plan->workspace_bytes) return SFC_EWORKSPACE;
   if (!plan->filter_ready) return SFC_ENOTREADY;
   if (plan->d.out == SFC_OUT_I8_RELU && plan->inv_y == 0.0f) return SFC_ENOTREADY;
-  const bool fused = plan->d.path == SFC_PATH_FUSED;
+  const Regrouped& op = statically && plan->static_pass == 0 ? plan->fused : plan->op;
+  const bool fused = plan->d.path == SFC_PATH_FUSED || &op == &plan->fused;
   if (plan->d.path == SFC_PATH_SINGLE) {
     if (stage_mask != SFC_STAGE_ALL) return SFC_EINVAL;  // one kernel: no stage runs alone
-    const FilterViews f = views(plan, plan->filter_dev);
+    const FilterViews f = views(plan, op, plan->filter_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    switch (plan->kernel) {
+    switch (op.kernel) {
       case sfc::Kernel::kSingleSmall:
         e = sfc::launch_single_small(plan->d.out, plan->g, x_dev, f, x_scale, plan->inv_y, y_dev, s);
         break;
@@ -523,7 +555,7 @@ static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
   if (fused && tail != 0 && tail != (SFC_STAGE_PRODUCT | SFC_STAGE_OUTPUT)) return SFC_EINVAL;
   const Geometry& g = plan->g;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const FilterViews f = views(plan, plan->filter_dev);
+  const FilterViews f = views(plan, op, plan->filter_dev);
   char* ws = static_cast<char*>(workspace_dev);
   void* V = ws + plan->off_V;
   if (stage_mask & SFC_STAGE_INPUT) {
@@ -534,7 +566,7 @@ static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
   if (fused) {
     if (!tail) return SFC_OK;
     hipError_t e;
-    switch (plan->kernel) {
+    switch (op.kernel) {
       case sfc::Kernel::kProductSmall:
         e = sfc::launch_product_small(plan->d.out, g, V, f, x_scale, plan->inv_y, y_dev, s);
         break;
@@ -553,24 +585,29 @@ static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
     return SFC_OK;
   }
   int32_t* M = reinterpret_cast<int32_t*>(ws + plan->off_M);
-  float inv_y = plan->inv_y;
-  // (int8 ties as the fused kernel of the layer rounds them: launch_quad16's product of the two scales)
-  if (plan->staged_instead && plan->d.out == SFC_OUT_I8_RELU &&
-      sfc::choose_kernel(SFC_PATH_FUSED, g) == sfc::Kernel::kQuad16) {
-    inv_y *= x_scale;
-    x_scale = 1.0f;
+  if (plan->fused.kernel != sfc::Kernel::kStaged) {
+    // int8 ties as the fused kernel of the layer rounds them (launch_quad16's product of the two scales), and its
+    // order of the float32 additions
+    const bool once = plan->fused.kernel == sfc::Kernel::kQuad16;
+    const float xs = once && plan->d.out == SFC_OUT_I8_RELU ? 1.0f : x_scale;
+    const float inv_y = once ? plan->inv_y * x_scale : plan->inv_y;
+    const int pass = statically ? plan->static_pass : g.Kp;
+    for (int f0 = 0; f0 < g.Cout; f0 += pass) {
+      if ((stage_mask & SFC_STAGE_PRODUCT) && sfc::launch_product_gemm_i8(g, V, f.U, M, s, f0, pass) != hipSuccess)
+        return SFC_EHIP;
+      if ((stage_mask & SFC_STAGE_OUTPUT) &&
+          sfc::launch_output_sums(plan->d.out, g, M, f, xs, inv_y, y_dev, s, false, f0, pass,
+                                  plan->fused.kernel == sfc::Kernel::kFusedQuad) != hipSuccess)
+        return SFC_EHIP;
+    }
+    return SFC_OK;
   }
-  for (int f0 = 0; pass > 0 && f0 < g.Cout; f0 += pass) {
-    if (sfc::launch_product_gemm_i8(g, V, f.U, M, s, f0, pass) != hipSuccess ||
-        sfc::launch_output_sums(plan->d.out, g, M, f, x_scale, inv_y, y_dev, s, false, f0, pass) != hipSuccess)
-      return SFC_EHIP;
-  }
-  if (pass > 0) return SFC_OK;
   if (stage_mask & SFC_STAGE_PRODUCT) {
     if (sfc::launch_product(plan->d.mode, g, V, f.U, M, s) != hipSuccess) return SFC_EHIP;
   }
   if (stage_mask & SFC_STAGE_OUTPUT) {
-    if (sfc::launch_output_transform(plan->d.mode, plan->d.out, g, M, f, x_scale, inv_y, y_dev, s) != hipSuccess)
+    if (sfc::launch_output_transform(plan->d.mode, plan->d.out, g, M, f, x_scale,
+                                     plan->inv_y, y_dev, s) != hipSuccess)
       return SFC_EHIP;
   }
   return SFC_OK;
@@ -579,7 +616,7 @@ static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
 sfc_status sfc_conv2d_stages(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale,
                              void* y_dev, void* workspace_dev, size_t workspace_bytes, void* stream,
                              int32_t stage_mask) {
-  return run_stages(plan, x_dev, x_scale, y_dev, workspace_dev, stream, stage_mask, workspace_bytes, 0);
+  return run_stages(plan, x_dev, x_scale, y_dev, workspace_dev, stream, stage_mask, workspace_bytes, false);
 }
 
 sfc_status sfc_conv2d_nchw(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale, void* y_dev,
@@ -591,13 +628,11 @@ sfc_status sfc_conv2d_nchw(const sfc_plan_t* plan, const int8_t* x_dev, float x_
 sfc_status sfc_conv2d_nchw_static(const sfc_plan_t* plan, const int8_t* x_dev, float x_scale,
                                   void* y_dev, void* stream) {
   if (!plan) return SFC_EINVAL;
-  // (a layer that the library sends through M of its own accord: as many filters at a time as fit)
-  const bool passes = plan->staged_instead && plan->workspace_bytes > SFC_STATIC_WORKSPACE_BYTES;
-  const int nf = passes ? filters_that_fit(plan->g, SFC_STATIC_WORKSPACE_BYTES) : 0;
-  if (plan->workspace_bytes > SFC_STATIC_WORKSPACE_BYTES && nf == 0) return SFC_EWORKSPACE;
+  const bool exceeds = plan->workspace_bytes > SFC_STATIC_WORKSPACE_BYTES;
+  if (exceeds && plan->static_pass == 0 && plan->fused.filters == 0) return SFC_EWORKSPACE;
   void* ws = static_workspace();
   if (!ws) return SFC_EHIP;
-  return run_stages(plan, x_dev, x_scale, y_dev, ws, stream, SFC_STAGE_ALL, SFC_STATIC_WORKSPACE_BYTES, nf);
+  return run_stages(plan, x_dev, x_scale, y_dev, ws, stream, SFC_STAGE_ALL, SFC_STATIC_WORKSPACE_BYTES, exceeds);
 }
 
 sfc_status sfc_tap_info(const sfc_plan_t* plan, const void* workspace_dev, int32_t which,

@@ -208,25 +208,29 @@ hipError_t launch_product_gemm_i8(const Geometry& g, const void* V, const void* 
 // have room for more: us a layer with 32 / 48 / 64 / 92 in flight, 5x5 filters, 98 channels, 60 7x7 maps
 // 30.6 / 29.7 / 30.0 / 29.3, twelve 28x28 maps 31.2 / 30.3 / 30.5 / 29.8; 7x7 filters, 512 channels, two
 // 14x14 maps 32.1 / 32.1 / 32.4 / 32.3.
-template <int ALG>
+// KEPT: the forms with 184 points keep the outputs, as their fused kernels do (the same sums in the same order).
+// Without it SFC-6(4x4,7x7) adds as fused_quad_kernel does, for the layers that kernel takes on request.
+template <int ALG, bool KEPT>
 constexpr int sum_ring() {
   using Tr = AlgTraits<ALG>;
-  return Tr::NC <= 6 ? Order<ALG>::PP : Tr::NC <= 8 ? 12 : Tr::NC < 12 || !Tr::kHermitian ? 32 : Tr::M == 6 ? 92 : 48;
+  return Tr::NC <= 6 ? Order<ALG>::PP : Tr::NC <= 8 ? 12 : !KEPT ? 32 : Tr::M == 6 ? 92 : 48;
 }
+template <int ALG>
+constexpr bool sums_kept() { return AlgTraits<ALG>::NC == 12 && AlgTraits<ALG>::kHermitian; }
 
 template <int ALG, bool PLANES, int NW>
 constexpr unsigned sums_stage_bytes() {
   return (unsigned)(NW * 64 * AlgTraits<ALG>::M * (PLANES ? AlgTraits<ALG>::M : 1) * 4);
 }
 
-template <int ALG, int OUT, bool VEC2, int NW, bool PLANES>
+template <int ALG, int OUT, bool VEC2, int NW, bool PLANES, bool KEPT>
 __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __restrict__ M,
                                                               const float* __restrict__ dequant,
                                                               float x_scale, float inv_y,
                                                               void* __restrict__ y, Geometry g,
                                                               int m_bytes, int f0, int nf) {
   using Tr = AlgTraits<ALG>;
-  constexpr int P = Tr::P, Mo = Tr::M, NC = Tr::NC, D = sum_ring<ALG>();
+  constexpr int P = Tr::P, Mo = Tr::M, NC = Tr::NC, D = sum_ring<ALG, KEPT>();
   constexpr Order<ALG> order{};
   extern __shared__ __align__(16) unsigned char lds[];  // staging blocks, then the tile table
   const int lane = threadIdx.x & 63;
@@ -291,11 +295,9 @@ __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __r
     ++j;
     return v;
   };
-  // The forms with 184 points keep the outputs, as their fused kernels do (the same sums in the same order).
-  constexpr bool kOutputs = NC == 12 && Tr::kHermitian;
-  constexpr int STORE = kOutputs ? kOutputColumns + Mo : ALG;
-  float z[kOutputs ? Mo : NC][Mo];
-  if constexpr (kOutputs) stream_outputs<ALG, float>(next, [](float& v) { asm volatile("" : "+v"(v)); }, z);
+  constexpr int STORE = KEPT ? kOutputColumns + Mo : ALG;
+  float z[KEPT ? Mo : NC][Mo];
+  if constexpr (KEPT) stream_outputs<ALG, float>(next, [](float& v) { asm volatile("" : "+v"(v)); }, z);
   else stream_vertical<ALG, float>(next, z);
   if constexpr (PLANES)
     store_planes<STORE, OUT>(z, stage, tile_tab, lane, kq, x_scale, inv_y, yres, g.Cout, g.th, g.tw);
@@ -303,7 +305,7 @@ __global__ __launch_bounds__(NW * 64) void output_sums_kernel(const int32_t* __r
     store_pairs<STORE, OUT, VEC2>(z, stage, tile_tab, lane, kq, x_scale, inv_y, yres, g.Cout, g.H, g.W);
 }
 
-template <int ALG, int OUT, bool VEC2, bool PLANES = false>
+template <int ALG, bool KEPT, int OUT, bool VEC2, bool PLANES = false>
 static hipError_t launch_sums_impl(const Geometry& g, const int32_t* M, const FilterViews& f,
                                    float x_scale, float inv_y, void* y, hipStream_t s,
                                    bool prepare, int f0, int nf) {
@@ -316,7 +318,7 @@ static hipError_t launch_sums_impl(const Geometry& g, const int32_t* M, const Fi
   constexpr int NW = AlgTraits<ALG>::NC == 8 ? 8 : 4;
   constexpr unsigned lds_bytes = sums_stage_bytes<ALG, PLANES, NW>() + 256;
   static_assert(lds_bytes <= 160u * 1024u, "staging blocks exceed the LDS of a compute unit");
-  auto kernel = output_sums_kernel<ALG, OUT, VEC2, NW, PLANES>;
+  auto kernel = output_sums_kernel<ALG, OUT, VEC2, NW, PLANES, KEPT>;
   if (prepare)
     return lds_bytes > 64u * 1024u ? raise_lds_limit(reinterpret_cast<const void*>(kernel))
                                    : hipSuccess;
@@ -326,7 +328,7 @@ static hipError_t launch_sums_impl(const Geometry& g, const int32_t* M, const Fi
   return hipGetLastError();
 }
 
-template <int ALG>
+template <int ALG, bool KEPT = sums_kept<ALG>()>
 static hipError_t launch_sums_alg(int out, const Geometry& g, const int32_t* M,
                                   const FilterViews& f, float x_scale, float inv_y, void* y,
                                   hipStream_t s, bool prepare, int f0, int nf) {
@@ -335,22 +337,22 @@ static hipError_t launch_sums_alg(int out, const Geometry& g, const int32_t* M,
   // pairs are whole planes of y
   if constexpr (AlgTraits<ALG>::M == 7 || AlgTraits<ALG>::M == 4) {
     if (whole_image_tiles(AlgTraits<ALG>::M, g.H, g.W, g.th, g.tw, g.Cout))
-      return out == 2 ? launch_sums_impl<ALG, 2, false, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
-                      : launch_sums_impl<ALG, 0, false, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+      return out == 2 ? launch_sums_impl<ALG, KEPT, 2, false, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                      : launch_sums_impl<ALG, KEPT, 0, false, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
   }
   if constexpr (kPairs) {
     if (g.W % 2 == 0)
-      return out == 2 ? launch_sums_impl<ALG, 2, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
-                      : launch_sums_impl<ALG, 0, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+      return out == 2 ? launch_sums_impl<ALG, KEPT, 2, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                      : launch_sums_impl<ALG, KEPT, 0, true>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
   }
-  return out == 2 ? launch_sums_impl<ALG, 2, false>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
-                  : launch_sums_impl<ALG, 0, false>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+  return out == 2 ? launch_sums_impl<ALG, KEPT, 2, false>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                  : launch_sums_impl<ALG, KEPT, 0, false>(g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
 }
 
 // out: 0 float32, 2 int8 with ReLU.  hipErrorNotSupported beyond the 32-bit offset limits.
 hipError_t launch_output_sums(int out, const Geometry& g, const int32_t* M, const FilterViews& f,
                               float x_scale, float inv_y, void* y, hipStream_t s, bool prepare, int f0,
-                              int nf) {
+                              int nf, bool as_fused_quad) {
   if (nf == 0) nf = g.Kp;
   const long long mbytes = 4ll * g.P * g.Tp * nf, ybytes = 4ll * g.N * g.Cout * g.H * g.W;
   if (mbytes >= (1ll << 31) || ybytes >= (1ll << 31) || out == 1) return hipErrorNotSupported;
@@ -363,7 +365,8 @@ hipError_t launch_output_sums(int out, const Geometry& g, const int32_t* M, cons
     case 5: return launch_sums_alg<5>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
     case 6: return launch_sums_alg<6>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
     case 7: return launch_sums_alg<7>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
-    case 8: return launch_sums_alg<8>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 8: return as_fused_quad ? launch_sums_alg<8, false>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                                 : launch_sums_alg<8>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
     case 9: return launch_sums_alg<9>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
   }
   return hipErrorInvalidValue;

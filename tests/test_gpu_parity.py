@@ -762,6 +762,53 @@ def test_static_workspace_in_passes(binding, alg, shape, out):
     plan.close()
 
 
+SENT_THROUGH_M = [  # (algorithm, shape, kernel of the fused path, what a call from the static workspace runs)
+    ("6x6_5x5_p184", (9, 60, 70, 13, 12), "pair16", "whole"),
+    ("6x6_5x5_p184", (12, 256, 500, 20, 24), "pair16", "fused"),
+    ("6x6_5x5_p184", (14, 460, 250, 24, 18), "pair16", "passes"),
+    ("4x4_7x7_p184", (12, 250, 500, 16, 15), "quad16", "fused"),
+    ("4x4_7x7_p184", (28, 100, 512, 7, 7), "fused_quad", "fused"),
+    ("4x4_7x7_p184", (14, 512, 200, 14, 13), "fused_quad", "passes"),
+    ("4x4_7x7_p184", (20, 512, 264, 16, 16), "fused_quad", "fused"),
+    ("4x4_7x7_p184", (21, 512, 70, 15, 14), "fused_quad", "fused"),
+]
+
+
+@pytest.mark.parametrize("out", ["f32", "i8"])
+@pytest.mark.parametrize("alg,shape,kernel,static", SENT_THROUGH_M)
+def test_layers_sent_through_m(binding, alg, shape, kernel, static, out):
+    """One plan, one result: from a caller's workspace, from the static one (whole, in passes, or by the fused
+    kernel), and that of the fused path on request wherever its kernel adds in the same order."""
+    import torch
+
+    x, w, xs, ws = uniform_case(shape, 4200 + sum(shape), r=binding.KERNEL_SIZE[alg])
+    print("case through M", alg, shape, static, out, flush=True)
+    sx, sw = oracle.calibrate_act_scales(x[:2], alg), oracle.calibrate_filter_scales(w, alg)
+    ys = []
+    for path in ("auto", "fused"):
+        plan = binding.Plan(*shape, alg=alg, mode="requant", path=path, out=out)
+        assert plan.path == ("staged" if path == "auto" else "fused")
+        plan.set_point_scales(sx, sw)
+        if out == "i8":
+            plan.set_output_scale(30.0)
+        fbuf, wbuf = binding.device_buffer(plan.filter_bytes), binding.device_buffer(plan.workspace_bytes)
+        plan.transform_filter(torch.from_numpy(w).cuda(), ws, fbuf)
+        xd = torch.from_numpy(x).cuda()
+        for call in ("workspace", "static"):
+            y = torch.full((shape[0], shape[2], *shape[3:]), 77, dtype=torch.int8 if out == "i8" else torch.float32,
+                           device="cuda")
+            if call == "workspace":
+                plan.conv2d(xd, xs, y, wbuf)
+            else:
+                plan.conv2d_static(xd, xs, y)
+            torch.cuda.synchronize()
+            ys.append(y)
+        plan.close()
+    assert ys[0].float().std() > 0
+    for y in ys[1:]:
+        assert torch.equal(ys[0], y)
+
+
 SINGLE_SHAPES = [
     (1, 16, 16, 32, 32),
     (2, 3, 5, 14, 14),

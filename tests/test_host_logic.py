@@ -406,6 +406,26 @@ def test_auto_path_on_both_sides_of_its_line(lib, alg, cin, cout, line):
         assert e.value.code == 2
 
 
+def test_static_workspace_of_layers_sent_through_m(lib, routes):
+    """A layer that the library sends through M and whose V and M exceed the static workspace: at most three passes, and
+    those with eight chunks of channels; else its plan holds the fused kernel's operand as well."""
+    from paper_2407_02913_amd import binding
+    import test_gpu_parity as parity
+
+    assert routes([("fused", alg, s) for alg, s, _, _ in parity.SENT_THROUGH_M]) == [k for _, _, k, _ in parity.SENT_THROUGH_M]
+    more = [("4x4_7x7_p184", (20, 512, 576, 16, 16), None, "fused"), ("6x6_5x5_p184", (16, 512, 256, 24, 24), None, "fused"),
+            ("6x6_5x5_p184", (16, 512, 192, 24, 24), None, "passes"), ("6x6_5x5_p184", (30, 128, 128, 24, 24), None, "fused"),
+            ("6x6_5x5_p184", (4, 512, 64, 12, 12), None, "whole"), ("4x4_7x7_p184", (23, 512, 64, 16, 16), None, "refused")]
+    for alg, shape, _, static in parity.SENT_THROUGH_M + more:
+        plan = binding.Plan(*shape, alg=alg, mode="requant", path="auto")
+        cp, kp = -(-shape[1] // 64) * 64, -(-shape[2] // 16) * 16
+        operand = 184 * kp * cp
+        assert plan.path == "staged"
+        assert (plan.workspace_bytes > binding.STATIC_WORKSPACE_BYTES) == (static != "whole"), shape
+        assert (plan.filter_bytes > 2 * operand) == (static == "fused"), shape
+        plan.close()
+
+
 def test_output_transforms_of_the_exact_shapes(lib, routes):
     """Either output transform has the shapes of the GPU parity tests that are there for it."""
     import test_gpu_parity as parity
