@@ -12,8 +12,8 @@
 // one pair per lane (sfc_fused_quad.hpp) the matrix instructions, reads of V and filter-operand bytes
 // of a product are half, and the matrix instructions of one position run under the arithmetic of the
 // one before, where all waves of a workgroup read V, multiplied and added at the same time.  128 channels
-// on 28x28 maps, batch 64: 64.0 -> 31.5 us (layer 78.7 -> 47); over 80 layers of the range of the 5x5
-// filters the layer takes 0.79 of the time (0.56 to 1.0; with 512 channels, 0.79 to 1.08).  With one pair per lane neither deeper rings of V
+// on 28x28 maps, batch 64: 64.0 -> 31.5 us (layer 78.7 -> 44.9); over 80 layers of the range of the 5x5
+// filters the layer takes 0.79 of the time (0.56 to 1.0; with 512 channels and eight waves, 0.79 to 1.08).  With one pair per lane neither deeper rings of V
 // (1, 2, 4 groups) nor of the filter operand (2, 4, 8 blocks) had changed the 64 us.
 #pragma once
 #include "sfc_device.hpp"
@@ -254,10 +254,16 @@ __global__ __launch_bounds__(NW * 64, 2) void pair16_kernel(
 
 // ---------------------------------------------------------------------------------------
 
-// Waves of a workgroup, eight filters each: four where eight would leave half of them without a filter,
-// or reach past the 32-bit offsets into the filter operand.
+// Waves of a workgroup, eight filters each.  Up to 128 workgroups of eight waves, half of the compute units have none: four
+// waves then, twice the workgroups.  us with four over us with eight, explicit fused path, layers of one, two, four and
+// eight chunks: up to 128 workgroups 0.85-0.90, 0.82-0.92, 0.74-0.86, 0.85-0.94 (at 128 with 512 filters 1.1), against
+// one pair per lane 0.64 to 0.97, where eight waves took up to 1.02, 0.91, 0.99 and 1.08; above 160 0.9-1.05, 0.92-1.28,
+// 0.93-1.56, 0.95-1.74.  Four as well where eight would leave half of them without a filter, or reach past the 32-bit
+// offsets into the filter operand.
 inline int pair16_waves(const Geometry& g) {
-  return g.Cout > 32 && (long long)((g.Cout + 63) / 64 * 64) * g.P * g.Cp < (1ll << 31) ? 8 : 4;
+  const int groups = (g.Cout + 63) / 64;
+  if (g.Cout <= 32 || (long long)(g.Tp / 16) * groups <= 128) return 4;
+  return (long long)groups * 64 * g.P * g.Cp < (1ll << 31) ? 8 : 4;
 }
 
 template <int KC, int OUT, int NW>

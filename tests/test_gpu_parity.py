@@ -712,6 +712,19 @@ def test_5x5_filters_two_pairs_per_lane(binding, shape):
     assert check_i8_against_oracle(y8, y_ref, y_scale) < 1e-3
 
 
+PAIR16_EIGHT_WAVES = [  # more than 128 workgroups of 64 filters
+    (2070, 3, 34, 6, 6),      # one tile an image: 130 workgroups, the second half of the waves with two filters
+    (1040, 70, 65, 5, 6),     # 65 tile blocks, a second workgroup of one filter
+    (520, 193, 130, 9, 7),    # four tiles an image, odd width
+    (1025, 449, 66, 6, 4),    # eight chunks, a ragged last tile block
+]
+
+
+@pytest.mark.parametrize("shape", PAIR16_EIGHT_WAVES)
+def test_5x5_filters_eight_waves(binding, shape):
+    test_5x5_filters_two_pairs_per_lane(binding, shape)
+
+
 @pytest.mark.parametrize("alg,shape", [
     ("6x6_5x5_p184", (2300, 130, 24, 5, 6)),   # three chunks of channels on the fused path
     ("6x6_5x5_p184", (2400, 300, 60, 3, 5)),   # five

@@ -406,6 +406,24 @@ def test_auto_path_on_both_sides_of_its_line(lib, alg, cin, cout, line):
         assert e.value.code == 2
 
 
+def test_waves_of_the_5x5_kernel(lib):
+    """Four up to 128 workgroups of 64 filters, then eight: the operand covers whole workgroups."""
+    from paper_2407_02913_amd import binding
+    import test_gpu_parity as parity
+
+    def filters(shape):
+        plan = binding.Plan(*shape, alg="6x6_5x5_p184", mode="requant", path="fused")
+        cp, kp = -(-shape[1] // 64) * 64, -(-shape[2] // 16) * 16
+        # U, the operand, the factors of points (twice) and of positions, the other tables
+        rest = plan.filter_bytes - 184 * kp * (cp + 8)
+        plan.close()
+        return rest // (184 * (cp + 4)) // 16 * 16
+
+    for cin in (64, 512):
+        assert filters((16 * 64, cin, 65, 6, 6)) == 96 and filters((16 * 64 + 1, cin, 65, 6, 6)) == 128
+    assert {-(-s[2] // 64) * 64 == filters(s) for s in parity.PAIR16_EIGHT_WAVES} == {True}
+
+
 def test_static_workspace_of_layers_sent_through_m(lib, routes):
     """A layer that the library sends through M and whose V and M exceed the static workspace: at most three passes, and
     those with eight chunks of channels; else its plan holds the fused kernel's operand as well."""
