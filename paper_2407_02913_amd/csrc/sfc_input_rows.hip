@@ -319,7 +319,8 @@ __global__ __launch_bounds__((RowsForm<ALG, EXACT>::NW * 64), 4) void input_rows
 // one are served at a time, and a workgroup costs its staging and so many tiles.  Of rectangles of up to eight, four, two
 // and one tiles, as many strips as fit in 40, 80 or 160 KB of LDS, the one with the least of
 //   6 rounds + tiles of a compute unit
-// is taken; at a tie more tiles (four, where a wave takes every tile of its workgroup), then less LDS.  The kernel alone
+// is taken (rounds: workgroups of a compute unit over those that share it, no less than one; as whole numbers 64
+// channels on 160 24x24 maps, 5x5 filters, layer, 33.1 -> 34.5 us); at a tie more tiles (four, where a wave takes every tile of its workgroup), then less LDS.  The kernel alone
 // against one wave to a tile, geometric mean over 16 layers of every algorithm, int8 and int16 (320): 0.87; eight tiles,
 // else four, two, one until there are 512 workgroups: 1.00 (272 that had a plan).  Of the fixed choices the rule misses
 // the best by 1 % in the mean.  Left behind, layers with many tiles: 7x7 tiles in int8, 64 channels on 56x56 maps, batch 32,
@@ -335,7 +336,7 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
   constexpr int kUnits = 256, kWaves = 16;  // compute units, waves that share one (128 registers)
   RowsPlan c{};
   c.tr.th_magic = ((1ull << 32) + (unsigned long long)g.th - 1) / (unsigned long long)g.th;
-  long long best = -1;
+  double best = -1;
   // (4x4 tiles, 46 points: a wave owns every position of its tile columns, with fewer than four tiles some waves
   // would have none)
   constexpr int kLeast = Form::PG == 1 ? Form::TG : 1;
@@ -360,7 +361,7 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
       if (c.lds_bytes > kLds) continue;
       const long long of_unit = ((long long)tile_rect_groups(g, c.tr) * (g.Cp / 64) + kUnits - 1) / kUnits;
       const int shared = std::max(1, std::min((int)(kLds / c.lds_bytes), kWaves / Form::NW));
-      const long long cost = 6 * ((of_unit + shared - 1) / shared) + of_unit * c.tr.ntiles;
+      const double cost = 6.0 * std::max(1.0, (double)of_unit / shared) + (double)(of_unit * c.tr.ntiles);
       if (best < 0 || cost < best || (cost == best && Form::TG == 1 && tiles == 4)) {
         best = cost;
         *rp = c;
