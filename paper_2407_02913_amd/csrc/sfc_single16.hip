@@ -138,8 +138,7 @@ __device__ __forceinline__ void stage_channels(const int8_t* __restrict__ x, uns
           unsigned v = __builtin_amdgcn_raw_buffer_load_b32(xres, voff, plane, 0);
           if constexpr (TAIL) {
             v &= bmask;
-            // (a plane in front of the last one too: maps of one or two samples)
-            if (xbytes - (unsigned)(n * g.Cin) * (unsigned)HW - plane < (unsigned)HW + 3u) {
+            if (n == g.N - 1 && c == g.Cin - 1) {  // (maps of one or two samples are whole images)
               if (ok && voff + plane + 4u > xbytes) {
                 v = 0;
                 for (int bb = 0; bb < nvalid; ++bb)

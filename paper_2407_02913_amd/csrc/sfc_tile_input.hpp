@@ -268,8 +268,7 @@ __device__ __forceinline__ void stage_tiles(const int8_t* __restrict__ x, unsign
           unsigned v = __builtin_amdgcn_raw_buffer_load_b32(xres, voff, plane, 0);
           if constexpr (kTail) {
             v &= bmask;
-            // (a plane in front of the last one too: maps of one or two samples)
-            if (xbytes - (unsigned)(n * g.Cin) * plane_stride - plane < plane_stride + 3u) {
+            if (n == g.N - 1 && c == g.Cin - 1) {  // (maps of one or two samples are whole images)
               if (ok && voff + plane + 4u > xbytes) {
                 v = 0;
                 for (int bb = 0; bb < nvalid; ++bb)
