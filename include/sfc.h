@@ -111,7 +111,10 @@ typedef enum {
   /* sfc_plan picks the fastest path that covers the layer (sfc_plan_choice tells which) */
   SFC_PATH_AUTO = -1,
   SFC_PATH_STAGED = 0, /* V and M pass through the workspace; taps available */
-  SFC_PATH_FUSED = 1,  /* product and output transform in one kernel; M never leaves the chip */
+  /* Product and output transform in one kernel; M never leaves the chip.  On request: 64, 128, 256 or
+   * 512 input channels once rounded up to a multiple of 64.  sfc_plan chooses it for other counts up
+   * to 512 as well, where it has a kernel for them. */
+  SFC_PATH_FUSED = 1,
   /* Input transform, products and output transform in one kernel; neither V nor M leaves the
    * chip, the workspace is used by calibration only.  Cin <= 64; with the SFC-4 forms also
    * Cin <= 128, and Cin <= 512 on feature maps of at most 16 tiles (16x16 and smaller). */
@@ -152,10 +155,13 @@ sfc_status sfc_plan(const sfc_conv_desc* desc, sfc_plan_t** out);
 void sfc_plan_destroy(sfc_plan_t* plan);
 
 /* What sfc_plan chose (or was given): the sfc_alg and sfc_path the plan runs.  Either output
- * pointer may be NULL. */
+ * pointer may be NULL.  A program that stores a choice plans by the algorithm and SFC_PATH_AUTO,
+ * which gives the same path again: not every path that is chosen may be asked for (SFC_PATH_FUSED). */
 sfc_status sfc_plan_choice(const sfc_plan_t* plan, int32_t* alg, int32_t* path);
 
-/* Sizes the caller must allocate (device bytes) and the derived counts:
+/* Sizes the caller must allocate (device bytes), which follow from the path that was chosen (staged: V
+ * and M; fused: V; so a small layer with 5x5 or 7x7 filters asks for more than a large one), and
+ * the derived counts:
  * P = multiplications per tile (88, 100, 132, 144, 46, 49, 184 or 196),
  * tiles = N*ceil(H/M)*ceil(W/M).
  * Any output pointer may be NULL. */

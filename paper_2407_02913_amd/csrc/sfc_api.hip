@@ -214,6 +214,9 @@ int static_pass_filters(const Geometry& g) {
 //         5  96: 0.81, 118: 0.94, 165: 1.27;  6  56: 0.49, 119: 0.90;  7  92: 0.88;  8  56: 0.43, 112: 0.69, 181: 0.91
 //   7x7   1 chunk  10: 0.81-0.89, 16: 0.96, 25: 1.05;  2  30: 0.83, 50: 0.89, 72: 1.16;  4  64: 0.64, 84: 0.85,
 //         100: 1.03, 136: 1.24;  8 (one pair per lane)  64: 0.45, 124: 0.86, 174: 0.72
+// The 5x5 side of the lines was measured with eight waves to a workgroup of pair16_kernel.  With four, up to 128
+// workgroups, it takes 0.74 to 0.94 of that and the two meet at 4, 14, 68 and 100 workgroups with one, two, four and
+// eight chunks (460 layers); between there and its line a layer takes up to 1.4 times as long as it could.
 bool staged_ahead(const Geometry& g) {
   constexpr int kLines[2][8] = {{36, 64, 92, 104, 130, 140, 150, 170}, {18, 60, 80, 100, 0, 0, 0, 200}};
   constexpr int kFewFilters[8] = {8, 30, 75, 85, 130, 150, 200, 300};  // 5x5, up to 32 filters

@@ -171,8 +171,7 @@ unsigned rows_table_offset(const Geometry& g) {
 // Returns hipErrorNotSupported when the geometry is outside this kernel's limits;
 // the caller then uses the generic kernel.
 hipError_t launch_input_transform_i8(const Geometry& g, const int8_t* x, void* V,
-                                     const float* inv_sx, const unsigned char* intab,
-                                     hipStream_t s, bool prepare) {
+                                     const unsigned char* intab, hipStream_t s, bool prepare) {
   if (image_input_supported(g))
     return launch_input_image(g, x, V, intab ? intab + image_table_offset(g) : nullptr, s, prepare);
   WaveInputPlan wp;

@@ -50,8 +50,7 @@ hipError_t launch_input_transform(int mode, const Geometry& g, const int8_t* x, 
 // current device, the dynamic-LDS limit of the kernel instantiation it would launch (the
 // data pointers are not looked at) and returns what the runtime said.
 hipError_t launch_input_transform_i8(const Geometry& g, const int8_t* x, void* V,
-                                     const float* inv_sx, const unsigned char* input_tab,
-                                     hipStream_t s, bool prepare = false);
+                                     const unsigned char* input_tab, hipStream_t s, bool prepare = false);
 // 3x3 filters on small feature maps (a patch within 128 bytes of a plane, at most 16 tiles per
 // image; sfc_input_image.hip):
 // whether the kernel applies, its table (image_table_bytes; in the filter buffer after the

@@ -383,7 +383,7 @@ hipError_t launch_input_transform(int mode, const Geometry& g, const int8_t* x, 
                                   const float* inv_sx, const unsigned char* input_tab,
                                   hipStream_t s) {
   if (mode == 1) {
-    const hipError_t e = launch_input_transform_i8(g, x, V, inv_sx, input_tab, s);
+    const hipError_t e = launch_input_transform_i8(g, x, V, input_tab, s);
     if (e != hipErrorNotSupported) return e;
     return launch_input_alg<1>(g, x, V, inv_sx, nullptr, s);
   }
@@ -411,7 +411,7 @@ hipError_t prepare_kernels(int path, int out, const Geometry& g) {
   const FilterViews none{};
   if (path != 2) {
     // the generic input kernel (geometries the int8 one does not take) stays under 64 KB
-    const hipError_t e = launch_input_transform_i8(g, nullptr, nullptr, nullptr, nullptr, nullptr, true);
+    const hipError_t e = launch_input_transform_i8(g, nullptr, nullptr, nullptr, nullptr, true);
     if (e != hipSuccess && e != hipErrorNotSupported) return e;
   }
   switch (choose_kernel(path, g)) {

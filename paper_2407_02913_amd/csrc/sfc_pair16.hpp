@@ -18,35 +18,14 @@
 #pragma once
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
+#include "sfc_lane_values.hpp"
 #include "sfc_points.hpp"
 #include "sfc_store.hpp"
 #include "sfc_stream_outputs.hpp"
 
 namespace sfc {
 
-// two floats that the add networks of sfc_points.hpp treat as one value
-struct f2 {
-  float v[2];
-  f2() = default;
-  __device__ __forceinline__ explicit f2(float s) : v{s, s} {}
-  __device__ __forceinline__ f2(float a, float b) : v{a, b} {}
-};
-__device__ __forceinline__ f2 operator+(const f2& a, const f2& b) { return f2(a.v[0] + b.v[0], a.v[1] + b.v[1]); }
-__device__ __forceinline__ f2 operator-(const f2& a, const f2& b) { return f2(a.v[0] - b.v[0], a.v[1] - b.v[1]); }
-__device__ __forceinline__ f2 operator*(const f2& a, const f2& b) { return f2(a.v[0] * b.v[0], a.v[1] * b.v[1]); }
-__device__ __forceinline__ f2 operator-(const f2& a) { return f2(-a.v[0], -a.v[1]); }
-template <>
-struct Third<f2> {
-  static __device__ __forceinline__ f2 apply(const f2& a) { return a * f2(1.0f / 3.0f); }
-};
-
 namespace pair16 {
-
-// Lane N of the reader's row of 16 lanes, as a DPP row broadcast (folds into the multiplication).
-template <int N>
-__device__ __forceinline__ float row_lane(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xf, 0xf, false));
-}
 
 // keeps a value that stays until a later product from being put off (stream_outputs)
 struct SettleF2 {

@@ -16,57 +16,12 @@
 
 #include "sfc_device.hpp"
 #include "sfc_internal.hpp"
+#include "sfc_lane_values.hpp"
 #include "sfc_points.hpp"
 #include "sfc_stream_outputs.hpp"
 #include "sfc_store.hpp"
 
 namespace sfc {
-
-// four floats that the add networks of sfc_points.hpp treat as one value
-struct f4 {
-  float v[4];
-  f4() = default;
-  __device__ __forceinline__ explicit f4(float s) : v{s, s, s, s} {}
-};
-__device__ __forceinline__ f4 operator+(const f4& a, const f4& b) {
-  f4 r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r.v[i] = a.v[i] + b.v[i];
-  return r;
-}
-__device__ __forceinline__ f4 operator-(const f4& a, const f4& b) {
-  f4 r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r.v[i] = a.v[i] - b.v[i];
-  return r;
-}
-__device__ __forceinline__ f4 operator*(const f4& a, const f4& b) {
-  f4 r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r.v[i] = a.v[i] * b.v[i];
-  return r;
-}
-__device__ __forceinline__ f4 operator-(const f4& a) {
-  f4 r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r.v[i] = -a.v[i];
-  return r;
-}
-template <>
-struct Half<f4> {
-  static __device__ __forceinline__ f4 apply(const f4& a) { return a * f4(0.5f); }
-};
-template <>
-struct Third<f4> {
-  static __device__ __forceinline__ f4 apply(const f4& a) { return a * f4(1.0f / 3.0f); }
-};
-
-// Lane n of the reader's row of 16 lanes (its quarter of the wave), as a DPP row broadcast:
-// folds into the instruction that takes the value.
-template <int N>
-__device__ __forceinline__ float row_lane(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xf, 0xf, false));
-}
 
 // waves per workgroup of the fused kernel = groups of 16 filters per workgroup
 constexpr int kQuad16Waves = 4;

@@ -51,9 +51,8 @@ __host__ __device__ constexpr int plane_stride_bytes(int hw) {
 // Strips are counted with the 64-byte rows above.  single16_kernel stages 4 (tlw + 2) bytes a row and
 // would hold more of them on narrow maps: with two chunks it gets three strips at most, 9 of 16 tile
 // slots on maps of three tile columns.
-// whole_images: false keeps to rectangles whatever the size of the feature map.
 inline bool make_tile_rect(const Geometry& g, unsigned stage_budget, TileRect* tr,
-                           int max_tiles = 16, bool partial_images = false, bool whole_images = true) {
+                           int max_tiles = 16, bool partial_images = false) {
   const int M = alg_tile(g.alg), PAD = alg_pad(g.alg);
   tr->whole = 0;
   tr->ipw = 0;
@@ -61,7 +60,7 @@ inline bool make_tile_rect(const Geometry& g, unsigned stage_budget, TileRect* t
   // Small feature maps: whole images, if the tile slots are used at least as well as a
   // rectangle would (always the case when the tiles of an image divide 16).
   const int tpi = g.th * g.tw;
-  if (whole_images && tpi <= max_tiles && g.H * g.W <= 1024) {
+  if (tpi <= max_tiles && g.H * g.W <= 1024) {
     const int cs = plane_stride_bytes(g.H * g.W);
     int ipw = max_tiles / tpi;
     if (ipw > g.N) ipw = g.N;

@@ -406,6 +406,29 @@ def test_auto_path_on_both_sides_of_its_line(lib, alg, cin, cout, line):
         assert e.value.code == 2
 
 
+def test_a_stored_choice_gives_the_same_path_again(lib):
+    """By its algorithm and SFC_PATH_AUTO, also where the path itself may not be asked for."""
+    from paper_2407_02913_amd import binding
+
+    asked = set()
+    for alg in ("auto", "4x4_p46", "6x6_5x5_p184", "4x4_7x7_p184", "6x6_p88"):
+        for n in (1, 40, 400):
+            for cin in (16, 130, 192, 256, 320, 450, 512):
+                for edge in (7, 14, 30):
+                    plan = binding.Plan(n, cin, 70, edge, edge, alg=alg, mode="requant", path="auto")
+                    again = binding.Plan(n, cin, 70, edge, edge, alg=plan.alg, mode="requant", path="auto")
+                    assert (again.alg, again.path, again.workspace_bytes) == (plan.alg, plan.path, plan.workspace_bytes)
+                    try:
+                        binding.Plan(n, cin, 70, edge, edge, alg=plan.alg, mode="requant", path=plan.path).close()
+                        asked.add(True)
+                    except binding.SfcError as e:
+                        assert e.code == 2 and plan.path == "fused" and -(-cin // 64) in (3, 5, 6, 7)
+                        asked.add(False)
+                    plan.close()
+                    again.close()
+    assert asked == {True, False}
+
+
 def test_waves_of_the_5x5_kernel(lib):
     """Four up to 128 workgroups of 64 filters, then eight: the operand covers whole workgroups."""
     from paper_2407_02913_amd import binding
