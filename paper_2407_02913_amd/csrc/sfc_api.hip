@@ -174,15 +174,15 @@ size_t sums_bytes(const Geometry& g, int nf, int bytes) {
 // 49.1 against 55.8 at batch 128; 512 channels at 7x7, batch 64: 31.2 against 38.9) -- except
 // on 7x7 maps, which one 7x7 tile covers exactly, once the layer has at least 96 K (tile,
 // filter) pairs: then the 31 % of surplus outputs of the ragged 4x4 tiles cost more than the
-// larger point set (512 channels at 7x7, batch 256: 64.5 us with 7x7 tiles against 78.8).
+// larger point set (512 channels at 7x7, batch 256: 53.8 us with 7x7 tiles against 68.0).
 // Exact mode: 6x6 tiles, the form Sec. 4 and the 3.68x figure are about.
 int choose_alg(const sfc_conv_desc& d) {
   if (d.mode == SFC_MODE_EXACT) return SFC_ALG_6X6_P88;
   if (d.H == 7 && d.W == 7) {
     const int64_t pairs = (int64_t)d.N * (d.H / 7) * (d.W / 7) * d.Cout;
     // (with 512 and more channels the 7x7 tiles go through the staged path, which is ahead
-    // from batch 128 on: 512 channels, 30.9 against 46.6 us with 4x4 tiles; batch 64: 28.1
-    // against 26.0)
+    // from batch 128 on: 512 channels, 30.9 against 42.4 us with 4x4 tiles; batch 64: 28.1
+    // against 25.0)
     if (pairs >= (d.Cin >= 512 ? 56 : 96) * 1024) return SFC_ALG_7X7_P132;
   }
   return SFC_ALG_4X4_P46;
