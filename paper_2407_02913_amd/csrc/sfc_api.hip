@@ -600,7 +600,7 @@ static sfc_status run_stages(const sfc_plan_t* plan, const int8_t* x_dev, float 
         return SFC_EHIP;
       if ((stage_mask & SFC_STAGE_OUTPUT) &&
           sfc::launch_output_sums(plan->d.out, g, M, f, xs, inv_y, y_dev, s, false, f0, pass,
-                                  plan->fused.kernel == sfc::Kernel::kFusedQuad) != hipSuccess)
+                                  plan->fused.kernel != sfc::Kernel::kFusedQuad) != hipSuccess)
         return SFC_EHIP;
     }
     return SFC_OK;

@@ -204,19 +204,16 @@ hipError_t launch_product_gemm_i8(const Geometry& g, const void* V, const void* 
 // that the eight waves a compute unit has on a small layer keep some 64 KB of M on the way
 // (512 channels on 7x7 maps, 256 images: the same 23 us either way when measured alone; the
 // kernel there is bound by the bytes of M, see m_sum_bytes).
-// The forms with 184 points keep their outputs (36 or 16 registers, 24 to 72 with the components) and
-// have room for more: us a layer with 32 / 48 / 64 / 92 in flight, 5x5 filters, 98 channels, 60 7x7 maps
+// KEPT: the forms with 184 points where three kernels stand in for pair16_kernel or quad16_kernel keep
+// their outputs, the float32 sums in the order of those kernels.  36 or 16 registers, 24 to 72 with the components,
+// leave room for more: us a layer with 32 / 48 / 64 / 92 in flight, 5x5 filters, 98 channels, 60 7x7 maps
 // 30.6 / 29.7 / 30.0 / 29.3, twelve 28x28 maps 31.2 / 30.3 / 30.5 / 29.8; 7x7 filters, 512 channels, two
 // 14x14 maps 32.1 / 32.1 / 32.4 / 32.3.
-// KEPT: the forms with 184 points keep the outputs, as their fused kernels do (the same sums in the same order).
-// Without it SFC-6(4x4,7x7) adds as fused_quad_kernel does, for the layers that kernel takes on request.
 template <int ALG, bool KEPT>
 constexpr int sum_ring() {
   using Tr = AlgTraits<ALG>;
   return Tr::NC <= 6 ? Order<ALG>::PP : Tr::NC <= 8 ? 12 : !KEPT ? 32 : Tr::M == 6 ? 92 : 48;
 }
-template <int ALG>
-constexpr bool sums_kept() { return AlgTraits<ALG>::NC == 12 && AlgTraits<ALG>::kHermitian; }
 
 template <int ALG, bool PLANES, int NW>
 constexpr unsigned sums_stage_bytes() {
@@ -328,7 +325,7 @@ static hipError_t launch_sums_impl(const Geometry& g, const int32_t* M, const Fi
   return hipGetLastError();
 }
 
-template <int ALG, bool KEPT = sums_kept<ALG>()>
+template <int ALG, bool KEPT = false>
 static hipError_t launch_sums_alg(int out, const Geometry& g, const int32_t* M,
                                   const FilterViews& f, float x_scale, float inv_y, void* y,
                                   hipStream_t s, bool prepare, int f0, int nf) {
@@ -352,7 +349,7 @@ static hipError_t launch_sums_alg(int out, const Geometry& g, const int32_t* M,
 // out: 0 float32, 2 int8 with ReLU.  hipErrorNotSupported beyond the 32-bit offset limits.
 hipError_t launch_output_sums(int out, const Geometry& g, const int32_t* M, const FilterViews& f,
                               float x_scale, float inv_y, void* y, hipStream_t s, bool prepare, int f0,
-                              int nf, bool as_fused_quad) {
+                              int nf, bool kept) {
   if (nf == 0) nf = g.Kp;
   const long long mbytes = 4ll * g.P * g.Tp * nf, ybytes = 4ll * g.N * g.Cout * g.H * g.W;
   if (mbytes >= (1ll << 31) || ybytes >= (1ll << 31) || out == 1) return hipErrorNotSupported;
@@ -363,10 +360,11 @@ hipError_t launch_output_sums(int out, const Geometry& g, const int32_t* M, cons
     case 3: return launch_sums_alg<3>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
     case 4: return launch_sums_alg<4>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
     case 5: return launch_sums_alg<5>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
-    case 6: return launch_sums_alg<6>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 6: return kept ? launch_sums_alg<6, true>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                        : launch_sums_alg<6>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
     case 7: return launch_sums_alg<7>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
-    case 8: return as_fused_quad ? launch_sums_alg<8, false>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
-                                 : launch_sums_alg<8>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
+    case 8: return kept ? launch_sums_alg<8, true>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf)
+                        : launch_sums_alg<8>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
     case 9: return launch_sums_alg<9>(out, g, M, f, x_scale, inv_y, y, s, prepare, f0, nf);
   }
   return hipErrorInvalidValue;

@@ -93,13 +93,13 @@ hipError_t launch_product(int mode, const Geometry& g, const void* V, const void
 // bytes per int32 sum of M as the GEMM stores it (3: 24-bit, when no sum can exceed that; 4)
 int m_sum_bytes(const Geometry& g);
 // f0, nf: filters f0 .. f0 + nf - 1 alone, M holding those (multiples of 16, for the forms with four-wave
-// workgroups; nf = 0: all).  as_fused_quad: the float32 additions of SFC-6(4x4,7x7) with 184 points in the order of
-// fused_quad_kernel, not in quad16_kernel's
+// workgroups; nf = 0: all).  kept: the float32 additions of the forms with 184 points in the order of pair16_kernel and
+// quad16_kernel, not in that of fused_quad_kernel
 hipError_t launch_product_gemm_i8(const Geometry& g, const void* V, const void* U, int32_t* M,
                                   hipStream_t s, int f0 = 0, int nf = 0);
 hipError_t launch_output_sums(int out, const Geometry& g, const int32_t* M, const FilterViews& f,
                               float x_scale, float inv_y, void* y, hipStream_t s,
-                              bool prepare = false, int f0 = 0, int nf = 0, bool as_fused_quad = false);
+                              bool prepare = false, int f0 = 0, int nf = 0, bool kept = false);
 // out: 0 float32, 1 int32 sums (exact mode), 2 int8 with ReLU (inv_y = 1 / output scale)
 hipError_t launch_output_transform(int mode, int out, const Geometry& g, const int32_t* M,
                                    const FilterViews& f, float x_scale, float inv_y, void* y,

@@ -822,6 +822,28 @@ def test_layers_sent_through_m(binding, alg, shape, kernel, static, out):
         assert torch.equal(ys[0], y)
 
 
+@pytest.mark.parametrize("shape", [(28, 100, 512, 7, 7), (21, 512, 70, 15, 14), (7, 490, 130, 13, 9)])
+def test_staged_path_of_7x7_filters_adds_as_fused_quad(binding, shape):
+    """On request the staged path of 4x4_7x7_p184 gives the bits of fused_quad_kernel."""
+    import torch
+
+    x, w, xs, ws = uniform_case(shape, 4300 + sum(shape), r=7)
+    print("case staged 7x7", shape, flush=True)
+    sx, sw = oracle.calibrate_act_scales(x[:2], "4x4_7x7_p184"), oracle.calibrate_filter_scales(w, "4x4_7x7_p184")
+    ys = []
+    for path in ("staged", "fused"):
+        plan = binding.Plan(*shape, alg="4x4_7x7_p184", mode="requant", path=path)
+        plan.set_point_scales(sx, sw)
+        fbuf, wbuf = binding.device_buffer(plan.filter_bytes), binding.device_buffer(plan.workspace_bytes)
+        plan.transform_filter(torch.from_numpy(w).cuda(), ws, fbuf)
+        y = torch.full((shape[0], shape[2], *shape[3:]), 77, dtype=torch.float32, device="cuda")
+        plan.conv2d(torch.from_numpy(x).cuda(), xs, y, wbuf)
+        torch.cuda.synchronize()
+        ys.append(y)
+        plan.close()
+    assert torch.equal(ys[0], ys[1]) and ys[0].std() > 0
+
+
 SINGLE_SHAPES = [
     (1, 16, 16, 32, 32),
     (2, 3, 5, 14, 14),
