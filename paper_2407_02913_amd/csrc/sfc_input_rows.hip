@@ -316,15 +316,18 @@ __global__ __launch_bounds__((RowsForm<ALG, EXACT>::NW * 64), 4) void input_rows
 // ---------------------------------------------------------------------------------------
 
 // The rectangle of a workgroup.  What a layer takes goes by rounds: compute units times the workgroups that share
-// one are served at a time, and a workgroup costs its staging and so many tiles.  Of rectangles of up to eight, four, two
-// and one tiles, as many strips as fit in 40, 80 or 160 KB of LDS, the one with the least of
+// one are served at a time, and a workgroup costs its staging and so many tiles.  Of rectangles of up to eight,
+// four, two and one tiles, as many strips as fit in 40, 80 or 160 KB of LDS, the one with the least of
 //   6 rounds + tiles of a compute unit
-// is taken (rounds: workgroups of a compute unit over those that share it, no less than one; as whole numbers 64
-// channels on 160 24x24 maps, 5x5 filters, layer, 33.1 -> 34.5 us); at a tie more tiles (four, where a wave takes every tile of its workgroup), then less LDS.  The kernel alone
-// against one wave to a tile, geometric mean over 16 layers of every algorithm, int8 and int16 (320): 0.87; eight tiles,
-// else four, two, one until there are 512 workgroups: 1.00 (272 that had a plan).  Of the fixed choices the rule misses
-// the best by 1 % in the mean.  Left behind, layers with many tiles: 7x7 tiles in int8, 64 channels on 56x56 maps, batch 32,
-// 10.0 -> 11.6 us (sixteen 29x31 maps of 70 channels 12.6 -> 9.6), 196 points of the 5x5 filters in int16 22.5 -> 27.4.
+// is taken.  Rounds: workgroups of a compute unit over those that share it, no less than one; as whole numbers 64
+// channels on 160 24x24 maps, 5x5 filters, layer, 33.1 -> 34.5 us.  At a tie more tiles (four, where a wave takes
+// every tile of its workgroup), then less LDS.  Workgroups of four waves keep to 40 KB (or one strip): a compute
+// unit holds four of those and three of 54 KB, 4x4 tiles, 7x7 filters, 512 channels on sixty 16x15 maps 40.8 -> 48.7 us.
+// The kernel alone against one wave to a tile, geometric mean over 16 layers of every algorithm, int8 and int16
+// (320): 0.87; eight tiles, else four, two, one until there are 512 workgroups: 1.00 (272 that had a plan).  Of the
+// fixed choices the rule misses the best by 1 % in the mean.  Left behind, layers with many tiles: 7x7 tiles in
+// int8, 64 channels on 56x56 maps, batch 32, 10.0 -> 11.6 us (sixteen 29x31 maps of 70 channels 12.6 -> 9.6), 196
+// points of the 5x5 filters in int16 22.5 -> 27.4.
 template <int ALG, bool EXACT>
 static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
   using Form = RowsForm<ALG, EXACT>;
@@ -333,6 +336,7 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
   if (xb >= (1ll << 31) || (!EXACT && vb >= (1ll << 31))) return false;  // 32-bit offsets
   if ((long long)g.strips * g.th >= (1ll << 32)) return false;  // strip_image's reciprocal
   constexpr unsigned kBlocks = (unsigned)Form::NW * (unsigned)Form::kBlockBytes, kLds = 160u * 1024u;
+  constexpr unsigned kMost = Form::NW > 4 ? kLds : kLds / 4;
   constexpr int kUnits = 256, kWaves = 16;  // compute units, waves that share one (128 registers)
   RowsPlan c{};
   c.tr.th_magic = ((1ull << 32) + (unsigned long long)g.th - 1) / (unsigned long long)g.th;
@@ -352,7 +356,7 @@ static bool make_rows_plan(const Geometry& g, RowsPlan* rp) {
     auto bytes = [&](int S) { return (((unsigned)S * 64u * c.cs + 32u + 15u) & ~15u) + kBlocks; };
     const int strips = std::max(1, std::min(tiles / c.tr.tlw, g.strips));
     c.tr.S = 0;
-    for (unsigned most = kLds / 4; most <= kLds && c.tr.S < strips; most *= 2) {
+    for (unsigned most = kLds / 4; most <= kMost && c.tr.S < strips; most *= 2) {
       c.tr.S = strips;
       while (c.tr.S > 1 && bytes(c.tr.S) > most) --c.tr.S;
       c.tr.ntiles = c.tr.S * c.tr.tlw;
