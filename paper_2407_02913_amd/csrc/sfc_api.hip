@@ -217,14 +217,18 @@ int static_pass_filters(const Geometry& g) {
 // The 5x5 side of the lines was measured with eight waves to a workgroup of pair16_kernel.  With four, up to 128
 // workgroups, it takes 0.74 to 0.94 of that and the two meet at 4, 14, 68 and 100 workgroups with one, two, four and
 // eight chunks (460 layers); between there and its line a layer takes up to 1.4 times as long as it could.
+// One chunk was behind its time with one pair per lane there, so maps of more than one tile have that line (64 to 64
+// channels, 24x24 maps, staged / fused / one pair per lane: eight 22.1 / 20.4 / 25.2, sixteen 25.3 / 20.8 / 25.6,
+// 24 28.9 / 21.6 / 25.8, 32 31.1 / 22.0 / 26.2; 128 filters, two 20.2 / 20.5 / 29.4, four 22.1 / 20.7 / 29.2).
 bool staged_ahead(const Geometry& g) {
   constexpr int kLines[2][8] = {{36, 64, 92, 104, 130, 140, 150, 170}, {18, 60, 80, 100, 0, 0, 0, 200}};
   constexpr int kFewFilters[8] = {8, 30, 75, 85, 130, 150, 200, 300};  // 5x5, up to 32 filters
   const int kc = g.Cp / 64;
   if ((g.alg != SFC_ALG_6X6_5X5_P184 && g.alg != SFC_ALG_4X4_7X7_P184) || kc > 8) return false;
   const long long workgroups = (long long)(g.Tp / 16) * ((g.Cout + 63) / 64);
-  const int line = g.alg == SFC_ALG_4X4_7X7_P184 ? kLines[1][kc - 1] : g.Cout > 32 ? kLines[0][kc - 1] : kFewFilters[kc - 1];
-  return workgroups < line;
+  if (g.alg == SFC_ALG_4X4_7X7_P184) return workgroups < kLines[1][kc - 1];
+  if (g.Cout <= 32) return workgroups < kFewFilters[kc - 1];
+  return workgroups < (kc == 1 && g.th * g.tw > 1 ? 5 : kLines[0][kc - 1]);
 }
 
 // SFC_PATH_AUTO: one kernel where the layer allows it, else input transform + fused

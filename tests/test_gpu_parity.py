@@ -776,7 +776,7 @@ def test_static_workspace_in_passes(binding, alg, shape, out):
 
 
 SENT_THROUGH_M = [  # (algorithm, shape, kernel of the fused path, what a call from the static workspace runs)
-    ("6x6_5x5_p184", (9, 60, 70, 13, 12), "pair16", "whole"),
+    ("6x6_5x5_p184", (5, 60, 70, 13, 12), "pair16", "whole"),
     ("6x6_5x5_p184", (12, 256, 500, 20, 24), "pair16", "fused"),
     ("6x6_5x5_p184", (14, 460, 250, 24, 18), "pair16", "passes"),
     ("4x4_7x7_p184", (12, 250, 500, 16, 15), "quad16", "fused"),

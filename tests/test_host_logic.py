@@ -406,6 +406,18 @@ def test_auto_path_on_both_sides_of_its_line(lib, alg, cin, cout, line):
         assert e.value.code == 2
 
 
+@pytest.mark.parametrize("cin,cout,tiles", [(64, 64, 64), (30, 40, 64), (64, 128, 32), (60, 300, 1)])
+def test_auto_path_of_5x5_filters_with_one_chunk(lib, cin, cout, tiles):
+    """Maps of more than one tile: the fused path from five workgroups on, there ahead of three kernels."""
+    from paper_2407_02913_amd import binding
+
+    for n, path in ((tiles // 4, "staged"), (tiles // 4 + 1, "fused"), (9 * tiles // 4 + 1, "fused")):
+        if n:
+            plan = binding.Plan(n, cin, cout, 12, 11, alg="6x6_5x5_p184", mode="requant", path="auto")
+            assert plan.path == path, n
+            plan.close()
+
+
 def test_a_stored_choice_gives_the_same_path_again(lib):
     """By its algorithm and SFC_PATH_AUTO, also where the path itself may not be asked for."""
     from paper_2407_02913_amd import binding
